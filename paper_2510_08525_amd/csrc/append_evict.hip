@@ -6,11 +6,12 @@
 // kept): position p < S lives in slot p, position p >= S in slot S + (p - S) mod R, where
 // it overwrites position p - R.
 //
-// The kernel is destination driven: every thread owns 16-byte units of the store, asks
-// "which appended position ends up in my slot?" (the largest one that maps to it), and
-// copies that row only.  A multi-token append therefore writes survivors only and gives
+// The kernel is destination driven: every workgroup owns a tile of slots, asks for each
+// "which appended position ends up in this slot?" (the largest one that maps to it), and
+// copies that row only (tiled layout: through LDS, tile_rows.h).  A multi-token append therefore writes survivors only and gives
 // the same store as the same tokens appended one at a time, whatever the write order.
 #include "rlkv_internal.h"
+#include "tile_rows.h"
 
 namespace rlkv {
 namespace {
@@ -115,63 +116,32 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
     int32_t* slot_pos = nullptr;
     if (!full) slot_pos = dv.slot_pos + dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window;
 
-    // K rows (both layouts) and V rows (row-major layout): one 16-byte chunk per unit
-    for (int u = threadIdx.x; u < kTile * kChunks; u += kBlock) {
-      const int slot = tile * kTile + u / kChunks, chunk = u % kChunks;
-      const int p = source_position(full, slot, len_old, len_new, S, R);
-      if (p < 0) continue;
-      const int64_t src = ((src_head + (p - len_old)) * kHeadDim + chunk * kElems) * sizeof(T);
-      const uint4 kv = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k_new) + src);
-      if (KERNEL == RLKV_KERNEL_MFMA) {
-        *reinterpret_cast<uint4*>(tile_base + tiled_k_offset(slot & (kTile - 1), chunk)) = kv;
-      } else {
-        const int64_t dst = (int64_t)slot * dv.row_bytes + chunk * 16;
-        *reinterpret_cast<uint4*>(kst + dst) = kv;
-        *reinterpret_cast<uint4*>(vst + dst) =
-            *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(v_new) + src);
+    if constexpr (KERNEL == RLKV_KERNEL_MFMA) {
+      // which appended row ends in each slot: once per slot, then the rows go through LDS into the tile
+      __shared__ TileRowsLds lds;
+      if (threadIdx.x < kTile) {
+        const int slot = tile * kTile + threadIdx.x;
+        const int p = source_position(full, slot, len_old, len_new, S, R);
+        lds.src[threadIdx.x] = p < 0 ? -1 : p - len_old;
+        if (slot_pos && p >= 0) slot_pos[slot] = p;
       }
-      if (slot_pos && chunk == 0) slot_pos[slot] = p;
-    }
-
-    if (KERNEL == RLKV_KERNEL_MFMA) {
-      // V, tiled layout: a unit is the 16 bytes that hold one d of eight slots.
-      const uint16_t* vsrc = reinterpret_cast<const uint16_t*>(v_new);
-      for (int u = threadIdx.x; u < 8 * 64; u += kBlock) {
-        const int dblk = u >> 6, kb = (u >> 4) & 3, dn = u & 15;
-        const int d = dblk * 16 + dn;
-        uint16_t vals[8];
-        unsigned have = 0;
-        bool wide = false;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int slot = tile * kTile + (e >> 2) * 16 + kb * 4 + (e & 3);
-          const int p = source_position(full, slot, len_old, len_new, S, R);
-          if (p >= 0) {
-            vals[e] = vsrc[(src_head + (p - len_old)) * kHeadDim + d];
-            wide |= bf16_beyond_fp16(vals[e]);
-            have |= 1u << e;
-          } else {
-            vals[e] = 0;
-          }
-        }
-        if (wide) dv.v_wide[layer] = 1;      // the prefill kernel takes this layer's V as bf16 from now on
-        char* dst = tile_base + tiled_v_offset(kb * 4, d);   // e = 0 of this unit
-        if (have == 0xffu) {
-          uint4 w;
-          w.x = vals[0] | ((uint32_t)vals[1] << 16);
-          w.y = vals[2] | ((uint32_t)vals[3] << 16);
-          w.z = vals[4] | ((uint32_t)vals[5] << 16);
-          w.w = vals[6] | ((uint32_t)vals[7] << 16);
-          *reinterpret_cast<uint4*>(dst) = w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (have & (1u << e)) reinterpret_cast<uint16_t*>(dst)[e] = vals[e];
-        }
+      __syncthreads();
+      const bool wide = rows_to_tile<false>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
+      if (wide) dv.v_wide[layer] = 1;        // the prefill kernel takes this layer's V as bf16 from now on
+    } else {
+      // K and V rows: one 16-byte chunk per unit
+      for (int u = threadIdx.x; u < kTile * kChunks; u += kBlock) {
+        const int slot = tile * kTile + u / kChunks, chunk = u % kChunks;
+        const int p = source_position(full, slot, len_old, len_new, S, R);
+        if (p < 0) continue;
+        const int64_t src = ((src_head + (p - len_old)) * kHeadDim + chunk * kElems) * sizeof(T);
+        const int64_t dst = (int64_t)slot * dv.row_bytes + chunk * 16;
+        *reinterpret_cast<uint4*>(kst + dst) = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k_new) + src);
+        *reinterpret_cast<uint4*>(vst + dst) = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(v_new) + src);
+        if (slot_pos && chunk == 0) slot_pos[slot] = p;
       }
     }
   }
-
 }
 
 __global__ void reset_kernel(DeviceView dv, int seq, int64_t slot_pos_elems) {

@@ -24,6 +24,7 @@
 
 #include "mfma_tile.h"
 #include "prefill_deal.h"
+#include "tile_rows.h"
 
 namespace rlkv {
 namespace {
@@ -192,34 +193,11 @@ __global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int 
   if (tile * kTile >= t) return;
   char* tile_base = staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes;
   const int64_t src_head = (int64_t)pair * stride_tokens;
-  for (int u = threadIdx.x; u < kTile * 16; u += kBlock) {          // K: one 16-byte chunk of a row per unit
-    const int slot = u >> 4, chunk = u & 15;
-    const int row = tile * kTile + slot;
-    uint4 kv = make_uint4(0, 0, 0, 0);
-    if (row < t) kv = *reinterpret_cast<const uint4*>(k_new + (src_head + row) * kHeadDim + chunk * 8);
-    *reinterpret_cast<uint4*>(tile_base + tiled_k_offset(slot, chunk)) = kv;
-  }
-  for (int u = threadIdx.x; u < 8 * 64; u += kBlock) {              // V: one d of eight slots per unit
-    const int dblk = u >> 6, kb = (u >> 4) & 3, dn = u & 15;
-    const int d = dblk * 16 + dn;
-    uint32_t w[4];
-    bool wide = false;
-#pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      uint32_t pack = 0;
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int e = 2 * e2 + k;
-        const int row = tile * kTile + (e >> 2) * 16 + kb * 4 + (e & 3);
-        const uint32_t val = row < t ? v_new[(src_head + row) * kHeadDim + d] : 0u;
-        wide |= bf16_beyond_fp16(val);
-        pack |= val << (16 * k);
-      }
-      w[e2] = pack;
-    }
-    if (wide) dv.v_wide[layer] = 1;        // seen by the attention kernel that follows on the stream
-    *reinterpret_cast<uint4*>(tile_base + tiled_v_offset(kb * 4, d)) = make_uint4(w[0], w[1], w[2], w[3]);
-  }
+  __shared__ TileRowsLds lds;
+  if (threadIdx.x < kTile) lds.src[threadIdx.x] = tile * kTile + threadIdx.x < t ? tile * kTile + (int)threadIdx.x : -1;
+  __syncthreads();
+  const bool wide = rows_to_tile<true>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
+  if (wide) dv.v_wide[layer] = 1;          // seen by the attention kernel that follows on the stream
 }
 
 // Grid row y of the prefill kernels -> (sequence, KV head): the pairs of full heads first, then those of
