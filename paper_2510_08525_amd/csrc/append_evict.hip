@@ -10,6 +10,8 @@
 // "which appended position ends up in this slot?" (the largest one that maps to it), and
 // copies that row only (tiled layout: through LDS, tile_rows.h).  A multi-token append therefore writes survivors only and gives
 // the same store as the same tokens appended one at a time, whatever the write order.
+#include <string.h>
+
 #include "rlkv_internal.h"
 #include "tile_rows.h"
 
@@ -48,13 +50,13 @@ template <int KERNEL, typename T>
 __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer, const int32_t* __restrict__ len_in,
                                                         int32_t* __restrict__ len_out, const T* __restrict__ k_new,
                                                         const T* __restrict__ v_new, int n_uniform,
-                                                        int stride_tokens, int ragged, int from_list) {
+                                                        int stride_tokens, int ragged, int from_list, SeqCounts seqs) {
   const int pair = blockIdx.y;
   const int b = pair / dv.n_kv_heads, h = pair % dv.n_kv_heads;
   const int job = blockIdx.x;
   const int S = dv.sink, R = dv.recent;
   // a uniform append skips inactive slots; a ragged append states its counts explicitly
-  const int n_tok = ragged ? dv.append_cnt[b] : (dv.active[b] ? n_uniform : 0);
+  const int n_tok = ragged ? tokens_of_seq(dv, seqs, b) : (dv.active[b] ? n_uniform : 0);
   int len_old;
   if (from_list) {
     // The append of a decode step whose launches carry no per-step argument (so that they can be recorded and
@@ -163,7 +165,50 @@ __global__ void table_update_kernel(DeviceView dv, TableUpdates up) {
   if (i < up.n) dv.block_table[up.index[i]] = up.value[i];
 }
 
+// Work lists go from their pinned staging slot to the device by this kernel: it reads the slot over the bus with
+// system-scope loads (nothing stale from a cache), all of a block's loads in flight before its stores.
+// Bound: one bus latency.  The copy engine that hipMemcpyAsync picked for these sizes (15 .. 60 KiB) left the GPU idle for
+// 27 .. 50 us around a copy of 5.8 us; this launch takes 4 us, 5 us after its event is recorded.
+constexpr int kFetchWords = 8;      // 8-byte words per thread
+__global__ __launch_bounds__(kBlock) void fetch_kernel(unsigned long long* __restrict__ dst, const unsigned long long* __restrict__ src,
+                                                       int64_t n) {
+  const int64_t base = (int64_t)blockIdx.x * kBlock * kFetchWords + threadIdx.x;
+  unsigned long long w[kFetchWords];
+#pragma unroll
+  for (int i = 0; i < kFetchWords; ++i)
+    if (base + i * kBlock < n) w[i] = __hip_atomic_load(src + base + i * kBlock, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+#pragma unroll
+  for (int i = 0; i < kFetchWords; ++i)
+    if (base + i * kBlock < n) dst[base + i * kBlock] = w[i];
+}
+
+constexpr int kValuesPerLaunch = 512;
+struct ValueBlock { int32_t v[kValuesPerLaunch]; };
+__global__ void write_values_kernel(int32_t* __restrict__ dst, ValueBlock values, int n) {
+  const int i = threadIdx.x;
+  if (i < n) dst[i] = values.v[i];
+}
+
 }  // namespace
+
+hipError_t launch_fetch(void* dst, const void* pinned_src, size_t bytes, hipStream_t stream) {
+  const int64_t n = (int64_t)(bytes / 8);
+  const int64_t per_block = kBlock * kFetchWords;
+  hipLaunchKernelGGL(fetch_kernel, dim3((unsigned)((n + per_block - 1) / per_block)), dim3(kBlock), 0, stream,
+                     static_cast<unsigned long long*>(dst), static_cast<const unsigned long long*>(pinned_src), n);
+  return hipGetLastError();
+}
+
+hipError_t launch_write_values(int32_t* dst, const int32_t* values, int n, hipStream_t stream) {
+  for (int at = 0; at < n; at += kValuesPerLaunch) {
+    const int m = n - at < kValuesPerLaunch ? n - at : kValuesPerLaunch;
+    ValueBlock block = {};
+    memcpy(block.v, values + at, (size_t)m * sizeof(int32_t));
+    hipLaunchKernelGGL(write_values_kernel, dim3(1), dim3(kValuesPerLaunch), 0, stream, dst + at, block, m);
+    if (hipError_t e = hipGetLastError()) return e;
+  }
+  return hipSuccess;
+}
 
 hipError_t launch_table_update(const DeviceView& dv, const TableUpdates& up, hipStream_t stream) {
   if (up.n <= 0) return hipSuccess;
@@ -172,8 +217,11 @@ hipError_t launch_table_update(const DeviceView& dv, const TableUpdates& up, hip
 }
 
 hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in, int32_t* len_out,
-                         const void* k, const void* v, int n_tokens_uniform, int stride_tokens, bool ragged,
+                         const void* k, const void* v, int n_tokens_uniform, int stride_tokens, const SeqCounts* seqs,
                          int max_tokens, hipStream_t stream, bool from_list) {
+  const SeqCounts none = {};
+  const SeqCounts& sq = seqs ? *seqs : none;
+  const int ragged = seqs != nullptr;
   // Tiles a pair can touch: a range of c >= 1 slots touches at most (c + 30) / 32 + 1 tiles;
   // a full head has one range, a compressed head up to three (new sinks, ring, wrapped
   // ring) whose sizes add up to at most max_tokens.  One token touches one tile.
@@ -181,13 +229,13 @@ hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in,
   const dim3 grid(jobs, dv.n_pairs), block(kBlock);
   if (dv.dtype == RLKV_F32) {
     hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, float>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const float*)k, (const float*)v, n_tokens_uniform, stride_tokens, (int)ragged, (int)from_list);
+                       len_in, len_out, (const float*)k, (const float*)v, n_tokens_uniform, stride_tokens, ragged, (int)from_list, sq);
   } else if (dv.kernel == RLKV_KERNEL_MFMA) {
     hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, (int)ragged, (int)from_list);
+                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, (int)from_list, sq);
   } else {
     hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, uint16_t>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, (int)ragged, (int)from_list);
+                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, (int)from_list, sq);
   }
   return hipGetLastError();
 }

@@ -184,12 +184,12 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
 // Copies the chunk's K/V rows (row-major [batch][n_kv_heads][stride][128]) into tiles of the MFMA
 // layout: staging tile t of a pair holds chunk rows 32 t .. 32 t + 31; rows past the sequence's
 // count are written as zeros, so a staged tile never holds stale bits.
-__global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int layer, const uint16_t* __restrict__ k_new,
+__global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int layer, SeqCounts seqs, const uint16_t* __restrict__ k_new,
                                                              const uint16_t* __restrict__ v_new, int stride_tokens,
                                                              char* __restrict__ staging, int staging_tiles) {
   const int pair = blockIdx.y, tile = blockIdx.x;
   const int b = pair / dv.n_kv_heads;
-  const int t = dv.append_cnt[b];
+  const int t = tokens_of_seq(dv, seqs, b);
   if (tile * kTile >= t) return;
   char* tile_base = staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes;
   const int64_t src_head = (int64_t)pair * stride_tokens;
@@ -211,14 +211,14 @@ struct PrefillHeads {
   int32_t dealt_rows;                      // of those, the leading ones that go one row per XCD (see prefill_deal)
   int32_t head[2][kPrefillArgHeads];       // [0]: the full heads in ascending order, [1]: the compressed ones
 };
-__device__ __forceinline__ void pair_of_grid_row(const DeviceView& dv, int layer, int y, const PrefillHeads& heads,
-                                                 int& b, int& h, bool& full) {
+__device__ __forceinline__ void pair_of_grid_row(const DeviceView& dv, const SeqOrder& order, int layer, int y, const PrefillHeads& heads,
+                                                 int& b, int& h, bool& full, int& tokens) {
   if (heads.n_full >= 0) {
     const int n_full_pairs = dv.batch * heads.n_full;
     full = y < n_full_pairs;
     const int per_seq = full ? heads.n_full : dv.n_kv_heads - heads.n_full;
     const int yy = full ? y : y - n_full_pairs;
-    b = dv.append_cnt[dv.batch + yy / per_seq];
+    seq_in_order(dv, order, yy / per_seq, b, tokens);
     h = heads.head[full ? 0 : 1][yy % per_seq];
     return;
   }
@@ -228,7 +228,7 @@ __device__ __forceinline__ void pair_of_grid_row(const DeviceView& dv, int layer
   const bool want_full = y < n_full_pairs;
   const int per_seq = want_full ? n_full_heads : dv.n_kv_heads - n_full_heads;
   const int yy = want_full ? y : y - n_full_pairs;
-  b = dv.append_cnt[dv.batch + yy / per_seq];
+  seq_in_order(dv, order, yy / per_seq, b, tokens);
   h = 0;
   for (int i = 0, k = yy % per_seq; i < dv.n_kv_heads; ++i) {
     if ((dv.full_mask[layer * dv.n_kv_heads + i] != 0) == want_full) {
@@ -272,6 +272,7 @@ constexpr int kPrefillBlock = kPrefillWaves * 64;
 // of a gated head), each wavefront on its own, with per-slot positions and masks.
 template <bool PAGED, bool GATED>
 __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView dv, int layer,
+                                                                     SeqOrder order,
                                                                      const int32_t* __restrict__ len_in,
                                                                      const uint16_t* __restrict__ q,
                                                                      uint16_t* __restrict__ out, int stride_tokens,
@@ -292,7 +293,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   int bx = blockIdx.x, by = blockIdx.y;
   if (gridDim.z == 1) prefill_deal((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)gridDim.x, (int)gridDim.y, heads.dealt_rows,
                                     heads.heavy_rows, bx, by);   // (a divided launch keeps the plain order: its merge kernel indexes by it)
-  pair_of_grid_row(dv, layer, by, heads, b, h, full);
+  int t;                                   // chunk length of the sequence
+  pair_of_grid_row(dv, order, layer, by, heads, b, h, full, t);
   const int pair = b * dv.n_kv_heads + h;
   const int block_x = gridDim.x - 1 - bx;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -303,7 +305,6 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   constexpr int LOCAL = NG;                              // index of the first local accumulator set (GATED)
   constexpr int kWaveCols = 16 * NG;
   const int wg_positions = kPrefillWaves * kWaveCols / G;    // chunk positions per workgroup
-  const int t = dv.append_cnt[b];          // chunk length of this sequence
   const int n_old = len_in[b];             // positions cached before the chunk
   const int c_wg = block_x * wg_positions; // the workgroup's first chunk index
   if (c_wg >= t) return;
@@ -748,15 +749,15 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 // Combines the shares of a divided workgroup: weights 2^(m_z - max m) on each share's accumulators and
 // normaliser (every share's weights carry the same 2^kWeightShift, which cancels).  A share that saw no
 // key has m = -inf and counts for nothing; the last share always holds the query's own position.
-__global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, const float* __restrict__ split_out,
+__global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, SeqOrder order, const float* __restrict__ split_out,
                                                                    int Z, uint16_t* __restrict__ out, int stride_tokens,
                                                                    PrefillHeads heads) {
   int b, h;
   bool full;
-  pair_of_grid_row(dv, layer, blockIdx.y, heads, b, h, full);
+  int t;
+  pair_of_grid_row(dv, order, layer, blockIdx.y, heads, b, h, full, t);
   const int G = dv.group;
   const int wg_positions = kSplitCols / G;
-  const int t = dv.append_cnt[b];
   const int c_wg = (gridDim.x - 1 - blockIdx.x) * wg_positions;
   if (c_wg >= t) return;
   const int c_last = (c_wg + wg_positions < t ? c_wg + wg_positions : t) - 1;
@@ -803,7 +804,7 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
 
 }  // namespace
 
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const int32_t* len_in, const void* q,
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
                                const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
                                float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int split_rows, int dealt_rows, const uint8_t* mask_row, hipStream_t stream,
@@ -821,14 +822,14 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
     heads.n_full = nf;
   }
   const int tiles = (max_tokens + kTile - 1) / kTile;
-  hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, (const uint16_t*)k,
+  hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, (const uint16_t*)k,
                      (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
   if (gated || n_split < 1 || !split_out) n_split = 1;         // (the blending form is never divided)
   const int per_block = kPrefillWaves * 16 * (gated ? 1 : 2) / dv.group;      // chunk positions per workgroup
   const dim3 grid((max_tokens + per_block - 1) / per_block, dv.n_pairs, n_split), block(kPrefillBlock);
 #define RLKV_LAUNCH(PG, GT)                                                                                          \
-  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, GT>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, len_in, \
+  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, GT>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
                         staging_tiles, split_out, heads)
   if (dv.page_shift >= 0) { if (gated) RLKV_LAUNCH(true, true); else RLKV_LAUNCH(true, false); }
@@ -836,7 +837,7 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
 #undef RLKV_LAUNCH
   if (hipError_t e = hipGetLastError()) return e;
   if (n_split > 1 && split_rows > 0)
-    hipLaunchKernelGGL(prefill_merge_kernel, dim3(grid.x, split_rows, kSplitCols / kMergeColsPerGroup), dim3(kSplitCols), 0, stream, dv, layer,
+    hipLaunchKernelGGL(prefill_merge_kernel, dim3(grid.x, split_rows, kSplitCols / kMergeColsPerGroup), dim3(kSplitCols), 0, stream, dv, layer, order,
                        (const float*)split_out, n_split, (uint16_t*)out, stride_tokens, heads);
   return hipGetLastError();
 }

@@ -197,7 +197,7 @@ struct rlkv_cache {
     std::vector<uint8_t> busy;
   };
   Ring list_ring;                        // work lists (one slot per layer up to a budget)
-  Ring small_ring;                       // token counts, the active table, the gates
+  Ring small_ring;                       // the active table, the gates
   hipStream_t last_stream = nullptr;     // the stream of the latest call that queued work
   std::vector<int32_t> new_len;          // [2B] host staging: new lengths for reserve_pages, counts + order for prefill
   std::vector<hipEvent_t> prof_events;   // start/stop pairs, created by rlkv_profile_enable
@@ -437,7 +437,7 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
     if (slots * lr.slot_bytes > budget) slots = budget / lr.slot_bytes;
     if (slots < 2) slots = 2;
     lr.n = (int)slots;
-    sr.slot_bytes = align_up(std::max({(size_t)2 * B * sizeof(int32_t), (size_t)L * H * sizeof(float), (size_t)B}));
+    sr.slot_bytes = align_up(std::max((size_t)L * H * sizeof(float), (size_t)B));
     sr.n = 64;
     c->pinned = acquire_pinned(lr.slot_bytes * lr.n + sr.slot_bytes * sr.n, &c->pinned_bytes);
     ok &= c->pinned != nullptr;
@@ -447,7 +447,7 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
       r->busy.assign((size_t)r->n, 0);
       for (int i = 0; ok && i < r->n; ++i) {
         hipEvent_t ev;
-        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) == hipSuccess) r->events.push_back(ev);
+        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming | hipEventDisableSystemFence) == hipSuccess) r->events.push_back(ev);
         else ok = false;
       }
     }
@@ -597,9 +597,22 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       if ((n_tokens[x] > 0) != (n_tokens[y] > 0)) return n_tokens[x] > 0;
       return (int64_t)lh[x] + n_tokens[x] > (int64_t)lh[y] + n_tokens[y];
     });
-    if (!send_small(cache, cache->dv.append_cnt, stage.data(), (size_t)2 * B * sizeof(int32_t), s)) return RLKV_ERR_HIP;
-  } else if (n_tokens) {
-    if (!send_small(cache, cache->dv.append_cnt, n_tokens, (size_t)B * sizeof(int32_t), s)) return RLKV_ERR_HIP;
+  }
+  // the counts (and the order) travel in the kernels' arguments, or, for a batch too large for that, are written first
+  SeqCounts seqs = {};
+  SeqOrder order = {};
+  if (n_tokens) {
+    seqs.in_args = order.in_args = B <= kArgSeqs;
+    if (seqs.in_args) {
+      memcpy(seqs.tok, n_tokens, (size_t)B * sizeof(int32_t));
+      for (int i = 0; prefill && i < B; ++i) {
+        order.seq[i] = cache->new_len[B + i];
+        order.tok[i] = n_tokens[order.seq[i]];
+      }
+    } else if (launch_write_values(cache->dv.append_cnt, prefill ? cache->new_len.data() : n_tokens, prefill ? 2 * B : B, s) !=
+               hipSuccess) {
+      return RLKV_ERR_HIP;
+    }
   }
   const int par = cache->parity[layer];
   if (prefill) {
@@ -628,7 +641,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       if (rlkv_plan_prefill_rows(n_full, B, n_tokens, lh, &dealt_rows, &heavy) != 0) return RLKV_ERR_INVALID_ARG;
       split_rows = heavy;
     }
-    if (launch_prefill_mfma(cache->dv, layer, narrow, len_of(cache->dv, par, layer), prefill->q,
+    if (launch_prefill_mfma(cache->dv, layer, narrow, seqs, order, len_of(cache->dv, par, layer), prefill->q,
                             k, v, prefill->out, stride,
                             max_tok, prefill->softmax_scale * 1.44269504088896340736f, cache->arena + cache->plan.staging,
                             cache->plan.staging_tiles, n_split,
@@ -639,7 +652,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     if (record) ++cache->prof_used;
   }
   if (launch_append(cache->dv, layer, len_of(cache->dv, par, layer), len_of(cache->dv, par ^ 1, layer), k, v,
-                    uniform, stride, n_tokens != nullptr, max_tok, s) != hipSuccess)
+                    uniform, stride, n_tokens ? &seqs : nullptr, max_tok, s) != hipSuccess)
     return RLKV_ERR_HIP;
   cache->parity[layer] = par ^ 1;
   for (int b = 0; b < B; ++b) lh[b] += tokens_of(b);
@@ -712,7 +725,7 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
     }
   }
   const size_t bytes = (size_t)dv.list_pair_off + (size_t)n_pairs * sizeof(PairDesc);
-  bool ok = hipMemcpyAsync(dv.list_base + layer * dv.list_stride, base, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
+  bool ok = launch_fetch(dv.list_base + layer * dv.list_stride, base, bytes, s) == hipSuccess;
   ok = ok && ring_sent(cache->list_ring, slot, s);
   if (!ok) return RLKV_ERR_HIP;
   // A list serves kWorklistSlack tokens of growth.  The layers' rebuilds are spread over that many steps instead of
@@ -925,7 +938,7 @@ rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, cons
     // row-major stores (vector-ALU kernel): the append is a launch of its own; it takes its lengths from the work
     // list, the attention kernel counts the appended token on top of the growth counter, the merge kernel
     // advances the counter - three launches whose arguments are the same at every step
-    if (launch_append(cache->dv, layer, len_of(cache->dv, 0, layer), len_of(cache->dv, 1, layer), k, v, 1, 1, false, 1,
+    if (launch_append(cache->dv, layer, len_of(cache->dv, 0, layer), len_of(cache->dv, 1, layer), k, v, 1, 1, nullptr, 1,
                       s, true) != hipSuccess)
       return RLKV_ERR_HIP;
     if (launch_decode_valu(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, s, e0, e1, 1) !=

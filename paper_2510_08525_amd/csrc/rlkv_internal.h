@@ -74,7 +74,7 @@ struct DeviceView {
   int32_t* slot_pos;              // per compressed (layer, head): [batch][window]
   int32_t* v_wide;                // [n_layers] 1 once a V value of magnitude >= 65536 (or Inf / NaN) has gone into the
                                   // layer's stores or staging (tiled layout): prefill then takes V as bf16
-  int32_t* append_cnt;            // [2][batch] staging: per-sequence token counts; sequence order of a prefill
+  int32_t* append_cnt;            // [2][batch] per-sequence token counts; sequence order of a prefill (batches beyond kArgSeqs)
   char* list_base;                // [n_layers] work-list blocks of list_stride bytes (see ListHeader)
   int64_t list_stride;
   int32_t list_pair_off;          // byte offset of the PairDesc array inside a block
@@ -102,6 +102,37 @@ struct TableUpdates {
   int32_t index[kTableUpdateMax];   // element index into block_table
   int32_t value[kTableUpdateMax];   // page
 };
+
+// Per-sequence token counts of a ragged append or a prefill chunk, and the prefill's sequence order: by value in the
+// kernel arguments, which costs the stream nothing.  (A copy through pinned memory took 10 us of it per call: 4.2 us of
+// copy and a 5.6 us gap behind it.)  A batch beyond kArgSeqs has them written to dv.append_cnt by a kernel first.
+constexpr int kArgSeqs = 128;
+struct SeqCounts {
+  int32_t in_args;                  // 1: the arrays below hold them, 0: dv.append_cnt does
+  int32_t tok[kArgSeqs];            // [sequence]
+};
+// The same in the order in which a prefill's grid takes the sequences (a workgroup asks for both words at once).
+struct SeqOrder {
+  int32_t in_args;
+  int32_t seq[kArgSeqs];            // [place in the order]
+  int32_t tok[kArgSeqs];
+};
+// (the same in all lanes; readfirstlane because the compiler loads through a pointer that is one or the other, takes the
+// result for a lane's own, and everything computed from it with it: 12 % on the blending prefill)
+__device__ inline int tokens_of_seq(const DeviceView& dv, const SeqCounts& seqs, int b) {
+  return __builtin_amdgcn_readfirstlane(seqs.in_args ? seqs.tok[b] : dv.append_cnt[b]);
+}
+__device__ inline void seq_in_order(const DeviceView& dv, const SeqOrder& order, int i, int& b, int& tokens) {
+  if (order.in_args) {
+    b = order.seq[i];
+    tokens = order.tok[i];
+  } else {
+    b = dv.append_cnt[dv.batch + i];
+    tokens = dv.append_cnt[b];
+  }
+  b = __builtin_amdgcn_readfirstlane(b);
+  tokens = __builtin_amdgcn_readfirstlane(tokens);
+}
 
 // ---- store addressing ------------------------------------------------------------
 // Row-major layout (VALU kernel): row `slot` of K (or V) at slot * row_bytes.
@@ -155,9 +186,14 @@ __host__ __device__ inline int32_t* len_of(const DeviceView& dv, int parity, int
 // layer's ListHeader::grow.  `from_list` (a uniform append of one token, the first launch of a decode step that
 // can be recorded): the lengths are taken from the layer's work list and its growth counter instead, both copies
 // of the table take the new lengths, and the counter is left to the merge kernel of the step (advance = 1).
+// `seqs` non-null: a ragged append (n_tokens_uniform unused).
 hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in, int32_t* len_out,
-                         const void* k, const void* v, int n_tokens_uniform, int stride_tokens, bool ragged,
+                         const void* k, const void* v, int n_tokens_uniform, int stride_tokens, const SeqCounts* seqs,
                          int max_tokens, hipStream_t stream, bool from_list = false);
+// Copies `bytes` (a multiple of 8) from pinned host memory to the device by a kernel that reads them over the bus.
+hipError_t launch_fetch(void* dst, const void* pinned_src, size_t bytes, hipStream_t stream);
+// Writes n values of host memory to `dst` through kernel arguments.
+hipError_t launch_write_values(int32_t* dst, const int32_t* values, int n, hipStream_t stream);
 hipError_t launch_reset(const DeviceView& dv, int seq, int64_t slot_pos_elems, hipStream_t stream);
 hipError_t launch_table_update(const DeviceView& dv, const TableUpdates& up, hipStream_t stream);
 // Host-side plan of the shares (share_plan.hip): rounds[p] = rounds of tiles of pair p (0 = none).
@@ -185,7 +221,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
 constexpr int kMergeArgPairs = 512;
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
                           const void* v_new = nullptr, const uint32_t* merge_words = nullptr);
-// Prefill attention of one chunk (counts in dv.append_cnt, lengths before the chunk in len_in):
+// Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):
 // stages the chunk's K/V as tiles in `staging` (staging_tiles tiles per pair), then attends.
 // `gated`: the kernel form with one column group of queries per wavefront, the only one that can blend
 // (Eq. 1: causal and local attention of a full head with a gate below 1).
@@ -196,7 +232,7 @@ hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_
 constexpr int kPrefillSplitSlots = 1024;
 constexpr int kPrefillArgHeads = 64;      // KV heads of a layer whose class lists travel in the prefill kernels' arguments
 constexpr size_t kPrefillSplitSlotBytes = 256 * (size_t)(kHeadDim + 2) * sizeof(float);
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const int32_t* len_in, const void* q,
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
                                const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
                                float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int split_rows, int dealt_rows,
