@@ -78,12 +78,14 @@ __device__ __forceinline__ void tile_accumulate(TileRegs& t, const float (&raw)[
 // attention into st_local when the tile touches the sink or the recent range.  The scores
 // are computed once; the full update runs first because its V clearing (slots past the
 // prefix) is a subset of the local one.
-template <bool GATED>
+// `scored` runs between the scores and the weights: the tile's K registers are free from there on.
+template <bool GATED, typename F>
 __device__ __forceinline__ void process_tile(TileRegs& t, const Frag (&qb)[4], Softmax& st_full, Softmax& st_local,
                                              bool two_sets, int tile, int n_eff, float scale_log2, int kb, int keep_lo,
-                                             int keep_from) {
+                                             int keep_from, F scored) {
   float raw[8];
   tile_scores(t, qb, scale_log2, raw);
+  scored();
   tile_accumulate<false>(t, raw, st_full, tile, n_eff, kb);
   if (GATED && two_sets && (tile * kTile < keep_lo || tile * kTile + kTile > keep_from))
     tile_accumulate<true>(t, raw, st_local, tile, n_eff, kb, keep_lo, keep_from);
@@ -91,22 +93,43 @@ __device__ __forceinline__ void process_tile(TileRegs& t, const Frag (&qb)[4], S
 
 // The gated variant carries two accumulator sets: it is built for one wavefront per SIMD (the
 // configuration the library launches), which leaves it 512 registers.
-template <bool FUSED, bool GATED, bool PAGED>
-__global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, int layer,
+//
+// WAVES = 8 (kWholeWaves): the form for lists of whole pairs (share_plan.hip), two wavefronts per SIMD.  A launch whose
+// `grow` is -1 (one that may be a recorded launch, replayed under other lists) takes the growth from the list's header,
+// and if the list is not of whole pairs, the upper four wavefronts have no tiles and every pair is worked as the
+// four-wavefront form does, to the bit.
+// Bound: a whole-pair launch is a chain of latencies (record, first tiles, merge, store) plus its longest pair at what
+// one CU can draw.  Decode call of 1 / 8 / 32 sequences of 300 tokens, 32 query and 8 KV heads: 7.4 / 7.4 / 8.3 us against
+// 10.6 / 10.5 / 10.7 us of shares and merge launch; 32 of 1500 tokens: 21.9 against 23.9 us.  (Four wavefronts with a tile
+// in flight behind the one in work need 450 registers; two per SIMD cover each other instead.)
+template <bool FUSED, bool GATED, bool PAGED, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView dv, int layer,
                                                                 const uint16_t* __restrict__ q,
                                                                 uint16_t* __restrict__ out, float scale_log2,
                                                                 const uint16_t* __restrict__ k_new,
-                                                                const uint16_t* __restrict__ v_new) {
-  __shared__ float sm_o[4][kMaxGroup][kHeadDim];
-  __shared__ float sm_m[4][kMaxGroup];
-  __shared__ float sm_l[4][kMaxGroup];
+                                                                const uint16_t* __restrict__ v_new, int grow_known,
+                                                                int in_turn) {
+  __shared__ float sm_o[WAVES][kMaxGroup][kHeadDim];
+  __shared__ float sm_m[WAVES][kMaxGroup];
+  __shared__ float sm_l[WAVES][kMaxGroup];
+  constexpr int kThreads = WAVES * 64;
 
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of
   // shares so that its L2 and TLBs see one compact slice of the stores.
   const int n_wg = gridDim.x;
-  const int wg = (n_wg & 7) == 0 ? (blockIdx.x & 7) * (n_wg >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+  // (Not where half of the shares or more are empty, `in_turn`: the others would sit on few XCDs.)
+  const int wg = (n_wg & 7) == 0 && !in_turn ? (blockIdx.x & 7) * (n_wg >> 3) + (blockIdx.x >> 3) : blockIdx.x;
   const WgDesc* __restrict__ wdp = wg_desc_of(dv, layer) + wg;
-  const int grow = list_header(dv, layer)->grow;     // tokens since the list was planned (asked for beside the record)
+  // tokens since the list was planned: asked for beside the record, or (eight wavefronts) known to the host
+  int grow = grow_known, stride = WAVES;               // stride: wavefronts that share a segment's tiles
+  if (WAVES == kRound) {
+    grow = list_header(dv, layer)->grow;
+  } else if (grow_known < 0) {
+    grow = list_header(dv, layer)->grow;
+    if (!list_header(dv, layer)->whole) stride = kRound;
+  } else if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) {
+    list_header(dv, layer)->grow = grow + 1;           // (no workgroup of this launch reads it)
+  }
   const int u_begin = wdp->u_begin, u_end = wdp->u_end;
   // The record this workgroup will start the next layer's launch with: asked for now, so that it is in
   // L2 by then (its record is the first thing a workgroup waits for).  Looked at only at the very end.
@@ -158,7 +181,7 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
       // position n_old goes to slot_new (sink / ring / next row of a full head)
       const int slot_new = (full || n_old < dv.sink) ? n_old : dv.sink + (n_old - dv.sink) % dv.recent;
       const int tile_new = slot_new >> 5;
-      if (tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & 3) == wave) {
+      if (tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & (stride - 1)) == wave) {
         // This wavefront will read the tile that holds the new slot: it writes the row first.
         // Every 16-byte unit below is written by the lane that later loads it, so program
         // order makes the loads see the new row.
@@ -186,6 +209,14 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
           for (int j = 0; j < 8; ++j)
             *reinterpret_cast<uint16_t*>(tile_base + 8192 + j * 1024 + lane * 16 + e * 2) = vn[j];
         }
+        if (WAVES > kRound) {
+          // (no merge kernel follows a list of whole pairs: the fp16 range test is made here; in the four-wavefront
+          // form it cost the launch 2 us)
+          bool wide = false;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) wide |= bf16_beyond_fp16(vn[j]);
+          if (wide) dv.v_wide[layer] = 1;
+        }
         if (lane == 0 && !full)
           dv.slot_pos[dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window + slot_new] = n_old;
       }
@@ -204,12 +235,12 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
       }
     }
     // each wavefront keeps one tile in flight behind the one it is working on
-    int tile = tile_lo + wave;
+    int tile = WAVES > kRound && wave >= stride ? tile_hi : tile_lo + wave;
     TileRegs ra, rb;
     if (tile < tile_hi) load_tile(ra, store.at(tile), lane);
     // address of the tile after this one; looked up one iteration ahead so that a block-table
     // read never sits between a wavefront and its next loads
-    const char* next_base = store.at(tile + kRound);
+    const char* next_base = store.at(tile + stride);
     // the next pair's record, for the (rare) share that crosses a pair boundary
     PairDesc pd_next = pd;
     if (seg_end < u_end) pd_next = pairs[pi + 1];     // fetched early, looked at after the segment
@@ -231,38 +262,50 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
     // its own loads only and the next tile's stay in flight beside it.  (With one loop and a conditional
     // load the compiler has to wait for every load in flight before the work, the next tile's included.)
     auto work = [&](TileRegs& t, int tl) {
-      process_tile<GATED>(t, qb, st[0], st[GATED ? 1 : 0], two_sets, tl, n_eff, scale_log2, kb, keep_lo, keep_from);
+      process_tile<GATED>(t, qb, st[0], st[GATED ? 1 : 0], two_sets, tl, n_eff, scale_log2, kb, keep_lo, keep_from,
+                          [] {});
     };
-    if constexpr (GATED) {
+    if constexpr (WAVES > kRound) {
+      // Half the registers per wavefront: one image, refilled as it is used up - K behind the scores, V behind the
+      // products.
+      for (; tile + stride < tile_hi; tile += stride) {
+        const char* refill = next_base;
+        next_base = store.at(tile + 2 * stride);
+        process_tile<GATED>(ra, qb, st[0], st[GATED ? 1 : 0], two_sets, tile, n_eff, scale_log2, kb, keep_lo, keep_from,
+                            [&] { load_tile_k(ra, refill, lane); });
+        load_tile_v(ra, refill, lane);
+      }
+      if (tile < tile_hi) work(ra, tile);
+    } else if constexpr (GATED) {
       // (the variant with two accumulator sets has no registers left for that and keeps the one loop)
       while (tile < tile_hi) {
-        if (tile + kRound < tile_hi) load_tile(rb, next_base, lane);
-        next_base = store.at(tile + 2 * kRound);
+        if (tile + stride < tile_hi) load_tile(rb, next_base, lane);
+        next_base = store.at(tile + 2 * stride);
         work(ra, tile);
         ra = rb;
-        tile += kRound;
+        tile += stride;
       }
     } else
     for (;;) {
-      if (tile + kRound >= tile_hi) {
+      if (tile + stride >= tile_hi) {
         if (tile < tile_hi) work(ra, tile);
         break;
       }
       load_tile(rb, next_base, lane);
-      next_base = store.at(tile + 2 * kRound);
+      next_base = store.at(tile + 2 * stride);
       work(ra, tile);
-      tile += kRound;
-      if (tile + kRound >= tile_hi) {
+      tile += stride;
+      if (tile + stride >= tile_hi) {
         work(rb, tile);
         break;
       }
       load_tile(ra, next_base, lane);
-      next_base = store.at(tile + 2 * kRound);
+      next_base = store.at(tile + 2 * stride);
       work(rb, tile);
-      tile += kRound;
+      tile += stride;
     }
 
-    float held[(kMaxGroup * kHeadDim) / kBlock];                     // full-attention results of a whole pair
+    float held[(kMaxGroup * kHeadDim) / kThreads];                     // full-attention results of a whole pair
 #pragma unroll
     for (int set = 0; set < (GATED ? 2 : 1); ++set) {
       if (set == 1 && !two_sets) break;
@@ -283,14 +326,14 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
       }
       __syncthreads();
       int it = 0;
-      for (int idx = tid; idx < G * kHeadDim; idx += kBlock, ++it) {
+      for (int idx = tid; idx < G * kHeadDim; idx += kThreads, ++it) {
         const int g = idx / kHeadDim, d = idx % kHeadDim;
         float M = sm_m[0][g];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) M = fmaxf(M, sm_m[w][g]);
+        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][g]);
         float O = 0.f, L = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
+        for (int w = 0; w < WAVES; ++w) {
           const float sc = exp2_or_zero(sm_m[w][g], M);
           O += sc * sm_o[w][g][d];
           L += sc * sm_l[w][g];
@@ -325,24 +368,28 @@ __global__ __launch_bounds__(kBlock, 1) void decode_mfma_kernel(DeviceView dv, i
 }  // namespace
 
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const void* q, void* out, float scale_log2,
-                              const void* k_new, const void* v_new, hipStream_t stream, hipEvent_t ev_start,
-                              hipEvent_t ev_stop) {
-  const dim3 grid(dv.n_wg), block(kBlock);
+                              const void* k_new, const void* v_new, bool whole, int grow, bool few, hipStream_t stream,
+                              hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const dim3 grid(dv.n_wg);
   // (the plain launch when no timestamps are asked for: that form can be recorded into a graph)
-#define RLKV_LAUNCH(F, GT, PG)                                                                                    \
+#define RLKV_LAUNCH(F, GT, PG, W)                                                                                 \
   do {                                                                                                            \
+    const dim3 block(W * 64);                                                                                     \
     if (ev_start || ev_stop)                                                                                      \
-      hipExtLaunchKernelGGL((decode_mfma_kernel<F, GT, PG>), grid, block, 0, stream, ev_start, ev_stop, 0, dv,    \
+      hipExtLaunchKernelGGL((decode_mfma_kernel<F, GT, PG, W>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, \
                             layer, (const uint16_t*)q, (uint16_t*)out, scale_log2, (const uint16_t*)k_new,       \
-                            (const uint16_t*)v_new);                                                              \
+                            (const uint16_t*)v_new, grow, (int)(few && !whole));                                  \
     else                                                                                                          \
-      hipLaunchKernelGGL((decode_mfma_kernel<F, GT, PG>), grid, block, 0, stream, dv, layer, (const uint16_t*)q,  \
-                         (uint16_t*)out, scale_log2, (const uint16_t*)k_new, (const uint16_t*)v_new);             \
+      hipLaunchKernelGGL((decode_mfma_kernel<F, GT, PG, W>), grid, block, 0, stream, dv, layer,                   \
+                         (const uint16_t*)q, (uint16_t*)out, scale_log2, (const uint16_t*)k_new,                  \
+                         (const uint16_t*)v_new, grow, (int)(few && !whole));                                     \
   } while (0)
-#define RLKV_PICK(F, GT) do { if (dv.page_shift >= 0) RLKV_LAUNCH(F, GT, true); else RLKV_LAUNCH(F, GT, false); } while (0)
+#define RLKV_WAVES(F, GT, PG) do { if (whole) RLKV_LAUNCH(F, GT, PG, kWholeWaves); else RLKV_LAUNCH(F, GT, PG, kRound); } while (0)
+#define RLKV_PICK(F, GT) do { if (dv.page_shift >= 0) RLKV_WAVES(F, GT, true); else RLKV_WAVES(F, GT, false); } while (0)
   if (k_new) { if (gated) RLKV_PICK(true, true); else RLKV_PICK(true, false); }
   else       { if (gated) RLKV_PICK(false, true); else RLKV_PICK(false, false); }
 #undef RLKV_PICK
+#undef RLKV_WAVES
 #undef RLKV_LAUNCH
   return hipGetLastError();
 }

@@ -7,9 +7,12 @@
 // attention does not depend on the order of the rows, so ring slots are read in slot
 // order.
 //
-// Mapping: a wavefront reads whole rows with 128-bit loads (16 lanes cover a 256-byte
-// bf16 row, 32 lanes a 512-byte fp32 row); every lane keeps the 8 (4) elements of its
-// column chunk of Q for all heads of the group, so a K/V row is loaded once per group.
+// Mapping: a wavefront reads whole rows with 128-bit loads, 16 lanes per row (a 256-byte bf16 row
+// in one load, a 512-byte fp32 row in two); every lane keeps its 8 elements of Q for all heads of the group, so a
+// K/V row is loaded once per group.  (32 lanes per fp32 row, 4 elements each, took twice the reductions, exponentials and
+// batches per tile.  With the batches asked for ahead and one round of tiles per workgroup, fp32 decode of one sequence of
+// 1000 tokens: 16.3 -> 11.3 us a call, 8 of 5000: 43.2 -> 35.2 us; with the append in the same launch, a step of one
+// sequence of 1000 tokens: 21 -> 13 us.)
 // Dot products are reduced across the lanes of a row with DPP row rotations; each group
 // of lanes that shares a row index runs its own online softmax, and the streams are
 // merged at the end of the segment (lane groups by shuffles, wavefronts through LDS).
@@ -41,33 +44,38 @@ __device__ inline float row_sum16(float x) {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct Elem;
 template <> struct Elem<float> {
-  static constexpr int kPerLane = 4;
-  struct Q { float f[4]; };
-  __device__ static void unpack(const uint4& r, float* f) {
-    f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y);
-    f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
+  static constexpr int kChunks = 2;            // 16-byte chunks of a row per lane
+  struct Q { float f[8]; };
+  __device__ static void unpack(const uint4 (&r)[2], float* f) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      f[4 * i + 0] = __uint_as_float(r[i].x); f[4 * i + 1] = __uint_as_float(r[i].y);
+      f[4 * i + 2] = __uint_as_float(r[i].z); f[4 * i + 3] = __uint_as_float(r[i].w);
+    }
   }
-  __device__ static Q query(const uint4& r) { Q q; unpack(r, q.f); return q; }
-  __device__ static float dot(const Q& q, const uint4& k) {
-    float kf[4];
+  __device__ static Q query(const uint4 (&r)[2]) { Q q; unpack(r, q.f); return q; }
+  __device__ static float dot(const Q& q, const uint4 (&k)[2]) {
+    float kf[8];
     unpack(k, kf);
     float d = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) d = fmaf(q.f[e], kf[e], d);
+    for (int e = 0; e < 8; ++e) d = fmaf(q.f[e], kf[e], d);
     return d;
   }
 };
 template <> struct Elem<uint16_t> {
-  static constexpr int kPerLane = 8;
+  static constexpr int kChunks = 1;
   struct Q { uint4 packed; };
-  __device__ static void unpack(const uint4& r, float* f) {
+  __device__ static void unpack(const uint4 (&rr)[1], float* f) {
+    const uint4& r = rr[0];
     f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
     f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
     f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xffff0000u);
     f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xffff0000u);
   }
-  __device__ static Q query(const uint4& r) { return Q{r}; }
-  __device__ static float dot(const Q& q, const uint4& k) {
+  __device__ static Q query(const uint4 (&r)[1]) { return Q{r[0]}; }
+  __device__ static float dot(const Q& q, const uint4 (&kk)[1]) {
+    const uint4& k = kk[0];
     float d = 0.f;
     d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.x), __builtin_bit_cast(bf16x2, k.x), d, false);
     d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.y), __builtin_bit_cast(bf16x2, k.y), d, false);
@@ -82,12 +90,17 @@ __device__ inline float exp2_or_zero(float m, float ref) {
   return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - ref);
 }
 
-template <typename T, int GB>
-__global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int layer,
+// FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the tile with the new
+// slot writes the row before it loads the tile, every 16 bytes by the lane that later loads them.
+template <typename T, int GB, bool FUSED>
+__global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, int layer,
                                                              const T* __restrict__ q, T* __restrict__ out,
-                                                             float scale_log2, int appended) {
-  constexpr int EPL = Elem<T>::kPerLane;        // elements per lane per 128-bit load
-  constexpr int LPR = kHeadDim / EPL;           // lanes per row
+                                                             float scale_log2, const T* __restrict__ k_new,
+                                                             const T* __restrict__ v_new, int grow_known) {
+  constexpr int LPR = 16;                       // lanes per row
+  constexpr int EPL = kHeadDim / LPR;           // elements per lane
+  constexpr int CH = Elem<T>::kChunks;          // 16-byte chunks they come in, 16 chunks apart
+  constexpr int EPC = EPL / CH;                 // elements per chunk
   constexpr int RPL = 64 / LPR;                 // rows per wavefront load
   constexpr int U = 4;                          // row loads in flight per K and per V
   constexpr int kBatches = kTile / (RPL * U);
@@ -98,8 +111,10 @@ __global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int 
 
   const int wg = blockIdx.x;
   const WgDesc* __restrict__ wdp = wg_desc_of(dv, layer) + wg;
-  // tokens since the list was planned (`appended`: by this step's append launch, not counted there yet)
-  const int grow = list_header(dv, layer)->grow + appended;
+  // tokens since the list was planned: known to the host, or asked for beside the record
+  const int grow = grow_known >= 0 ? grow_known : list_header(dv, layer)->grow;
+  if (FUSED && grow_known >= 0 && blockIdx.x == 0 && threadIdx.x == 0)
+    list_header(dv, layer)->grow = grow + 1;           // (no workgroup of this launch reads it)
   const int u_begin = wdp->u_begin, u_end = wdp->u_end;
   if (u_begin >= u_end) return;
   int pi = wdp->first_pair;
@@ -123,24 +138,56 @@ __global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int 
     if (seg_end < u_end) pd_next = pairs[pi + 1];     // fetched early, looked at after the segment
 
     const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
-    const int n = pd.n_build + grow;
+    const int n_old = pd.n_build + grow;
+    const int n = FUSED ? n_old + 1 : n_old;
     const bool full = pd.full != 0;
     const int n_eff = full ? n : (n < dv.window ? n : dv.window);
-    const char* kst = dv.kv_base + pd.koff;
-    const char* vst = kst + (int64_t)pd.cap * dv.row_bytes;
+    char* kst = dv.kv_base + pd.koff;
+    char* vst = kst + (int64_t)pd.cap * dv.row_bytes;
     // the list was built with room to grow: tiles past the valid prefix are still empty
     const int tiles_valid = (n_eff + kTile - 1) / kTile;
     const int tile_hi = r_hi * kRound < tiles_valid ? r_hi * kRound : tiles_valid;
+
+    if (FUSED) {
+      // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads
+      // either during this launch)
+      if (h == 0 && tile_lo == 0 && tid == 0) { len_of(dv, 0, layer)[b] = n; len_of(dv, 1, layer)[b] = n; }
+      const int slot_new = (full || n_old < dv.sink) ? n_old : dv.sink + (n_old - dv.sink) % dv.recent;
+      const int tile_new = slot_new / kTile;
+      if (tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & 3) == wave) {
+        if (rg == slot_new % RPL) {                        // the lanes that load row slot_new below
+          const int64_t src = ((int64_t)b * dv.n_kv_heads + h) * dv.row_bytes + c * 16;
+          const int64_t dst = (int64_t)slot_new * dv.row_bytes + c * 16;
+          uint4 kn[CH], vn[CH];
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            kn[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k_new) + src + i * LPR * 16);
+            vn[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(v_new) + src + i * LPR * 16);
+          }
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            *reinterpret_cast<uint4*>(kst + dst + i * LPR * 16) = kn[i];
+            *reinterpret_cast<uint4*>(vst + dst + i * LPR * 16) = vn[i];
+          }
+        }
+        if (lane == 0 && !full)
+          dv.slot_pos[dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window + slot_new] = n_old;
+      }
+    }
 
     for (int gb = 0; gb < G; gb += GB) {
       const int gcount = G - gb < GB ? G - gb : GB;
       typename Elem<T>::Q qf[GB];
 #pragma unroll
       for (int g = 0; g < GB; ++g) {
-        uint4 r = make_uint4(0, 0, 0, 0);                  // (no such head: zeros, in either element type)
-        if (g < gcount) {
-          const int64_t qrow = (int64_t)b * dv.n_q_heads + h * G + gb + g;
-          r = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) + (qrow * kHeadDim + c * EPL) * sizeof(T));
+        uint4 r[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+          r[i] = make_uint4(0, 0, 0, 0);                   // (no such head: zeros, in either element type)
+          if (g < gcount) {
+            const int64_t qrow = (int64_t)b * dv.n_q_heads + h * G + gb + g;
+            r[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) + qrow * dv.row_bytes + (i * LPR + c) * 16);
+          }
         }
         qf[g] = Elem<T>::query(r);
       }
@@ -162,68 +209,94 @@ __global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int 
         for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
       }
 
-      for (int tile = tile_lo + wave; tile < tile_hi; tile += 4) {
-        if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) {
-          tile += (recent_tile0 - tile - 1) / 4 * 4;                   // hop over the evicted middle
-          continue;
+      // The wavefront's rows in batches of U loads of K and of V.  Two register images that swap roles: a batch is asked
+      // for before the one ahead of it is worked on, so that a latency is paid once and not per batch.
+      struct Rows { uint4 k[U][CH], v[U][CH]; };
+      auto row_of = [&](int tile, int bt, int u) { return tile * kTile + (bt * U + u) * RPL + rg; };
+      auto counts = [&](int tok) { return tok < n_eff && (pass == 0 || tok < keep_lo || tok >= keep_from); };
+      auto load = [&](Rows& r, int tile, int bt) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int tok = row_of(tile, bt, u);
+          const int tc = counts(tok) ? tok : n_eff - 1;      // stay inside the valid prefix
+          const int64_t off = (int64_t)tc * dv.row_bytes + c * 16;
+          // rows are read once per step: stream them past the caches
+#pragma unroll
+          for (int i = 0; i < CH; ++i) {
+            const u32x4 kk = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kst + off + i * LPR * 16));
+            const u32x4 vv = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vst + off + i * LPR * 16));
+            r.k[u][i] = make_uint4(kk.x, kk.y, kk.z, kk.w);
+            r.v[u][i] = make_uint4(vv.x, vv.y, vv.z, vv.w);
+          }
         }
-        const int tok0 = tile * kTile;
-#pragma unroll 1
-        for (int bt = 0; bt < kBatches; ++bt) {
-          uint4 kr[U], vr[U];
-          bool valid[U];
+      };
+      auto work = [&](Rows& r, int tile, int bt) {
+        float s[U][GB];
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int tok = tok0 + (bt * U + u) * RPL + rg;
-            valid[u] = tok < n_eff && (pass == 0 || tok < keep_lo || tok >= keep_from);
-            const int tc = valid[u] ? tok : n_eff - 1;       // stay inside the valid prefix
-            const int64_t off = (int64_t)tc * dv.row_bytes + c * 16;
-            // rows are read once per step: stream them past the caches
-            const u32x4 kk = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kst + off));
-            const u32x4 vv = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vst + off));
-            kr[u] = make_uint4(kk.x, kk.y, kk.z, kk.w);
-            vr[u] = make_uint4(vv.x, vv.y, vv.z, vv.w);
-          }
-          float s[U][GB];
+        for (int u = 0; u < U; ++u) {
+          const bool on = counts(row_of(tile, bt, u));
+          // (a row that does not count may be the one another wavefront is writing: nothing of it may reach a sum)
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-#pragma unroll
-            for (int g = 0; g < GB; ++g) {
-              float d = Elem<T>::dot(qf[g], kr[u]);
-              d = row_sum16(d);
-              if (LPR == 32) d += __shfl_xor(d, 16);
-              s[u][g] = valid[u] ? d * scale_log2 : -INFINITY;
-            }
-          }
-          float p[U][GB];
+          for (int i = 0; i < CH; ++i)
+            if (FUSED && !on) r.v[u][i] = make_uint4(0, 0, 0, 0);
 #pragma unroll
           for (int g = 0; g < GB; ++g) {
-            float mx = s[0][g];
-#pragma unroll
-            for (int u = 1; u < U; ++u) mx = fmaxf(mx, s[u][g]);
-            const float m_new = fmaxf(m[g], mx);
-            const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m[g] - m_ref);   // 2^-inf = 0 for a fresh stream
-            m[g] = m_new;
-            float ps_ = 0.f;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              p[u][g] = __builtin_amdgcn_exp2f(s[u][g] - m_ref);
-              ps_ += p[u][g];
-            }
-            l[g] = l[g] * alpha + ps_;
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
+            float d = Elem<T>::dot(qf[g], r.k[u]);
+            d = row_sum16(d);
+            s[u][g] = on ? d * scale_log2 : -INFINITY;
           }
+        }
+        float p[U][GB];
+#pragma unroll
+        for (int g = 0; g < GB; ++g) {
+          float mx = s[0][g];
+#pragma unroll
+          for (int u = 1; u < U; ++u) mx = fmaxf(mx, s[u][g]);
+          const float m_new = fmaxf(m[g], mx);
+          const float m_ref = m_new == -INFINITY ? 0.f : m_new;
+          const float alpha = __builtin_amdgcn_exp2f(m[g] - m_ref);   // 2^-inf = 0 for a fresh stream
+          m[g] = m_new;
+          float ps_ = 0.f;
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            float vf[EPL];
-            Elem<T>::unpack(vr[u], vf);
-#pragma unroll
-            for (int g = 0; g < GB; ++g)
-#pragma unroll
-              for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p[u][g], vf[e], acc[g][e]);
+            p[u][g] = __builtin_amdgcn_exp2f(s[u][g] - m_ref);
+            ps_ += p[u][g];
           }
+          l[g] = l[g] * alpha + ps_;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          float vf[EPL];
+          Elem<T>::unpack(r.v[u], vf);
+#pragma unroll
+          for (int g = 0; g < GB; ++g)
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p[u][g], vf[e], acc[g][e]);
+        }
+      };
+      // the tile at or behind `tile` (in this wavefront's steps of 4) that this pass looks at
+      auto settle = [&](int tile) {
+        if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + 3) / 4 * 4;   // hop over the evicted middle
+        return tile;
+      };
+      int tile = settle(tile_lo + wave), bt = 0;
+      auto step_on = [&]() { if (++bt == kBatches) { bt = 0; tile = settle(tile + 4); } };
+      if (tile < tile_hi) {
+        Rows ra, rb;
+        load(ra, tile, bt);
+        for (;;) {
+          int wt = tile, wb = bt;
+          step_on();
+          if (tile >= tile_hi) { work(ra, wt, wb); break; }
+          load(rb, tile, bt);
+          work(ra, wt, wb);
+          wt = tile; wb = bt;
+          step_on();
+          if (tile >= tile_hi) { work(rb, wt, wb); break; }
+          load(ra, tile, bt);
+          work(rb, wt, wb);
         }
       }
 
@@ -246,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int 
 #pragma unroll
         for (int g = 0; g < GB; ++g) {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) sm_o[wave][g][c * EPL + e] = acc[g][e];
+          for (int e = 0; e < EPL; ++e) sm_o[wave][g][(e / EPC * LPR + c) * EPC + e % EPC] = acc[g][e];
           if (c == 0) { sm_m[wave][g] = m[g]; sm_l[wave][g] = l[g]; }
         }
       }
@@ -293,22 +366,22 @@ __global__ __launch_bounds__(kBlock) void decode_valu_kernel(DeviceView dv, int 
   }
 }
 
-template <typename T>
-hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
-                    hipStream_t stream, hipEvent_t e0, hipEvent_t e1, int appended) {
+template <typename T, bool FUSED>
+hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2, const void* k_new,
+                    const void* v_new, int grow, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid(dv.n_wg), block(kBlock);
-  const T* qp = (const T*)q;
+  const T *qp = (const T*)q, *kp = (const T*)k_new, *vp = (const T*)v_new;
   T* op = (T*)out;
   const int G = dv.group;
   // (without events: the plain launch, which a stream capture can record)
 #define RLKV_LAUNCH_VALU(GB)                                                                                         \
   do {                                                                                                               \
     if (e0 || e1)                                                                                                    \
-      hipExtLaunchKernelGGL((decode_valu_kernel<T, GB>), grid, block, 0, stream, e0, e1, 0, dv, layer, qp, op,      \
-                            scale_log2, appended);                                                                   \
+      hipExtLaunchKernelGGL((decode_valu_kernel<T, GB, FUSED>), grid, block, 0, stream, e0, e1, 0, dv, layer, qp,   \
+                            op, scale_log2, kp, vp, grow);                                                           \
     else                                                                                                             \
-      hipLaunchKernelGGL((decode_valu_kernel<T, GB>), grid, block, 0, stream, dv, layer, qp, op, scale_log2,        \
-                         appended);                                                                                  \
+      hipLaunchKernelGGL((decode_valu_kernel<T, GB, FUSED>), grid, block, 0, stream, dv, layer, qp, op, scale_log2, \
+                         kp, vp, grow);                                                                              \
   } while (0)
   if (G <= 1) RLKV_LAUNCH_VALU(1);
   else if (G <= 2) RLKV_LAUNCH_VALU(2);
@@ -321,11 +394,14 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
 
 }  // namespace
 
-hipError_t launch_decode_valu(const DeviceView& dv, int layer, bool /*gated: decided per pair*/,
-                              const void* q, void* out, float scale_log2, hipStream_t stream, hipEvent_t ev_start,
-                              hipEvent_t ev_stop, int appended) {
-  return dv.dtype == RLKV_F32 ? launch_t<float>(dv, layer, q, out, scale_log2, stream, ev_start, ev_stop, appended)
-                              : launch_t<uint16_t>(dv, layer, q, out, scale_log2, stream, ev_start, ev_stop, appended);
+hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
+                              const void* k_new, const void* v_new, int grow, hipStream_t stream, hipEvent_t ev_start,
+                              hipEvent_t ev_stop) {
+  if (dv.dtype == RLKV_F32)
+    return k_new ? launch_t<float, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop)
+                 : launch_t<float, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop);
+  return k_new ? launch_t<uint16_t, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop)
+               : launch_t<uint16_t, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop);
 }
 
 }  // namespace rlkv

@@ -159,6 +159,9 @@ struct rlkv_cache {
   std::vector<int32_t> max_len;     // host copy [B]
   std::vector<int32_t> len_host;    // host mirror of the lengths [L][B]
   std::vector<int32_t> wl_slack;    // [L] tokens the layer's work list is still valid for; -1 = rebuild
+  std::vector<int32_t> list_grow;   // [L] tokens since the layer's work list was planned (steps prepared included)
+  std::vector<int32_t> list_used;   // [L] workgroups the layer's list of shares uses
+  std::vector<uint8_t> list_whole;  // [L] the layer's work list is one of whole pairs
   std::vector<int64_t> decode_calls; // [L] decode launches so far (fused or not): the clock of the rebuild schedule
   std::vector<uint8_t> step_ready;  // [L] a fused step was prepared (rlkv_append_decode_prepare) and no launch has run since
   int64_t lists_built = 0;          // work lists planned and sent so far
@@ -302,6 +305,9 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
   c->max_len.assign(cfg->max_len, cfg->max_len + B);
   c->len_host.assign((size_t)L * B, 0);
   c->wl_slack.assign((size_t)L, -1);
+  c->list_grow.assign((size_t)L, 0);
+  c->list_whole.assign((size_t)L, 0);
+  c->list_used.assign((size_t)L, 0);
   c->decode_calls.assign((size_t)L, 0);
   c->step_ready.assign((size_t)L, 0);
   c->parity.assign((size_t)L, 0);
@@ -659,12 +665,39 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
   // the work list tracks growth as one number per layer: uniform appends keep it valid
   int32_t& slack = cache->wl_slack[layer];
   slack = (!n_tokens && slack >= max_tok) ? slack - max_tok : -1;
+  cache->list_grow[layer] += max_tok;        // (a list that does not survive the append starts at 0 again)
   return RLKV_OK;
 }
 
 // Makes sure the layer's work list covers the current lengths plus `growth` more tokens.  The list
 // is planned here, on the host, from the mirror of the lengths (see share_plan.hip), written into
 // a pinned staging slot and copied to the device on `s`: no kernel, no synchronisation.
+// Where a list of whole pairs (one workgroup per pair, no partials, no merge launch) takes over.  It saves the merge
+// launch (3.3 us, and the host's time for it) and costs the time that the longest pair takes one CU beyond an even share
+// of all rows: a CU draws about 100 GB/s when many do (64 pairs), 190 GB/s when few do (8 pairs).
+// Measured, whole pairs against shares, 32 query and 8 KV heads, half the heads compressed: one sequence of 1000 / 1500 /
+// 2000 tokens 8.5 / 10.4 / 13.9 against 10.5 / 10.6 / 10.5 us; 8 of 500 / 1000: 8.0 / 11.2 against 10.4 / 10.5 us;
+// 32 of 1000 / 2000: 16.2 / 27.5 against 19.9 / 28.0 us.
+// Row-major stores (four wavefronts, no matrix cores; fp32): 8 sequences of 100 / 300 tokens 8.7 / 15.4 against 12 us.
+static bool wants_whole_pairs(const rlkv_cache_t* cache, int32_t layer) {
+  const DeviceView& dv = cache->dv;
+  const int B = dv.batch, H = dv.n_kv_heads;
+  const int32_t* lh = cache->len_host.data() + (size_t)layer * B;
+  const uint8_t* mask = cache->mask.data() + (size_t)layer * H;
+  int64_t n_full = 0, pairs = 0, longest = 0, all = 0;
+  for (int h = 0; h < H; ++h) n_full += mask[h] ? 1 : 0;
+  for (int b = 0; b < B; ++b) {
+    if (!cache->active[b]) continue;
+    pairs += H;
+    const int64_t n = lh[b], n_comp = std::min<int64_t>(n, dv.window);
+    longest = std::max(longest, n_full > 0 ? n : n_comp);
+    all += n_full * n + (H - n_full) * n_comp;
+  }
+  const int64_t excess = (longest - all / dv.n_wg) * 2 * dv.row_bytes;
+  const int64_t most = dv.kernel != RLKV_KERNEL_MFMA ? kWholeExcessRows : pairs <= kWholeFewPairs ? kWholeExcessFew : kWholeExcess;
+  return pairs <= dv.n_wg && excess <= most;
+}
+
 static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int growth, hipStream_t s) {
   if (cache->wl_slack[layer] >= growth) return RLKV_OK;
   const DeviceView& dv = cache->dv;
@@ -681,7 +714,9 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   int32_t* wg_begin = cache->plan_begin.data();
   int32_t* seg_first = cache->plan_first.data();
   int32_t* seg_count = cache->plan_count.data();
-  plan_shares(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
+  const bool whole = wants_whole_pairs(cache, layer);
+  if (whole) plan_whole_pairs(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
+  else cache->list_used[layer] = plan_shares(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
 
   int slot;
   char* base = ring_take(cache->list_ring, &slot);
@@ -690,6 +725,7 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   WgDesc* wd = reinterpret_cast<WgDesc*>(base + sizeof(ListHeader));
   PairDesc* pd = reinterpret_cast<PairDesc*>(base + dv.list_pair_off);
   memset(hd, 0, sizeof(ListHeader));          // grow = 0: the lengths in the records are the current ones
+  hd->whole = whole ? 1 : 0;
   int32_t us = 0;
   for (int pi = 0; pi < n_pairs; ++pi) {
     const int b = pi / H, h = pi % H;
@@ -734,6 +770,8 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   // only lives until then.
   const int64_t phase = (cache->decode_calls[layer] + (int64_t)layer * kWorklistSlack / dv.n_layers) % kWorklistSlack;
   cache->wl_slack[layer] = kWorklistSlack - (int32_t)phase;
+  cache->list_grow[layer] = 0;
+  cache->list_whole[layer] = whole ? 1 : 0;
   ++cache->lists_built;
   return RLKV_OK;
 }
@@ -782,12 +820,19 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
   hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
   const bool gated = cache->layer_gated[layer] != 0;
+  // A launch that is recorded may run under other lists and lengths than the present ones, and a step that was prepared may
+  // have run (as a replay) or not: both take the growth from the list's header.
+  const bool capturing = stream_is_capturing(s);
+  const bool whole = cache->list_whole[layer] != 0;
+  const int grow = !whole || capturing || cache->step_ready[layer] ? -1 : cache->list_grow[layer];
+  const bool few = 2 * cache->list_used[layer] <= dv.n_wg && !capturing;
   hipError_t e = dv.kernel == RLKV_KERNEL_MFMA
-                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, s, e0, e1)
-                     : launch_decode_valu(dv, layer, gated, q, out, scale_log2, s, e0, e1);
+                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, whole, grow, few, s, e0, e1)
+                     : launch_decode_valu(dv, layer, q, out, scale_log2, nullptr, nullptr, grow, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
   ++cache->decode_calls[layer];
+  if (whole && !capturing) return RLKV_OK;       // every pair was finished by its one workgroup
   const uint32_t* words = (cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * dv.n_pairs;
   if (launch_combine(dv, layer, out, s, 0, nullptr, words) != hipSuccess) return RLKV_ERR_HIP;
@@ -905,16 +950,16 @@ rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, voi
   // the mirrors take the step now; the launch (or the replay of a recorded launch) performs it on the device
   for (int b = 0; b < B; ++b) lh[b] += cache->active[b] ? 1 : 0;
   cache->wl_slack[layer] -= 1;
+  cache->list_grow[layer] += 1;
   ++cache->decode_calls[layer];
   cache->step_ready[layer] = 1;
   return RLKV_OK;
 }
 
-rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q,
-                                        void* out, float softmax_scale, void* stream) {
-  if (!cache || !k || !v || !q || !out) return RLKV_ERR_INVALID_ARG;
-  if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
-  if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
+// `grow_known`: the step was prepared just now and none before it is outstanding, so that the host's count of the list's
+// growth is the device's.
+static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q, void* out,
+                                 float softmax_scale, void* stream, bool grow_known) {
   if (hipSetDevice(cache->cfg.device) != hipSuccess) return RLKV_ERR_HIP;
   hipStream_t s = as_stream(stream);
   const bool capturing = stream_is_capturing(s);
@@ -930,22 +975,18 @@ rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, cons
   hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
   hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
   const bool tiled = cache->dv.kernel == RLKV_KERNEL_MFMA;
-  if (tiled) {
-    if (launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v, s, e0, e1) !=
-        hipSuccess)
-      return RLKV_ERR_HIP;
-  } else {
-    // row-major stores (vector-ALU kernel): the append is a launch of its own; it takes its lengths from the work
-    // list, the attention kernel counts the appended token on top of the growth counter, the merge kernel
-    // advances the counter - three launches whose arguments are the same at every step
-    if (launch_append(cache->dv, layer, len_of(cache->dv, 0, layer), len_of(cache->dv, 1, layer), k, v, 1, 1, nullptr, 1,
-                      s, true) != hipSuccess)
-      return RLKV_ERR_HIP;
-    if (launch_decode_valu(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, s, e0, e1, 1) !=
-        hipSuccess)
-      return RLKV_ERR_HIP;
-  }
+  // (a recorded launch takes the form that suits the present lengths)
+  const bool whole = capturing ? wants_whole_pairs(cache, layer) : cache->list_whole[layer] != 0;
+  // (a list of shares has a merge kernel behind it that advances the counter; written by the attention kernel of a
+  // 28-layer step of 16 x 16384 tokens instead, it cost 0.7 us per launch)
+  const int grow = whole && grow_known && !capturing ? cache->list_grow[layer] - 1 : -1;
+  const bool few = !capturing && 2 * cache->list_used[layer] <= cache->dv.n_wg;
+  const hipError_t e = tiled ? launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v,
+                                                  whole, grow, few, s, e0, e1)
+                             : launch_decode_valu(cache->dv, layer, q, out, scale_log2, k, v, grow, s, e0, e1);
+  if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
+  if (grow >= 0) return RLKV_OK;                 // every pair was finished by its one workgroup, the counter is advanced
   // (a recorded launch outlives the work list it was recorded under, so its merge kernel reads the pair records
   // from memory instead of taking them as arguments)
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
@@ -955,13 +996,22 @@ rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, cons
   return RLKV_OK;
 }
 
+rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q,
+                                        void* out, float softmax_scale, void* stream) {
+  if (!cache || !k || !v || !q || !out) return RLKV_ERR_INVALID_ARG;
+  if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
+  if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
+  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, false);
+}
+
 rlkv_status_t rlkv_append_decode(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q,
                                  void* out, float softmax_scale, void* stream) {
   if (!cache || !k || !v || !q || !out) return RLKV_ERR_INVALID_ARG;
   if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
   if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
+  const bool grow_known = !cache->step_ready[layer];
   if (rlkv_status_t st = rlkv_append_decode_prepare(cache, layer, stream)) return st;
-  return rlkv_append_decode_launch(cache, layer, k, v, q, out, softmax_scale, stream);
+  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, grow_known);
 }
 
 int64_t rlkv_worklists_built(const rlkv_cache_t* cache) { return cache ? cache->lists_built : -1; }

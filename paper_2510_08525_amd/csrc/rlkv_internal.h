@@ -19,6 +19,9 @@ constexpr int kPairOverheadUnits = 1;  // units at the head of every pair that c
 constexpr int kRoundCost = 2;          // cost model of the share partition, in half rounds: one round of tiles ...
 constexpr int kPairStartCost = 3;      // ... and the start of a pair (pipeline restart on a new store, Q load,
                                        // merge, output write): about 1.5 rounds, from per-workgroup timestamps
+constexpr int kWholeWaves = 8;         // wavefronts of a workgroup that works one whole pair of the tiled layout
+constexpr int64_t kWholeExcess = 384 << 10, kWholeExcessFew = 768 << 10, kWholeExcessRows = 128 << 10;   // see wants_whole_pairs
+constexpr int kWholeFewPairs = 16;
 constexpr int kWorklistSlack = 32; // tokens a work list stays valid for after it was built
 
 // Work-list records, written by the host (share_plan.hip, ensure_worklist) and read by the attention and merge
@@ -31,7 +34,8 @@ struct ListHeader {      // 64 bytes
                          // brings a new list sets it to 0; the kernels that append advance it (the merge kernel
                          // behind a fused step by 1, a uniform multi-token append by its token count), so that a
                          // decode launch needs no per-step argument and a captured step can be replayed
-  int32_t pad[15];
+  int32_t whole;         // 1: every share is one whole pair (plan_whole_pairs)
+  int32_t pad[14];
 };
 struct PairDesc {        // 40 bytes
   int64_t koff;          // byte offset of the pair's K store from kv_base
@@ -183,13 +187,10 @@ __host__ __device__ inline int32_t* len_of(const DeviceView& dv, int parity, int
 // ---- launchers (defined next to their kernels) -------------------------------------
 // `len_in` is the current copy of the layer's lengths; kernels that append write the
 // advanced lengths to `len_out` (the other copy).  A uniform append also adds its token count to the
-// layer's ListHeader::grow.  `from_list` (a uniform append of one token, the first launch of a decode step that
-// can be recorded): the lengths are taken from the layer's work list and its growth counter instead, both copies
-// of the table take the new lengths, and the counter is left to the merge kernel of the step (advance = 1).
-// `seqs` non-null: a ragged append (n_tokens_uniform unused).
+// layer's ListHeader::grow.  `seqs` non-null: a ragged append (n_tokens_uniform unused).
 hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in, int32_t* len_out,
                          const void* k, const void* v, int n_tokens_uniform, int stride_tokens, const SeqCounts* seqs,
-                         int max_tokens, hipStream_t stream, bool from_list = false);
+                         int max_tokens, hipStream_t stream);
 // Copies `bytes` (a multiple of 8) from pinned host memory to the device by a kernel that reads them over the bus.
 hipError_t launch_fetch(void* dst, const void* pinned_src, size_t bytes, hipStream_t stream);
 // Writes n values of host memory to `dst` through kernel arguments.
@@ -201,19 +202,25 @@ hipError_t launch_table_update(const DeviceView& dv, const TableUpdates& up, hip
 // (the workgroups that hold units of pair p); returns the number of workgroups used.
 int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
                 int32_t* seg_count);
+// The plan of a list of whole pairs, one workgroup each (n_used of them have rounds; at most n_wg do): pairs spread evenly over
+// the shares, so that few pairs still meet all XCDs.
+void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
+                      int32_t* seg_count);
 // ev_start / ev_stop (both or neither): events that receive the kernel's own begin and end
 // timestamps (the dispatch's completion signal), for the measurement aid.
 // `gated`: some full head of the layer has a gate below 1 (two passes for those heads).
-// `appended`: tokens appended by the step's own append launch that the growth counter does not count yet (0 or 1).
-hipError_t launch_decode_valu(const DeviceView& dv, int layer, bool gated, const void* q, void* out,
-                              float scale_log2, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                              int appended = 0);
 // k_new / v_new non-null: fused single-token append (rows [batch][n_kv_heads][1][head_dim]); the advanced
-// lengths are written to both copies of the length table, and the merge kernel that follows must be launched
-// with advance = 1.
+// lengths are written to both copies of the length table.
+// `grow` (lists of whole pairs): tokens since the layer's list was planned, as the host knows them; a fused launch then also
+// writes the advanced growth counter.  -1 (a launch that may be replayed, or whose count the host does not know): read from the
+// list's header, and a fused launch must be followed by the merge kernel with advance = 1.
+hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
+                              const void* k_new, const void* v_new, int grow, hipStream_t stream, hipEvent_t ev_start,
+                              hipEvent_t ev_stop);
+// `few`: at most half of the list's shares hold units.  `whole`: the eight-wavefront form (right for any list, made for lists of whole pairs; with `grow` >= 0 only for those).
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
                               const void* q, void* out, float scale_log2, const void* k_new, const void* v_new,
-                              hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+                              bool whole, int grow, bool few, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 // merge_words (host, [n_pairs], optional): per pair (first partial slot << 12) | partials, as planned for the
 // work list now on the device; with it and at most kMergeArgPairs pairs the merge kernel takes these from its
 // arguments instead of from the pair records (not for a layer with gates: their records carry more).

@@ -20,8 +20,8 @@ namespace rlkv {
 // Deals the rounds out at capacity `cap`; returns the number of workgroups used.  With wg_begin /
 // seg_first / seg_count non-null also records the shares.
 static int deal_rounds(const int32_t* rounds, int n_pairs, int cap, int32_t* wg_begin, int32_t* seg_first,
-                       int32_t* seg_count) {
-  const int per_fresh = cap / kRoundCost;                  // rounds a workgroup takes of a pair it does not start
+                       int32_t* seg_count, bool single = false) {
+  const int per_fresh = single ? 1 : cap / kRoundCost;                  // rounds a workgroup takes of a pair it does not start
   int w = 0, used = 0, us = 0;                             // us: first unit of the pair in the end-to-end numbering
   for (int p = 0; p < n_pairs; ++p) {
     const int r = rounds[p];
@@ -53,12 +53,13 @@ static int deal_rounds(const int32_t* rounds, int n_pairs, int cap, int32_t* wg_
 
 int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
                 int32_t* seg_count) {
-  int64_t cost = 0, units = 0;
+  int64_t cost = 0, units = 0, all_rounds = 0;
   int longest = 0;
   for (int p = 0; p < n_pairs; ++p)
     if (rounds[p] > 0) {
       cost += (int64_t)rounds[p] * kRoundCost + kPairStartCost;
       units += rounds[p] + kPairOverheadUnits;
+      all_rounds += rounds[p];
       if (rounds[p] > longest) longest = rounds[p];
     }
   for (int w = 0; w <= n_wg; ++w) wg_begin[w] = (int32_t)units;      // workgroups the deal does not reach stay empty
@@ -67,6 +68,10 @@ int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin,
     for (int p = 0; p < n_pairs; ++p) seg_first[p] = seg_count[p] = 0;
     return 0;
   }
+  // A list that the grid takes at one round per workgroup: the shortest chain of latencies there is, as long as the merge
+  // kernel still takes a pair's partials in one go (16).
+  if (all_rounds <= n_wg && longest <= 16)
+    return deal_rounds(rounds, n_pairs, kPairStartCost + kRoundCost, wg_begin, seg_first, seg_count, true);
   // feasible for sure: the whole list in one workgroup; look upward from the average
   int64_t cap = (cost + n_wg - 1) / n_wg;
   if (cap < kPairStartCost + kRoundCost) cap = kPairStartCost + kRoundCost;
@@ -83,6 +88,23 @@ int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin,
     cap = probe;
   }
   return deal_rounds(rounds, n_pairs, (int)cap, wg_begin, seg_first, seg_count);
+}
+
+void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
+                      int32_t* seg_count) {
+  int n_used = 0;
+  for (int p = 0; p < n_pairs; ++p) n_used += rounds[p] > 0;
+  int w = 0, us = 0, k = 0;                                // share w is the next whose begin is not set yet
+  for (int p = 0; p < n_pairs; ++p) {
+    seg_first[p] = seg_count[p] = 0;
+    if (rounds[p] == 0) continue;
+    const int at = (int)((int64_t)k++ * n_wg / n_used);    // k-th pair with units: share k * n_wg / n_used
+    while (w <= at) wg_begin[w++] = us;
+    us += rounds[p] + kPairOverheadUnits;
+    seg_first[p] = at;
+    seg_count[p] = 1;
+  }
+  while (w <= n_wg) wg_begin[w++] = us;
 }
 
 }  // namespace rlkv
