@@ -420,17 +420,17 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   const int n_stage = c_hi / kTile + 1;
   const int total = busy && (!split || z == Z - 1) ? n_store + n_stage : 0;
   const int band_lo = c0 - R + 1;            // first chunk index inside the recent band of the wavefront's first query
-  auto needed = [&](int x) {
-    if (x < n_store) return x < hs_lo || x >= hs_hi;
-    const int j = x - n_store;
-    if (j >= stg_lo && j < stg_hi) return false;
-    if (full) return true;
-    const int first = j * kTile;
-    return first < sink_in_chunk || first + kTile - 1 >= band_lo;
-  };
+  // The first tile at or behind x that is not a hot one and that some query of the wavefront may see.  Ranges are hopped
+  // over, not walked: at 16 384 cached tokens the walk over a full head's 512 hot tiles took longer than the tiles here.
+  const int sink_tiles = !full && sink_in_chunk > 0 ? (sink_in_chunk + kTile - 1) / kTile : 0;   // staging tiles with sink positions
+  const int band_tile = !full && band_lo > 0 ? band_lo / kTile : 0;                              // the band's first staging tile
   auto next_needed = [&](int x) {
-    while (x < total && !needed(x)) ++x;
-    return x;
+    if (x >= hs_lo && x < hs_hi) x = hs_hi;
+    if (x < n_store) return x;
+    int j = x - n_store;
+    if (j >= sink_tiles && j < band_tile) j = band_tile;
+    if (j >= stg_lo && j < stg_hi) j = stg_hi;
+    return j + n_store;
   };
   auto address = [&](int x) -> const char* {
     return x < n_store ? store.at(x) : stage + (int64_t)(x - n_store) * kTileBytes;
@@ -449,8 +449,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 
   // The softmax scale rides in the exponent's multiply-add.  A negative one (unusual) would turn the
   // running maximum into a minimum, and zero times the -inf of a masked score is not a number, so
-  // those two are applied to the scores up front instead.
-  const float pre_scale = scale_log2 > 0.f ? 1.f : scale_log2;
+  // those two are applied to the scores up front (general loop) instead.
   const float exp_scale = scale_log2 > 0.f ? scale_log2 : 1.f;
 
   // ---- hot loop: the whole workgroup, tiles through LDS ---------------------------------------
@@ -638,64 +637,83 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 
   // ---- general loop: this wavefront alone, tiles straight from memory -------------------------
   // One tile: mask the scores of each column group and fold the tile into its softmax state.
+  // Bound: vector instructions (the matrix work of a tile and group is 26 instructions of 16 clocks, and two wavefronts
+  // share a SIMD).  So the mask of a tile is chosen once per group, the same in all lanes: none, one comparison per slot
+  // (causal diagonal, end of the store), two (the band's edge), and only a tile whose slots are in no order of positions
+  // (a compressed head's ring) or that holds the end of the sinks looks every position up.  With the hops above, against every
+  // position looked up and compared three ways: 16 x 16 384 tokens in chunks of 2048 (28 query, 4 KV heads, 2 full)
+  // 16.2 -> 15.2 ms, one sequence of 32 500 4.53 -> 4.11 ms, blending heads (8 x 1000 .. 4000) 1157 -> 1020 us.
   auto process = [&](TileRegs& tr, int x) {
     const bool from_store = x < n_store;
     const int tile = from_store ? x : x - n_store;
     const int held = from_store ? n_st : t;                     // slots of this source that hold a position
     const bool complete = tile * kTile + kTile <= held;         // every slot of the tile does
-    // position held by each of the lane's eight slots (-1 = the slot holds nothing)
-    int pos[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int slot = tile * kTile + (e >> 2) * 16 + kb * 4 + (e & 3);
-      int p = from_store ? slot : n_old + slot;
-      if (from_store && !full) p = slot_pos[slot < held ? slot : held - 1];
-      pos[e] = slot < held ? p : -1;
-    }
+    const bool ring = from_store && !full;                      // the slot table says which positions the slots hold
+    const int base = from_store ? tile * kTile : n_old + tile * kTile;      // position of slot 0 (not `ring`)
+    const int slot0 = tile * kTile + kb * 4;                    // the lane's slots: slot0 + offset(e)
+    auto offset = [](int e) { return (e >> 2) * 16 + (e & 3); };
     if (from_store && !complete) {
       // slots of the store that were never written may hold anything: clear their V operands
       uint32_t msk[4];
 #pragma unroll
       for (int jw = 0; jw < 4; ++jw)
-        msk[jw] = (pos[2 * jw] >= 0 ? 0x0000ffffu : 0u) | (pos[2 * jw + 1] >= 0 ? 0xffff0000u : 0u);
+        msk[jw] = (offset(2 * jw) < held - slot0 ? 0x0000ffffu : 0u) | (offset(2 * jw + 1) < held - slot0 ? 0xffff0000u : 0u);
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         tr.v[j].u.x &= msk[0]; tr.v[j].u.y &= msk[1]; tr.v[j].u.z &= msk[2]; tr.v[j].u.w &= msk[3];
       }
     }
     // positions this tile can hold (store tiles of a compressed head: anything before the chunk)
-    const int p_first = from_store ? (full ? tile * kTile : 0) : n_old + tile * kTile;
-    const int p_last = from_store ? (full ? tile * kTile + kTile - 1 : n_old - 1) : n_old + tile * kTile + kTile - 1;
+    const int p_first = ring ? 0 : base;
+    const int p_last = ring ? n_old - 1 : base + kTile - 1;
+    auto masked = [&](int cg, bool local, const float (&raw)[8], float (&sc)[8]) {
+      const int i = qpos[cg];
+      if (ring || (local && p_first < S && p_last >= S)) {
+        int p[8];
+        if (ring) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) p[e] = slot_pos[min(slot0 + offset(e), held - 1)];    // (all asked for side by side)
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) p[e] = base + kb * 4 + offset(e);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int on = (slot0 + offset(e) < held) & (p[e] <= i) & (!local | (p[e] < S) | (i - p[e] < R));
+          sc[e] = on ? raw[e] : -INFINITY;
+        }
+        return;
+      }
+      const int own = i - base - kb * 4;                        // offset of the query's own position
+      const int top = complete ? own : min(own, held - 1 - slot0);
+      if (local && p_first >= S && g_hi[cg] - p_first >= R) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sc[e] = offset(e) <= top && offset(e) > own - R ? raw[e] : -INFINITY;
+      } else if (!complete || p_last > g_lo[cg]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sc[e] = offset(e) <= top ? raw[e] : -INFINITY;
+      } else {
+        // (columns that stand for no query compute on zeros and are never written out)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sc[e] = raw[e];
+      }
+    };
 #pragma unroll
     for (int cg = 0; cg < NG; ++cg) {
       if (!g_on[cg]) continue;
       if (p_first > g_hi[cg]) continue;                                        // wholly above the causal diagonal
       if (!full && p_first >= S && p_last < g_lo[cg] - R + 1) continue;        // wholly before the recent band
       float raw[8], sc[8];
-      tile_scores(tr, qb[cg], pre_scale, raw);
-      const int i = qpos[cg];
-      // a full head's tile at or below every query of the group needs no masking (columns that
-      // stand for no query compute on zeros and are never written out)
-      if (full && complete && p_last <= g_lo[cg]) {
+      raw_scores(tr, qb[cg], raw);
+      if (!hot) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sc[e] = raw[e];
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int p = pos[e];
-          const bool on = p >= 0 && p <= i && (full || p < S || i - p < R);
-          sc[e] = on ? raw[e] : -INFINITY;
-        }
+        for (int e = 0; e < 8; ++e) raw[e] *= scale_log2;
       }
+      masked(cg, !full, raw, sc);
       group_update(tr, sc, exp_scale, st[cg], kb, ones);
       if (GATED && mix && (p_first < S || p_last >= g_lo[cg] - R + 1)) {
         // the same scores under the local mask, into the group's second accumulator set
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int p = pos[e];
-          const bool on = p >= 0 && p <= i && (p < S || i - p < R);
-          sc[e] = on ? raw[e] : -INFINITY;
-        }
+        masked(cg, true, raw, sc);
         group_update(tr, sc, exp_scale, st[GATED ? LOCAL : 0], kb, ones);
       }
     }
