@@ -31,13 +31,15 @@ namespace {
 
 
 // Tiles re-read by many query blocks: ordinary (cached) loads.
-__device__ __forceinline__ void load_tile_cached(TileRegs& r, const char* tile_base, int lane) {
+__device__ __forceinline__ void load_k_cached(TileRegs& r, const char* tile_base, int lane) {
   const char* kb = tile_base + lane * 16;
-  const char* vb = kb + 8192;
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
     for (int s = 0; s < 4; ++s) r.k[hf][s].u = *reinterpret_cast<const uint4*>(kb + hf * 4096 + s * 1024);
+}
+__device__ __forceinline__ void load_v_cached(TileRegs& r, const char* tile_base, int lane) {
+  const char* vb = tile_base + 8192 + lane * 16;
 #pragma unroll
   for (int j = 0; j < 8; ++j) r.v[j].u = *reinterpret_cast<const uint4*>(vb + j * 1024);
 }
@@ -54,6 +56,13 @@ __device__ __forceinline__ void raw_scores(const TileRegs& t, const Frag (&qb)[4
   for (int e = 0; e < 8; ++e) raw[e] = e < 4 ? s0[e] : s1[e - 4];
 }
 
+// Two fp32 values rounded to bf16 (to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 r = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, r);
+}
+
 // Eight fp32 weights as two bf16 operands: the head keeps the top 16 bits of each weight
 // (truncated, one byte permute per pair), the remainder p - head is exact in fp32 and is rounded
 // to bf16; together they carry ~16 mantissa bits.
@@ -65,9 +74,7 @@ __device__ __forceinline__ void split_weights(const float (&p)[8], Frag& hi, Fra
     h[k] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);            // {b1.hi16, b0.hi16}
     const float r0 = p[2 * k] - __uint_as_float(b0 & 0xffff0000u);
     const float r1 = p[2 * k + 1] - __uint_as_float(b1 & 0xffff0000u);
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    bf16x2 r = {(__bf16)r0, (__bf16)r1};
-    l[k] = *reinterpret_cast<uint32_t*>(&r);
+    l[k] = bf16_pair(r0, r1);
   }
   hi.u = make_uint4(h[0], h[1], h[2], h[3]);
   lo.u = make_uint4(l[0], l[1], l[2], l[3]);
@@ -208,6 +215,7 @@ __global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int 
 struct PrefillHeads {
   int32_t n_full;                          // full heads of the layer; -1: not given, read the mask
   int32_t heavy_rows;                      // leading grid rows that are full heads of sequences with a chunk
+  int32_t inv_group;                       // 65536 / group, rounded up
   int32_t dealt_rows;                      // of those, the leading ones that go one row per XCD (see prefill_deal)
   int32_t head[2][kPrefillArgHeads];       // [0]: the full heads in ascending order, [1]: the compressed ones
 };
@@ -304,7 +312,10 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   constexpr int NG = GATED ? 1 : 2;                      // column groups of queries per wavefront
   constexpr int LOCAL = NG;                              // index of the first local accumulator set (GATED)
   constexpr int kWaveCols = 16 * NG;
-  const int wg_positions = kPrefillWaves * kWaveCols / G;    // chunk positions per workgroup
+  // Columns are at most 256 and groups at most 16, so that col / G is exact as a product with the reciprocal rounded up.
+  const int inv_g = heads.inv_group;
+  auto div_g = [&](int col) { return (col * inv_g) >> 16; };
+  const int wg_positions = div_g(kPrefillWaves * kWaveCols);   // chunk positions per workgroup
   const int n_old = len_in[b];             // positions cached before the chunk
   const int c_wg = block_x * wg_positions; // the workgroup's first chunk index
   if (c_wg >= t) return;
@@ -314,13 +325,14 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   const int Z = gridDim.z, z = Z - 1 - (int)blockIdx.z;
   if (!full && blockIdx.z > 0) return;       // a compressed head's workgroup is short: never divided
   const bool split = !GATED && full && Z > 1;
+  const bool wide = dv.v_wide[layer] != 0;   // (asked for early: read in front of the hot loop)
   const float gate = (GATED && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
   const bool mix = GATED && full && gate < 1.f;          // this head blends causal and local attention
 
   // This wavefront's columns: kWaveCols of the workgroup's flattened (position, head) pairs.
   const int col0 = wave * kWaveCols;
-  const int c0 = c_wg + col0 / G;                                        // first chunk index it touches
-  const int c_hi_raw = c_wg + (col0 + kWaveCols - 1) / G;
+  const int c0 = c_wg + div_g(col0);                                      // first chunk index it touches
+  const int c_hi_raw = c_wg + div_g(col0 + kWaveCols - 1);
   const int c_hi = c_hi_raw < c_last ? c_hi_raw : c_last;               // last one
   const bool busy = c0 <= c_last;                                        // it has at least one query
   Frag qb[NG][4];               // Q as the B operand of the score MFMA
@@ -330,7 +342,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) {
     const int col = col0 + 16 * cg + hd;
-    const int cl = col / G, hh = col - cl * G;
+    const int cl = div_g(col), hh = col - cl * G;
     const bool valid = c_wg + cl <= c_last;
     qpos[cg] = valid ? n_old + c_wg + cl : -1;
     const int64_t qrow = ((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl;
@@ -341,7 +353,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
         qv = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) + (qrow * kHeadDim + s * 32 + kb * 8) * 2);
       qb[cg][s].u = qv;
     }
-    const int cl_lo = (col0 + 16 * cg) / G, cl_hi = (col0 + 16 * cg + 15) / G;
+    const int cl_lo = div_g(col0 + 16 * cg), cl_hi = div_g(col0 + 16 * cg + 15);
     g_on[cg] = c_wg + cl_lo <= c_last;
     g_lo[cg] = n_old + c_wg + cl_lo;
     g_hi[cg] = n_old + (c_wg + cl_hi < c_last ? c_wg + cl_hi : c_last);
@@ -630,7 +642,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt 0: no load into LDS is left in flight behind the loop
   };
   if (n_plain > 0) {
-    if (dv.v_wide[layer] == 0) hot_loop(std::true_type{});
+    if (!wide) hot_loop(std::true_type{});
     else hot_loop(std::false_type{});
   }
   if (!busy) return;            // no barrier lies ahead
@@ -643,7 +655,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // (a compressed head's ring) or that holds the end of the sinks looks every position up.  With the hops above, against every
   // position looked up and compared three ways: 16 x 16 384 tokens in chunks of 2048 (28 query, 4 KV heads, 2 full)
   // 16.2 -> 15.2 ms, one sequence of 32 500 4.53 -> 4.11 ms, blending heads (8 x 1000 .. 4000) 1157 -> 1020 us.
-  auto process = [&](TileRegs& tr, int x) {
+  auto process = [&](TileRegs& tr, int x, const char* refill) {
     const bool from_store = x < n_store;
     const int tile = from_store ? x : x - n_store;
     const int held = from_store ? n_st : t;                     // slots of this source that hold a position
@@ -698,31 +710,50 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
         for (int e = 0; e < 8; ++e) sc[e] = raw[e];
       }
     };
+    // the scores of every group that sees the tile; then the K registers take the next tile, and behind the last products
+    // the V registers do
+    bool sees[NG];
+    float raw[NG][8];
 #pragma unroll
     for (int cg = 0; cg < NG; ++cg) {
-      if (!g_on[cg]) continue;
-      if (p_first > g_hi[cg]) continue;                                        // wholly above the causal diagonal
-      if (!full && p_first >= S && p_last < g_lo[cg] - R + 1) continue;        // wholly before the recent band
-      float raw[8], sc[8];
-      raw_scores(tr, qb[cg], raw);
+      // (not: wholly above the causal diagonal, or wholly before the recent band)
+      sees[cg] = g_on[cg] && p_first <= g_hi[cg] && (full || p_first < S || p_last >= g_lo[cg] - R + 1);
+      if (!sees[cg]) continue;
+      raw_scores(tr, qb[cg], raw[cg]);
       if (!hot) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) raw[e] *= scale_log2;
+        for (int e = 0; e < 8; ++e) raw[cg][e] *= scale_log2;
       }
-      masked(cg, !full, raw, sc);
+    }
+    load_k_cached(tr, refill, lane);
+#pragma unroll
+    for (int cg = 0; cg < NG; ++cg) {
+      if (!sees[cg]) continue;
+      float sc[8];
+      masked(cg, !full, raw[cg], sc);
       group_update(tr, sc, exp_scale, st[cg], kb, ones);
       if (GATED && mix && (p_first < S || p_last >= g_lo[cg] - R + 1)) {
         // the same scores under the local mask, into the group's second accumulator set
-        masked(cg, true, raw, sc);
+        masked(cg, true, raw[cg], sc);
         group_update(tr, sc, exp_scale, st[GATED ? LOCAL : 0], kb, ones);
       }
     }
+    load_v_cached(tr, refill, lane);
   };
   {
     TileRegs tr;
-    for (int x = next_needed(0); x < total; x = next_needed(x + 1)) {
-      load_tile_cached(tr, address(x), lane);
-      process(tr, x);
+    int x = next_needed(0);
+    if (x < total) {
+      const char* base = address(x);
+      load_k_cached(tr, base, lane);
+      load_v_cached(tr, base, lane);
+      while (x < total) {
+        // (behind the last tile it is asked for once more: no branch around the loads, so that nothing waits for the newest)
+        const int nx = next_needed(x + 1);
+        if (nx < total) base = address(nx);
+        process(tr, x, base);
+        x = nx;
+      }
     }
   }
 
@@ -742,22 +773,30 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     return;
   }
   // out[b][head][c][d] = O / l (blended with the local result for a gated head); the accumulator
-  // rows of group cg are its columns 4 kb + r
+  // rows of group cg are its columns 4 kb + r.  (Bound: vector instructions; rounded by the packed conversion, two values
+  // at a time: 1.4 us per workgroup, against 3.3 us with the rounding written out.  Whole rows through LDS instead of these
+  // two-byte stores changed nothing: the stores are not waited for.)
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int col = col0 + 16 * cg + kb * 4 + r;
-      const int cl = col / G, hh = col - cl * G;
+      const int cl = div_g(col), hh = col - cl * G;
       if (c_wg + cl <= c_last) {
-        const int64_t orow = ((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl;
+        uint16_t* dst = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + hd;
         const float inv = 1.f / st[cg].l[r];
         const float inv_local = mix ? 1.f / st[GATED ? LOCAL : 0].l[r] : 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float res = st[cg].o[j][r] * inv;
-          if (GATED && mix) res = gate * res + (1.f - gate) * (st[GATED ? LOCAL : 0].o[j][r] * inv_local);
-          out[orow * kHeadDim + j * 16 + hd] = f32_to_bf16_rne(res);
+        for (int j = 0; j < 8; j += 2) {
+          float res[2];
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            res[k] = st[cg].o[j + k][r] * inv;
+            if (GATED && mix) res[k] = gate * res[k] + (1.f - gate) * (st[GATED ? LOCAL : 0].o[j + k][r] * inv_local);
+          }
+          const uint32_t two = bf16_pair(res[0], res[1]);
+          dst[j * 16] = (uint16_t)two;
+          dst[j * 16 + 16] = (uint16_t)(two >> 16);
         }
       }
     }
@@ -829,6 +868,7 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
                                hipEvent_t ev_start, hipEvent_t ev_stop) {
   PrefillHeads heads;
   heads.n_full = -1;
+  heads.inv_group = (65536 + dv.group - 1) / dv.group;
   heads.heavy_rows = split_rows;
   heads.dealt_rows = dealt_rows;
   if (mask_row && dv.n_kv_heads <= kPrefillArgHeads) {
