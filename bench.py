@@ -491,8 +491,8 @@ def measure_graph(w, mask, device, steps, warmup):
     the same step issued call by call (Sec. 4.3: per-layer dispatch overhead).  Both legs run the same work: one
     copy of the step's rows (K, V, Q of all layers, packed) into the fixed buffers a recorded launch reads, then
     the L fused launches; the replayed leg calls rlkv_append_decode_prepare for every layer before each replay.
-    The two legs use two caches filled alike.  (fp32 runs on the vector-ALU kernel, whose recorded step is three
-    launches per layer: append, attention, merge.)"""
+    The two legs use two caches filled alike.  (fp32 runs on the vector-ALU kernel, whose recorded step is the
+    same two launches per layer: attention with the append, merge.)"""
     layers = list(range(w.n_layers))
     L, B, D = w.n_layers, w.batch, w.head_dim
     # the first graph a process replays runs slowly at first (the runtime is still setting up): a throwaway graph
