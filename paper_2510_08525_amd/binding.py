@@ -344,6 +344,12 @@ class Cache:
             self.arena.fill_(arena_fill)
             torch.cuda.synchronize(self.device)
         self.handle = rlkv_cache_create(arena_ptr=self.arena.data_ptr(), arena_bytes=need, **kw)
+        # what every call of a decode step asks for (torch.cuda.current_stream() builds an object: 2 us a call)
+        self._raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        self._device_index = self.device.index or 0
+        self._append_decode = load_library().rlkv_append_decode
+        self._q_shape = (batch, n_q_heads, head_dim)
+        self._row_shape = (batch, n_kv_heads, 1, head_dim)
 
     def close(self):
         if getattr(self, "handle", None):
@@ -358,12 +364,14 @@ class Cache:
             pass
 
     def _stream(self) -> int:
+        if self._raw_stream is not None and self.device.index is not None:
+            return self._raw_stream(self._device_index)
         return self._torch.cuda.current_stream(self.device).cuda_stream
 
     def _ptr(self, t, shape, what):
         if t.device != self.device or t.dtype != self.torch_dtype or not t.is_contiguous():
             raise ValueError(f"{what}: need a contiguous {self.torch_dtype} tensor on {self.device}")
-        if tuple(t.shape) != tuple(shape):
+        if t.shape != shape:
             raise ValueError(f"{what}: shape {tuple(t.shape)} != {tuple(shape)}")
         return t.data_ptr()
 
@@ -381,8 +389,7 @@ class Cache:
                            self._stream())
 
     def decode_attention(self, layer: int, q, out, softmax_scale: float):
-        s = self.shape
-        shp = (s["batch"], s["n_q_heads"], s["head_dim"])
+        shp = self._q_shape
         rlkv_decode_attention(self.handle, layer, self._ptr(q, shp, "q"), self._ptr(out, shp, "out"),
                               softmax_scale, self._stream())
 
@@ -393,11 +400,10 @@ class Cache:
                                       softmax_scale, self._stream())
 
     def append_decode(self, layer: int, k, v, q, out, softmax_scale: float):
-        s = self.shape
-        kshp = (s["batch"], s["n_kv_heads"], 1, s["head_dim"])
-        qshp = (s["batch"], s["n_q_heads"], s["head_dim"])
-        rlkv_append_decode(self.handle, layer, self._ptr(k, kshp, "k"), self._ptr(v, kshp, "v"),
-                           self._ptr(q, qshp, "q"), self._ptr(out, qshp, "out"), softmax_scale, self._stream())
+        kshp, qshp = self._row_shape, self._q_shape
+        _check(self._append_decode(self.handle, layer, self._ptr(k, kshp, "k"), self._ptr(v, kshp, "v"),
+                                   self._ptr(q, qshp, "q"), self._ptr(out, qshp, "out"), softmax_scale, self._stream()),
+               "rlkv_append_decode")
 
     def append_decode_prepare(self, layer: int):
         rlkv_append_decode_prepare(self.handle, layer, self._stream())

@@ -956,13 +956,13 @@ rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, voi
   return RLKV_OK;
 }
 
-// `grow_known`: the step was prepared just now and none before it is outstanding, so that the host's count of the list's
-// growth is the device's.
+// `prepared`: by the same call, so the device is set and the stream does not capture.  `grow_known`: and no step prepared
+// before it is outstanding, so that the host's count of the list's growth is the device's.
 static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q, void* out,
-                                 float softmax_scale, void* stream, bool grow_known) {
-  if (hipSetDevice(cache->cfg.device) != hipSuccess) return RLKV_ERR_HIP;
+                                 float softmax_scale, void* stream, bool prepared, bool grow_known) {
+  if (!prepared && hipSetDevice(cache->cfg.device) != hipSuccess) return RLKV_ERR_HIP;
   hipStream_t s = as_stream(stream);
-  const bool capturing = stream_is_capturing(s);
+  const bool capturing = !prepared && stream_is_capturing(s);
   // a launch that runs now consumes a prepared step; one that is only recorded runs at every replay, each of which
   // the caller prepares
   if (!capturing) {
@@ -1001,7 +1001,7 @@ rlkv_status_t rlkv_append_decode_launch(rlkv_cache_t* cache, int32_t layer, cons
   if (!cache || !k || !v || !q || !out) return RLKV_ERR_INVALID_ARG;
   if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
   if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
-  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, false);
+  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, false, false);
 }
 
 rlkv_status_t rlkv_append_decode(rlkv_cache_t* cache, int32_t layer, const void* k, const void* v, const void* q,
@@ -1011,7 +1011,7 @@ rlkv_status_t rlkv_append_decode(rlkv_cache_t* cache, int32_t layer, const void*
   if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
   const bool grow_known = !cache->step_ready[layer];
   if (rlkv_status_t st = rlkv_append_decode_prepare(cache, layer, stream)) return st;
-  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, grow_known);
+  return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, true, grow_known);
 }
 
 int64_t rlkv_worklists_built(const rlkv_cache_t* cache) { return cache ? cache->lists_built : -1; }
