@@ -102,6 +102,17 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       r = n_sets == 1 ? res : (set == 0 ? pd.gate * res : r + (1.f - pd.gate) * res);
       continue;
     }
+    // Many partials (few pairs with long contexts): 32 loads are on their way at a time, the first 32 before anything else is
+    // waited for and each further batch before the one ahead of it is added up (four at a time: one pair of 65 536 rows in 256 partials, a call of 28.2 us, now
+    // 21.9; 8 pairs, half of them 20 000 rows, 16.7 against 15.3 us).
+    constexpr int kDeep = 32;
+    const float* po = part_o + (slot0 * G + g) * kHeadDim + d;
+    float o[kDeep];
+    auto load = [&](int first) {
+#pragma unroll
+      for (int j = 0; j < kDeep; ++j) o[j] = first + j < nseg ? po[(int64_t)(first + j) * G * kHeadDim] : 0.f;
+    };
+    load(0);
     if (set == 0) range_test();
     // maximum over the partial maxima
     float M = -INFINITY;
@@ -129,15 +140,14 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       if ((d & 63) == 0) sm_red[d >> 6] = ls;
       __syncthreads();
       L += sm_red[0] + sm_red[1];
-      const int cnt = nseg - base < kHeadDim ? nseg - base : kHeadDim;
-      const float* po = part_o + ((slot0 + base) * G + g) * kHeadDim + d;
-      int j = 0;
-      for (; j + 4 <= cnt; j += 4) {
-        const float a0 = po[(int64_t)(j + 0) * G * kHeadDim], a1 = po[(int64_t)(j + 1) * G * kHeadDim];
-        const float a2 = po[(int64_t)(j + 2) * G * kHeadDim], a3 = po[(int64_t)(j + 3) * G * kHeadDim];
-        acc += sm_scale[j] * a0; acc += sm_scale[j + 1] * a1; acc += sm_scale[j + 2] * a2; acc += sm_scale[j + 3] * a3;
+      for (int j0 = 0; j0 < kHeadDim && base + j0 < nseg; j0 += kDeep) {
+        float now[kDeep];
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) now[j] = o[j];
+        load(base + j0 + kDeep);
+#pragma unroll
+        for (int j = 0; j < kDeep; ++j) acc += sm_scale[j0 + j] * now[j];       // (scale and value are 0 beyond nseg)
       }
-      for (; j < cnt; ++j) acc += sm_scale[j] * po[(int64_t)j * G * kHeadDim];
     }
     const float res = acc / L;
     r = n_sets == 1 ? res : (set == 0 ? pd.gate * res : r + (1.f - pd.gate) * res);
