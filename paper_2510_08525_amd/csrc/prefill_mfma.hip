@@ -324,7 +324,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // (it also takes the masked tiles)
   const int Z = gridDim.z, z = Z - 1 - (int)blockIdx.z;
   if (!full && blockIdx.z > 0) return;       // a compressed head's workgroup is short: never divided
-  const bool split = !GATED && full && Z > 1;
+  const bool split = full && Z > 1;
   const bool wide = dv.v_wide[layer] != 0;   // (asked for early: read in front of the hot loop)
   const float gate = (GATED && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
   const bool mix = GATED && full && gate < 1.f;          // this head blends causal and local attention
@@ -760,14 +760,16 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   if (split) {
     float* slot = split_out + (((int64_t)by * gridDim.x + bx) * Z + z) * kSplitSlotFloats;
 #pragma unroll
-    for (int cg = 0; cg < NG; ++cg) {
-      if (kb == 0) slot[kSplitCols * kHeadDim + col0 + 16 * cg + hd] = st[cg].m;      // the lane's own column
+    for (int k = 0; k < 2; ++k) {            // two column groups; GATED: one and its local set, as columns 128 and up
+      if (GATED && k == LOCAL && !mix) break;
+      const int first = col0 + (GATED ? kSplitCols / 2 : 16) * k;
+      if (kb == 0) slot[kSplitCols * kHeadDim + first + hd] = st[k].m;      // the lane's own column
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int col = col0 + 16 * cg + kb * 4 + r;
-        if (hd == 0) slot[kSplitCols * (kHeadDim + 1) + col] = st[cg].l[r];
+        const int col = first + kb * 4 + r;
+        if (hd == 0) slot[kSplitCols * (kHeadDim + 1) + col] = st[k].l[r];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) slot[col * kHeadDim + j * 16 + hd] = st[cg].o[j][r];
+        for (int j = 0; j < 8; ++j) slot[col * kHeadDim + j * 16 + hd] = st[k].o[j][r];
       }
     }
     return;
@@ -806,6 +808,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 // Combines the shares of a divided workgroup: weights 2^(m_z - max m) on each share's accumulators and
 // normaliser (every share's weights carry the same 2^kWeightShift, which cancels).  A share that saw no
 // key has m = -inf and counts for nothing; the last share always holds the query's own position.
+// GATED: a block has 128 columns, and a blending head's local sets are columns 128 and up.
+template <bool GATED>
 __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, SeqOrder order, const float* __restrict__ split_out,
                                                                    int Z, uint16_t* __restrict__ out, int stride_tokens,
                                                                    PrefillHeads heads) {
@@ -814,40 +818,55 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
   int t;
   pair_of_grid_row(dv, order, layer, blockIdx.y, heads, b, h, full, t);
   const int G = dv.group;
-  const int wg_positions = kSplitCols / G;
+  const int wg_positions = (GATED ? kSplitCols / 2 : kSplitCols) / G;
   const int c_wg = (gridDim.x - 1 - blockIdx.x) * wg_positions;
   if (c_wg >= t) return;
+  const float gate = GATED ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
+  const bool mix = GATED && gate < 1.f;
   const int c_last = (c_wg + wg_positions < t ? c_wg + wg_positions : t) - 1;
   const float* slot0 = split_out + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * Z * kSplitSlotFloats;
   // eight columns per workgroup, four per thread: the loads behind the four outputs are independent, so
   // their latencies overlap, and there are still thousands of workgroups
   const int d = threadIdx.x & (kHeadDim - 1);
   constexpr int kPer = kMergeColsPerGroup / 2;
-  float M[kPer], num[kPer], den[kPer];
   int col[kPer];
   bool on[kPer];
+  float res[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     col[i] = blockIdx.z * kMergeColsPerGroup + 2 * i + (threadIdx.x >> 7);
     on[i] = c_wg + col[i] / G <= c_last;
-    M[i] = -INFINITY;
-    num[i] = den[i] = 0.f;
+    res[i] = 0.f;
   }
-  for (int zz = 0; zz < Z; ++zz) {
-    const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i)
-      if (on[i]) M[i] = fmaxf(M[i], sl[kSplitCols * kHeadDim + col[i]]);
-  }
-  for (int zz = 0; zz < Z; ++zz) {
-    const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
+  for (int set = 0; set < (mix ? 2 : 1); ++set) {
+    const int shift = set * (kSplitCols / 2);
+    float M[kPer], num[kPer], den[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      if (!on[i]) continue;
-      const float m = sl[kSplitCols * kHeadDim + col[i]];
-      const float w = m == -INFINITY ? 0.f : exp2f(m - M[i]);
-      num[i] += w * sl[col[i] * kHeadDim + d];
-      den[i] += w * sl[kSplitCols * (kHeadDim + 1) + col[i]];
+      M[i] = -INFINITY;
+      num[i] = den[i] = 0.f;
+    }
+    for (int zz = 0; zz < Z; ++zz) {
+      const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (on[i]) M[i] = fmaxf(M[i], sl[kSplitCols * kHeadDim + shift + col[i]]);
+    }
+    for (int zz = 0; zz < Z; ++zz) {
+      const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        if (!on[i]) continue;
+        const float m = sl[kSplitCols * kHeadDim + shift + col[i]];
+        const float w = m == -INFINITY ? 0.f : exp2f(m - M[i]);
+        num[i] += w * sl[(shift + col[i]) * kHeadDim + d];
+        den[i] += w * sl[kSplitCols * (kHeadDim + 1) + shift + col[i]];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const float r = num[i] / den[i];
+      res[i] = !mix ? r : set == 0 ? gate * r : res[i] + (1.f - gate) * r;
     }
   }
 #pragma unroll
@@ -855,7 +874,7 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
     if (!on[i]) continue;
     const int cl = col[i] / G, hh = col[i] - cl * G;
     const int64_t orow = ((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl;
-    out[orow * kHeadDim + d] = f32_to_bf16_rne(num[i] / den[i]);
+    out[orow * kHeadDim + d] = f32_to_bf16_rne(res[i]);
   }
 }
 
@@ -883,9 +902,10 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
   hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, (const uint16_t*)k,
                      (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
-  if (gated || n_split < 1 || !split_out) n_split = 1;         // (the blending form is never divided)
+  if (n_split < 1 || !split_out) n_split = 1;
   const int per_block = kPrefillWaves * 16 * (gated ? 1 : 2) / dv.group;      // chunk positions per workgroup
-  const dim3 grid((max_tokens + per_block - 1) / per_block, dv.n_pairs, n_split), block(kPrefillBlock);
+  const int gx = (max_tokens + per_block - 1) / per_block;
+  const dim3 grid(gx, dv.n_pairs, n_split), block(kPrefillBlock);
 #define RLKV_LAUNCH(PG, GT)                                                                                          \
   hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, GT>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
@@ -894,9 +914,15 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
   else                    { if (gated) RLKV_LAUNCH(false, true); else RLKV_LAUNCH(false, false); }
 #undef RLKV_LAUNCH
   if (hipError_t e = hipGetLastError()) return e;
-  if (n_split > 1 && split_rows > 0)
-    hipLaunchKernelGGL(prefill_merge_kernel, dim3(grid.x, split_rows, kSplitCols / kMergeColsPerGroup), dim3(kSplitCols), 0, stream, dv, layer, order,
-                       (const float*)split_out, n_split, (uint16_t*)out, stride_tokens, heads);
+  if (n_split > 1 && split_rows > 0) {
+    const dim3 mgrid(gx, split_rows, kSplitCols / (gated ? 2 : 1) / kMergeColsPerGroup), mblock(kSplitCols);
+    if (gated)
+      hipLaunchKernelGGL(prefill_merge_kernel<true>, mgrid, mblock, 0, stream, dv, layer, order, (const float*)split_out, n_split,
+                         (uint16_t*)out, stride_tokens, heads);
+    else
+      hipLaunchKernelGGL(prefill_merge_kernel<false>, mgrid, mblock, 0, stream, dv, layer, order, (const float*)split_out, n_split,
+                         (uint16_t*)out, stride_tokens, heads);
+  }
   return hipGetLastError();
 }
 

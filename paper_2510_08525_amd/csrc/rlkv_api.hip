@@ -626,7 +626,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
     hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
     // The kernel form and the division of long workgroups: rlkv_plan_prefill_form (a blending layer always takes
-    // the single-group form, undivided).
+    // the single-group form, divided by plan_blend_split).
     bool narrow = cache->layer_gated[layer] != 0;
     int n_split = 1, n_full = 0, split_rows = 0;      // split_rows: grid rows of full heads that have a chunk (they come first)
     {
@@ -641,6 +641,8 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       narrow = nw != 0;
       n_split = ns;
     }
+    if (cache->layer_gated[layer])
+      n_split = plan_blend_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, cache->min_share_tiles / 2);
     int32_t dealt_rows = 0;
     {
       int32_t heavy = 0;

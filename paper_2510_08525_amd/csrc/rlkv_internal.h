@@ -232,7 +232,7 @@ hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_
 // stages the chunk's K/V as tiles in `staging` (staging_tiles tiles per pair), then attends.
 // `gated`: the kernel form with one column group of queries per wavefront, the only one that can blend
 // (Eq. 1: causal and local attention of a full head with a gate below 1).
-// `n_split` > 1 (other form only): the unmasked tiles of every full head's workgroup are divided among
+// `n_split` > 1: the unmasked tiles of every full head's workgroup are divided among
 // n_split workgroups, which leave their shares in `split_out` (kPrefillSplitSlotBytes per divided
 // workgroup; at most kPrefillSplitSlots: split_rows (the grid's first rows: full heads of sequences
 // that have a chunk) x blocks x n_split) for a merge kernel that follows.
@@ -245,6 +245,9 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
                                int split_rows, int dealt_rows,
                                const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+
+int plan_blend_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
+                     const int32_t* cached, int min_share_tiles);
 
 // Measurement aid: reads `bytes` (whole 16 KiB blocks) of `buf` once with `workgroups` workgroups.
 hipError_t launch_stream_read(const void* buf, size_t bytes, void* sink, int workgroups, hipStream_t stream);

@@ -152,6 +152,34 @@ extern "C" int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_h
   return 0;
 }
 
+namespace rlkv {
+
+// Shares that every full-head workgroup of a blending layer's chunk is divided into (the form with one column group per
+// wavefront, 128 columns to a workgroup).  As above: only where the shares still fit the CUs in one round.
+int plan_blend_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
+                     const int32_t* cached, int min_share_tiles) {
+  const int per_block = 128 / group;
+  int64_t blocks = 0, n_active = 0;
+  int max_tok = 0, min_tiles = INT32_MAX;
+  for (int b = 0; b < batch; ++b) {
+    if (n_tokens[b] == 0) continue;
+    blocks += (n_tokens[b] + per_block - 1) / per_block;
+    ++n_active;
+    if (n_tokens[b] > max_tok) max_tok = n_tokens[b];
+    if (cached[b] / kTile < min_tiles) min_tiles = cached[b] / kTile;
+  }
+  const int64_t rows = (int64_t)((max_tok + per_block - 1) / per_block) * n_active * n_full_heads;
+  int n_split = 1;
+  constexpr int kMaxSplit = 8;
+  for (int z = 2; z <= kMaxSplit && rows > 0; ++z) {
+    if (blocks * n_full_heads * z > n_compute_units || rows * z > kPrefillSplitSlots || min_tiles / z < min_share_tiles) break;
+    n_split = z;
+  }
+  return n_split;
+}
+
+}  // namespace rlkv
+
 extern "C" int32_t rlkv_plan_prefill_rows(int32_t n_full_heads, int32_t batch, const int32_t* n_tokens,
                                           const int32_t* cached, int32_t* dealt_rows, int32_t* heavy_rows) {
   if (!n_tokens || !cached || !dealt_rows || !heavy_rows || n_full_heads < 0 || batch < 1) return -1;
