@@ -626,7 +626,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
     hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
     // The kernel form and the division of long workgroups: rlkv_plan_prefill_form (a blending layer always takes
-    // the single-group form, divided by plan_blend_split).
+    // the single-group form); the single-group form is divided by plan_narrow_split.
     bool narrow = cache->layer_gated[layer] != 0;
     int n_split = 1, n_full = 0, split_rows = 0;      // split_rows: grid rows of full heads that have a chunk (they come first)
     {
@@ -641,8 +641,11 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       narrow = nw != 0;
       n_split = ns;
     }
-    if (cache->layer_gated[layer])
-      n_split = plan_blend_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, cache->min_share_tiles / 2);
+    // (Shares of that form pay from about 26 tiles on, 40 where a share leaves two accumulator sets.  One sequence of 3000 / 6000
+    // tokens, 28 query and 4 KV heads, 2 full, chunks of 512 / 1024, whole / shares of 40 / 30 / 20 / 12 tiles: 277 / 263 / 251 /
+    // 255 / 271, 480 / 436 / 437 / 407 / 443 us; blending, two of 4000 and 5000: 623 / 588 / 594 / 607 / 621 us.)
+    if (narrow)
+      n_split = plan_narrow_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, cache->min_share_tiles / (cache->layer_gated[layer] ? 2 : 3));
     int32_t dealt_rows = 0;
     {
       int32_t heavy = 0;

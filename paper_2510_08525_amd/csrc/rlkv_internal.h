@@ -246,7 +246,7 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
                                const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
-int plan_blend_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
+int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
                      const int32_t* cached, int min_share_tiles);
 
 // Measurement aid: reads `bytes` (whole 16 KiB blocks) of `buf` once with `workgroups` workgroups.

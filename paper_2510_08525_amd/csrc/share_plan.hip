@@ -154,9 +154,9 @@ extern "C" int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_h
 
 namespace rlkv {
 
-// Shares that every full-head workgroup of a blending layer's chunk is divided into (the form with one column group per
-// wavefront, 128 columns to a workgroup).  As above: only where the shares still fit the CUs in one round.
-int plan_blend_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
+// Shares that every full-head workgroup of a chunk is divided into in the form with one column group per wavefront (128 columns
+// to a workgroup).  As above: only where the shares still fit the CUs in one round.
+int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
                      const int32_t* cached, int min_share_tiles) {
   const int per_block = 128 / group;
   int64_t blocks = 0, n_active = 0;
