@@ -161,6 +161,7 @@ struct rlkv_cache {
   std::vector<int32_t> wl_slack;    // [L] tokens the layer's work list is still valid for; -1 = rebuild
   std::vector<int32_t> list_grow;   // [L] tokens since the layer's work list was planned (steps prepared included)
   std::vector<int32_t> list_used;   // [L] workgroups the layer's list of shares uses
+  std::vector<int32_t> list_partials; // [L] most workgroups that share a pair of the layer's list
   std::vector<uint8_t> list_whole;  // [L] the layer's work list is one of whole pairs
   std::vector<int64_t> decode_calls; // [L] decode launches so far (fused or not): the clock of the rebuild schedule
   std::vector<uint8_t> step_ready;  // [L] a fused step was prepared (rlkv_append_decode_prepare) and no launch has run since
@@ -308,6 +309,7 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
   c->list_grow.assign((size_t)L, 0);
   c->list_whole.assign((size_t)L, 0);
   c->list_used.assign((size_t)L, 0);
+  c->list_partials.assign((size_t)L, 0);
   c->decode_calls.assign((size_t)L, 0);
   c->step_ready.assign((size_t)L, 0);
   c->parity.assign((size_t)L, 0);
@@ -776,6 +778,7 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   const int64_t phase = (cache->decode_calls[layer] + (int64_t)layer * kWorklistSlack / dv.n_layers) % kWorklistSlack;
   cache->wl_slack[layer] = kWorklistSlack - (int32_t)phase;
   cache->list_grow[layer] = 0;
+  cache->list_partials[layer] = *std::max_element(seg_count, seg_count + n_pairs);
   cache->list_whole[layer] = whole ? 1 : 0;
   ++cache->lists_built;
   return RLKV_OK;
@@ -840,7 +843,8 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   if (whole && !capturing) return RLKV_OK;       // every pair was finished by its one workgroup
   const uint32_t* words = (cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * dv.n_pairs;
-  if (launch_combine(dv, layer, out, s, 0, nullptr, words) != hipSuccess) return RLKV_ERR_HIP;
+  if (launch_combine(dv, layer, out, s, 0, nullptr, words, capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
+    return RLKV_ERR_HIP;
   return RLKV_OK;
 }
 
@@ -997,7 +1001,9 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * cache->dv.n_pairs;
   // (the merge kernel of the tiled layout also looks at the appended V rows, for the fp16 range flag of prefill)
-  if (launch_combine(cache->dv, layer, out, s, 1, tiled ? v : nullptr, words) != hipSuccess) return RLKV_ERR_HIP;
+  if (launch_combine(cache->dv, layer, out, s, 1, tiled ? v : nullptr, words,
+                     capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
+    return RLKV_ERR_HIP;
   return RLKV_OK;
 }
 

@@ -224,10 +224,11 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
 // merge_words (host, [n_pairs], optional): per pair (first partial slot << 12) | partials, as planned for the
 // work list now on the device; with it and at most kMergeArgPairs pairs the merge kernel takes these from its
 // arguments instead of from the pair records (not for a layer with gates: their records carry more).
+// most_partials: of any pair of the list (0 where the launch may run under another list; the kernel's form only).
 // advance: tokens to add to the layer's ListHeader::grow (1 behind a fused append + decode launch).
 constexpr int kMergeArgPairs = 512;
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
-                          const void* v_new = nullptr, const uint32_t* merge_words = nullptr);
+                          const void* v_new, const uint32_t* merge_words, int most_partials);
 // Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):
 // stages the chunk's K/V as tiles in `staging` (staging_tiles tiles per pair), then attends.
 // `gated`: the kernel form with one column group of queries per wavefront, the only one that can blend

@@ -23,7 +23,15 @@ namespace {
 struct MergeWords {
   uint32_t w[kMergeArgPairs];     // (first slot << 12) | partials
 };
-template <typename T, bool IN_ARGS>
+//
+// MANY (some pair has more than kManyPartials): 32 loads of a pair with more than kFew partials are on their way at a time, the
+// first 32 before anything else is waited for and each further batch before the one ahead of it is added up, where the
+// usual form takes four at a time.  One pair of 65 536 rows in 256 partials: a decode call 28.1 -> 21.9 us; 64 partials:
+// 18.4 -> 18.2 us; 40 partials in two sets (gates): 19.6 -> 22.9 us, hence the line.  A kernel of its own also because the
+// registers cost the usual form 0.2 us a launch.
+constexpr int kManyPartials = 64;
+constexpr int kFew = 16;
+template <typename T, bool IN_ARGS, bool MANY>
 __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int layer, T* __restrict__ out,
                                                            const uint16_t* __restrict__ v_new, MergeWords words,
                                                            int advance) {
@@ -71,7 +79,6 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
     const float* part_l = dv.part_l + set * dv.part_set_ml;
     const float* part_o = dv.part_o + set * dv.part_set_o;
     __syncthreads();
-    constexpr int kFew = 16;
     if (nseg <= kFew) {
       // The usual case, a handful of partials: every load is issued before anything is waited for
       // (this kernel is a chain of memory latencies and little else), one barrier, same ascending
@@ -102,17 +109,14 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       r = n_sets == 1 ? res : (set == 0 ? pd.gate * res : r + (1.f - pd.gate) * res);
       continue;
     }
-    // Many partials (few pairs with long contexts): 32 loads are on their way at a time, the first 32 before anything else is
-    // waited for and each further batch before the one ahead of it is added up (four at a time: one pair of 65 536 rows in 256 partials, a call of 28.2 us, now
-    // 21.9; 8 pairs, half of them 20 000 rows, 16.7 against 15.3 us).
-    constexpr int kDeep = 32;
+    constexpr int kDeep = MANY ? 32 : 1;
     const float* po = part_o + (slot0 * G + g) * kHeadDim + d;
     float o[kDeep];
     auto load = [&](int first) {
 #pragma unroll
       for (int j = 0; j < kDeep; ++j) o[j] = first + j < nseg ? po[(int64_t)(first + j) * G * kHeadDim] : 0.f;
     };
-    load(0);
+    if (MANY) load(0);
     if (set == 0) range_test();
     // maximum over the partial maxima
     float M = -INFINITY;
@@ -140,13 +144,25 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       if ((d & 63) == 0) sm_red[d >> 6] = ls;
       __syncthreads();
       L += sm_red[0] + sm_red[1];
-      for (int j0 = 0; j0 < kHeadDim && base + j0 < nseg; j0 += kDeep) {
-        float now[kDeep];
+      if constexpr (MANY) {
+        for (int j0 = 0; j0 < kHeadDim && base + j0 < nseg; j0 += kDeep) {
+          float now[kDeep];
 #pragma unroll
-        for (int j = 0; j < kDeep; ++j) now[j] = o[j];
-        load(base + j0 + kDeep);
+          for (int j = 0; j < kDeep; ++j) now[j] = o[j];
+          load(base + j0 + kDeep);
 #pragma unroll
-        for (int j = 0; j < kDeep; ++j) acc += sm_scale[j0 + j] * now[j];       // (scale and value are 0 beyond nseg)
+          for (int j = 0; j < kDeep; ++j) acc += sm_scale[j0 + j] * now[j];       // (scale and value are 0 beyond nseg)
+        }
+      } else {
+        const int cnt = nseg - base < kHeadDim ? nseg - base : kHeadDim;
+        const float* pb = po + (int64_t)base * G * kHeadDim;
+        int j = 0;
+        for (; j + 4 <= cnt; j += 4) {
+          const float a0 = pb[(int64_t)(j + 0) * G * kHeadDim], a1 = pb[(int64_t)(j + 1) * G * kHeadDim];
+          const float a2 = pb[(int64_t)(j + 2) * G * kHeadDim], a3 = pb[(int64_t)(j + 3) * G * kHeadDim];
+          acc += sm_scale[j] * a0; acc += sm_scale[j + 1] * a1; acc += sm_scale[j + 2] * a2; acc += sm_scale[j + 3] * a3;
+        }
+        for (; j < cnt; ++j) acc += sm_scale[j] * pb[(int64_t)j * G * kHeadDim];
       }
     }
     const float res = acc / L;
@@ -161,19 +177,22 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
 }  // namespace
 
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance, const void* v_new,
-                          const uint32_t* merge_words) {
+                          const uint32_t* merge_words, int most_partials) {
   const dim3 grid(dv.n_pairs, dv.group), block(kHeadDim);
   const uint16_t* vn = (dv.dtype != RLKV_F32 && dv.kernel == RLKV_KERNEL_MFMA) ? (const uint16_t*)v_new : nullptr;
   MergeWords words;
   const bool in_args = merge_words != nullptr && dv.n_pairs <= kMergeArgPairs;
   if (in_args) memcpy(words.w, merge_words, (size_t)dv.n_pairs * sizeof(uint32_t));
-  if (dv.dtype == RLKV_F32) {
-    if (in_args) hipLaunchKernelGGL((combine_kernel<float, true>), grid, block, 0, stream, dv, layer, (float*)out, vn, words, advance);
-    else hipLaunchKernelGGL((combine_kernel<float, false>), grid, block, 0, stream, dv, layer, (float*)out, vn, words, advance);
-  } else {
-    if (in_args) hipLaunchKernelGGL((combine_kernel<uint16_t, true>), grid, block, 0, stream, dv, layer, (uint16_t*)out, vn, words, advance);
-    else hipLaunchKernelGGL((combine_kernel<uint16_t, false>), grid, block, 0, stream, dv, layer, (uint16_t*)out, vn, words, advance);
-  }
+#define RLKV_LAUNCH(T, IA, MN) hipLaunchKernelGGL((combine_kernel<T, IA, MN>), grid, block, 0, stream, dv, layer, (T*)out, vn, words, advance)
+#define RLKV_PICK(T)                                                                                       \
+  do {                                                                                                     \
+    if (most_partials > kManyPartials) { if (in_args) RLKV_LAUNCH(T, true, true); else RLKV_LAUNCH(T, false, true); } \
+    else                      { if (in_args) RLKV_LAUNCH(T, true, false); else RLKV_LAUNCH(T, false, false); } \
+  } while (0)
+  if (dv.dtype == RLKV_F32) RLKV_PICK(float);
+  else RLKV_PICK(uint16_t);
+#undef RLKV_PICK
+#undef RLKV_LAUNCH
   return hipGetLastError();
 }
 
