@@ -343,6 +343,18 @@ int32_t rlkv_plan_shares(const int32_t* rounds /* host */, int32_t n_pairs, int3
                          int32_t* wg_begin /* host */, int32_t* seg_first /* host */,
                          int32_t* seg_count /* host */);
 
+/* The plan of a list of whole pairs, one workgroup each, spread evenly over the shares; exposed for tests.  Arguments
+ * and result as above; -1 also if more pairs have rounds than there are workgroups. */
+int32_t rlkv_plan_whole_pairs(const int32_t* rounds /* host */, int32_t n_pairs, int32_t n_workgroups,
+                              int32_t* wg_begin /* host */, int32_t* seg_first /* host */,
+                              int32_t* seg_count /* host */);
+
+/* Shares that every full-head workgroup of a prefill chunk is divided into in the single-group form (1 = undivided);
+ * exposed for tests.  -1 on an invalid argument. */
+int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
+                               const int32_t* n_tokens /* host */, const int32_t* cached /* host */,
+                               int32_t min_share_tiles);
+
 /* Measurement aid, independent of any cache: one plain streaming read of `bytes` (rounded down to
  * whole 16 KiB blocks) of `buf` with 128-bit non-temporal loads and no arithmetic, launched with
  * `workgroups` workgroups of 256 threads on `stream` of the current device.  Timed by the caller,

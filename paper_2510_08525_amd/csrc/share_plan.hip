@@ -217,3 +217,25 @@ extern "C" int32_t rlkv_plan_prefill_block(int32_t linear_index, int32_t grid_x,
   *block_y = by;
   return 0;
 }
+
+extern "C" int32_t rlkv_plan_whole_pairs(const int32_t* rounds, int32_t n_pairs, int32_t n_workgroups, int32_t* wg_begin,
+                                         int32_t* seg_first, int32_t* seg_count) {
+  if (!rounds || !wg_begin || !seg_first || !seg_count || n_pairs < 1 || n_workgroups < 1) return -1;
+  int used = 0;
+  for (int p = 0; p < n_pairs; ++p) {
+    if (rounds[p] < 0 || rounds[p] > (1 << 24)) return -1;
+    used += rounds[p] > 0;
+  }
+  if (used > n_workgroups) return -1;
+  rlkv::plan_whole_pairs(rounds, n_pairs, n_workgroups, wg_begin, seg_first, seg_count);
+  return used;
+}
+
+extern "C" int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
+                                          const int32_t* n_tokens, const int32_t* cached, int32_t min_share_tiles) {
+  if (!n_tokens || !cached || n_compute_units < 1 || group < 1 || group > rlkv::kMaxGroup || n_full_heads < 0 || batch < 1)
+    return -1;
+  for (int b = 0; b < batch; ++b)
+    if (n_tokens[b] < 0 || cached[b] < 0) return -1;
+  return rlkv::plan_narrow_split(n_compute_units, group, n_full_heads, batch, n_tokens, cached, min_share_tiles);
+}
