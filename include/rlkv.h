@@ -145,7 +145,11 @@ rlkv_status_t rlkv_append_ragged(rlkv_cache_t* cache, int32_t layer, const void*
  * KV head retains: all n for a full head; {j < S} U {j >= n - R} for a compressed head.
  *   q, out : device, [batch][n_q_heads][head_dim] in cfg.dtype.
  * Scores, softmax and accumulation are fp32; the output is rounded to cfg.dtype (RNE).
- * RLKV_ERR_STATE if any active sequence of the layer is empty (see rlkv_set_active). */
+ * RLKV_ERR_STATE if any active sequence of the layer is empty (see rlkv_set_active).
+ * Recorded into a HIP graph, the call runs at every replay over the positions cached by then, under the layer's work
+ * list of that time.  A list serves 32 tokens of growth by uniform appends and is planned by calls that are not recorded:
+ * call once before recording, and again, before the next replay, whenever a list is due (after more growth, a ragged
+ * append, a reset or a change of the active slots).  Record again after rlkv_set_gates changes whether the layer blends. */
 rlkv_status_t rlkv_decode_attention(rlkv_cache_t* cache, int32_t layer, const void* q /* device */,
                                     void* out /* device */, float softmax_scale, void* stream);
 

@@ -841,7 +841,8 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   if (record) ++cache->prof_used;
   ++cache->decode_calls[layer];
   if (whole && !capturing) return RLKV_OK;       // every pair was finished by its one workgroup
-  const uint32_t* words = (cache->merge_words.empty() || cache->layer_gated[layer])
+  // (the merge kernel of a recorded launch reads the pair records of the list it runs under from memory)
+  const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * dv.n_pairs;
   if (launch_combine(dv, layer, out, s, 0, nullptr, words, capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
     return RLKV_ERR_HIP;
