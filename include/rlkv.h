@@ -84,7 +84,9 @@ typedef struct {
   /* Tuning, 0 = the library's default everywhere (what every measured figure uses): */
   int32_t decode_wgs_per_cu;       /* decode workgroups per compute unit, 1..8; default 1        */
   int32_t prefill_min_share_tiles; /* fewest 32-key tiles a share of a divided prefill workgroup may
-                                      have (see rlkv_prefill_attention); default 80              */
+                                      have, in every form of the kernel (see rlkv_prefill_attention);
+                                      default 80, in the single-group form 26 and, for a layer that
+                                      blends, 40                                                 */
   int32_t prefill_two_group_only;  /* 1: rlkv_prefill_attention never picks its single-group kernel form
                                       for a layer that does not blend (tests run small shapes through
                                       the form the large ones take); default 0                   */
@@ -301,7 +303,9 @@ rlkv_status_t rlkv_pool_shuffle(rlkv_cache_t* cache, uint64_t seed);
  * shortest cached context leaves every share min_share_tiles 32-key tiles and the shares fit the
  * scratch slots; when none does and allow_narrow is set, the single-group form is used.
  *   n_tokens, cached : host [batch], chunk length and positions already cached per sequence
- *   narrow, n_split  : host, out: 1 = single-group form; shares per full-head workgroup (1 = undivided)
+ *   narrow, n_split  : host, out: 1 = single-group form; shares per full-head workgroup of the two-group
+ *                      form (1 = undivided, and always 1 with narrow = 1: the shares of the single-group
+ *                      form are those of rlkv_plan_narrow_split)
  * Returns 0, or -1 on an invalid argument. */
 int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_heads, int32_t n_kv_heads, int32_t n_full_heads,
                                int32_t batch, const int32_t* n_tokens /* host */, const int32_t* cached /* host */,
@@ -353,8 +357,10 @@ int32_t rlkv_plan_whole_pairs(const int32_t* rounds /* host */, int32_t n_pairs,
                               int32_t* wg_begin /* host */, int32_t* seg_first /* host */,
                               int32_t* seg_count /* host */);
 
-/* Shares that every full-head workgroup of a prefill chunk is divided into in the single-group form (1 = undivided);
- * exposed for tests.  -1 on an invalid argument. */
+/* Shares that every full-head workgroup of a prefill chunk (128 / group chunk positions) is divided into in the
+ * single-group form of the kernel, the one that blends and the one rlkv_plan_prefill_form calls narrow: as many (at most 8) as
+ * fit one round over the compute units and the scratch slots and leave every share min_share_tiles tiles; 1 = undivided.
+ * Exposed for tests and tools.  -1 on an invalid argument (min_share_tiles < 1 among them). */
 int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
                                const int32_t* n_tokens /* host */, const int32_t* cached /* host */,
                                int32_t min_share_tiles);

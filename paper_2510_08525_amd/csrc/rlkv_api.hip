@@ -172,7 +172,6 @@ struct rlkv_cache {
   std::vector<uint8_t> layer_gated; // [L] some full head of the layer has a gate below 1
   std::vector<uint32_t> merge_words; // [L][pairs] (first partial slot << 12) | partials of the layer's work list; empty if too many pairs
   int n_cu;                         // compute units of the device
-  int min_share_tiles;              // a divided prefill workgroup's share is at least this many tiles
   bool allow_narrow;                // prefill may pick the one-group kernel form for a layer that does not blend
   DeviceView dv;
   Plan plan;
@@ -350,9 +349,6 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
     return RLKV_ERR_HIP;
   }
   c->n_cu = prop.multiProcessorCount;
-  // Measured on the Qwen shape, one sequence: dividing beats the narrow form from about 85 tiles per share on
-  // (the shares' accumulators go through memory and a merge kernel follows).
-  c->min_share_tiles = cfg->prefill_min_share_tiles > 0 ? cfg->prefill_min_share_tiles : 80;
   c->allow_narrow = cfg->prefill_two_group_only == 0;
   // measured best: one 4-wave workgroup per CU (see decode_mfma.hip)
   const int wgs_per_cu = cfg->decode_wgs_per_cu > 0 ? cfg->decode_wgs_per_cu : 1;
@@ -629,6 +625,9 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
     // The kernel form and the division of long workgroups: rlkv_plan_prefill_form (a blending layer always takes
     // the single-group form); the single-group form is divided by plan_narrow_split.
+    // Measured on the Qwen shape, one sequence: dividing beats the narrow form from about 85 tiles per share on
+    // (the shares' accumulators go through memory and a merge kernel follows).
+    const int set_tiles = cache->cfg.prefill_min_share_tiles;      // 0: the defaults
     bool narrow = cache->layer_gated[layer] != 0;
     int n_split = 1, n_full = 0, split_rows = 0;      // split_rows: grid rows of full heads that have a chunk (they come first)
     {
@@ -638,7 +637,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     if (!narrow) {
       int32_t nw = 0, ns = 1;
       if (rlkv_plan_prefill_form(cache->n_cu, cache->cfg.n_q_heads, cache->cfg.n_kv_heads, n_full, B, n_tokens, lh,
-                                 cache->min_share_tiles, cache->allow_narrow ? 1 : 0, &nw, &ns) != 0)
+                                 set_tiles > 0 ? set_tiles : kShareTiles, cache->allow_narrow ? 1 : 0, &nw, &ns) != 0)
         return RLKV_ERR_INVALID_ARG;
       narrow = nw != 0;
       n_split = ns;
@@ -646,8 +645,10 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     // (Shares of that form pay from about 26 tiles on, 40 where a share leaves two accumulator sets.  One sequence of 3000 / 6000
     // tokens, 28 query and 4 KV heads, 2 full, chunks of 512 / 1024, whole / shares of 40 / 30 / 20 / 12 tiles: 277 / 263 / 251 /
     // 255 / 271, 480 / 436 / 437 / 407 / 443 us; blending, two of 4000 and 5000: 623 / 588 / 594 / 607 / 621 us.)
-    if (narrow)
-      n_split = plan_narrow_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, cache->min_share_tiles / (cache->layer_gated[layer] ? 2 : 3));
+    if (narrow) {
+      const int tiles = set_tiles > 0 ? set_tiles : cache->layer_gated[layer] ? kShareTilesBlend : kShareTilesNarrow;
+      n_split = plan_narrow_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, tiles);
+    }
     int32_t dealt_rows = 0;
     {
       int32_t heavy = 0;

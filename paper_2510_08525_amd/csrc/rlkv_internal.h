@@ -247,8 +247,11 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
                                const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
+// Fewest 32-key tiles a share of a divided prefill workgroup has, where cfg.prefill_min_share_tiles does not say: in the
+// form with two column groups per wavefront, in the single-group form, and in that form with two accumulator sets.
+constexpr int kShareTiles = 80, kShareTilesNarrow = 26, kShareTilesBlend = 40;
 int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
-                     const int32_t* cached, int min_share_tiles);
+                      const int32_t* cached, int min_share_tiles);
 
 // Measurement aid: reads `bytes` (whole 16 KiB blocks) of `buf` once with `workgroups` workgroups.
 hipError_t launch_stream_read(const void* buf, size_t bytes, void* sink, int workgroups, hipStream_t stream);

@@ -157,7 +157,7 @@ namespace rlkv {
 // Shares that every full-head workgroup of a chunk is divided into in the form with one column group per wavefront (128 columns
 // to a workgroup).  As above: only where the shares still fit the CUs in one round.
 int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
-                     const int32_t* cached, int min_share_tiles) {
+                      const int32_t* cached, int min_share_tiles) {
   const int per_block = 128 / group;
   int64_t blocks = 0, n_active = 0;
   int max_tok = 0, min_tiles = INT32_MAX;
@@ -233,7 +233,8 @@ extern "C" int32_t rlkv_plan_whole_pairs(const int32_t* rounds, int32_t n_pairs,
 
 extern "C" int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
                                           const int32_t* n_tokens, const int32_t* cached, int32_t min_share_tiles) {
-  if (!n_tokens || !cached || n_compute_units < 1 || group < 1 || group > rlkv::kMaxGroup || n_full_heads < 0 || batch < 1)
+  if (!n_tokens || !cached || n_compute_units < 1 || group < 1 || group > rlkv::kMaxGroup || n_full_heads < 0 || batch < 1 ||
+      min_share_tiles < 1)
     return -1;
   for (int b = 0; b < batch; ++b)
     if (n_tokens[b] < 0 || cached[b] < 0) return -1;

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
     (6, 2, [0, 1], [1, 0.7], 3),
 ], ids=["one of two full heads blends", "two sequences", "group of 16", "group of 3"])
 def test_blending_workgroups_divided(gpu_device, Hq, Hkv, mask, gates, B, page, monkeypatch):
-    monkeypatch.setattr(harness, "TUNING", {"prefill_min_share_tiles": 8})      # shares from 4 tiles on
+    monkeypatch.setattr(harness, "TUNING", {"prefill_min_share_tiles": 4})
     c = Case(Hq=Hq, Hkv=Hkv, B=B, S=33, R=96, dtype=rl.RLKV_BF16, kernel=rl.RLKV_KERNEL_MFMA, mask=mask, cap=2300, seed=7,
              prefill_tokens=160, page_tokens=page, pool_pages=B * 36 if page else 0, arena_fill=0xFF)
     g = np.asarray(gates, dtype=np.float32)

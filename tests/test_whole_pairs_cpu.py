@@ -59,3 +59,5 @@ def test_narrow_split_stays_within_grid_and_scratch():
     assert seen == set(range(1, 9))
     one = np.ones(1, np.int32)
     assert lib.rlkv_plan_narrow_split(256, 17, 1, 1, one.ctypes.data, one.ctypes.data, 1) == -1
+    for minimum in (0, -1):                                  # a share without tiles is none
+        assert lib.rlkv_plan_narrow_split(256, 7, 1, 1, one.ctypes.data, one.ctypes.data, minimum) == -1
