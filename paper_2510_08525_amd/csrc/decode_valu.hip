@@ -57,10 +57,11 @@ template <> struct Elem<float> {
   __device__ static float dot(const Q& q, const uint4 (&k)[2]) {
     float kf[8];
     unpack(k, kf);
-    float d = 0.f;
+    // (a sum of its own per chunk: one chain over both loses more of the small products behind large ones)
+    float d[2] = {0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < 8; ++e) d = fmaf(q.f[e], kf[e], d);
-    return d;
+    for (int e = 0; e < 8; ++e) d[e >> 2] = fmaf(q.f[e], kf[e], d[e >> 2]);
+    return d[0] + d[1];
   }
 };
 template <> struct Elem<uint16_t> {
