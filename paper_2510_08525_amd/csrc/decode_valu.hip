@@ -10,9 +10,9 @@
 // Mapping: a wavefront reads whole rows with 128-bit loads, 16 lanes per row (a 256-byte bf16 row
 // in one load, a 512-byte fp32 row in two); every lane keeps its 8 elements of Q for all heads of the group, so a
 // K/V row is loaded once per group.  (32 lanes per fp32 row, 4 elements each, took twice the reductions, exponentials and
-// batches per tile.  With the batches asked for ahead and one round of tiles per workgroup, fp32 decode of one sequence of
-// 1000 tokens: 16.3 -> 11.3 us a call, 8 of 5000: 43.2 -> 35.2 us; with the append in the same launch, a step of one
-// sequence of 1000 tokens: 21 -> 13 us.)
+// batches per tile.  With one round of tiles per workgroup where the grid allows it, fp32 decode of one sequence of 1000 tokens:
+// 15.7 -> 10.7 us a call, 8 of 5000: 43.2 -> 33.4 us; with the append in the same launch, a step of one sequence of 1000
+// tokens: 18.2 -> 11.2 us.)
 // Dot products are reduced across the lanes of a row with DPP row rotations; each group
 // of lanes that shares a row index runs its own online softmax, and the streams are
 // merged at the end of the segment (lane groups by shuffles, wavefronts through LDS).
@@ -210,16 +210,20 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
         for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
       }
 
-      // The wavefront's rows in batches of U loads of K and of V.  Two register images that swap roles: a batch is asked
-      // for before the one ahead of it is worked on, so that a latency is paid once and not per batch.
-      struct Rows { uint4 k[U][CH], v[U][CH]; };
-      auto row_of = [&](int tile, int bt, int u) { return tile * kTile + (bt * U + u) * RPL + rg; };
-      auto counts = [&](int tok) { return tok < n_eff && (pass == 0 || tok < keep_lo || tok >= keep_from); };
+      // The wavefront's rows in batches of U loads of K and of V.
+      // fp32, and groups beyond 4: one loop, one copy of its body.  bf16 up to group 4: two register images that swap roles, a
+      // batch asked for before the one ahead of it is worked on.  With the images everywhere the body stands four times,
+      // 29 to 43 KB of code at group 8, and half the registers are reached through copies.  Two images / one loop (us per
+      // call): bf16, 8 sequences of 5000 tokens, 32 query and 8 KV heads 22.1 / 27.6, group 16 (one sequence) 35.7 / 32.6; fp32,
+      // group 16, 8 of 5000 95.6 / 84.8, one of 60 23.8 / 19.0; fp32, group 4: one of 1000 tokens, a fused step 11.8 / 11.2.
+      struct Rows { uint4 k[U][CH], v[U][CH]; bool on[U]; };
       auto load = [&](Rows& r, int tile, int bt) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const int tok = row_of(tile, bt, u);
-          const int tc = counts(tok) ? tok : n_eff - 1;      // stay inside the valid prefix
+          const int tok = tile * kTile + (bt * U + u) * RPL + rg;
+          // (no short circuits: they make a branch around every row's loads)
+          r.on[u] = (tok < n_eff) & ((pass == 0) | (tok < keep_lo) | (tok >= keep_from));
+          const int tc = r.on[u] ? tok : n_eff - 1;          // stay inside the valid prefix
           const int64_t off = (int64_t)tc * dv.row_bytes + c * 16;
           // rows are read once per step: stream them past the caches
 #pragma unroll
@@ -231,20 +235,19 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
           }
         }
       };
-      auto work = [&](Rows& r, int tile, int bt) {
+      auto work = [&](Rows& r) {
         float s[U][GB];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-          const bool on = counts(row_of(tile, bt, u));
           // (a row that does not count may be the one another wavefront is writing: nothing of it may reach a sum)
 #pragma unroll
           for (int i = 0; i < CH; ++i)
-            if (FUSED && !on) r.v[u][i] = make_uint4(0, 0, 0, 0);
+            if (FUSED && !r.on[u]) r.v[u][i] = make_uint4(0, 0, 0, 0);
 #pragma unroll
           for (int g = 0; g < GB; ++g) {
             float d = Elem<T>::dot(qf[g], r.k[u]);
             d = row_sum16(d);
-            s[u][g] = on ? d * scale_log2 : -INFINITY;
+            s[u][g] = r.on[u] ? d * scale_log2 : -INFINITY;
           }
         }
         float p[U][GB];
@@ -282,22 +285,31 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
         if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + 3) / 4 * 4;   // hop over the evicted middle
         return tile;
       };
-      int tile = settle(tile_lo + wave), bt = 0;
-      auto step_on = [&]() { if (++bt == kBatches) { bt = 0; tile = settle(tile + 4); } };
-      if (tile < tile_hi) {
-        Rows ra, rb;
-        load(ra, tile, bt);
-        for (;;) {
-          int wt = tile, wb = bt;
-          step_on();
-          if (tile >= tile_hi) { work(ra, wt, wb); break; }
-          load(rb, tile, bt);
-          work(ra, wt, wb);
-          wt = tile; wb = bt;
-          step_on();
-          if (tile >= tile_hi) { work(rb, wt, wb); break; }
+      if constexpr (GB > 4 || sizeof(T) == 4) {
+        for (int tile = settle(tile_lo + wave); tile < tile_hi; tile = settle(tile + 4)) {
+#pragma unroll 1
+          for (int bt = 0; bt < kBatches; ++bt) {
+            Rows r;
+            load(r, tile, bt);
+            work(r);
+          }
+        }
+      } else {
+        int tile = settle(tile_lo + wave), bt = 0;
+        auto step_on = [&]() { if (++bt == kBatches) { bt = 0; tile = settle(tile + 4); } };
+        if (tile < tile_hi) {
+          Rows ra, rb;
           load(ra, tile, bt);
-          work(rb, wt, wb);
+          for (;;) {
+            step_on();
+            if (tile >= tile_hi) { work(ra); break; }
+            load(rb, tile, bt);
+            work(ra);
+            step_on();
+            if (tile >= tile_hi) { work(rb); break; }
+            load(ra, tile, bt);
+            work(rb);
+          }
         }
       }
 
