@@ -677,36 +677,13 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
   return RLKV_OK;
 }
 
+// What a list is planned for: a decode call, a whole step in one call, or a step whose launch may be a recorded one.
+enum class ListUse { kDecode, kStep, kPrepared };
+
 // Makes sure the layer's work list covers the current lengths plus `growth` more tokens.  The list
 // is planned here, on the host, from the mirror of the lengths (see share_plan.hip), written into
-// a pinned staging slot and copied to the device on `s`: no kernel, no synchronisation.
-// Where a list of whole pairs (one workgroup per pair, no partials, no merge launch) takes over.  It saves the merge
-// launch (3.3 us, and the host's time for it) and costs the time that the longest pair takes one CU beyond an even share
-// of all rows: a CU draws about 100 GB/s when many do (64 pairs), 190 GB/s when few do (8 pairs).
-// Measured, whole pairs against shares, 32 query and 8 KV heads, half the heads compressed: one sequence of 1000 / 1500 /
-// 2000 tokens 8.5 / 10.4 / 13.9 against 10.5 / 10.6 / 10.5 us; 8 of 500 / 1000: 8.0 / 11.2 against 10.4 / 10.5 us;
-// 32 of 1000 / 2000: 16.2 / 27.5 against 19.9 / 28.0 us.
-// Row-major stores (four wavefronts, no matrix cores; fp32): 8 sequences of 100 / 300 tokens 8.7 / 15.4 against 12 us.
-static bool wants_whole_pairs(const rlkv_cache_t* cache, int32_t layer) {
-  const DeviceView& dv = cache->dv;
-  const int B = dv.batch, H = dv.n_kv_heads;
-  const int32_t* lh = cache->len_host.data() + (size_t)layer * B;
-  const uint8_t* mask = cache->mask.data() + (size_t)layer * H;
-  int64_t n_full = 0, pairs = 0, longest = 0, all = 0;
-  for (int h = 0; h < H; ++h) n_full += mask[h] ? 1 : 0;
-  for (int b = 0; b < B; ++b) {
-    if (!cache->active[b]) continue;
-    pairs += H;
-    const int64_t n = lh[b], n_comp = std::min<int64_t>(n, dv.window);
-    longest = std::max(longest, n_full > 0 ? n : n_comp);
-    all += n_full * n + (H - n_full) * n_comp;
-  }
-  const int64_t excess = (longest - all / dv.n_wg) * 2 * dv.row_bytes;
-  const int64_t most = dv.kernel != RLKV_KERNEL_MFMA ? kWholeExcessRows : pairs <= kWholeFewPairs ? kWholeExcessFew : kWholeExcess;
-  return pairs <= dv.n_wg && excess <= most;
-}
-
-static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int growth, hipStream_t s) {
+// a pinned staging slot and read from there by a small kernel on `s`: no synchronisation.
+static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int growth, ListUse use, hipStream_t s) {
   if (cache->wl_slack[layer] >= growth) return RLKV_OK;
   const DeviceView& dv = cache->dv;
   const int B = dv.batch, H = dv.n_kv_heads, n_pairs = dv.n_pairs, n_wg = dv.n_wg;
@@ -722,7 +699,14 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   int32_t* wg_begin = cache->plan_begin.data();
   int32_t* seg_first = cache->plan_first.data();
   int32_t* seg_count = cache->plan_count.data();
-  const bool whole = wants_whole_pairs(cache, layer);
+  // (a prepared step is followed by the merge launch whatever its list, for the growth counter: whole pairs save it nothing)
+  bool whole = false;
+  if (use != ListUse::kPrepared) {
+    int n_full = 0;
+    for (int h = 0; h < H; ++h) n_full += mask[h] ? 1 : 0;
+    whole = wants_whole_pairs(dv.kernel, dv.dtype, dv.group, cache->layer_gated[layer] != 0, use == ListUse::kStep, n_wg, H, n_full,
+                              dv.window, B, lh, cache->active.data());
+  }
   if (whole) plan_whole_pairs(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
   else cache->list_used[layer] = plan_shares(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
 
@@ -809,8 +793,6 @@ rlkv_status_t rlkv_prefill_attention(rlkv_cache_t* cache, int32_t layer, const v
   return append_impl(cache, layer, k, v, n_tokens, 0, stride_tokens, stream, &args);
 }
 
-// Decode attention of one layer with the kernels looking for their tables and partials in `dv` (the cache's own
-// view, or a copy whose partials point elsewhere).
 // Is `s` recording into a graph?  (A failing query counts as "no".)
 static bool stream_is_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -824,7 +806,7 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
                                       float softmax_scale, hipStream_t s) {
   cache->last_stream = s;
   const float scale_log2 = softmax_scale * 1.44269504088896340736f;
-  if (rlkv_status_t st = ensure_worklist(cache, layer, 0, s)) return st;
+  if (rlkv_status_t st = ensure_worklist(cache, layer, 0, ListUse::kDecode, s)) return st;
   const bool record = (size_t)cache->prof_used * 2 + 1 < cache->prof_events.size();
   hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
   hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
@@ -937,7 +919,7 @@ rlkv_status_t rlkv_set_gates(rlkv_cache_t* cache, const float* gates, void* stre
   return RLKV_OK;
 }
 
-rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, void* stream) {
+static rlkv_status_t prepare_step(rlkv_cache_t* cache, int32_t layer, ListUse use, void* stream) {
   if (!cache) return RLKV_ERR_INVALID_ARG;
   if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
   const int B = cache->cfg.batch;
@@ -957,7 +939,7 @@ rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, voi
     for (int b = 0; b < B; ++b) cache->new_len[b] = lh[b] + (cache->active[b] ? 1 : 0);
     if (rlkv_status_t st = reserve_pages(cache, cache->new_len, s)) return st;
   }
-  if (rlkv_status_t st = ensure_worklist(cache, layer, 1, s)) return st;
+  if (rlkv_status_t st = ensure_worklist(cache, layer, 1, use, s)) return st;
   // the mirrors take the step now; the launch (or the replay of a recorded launch) performs it on the device
   for (int b = 0; b < B; ++b) lh[b] += cache->active[b] ? 1 : 0;
   cache->wl_slack[layer] -= 1;
@@ -965,6 +947,10 @@ rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, voi
   ++cache->decode_calls[layer];
   cache->step_ready[layer] = 1;
   return RLKV_OK;
+}
+
+rlkv_status_t rlkv_append_decode_prepare(rlkv_cache_t* cache, int32_t layer, void* stream) {
+  return prepare_step(cache, layer, ListUse::kPrepared, stream);
 }
 
 // `prepared`: by the same call, so the device is set and the stream does not capture.  `grow_known`: and no step prepared
@@ -986,11 +972,11 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
   hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
   const bool tiled = cache->dv.kernel == RLKV_KERNEL_MFMA;
-  // (a recorded launch takes the form that suits the present lengths)
-  const bool whole = capturing ? wants_whole_pairs(cache, layer) : cache->list_whole[layer] != 0;
+  // (a recorded launch takes the form for shares: its replays are prepared)
+  const bool whole = !capturing && cache->list_whole[layer] != 0;
   // (a list of shares has a merge kernel behind it that advances the counter; written by the attention kernel of a
   // 28-layer step of 16 x 16384 tokens instead, it cost 0.7 us per launch)
-  const int grow = whole && grow_known && !capturing ? cache->list_grow[layer] - 1 : -1;
+  const int grow = whole && grow_known ? cache->list_grow[layer] - 1 : -1;
   const bool few = !capturing && 2 * cache->list_used[layer] <= cache->dv.n_wg;
   const hipError_t e = tiled ? launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v,
                                                   whole, grow, few, s, e0, e1)
@@ -1023,7 +1009,7 @@ rlkv_status_t rlkv_append_decode(rlkv_cache_t* cache, int32_t layer, const void*
   if (layer < 0 || layer >= cache->cfg.n_layers) return RLKV_ERR_INVALID_ARG;
   if (!(softmax_scale == softmax_scale)) return RLKV_ERR_INVALID_ARG;
   const bool grow_known = !cache->step_ready[layer];
-  if (rlkv_status_t st = rlkv_append_decode_prepare(cache, layer, stream)) return st;
+  if (rlkv_status_t st = prepare_step(cache, layer, ListUse::kStep, stream)) return st;
   return launch_step(cache, layer, k, v, q, out, softmax_scale, stream, true, grow_known);
 }
 

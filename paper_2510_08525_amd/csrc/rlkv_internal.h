@@ -20,8 +20,6 @@ constexpr int kRoundCost = 2;          // cost model of the share partition, in 
 constexpr int kPairStartCost = 3;      // ... and the start of a pair (pipeline restart on a new store, Q load,
                                        // merge, output write): about 1.5 rounds, from per-workgroup timestamps
 constexpr int kWholeWaves = 8;         // wavefronts of a workgroup that works one whole pair of the tiled layout
-constexpr int64_t kWholeExcess = 384 << 10, kWholeExcessFew = 768 << 10, kWholeExcessRows = 128 << 10;   // see wants_whole_pairs
-constexpr int kWholeFewPairs = 16;
 constexpr int kWorklistSlack = 32; // tokens a work list stays valid for after it was built
 
 // Work-list records, written by the host (share_plan.hip, ensure_worklist) and read by the attention and merge
@@ -206,6 +204,9 @@ int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin,
 // the shares, so that few pairs still meet all XCDs.
 void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
                       int32_t* seg_count);
+// Whether a list of whole pairs is the faster one for sequences of these lengths (see share_plan.hip).
+bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
+                       int batch, const int32_t* lengths, const uint8_t* active);
 // ev_start / ev_stop (both or neither): events that receive the kernel's own begin and end
 // timestamps (the dispatch's completion signal), for the measurement aid.
 // `gated`: some full head of the layer has a gate below 1 (two passes for those heads).

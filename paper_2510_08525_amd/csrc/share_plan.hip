@@ -10,6 +10,7 @@
 // The plan is the in-order greedy deal at the smallest capacity that needs no more workgroups than
 // the grid has; greedy is optimal for a contiguous partition once the capacity is fixed.
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "prefill_deal.h"
@@ -105,6 +106,53 @@ void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_
     seg_count[p] = 1;
   }
   while (w <= n_wg) wg_begin[w++] = us;
+}
+
+// Where a list of whole pairs takes over from one of shares.  It saves the merge launch (3.3 us, and the host's time for it)
+// and costs the time that the longest pair takes one CU beyond an even share of all rows.
+// Tiled stores: the difference in us, whole pairs minus shares, as a sum over what both depend on; the factors were fitted to 1277
+// pairs of timings (1 to 64 sequences of 100 to 8000 tokens, even and ragged, groups 1 to 16, 1 to 256 pairs), of which this
+// rule picks the slower side by 0.2 to 0.4 % on average and by more than 10 % five times; limits on the rows alone, which had
+// been measured at group 4, were up to 1.7 x slower at others.  Whole / shares, us: decode, one sequence of 32 query and 8 KV
+// heads, half compressed, 800 tokens 7.5 / 8.1, 1000 8.8 / 8.3; 16 of them, 800 11.7 / 13.0, 1200 16.2 / 13.6; 32, 1400 20.8 / 22.8;
+// one of 16 heads on 1, 700 8.8 / 9.2, 1000 11.0 / 9.5; a step of 4 of 28 and 4 heads that blend, 300 12.6 / 14.0, 700 16.2 / 13.6;
+// 3 of 8 and 8 of 182, 316 and 500 tokens 6.6 / 8.2.  (Beyond 800 rows of excess nothing was fitted.)
+// Row-major stores have no wide form, so rounds of four tiles count: one always pays (fp32, group 16, one sequence of 100 tokens
+// 20.6 / 24.0, of 130 27.0 / 24.0); bf16 without gates two up to group 4 (one sequence, group 4: 200 9.0 / 10.1, 260 10.8 /
+// 10.2), three up to group 2 (300 7.2 / 8.1, 400 8.2 / 8.1); fp32, group 4: 130 10.2 / 11.0, 260 13.2 / 11.2; beyond that only
+// pairs that fill the CUs about evenly (fp32, 64 of 28 and 4 heads, 400 tokens: 27.8 / 29.6; 32 of 64 and 4, 130: 31.7 / 26.7).
+struct WholeCost {
+  double fixed;          // merge launch saved, start of eight wavefronts
+  double longest, even;  // per 1000 rows of the longest pair; of an even share
+  double alike;          // per doubling of the pairs as long as the longest: they share the memory
+  double wide;           // group beyond 8
+  double filled;         // per pair and CU: shares cut the more pairs in two, the nearer these are in number
+};
+constexpr WholeCost kWholeCost[2][2] = {      // [some full head blends][planned by a fused step]
+    {{-4.1, 3.9, -4.8, 0.4, 0.4, -1.3}, {-4.1, 3.9, -3.9, 0.4, 0.3, -2.1}},
+    {{-2.9, 3.8, -3.9, 0.1, 0.4, -1.8}, {-3.3, 4.0, -3.2, 0.4, 0.8, -5.3}}};
+bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
+                       int batch, const int32_t* lengths, const uint8_t* active) {
+  int64_t pairs = 0, longest = 0, all = 0;
+  for (int b = 0; b < batch; ++b) {
+    if (active && !active[b]) continue;
+    pairs += n_kv_heads;
+    const int64_t n = lengths[b], n_comp = std::min<int64_t>(n, window);
+    longest = std::max(longest, n_full > 0 ? n : n_comp);
+    all += n_full * n + (n_kv_heads - n_full) * n_comp;
+  }
+  if (pairs > n_wg) return false;
+  const int64_t excess = longest - all / n_wg;
+  if (kernel != RLKV_KERNEL_MFMA) {
+    const bool light = group <= 4 && !gated;
+    const int rounds = !light || dtype == RLKV_F32 ? 1 : group <= 2 ? 3 : 2;
+    return longest <= rounds * kRound * kTile || excess <= (light ? 128 : 64);
+  }
+  if (longest == 0) return true;
+  const WholeCost& c = kWholeCost[gated][step];
+  const double diff = c.fixed + (c.longest * longest + c.even * all / n_wg) * 1e-3 + c.alike * std::log2(1.0 + (double)all / longest) +
+                      (group > 8 ? c.wide : 0.0) + c.filled * pairs / n_wg;
+  return excess <= 800 && diff <= 0.0;
 }
 
 }  // namespace rlkv
@@ -229,6 +277,19 @@ extern "C" int32_t rlkv_plan_whole_pairs(const int32_t* rounds, int32_t n_pairs,
   if (used > n_workgroups) return -1;
   rlkv::plan_whole_pairs(rounds, n_pairs, n_workgroups, wg_begin, seg_first, seg_count);
   return used;
+}
+
+extern "C" int32_t rlkv_plan_list_whole(int32_t kernel, int32_t dtype, int32_t group, int32_t gated, int32_t step, int32_t n_workgroups,
+                                        int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
+                                        const int32_t* lengths, const uint8_t* active) {
+  if (!lengths || (kernel != RLKV_KERNEL_VALU && kernel != RLKV_KERNEL_MFMA) || (dtype != RLKV_F32 && dtype != RLKV_BF16)) return -1;
+  if (group < 1 || group > rlkv::kMaxGroup || n_workgroups < 1 || n_kv_heads < 1 || n_full_heads < 0 || n_full_heads > n_kv_heads ||
+      window < 1 || batch < 1)
+    return -1;
+  for (int b = 0; b < batch; ++b)
+    if (lengths[b] < 0) return -1;
+  return rlkv::wants_whole_pairs(kernel, dtype, group, gated != 0, step != 0, n_workgroups, n_kv_heads, n_full_heads, window, batch,
+                                 lengths, active);
 }
 
 extern "C" int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,

@@ -56,8 +56,8 @@ def test_growth_across_the_rule(gpu_device, dtype, kernel, at, gated):
 @pytest.mark.parametrize("page", [0, 64])
 @pytest.mark.parametrize("first,second", [(300, 2600), (2600, 300)])
 def test_recorded_launch_outlives_its_kind_of_list(gpu_device, page, first, second):
-    """Recorded while the lengths call for one kind of list, replayed under the other; then steps by call again, the first
-    of which follows a prepared step the host cannot know to have run."""
+    """Recorded and replayed under lists that a decode call planned, of whole pairs at 300 tokens and of shares at 2600; then
+    steps by call again, the first of which follows a prepared step the host cannot know to have run."""
     steps = 3
     cap = max(first, second) + 16
     c = Case(Hq=28, Hkv=4, B=2, S=8, R=56, dtype=BF16, kernel=MFMA, mask=[1, 0, 0, 1], cap=cap, seed=6, page_tokens=page,
@@ -66,6 +66,7 @@ def test_recorded_launch_outlives_its_kind_of_list(gpu_device, page, first, seco
     v, q = torch.zeros_like(k), torch.zeros(2, 28, 128, dtype=torch.bfloat16, device=c.device)
     out = torch.zeros_like(q)
     c.append([first, first // 2])
+    c.check_decode(40, "the call that plans the first list")
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         c.cache.append_decode_launch(0, k, v, q, out, c.scale)
@@ -91,6 +92,7 @@ def test_recorded_launch_outlives_its_kind_of_list(gpu_device, page, first, seco
         c.cache.reset()
         c.n[:] = 0
         c.append([second, second // 2])
+    c.check_decode(41, "the call that plans the second list")
     for s in range(steps):
         replay(10 + s)
     c.check_indices()
