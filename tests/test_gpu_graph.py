@@ -48,7 +48,7 @@ def _setup(L, Hq, Hkv, B, S, R, mask, ctx, steps, seed, page_tokens=0, dtype=BF1
 @pytest.mark.parametrize("page_tokens,dtype,kernel", [(0, BF16, MFMA), (64, BF16, MFMA), (0, F32, VALU), (0, BF16, VALU)],
                          ids=["contiguous", "paged", "f32 vector-ALU kernel", "bf16 vector-ALU kernel"])
 def test_replayed_step_matches_per_call_path_and_oracle(gpu_device, page_tokens, dtype, kernel):
-    """(With the vector-ALU kernel a recorded step is three launches - append, attention, merge - and the
+    """(The step is two launches, attention with the append and merge, with either kernel; with the vector-ALU kernel the
     per-call leg takes the two separate calls rlkv_append and rlkv_decode_attention.)"""
     L, Hq, Hkv, B, S, R = 3, 28, 4, 4, 8, 24
     mask = np.array([[1, 0, 0, 1], [0, 0, 1, 0], [1, 1, 0, 0]], dtype=np.uint8)
