@@ -151,17 +151,9 @@ __device__ inline void seq_in_order(const DeviceView& dv, const SeqOrder& order,
 //         16x16x32 B operand whose k index runs over the 32 slots of the tile in the
 //         same order the score tile leaves them in the accumulator registers.
 // K and V tiles of the same 32 slots sit next to each other (16 KiB: K then V), so the 16
-// loads a wavefront issues per tile fall into one contiguous block.  Offsets are relative
-// to the start of the pair's store.
+// loads a wavefront issues per tile fall into one contiguous block.  Rows are brought into this order by rows_to_tile
+// (tile_rows.h) and by the append of a fused step (decode_mfma.hip).
 constexpr int kTileBytes = 16384;
-__host__ __device__ inline int64_t tiled_k_offset(int slot, int chunk) {
-  return (int64_t)(slot >> 5) * kTileBytes + ((slot >> 4) & 1) * 4096 + chunk * 256 + (slot & 15) * 16;
-}
-__host__ __device__ inline int64_t tiled_v_offset(int slot, int d) {
-  const int st = slot & 31;
-  const int half = st >> 4, kb = (st & 15) >> 2, r = st & 3;
-  return (int64_t)(slot >> 5) * kTileBytes + 8192 + (d >> 4) * 1024 + (kb * 16 + (d & 15)) * 16 + (half * 4 + r) * 2;
-}
 
 // bf16 bits whose value lies beyond the fp16 range (exponent field >= 127 + 16; Inf and NaN included)
 __host__ __device__ inline bool bf16_beyond_fp16(uint32_t bits) { return (bits & 0x7f80u) >= 0x4780u; }
