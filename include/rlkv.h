@@ -51,8 +51,7 @@ typedef enum { RLKV_F32 = 0, RLKV_BF16 = 1 } rlkv_dtype_t;
  *                      ALU with wavefront DPP reductions.  fp32 and bf16.  The fp32 path, and
  *                      for bf16 the comparison baseline: at a group size of 7 its bf16 form
  *                      is bound by the vector ALU, not by memory, and streams at less than
- *                      60 % of the rate of the MFMA kernel; the append of a fused step is a
- *                      launch of its own; no paging, no prefill.
+ *                      60 % of the rate of the MFMA kernel; no paging, no prefill.
  *   RLKV_KERNEL_MFMA : stores tiled so that a 128-bit load per lane lands directly in
  *                      MFMA operand registers; bf16 only.
  *   RLKV_KERNEL_AUTO : MFMA for bf16, VALU for fp32. */
@@ -110,8 +109,8 @@ size_t rlkv_cache_required_bytes(const rlkv_config_t* cfg /* host */);
  * stores): lays the stores out in the arena, uploads the tables, sets all lengths to 0
  * and every ring slot to "empty".  `arena` must be 256-byte aligned and at least
  * rlkv_cache_required_bytes(cfg) long.  On success *out owns the handle.  A cache also holds a
- * block of pinned host memory (up to 64 MiB) in which the split-K work lists are written before
- * they are copied to the device; such blocks are recycled between caches and kept for the life
+ * block of pinned host memory (up to 64 MiB) in which the split-K work lists are written and from
+ * which a kernel reads them; such blocks are recycled between caches and kept for the life
  * of the process. */
 rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg /* host */, rlkv_cache_t** out /* host */);
 
@@ -196,10 +195,10 @@ rlkv_status_t rlkv_set_gates(rlkv_cache_t* cache, const float* gates /* host */,
 
 /* One whole decode step of a layer in one call: rlkv_append of a single token per
  * sequence (k, v: device [batch][n_kv_heads][1][head_dim]) followed by
- * rlkv_decode_attention, with the same results and error codes as the two calls.  With
- * the MFMA kernel the append runs inside the attention kernel (the wavefront that reads
- * the tile holding a new slot also writes the row), which removes a launch per layer -
- * the counterpart of the dual-dispatch overhead the paper names in Sec. 4.3. */
+ * rlkv_decode_attention, with the same results and error codes as the two calls.  The
+ * append runs inside the attention kernel (the wavefront that reads the tile holding a
+ * new slot also writes the row), which removes a launch per layer - the counterpart of
+ * the dual-dispatch overhead the paper names in Sec. 4.3. */
 rlkv_status_t rlkv_append_decode(rlkv_cache_t* cache, int32_t layer, const void* k /* device */,
                                  const void* v /* device */, const void* q /* device */,
                                  void* out /* device */, float softmax_scale, void* stream);

@@ -18,7 +18,7 @@ SOURCES = ["rlkv_api.hip", "append_evict.hip", "worklist_combine.hip", "decode_v
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-    # no packed-fp32 VALU forms: some have given wrong results on this part
+    # without the packed-fp32 VALU forms: every test and figure of the library is of code compiled like this
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 

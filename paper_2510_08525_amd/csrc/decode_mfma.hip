@@ -32,10 +32,12 @@
 // position p - R - or next row of a full head) before it loads that tile; each lane writes
 // exactly the bytes it later loads, so no other wavefront ever depends on the write.  No
 // workgroup reads a length from the table: a pair's length is its length when the work list was
-// planned plus the list's growth counter (ListHeader::grow), which this kernel only reads - the
-// merge kernel that follows advances it - so the kernel needs no grid-wide fence, takes no
-// per-step argument, and a captured launch can be replayed.  The new lengths are written to
-// both copies of the length table for the kernels that do read it.
+// planned plus the list's growth counter (ListHeader::grow), which no workgroup writes while another
+// one reads it, so the kernel needs no grid-wide fence: under a list of shares every workgroup reads
+// the counter and the merge kernel that follows advances it - no per-step argument, and a captured
+// launch can be replayed; under a list of whole pairs, which has no merge kernel, the count comes as an
+// argument, nobody reads the counter, and the first workgroup writes it.  The new lengths are written
+// to both copies of the length table for the kernels that do read it.
 #include "mfma_tile.h"
 
 namespace rlkv {
@@ -95,8 +97,8 @@ __device__ __forceinline__ void process_tile(TileRegs& t, const Frag (&qb)[4], S
 // configuration the library launches), which leaves it 512 registers.
 //
 // WAVES = 8 (kWholeWaves): the form for lists of whole pairs (share_plan.hip), two wavefronts per SIMD.  A launch whose
-// `grow` is -1 (one that may be a recorded launch, replayed under other lists) takes the growth from the list's header,
-// and if the list is not of whole pairs, the upper four wavefronts have no tiles and every pair is worked as the
+// `grow` is -1 (one whose growth only the device knows, or a recorded decode call, replayed under other lists) takes the growth from
+// the list's header, and if the list is not of whole pairs, the upper four wavefronts have no tiles and every pair is worked as the
 // four-wavefront form does, to the bit.
 // Bound: a whole-pair launch is a chain of latencies (record, first tiles, merge, store) plus its longest pair at what
 // one CU can draw.  Decode call of 1 / 8 / 32 sequences of 300 tokens, 32 query and 8 KV heads: 7.4 / 7.4 / 8.3 us against

@@ -182,14 +182,15 @@ struct rlkv_cache {
   std::vector<int32_t> free_pages;       // stack of free page indices
   std::vector<int32_t> pages_held;       // [B] pages the sequence holds
   std::vector<int32_t> table_host;       // [B][table_stride]
-  // work lists are planned on the host and copied over: host copies of the tables the records need,
-  // and pinned staging slots (one per layer up to a budget) with an event each that tells when
-  // the slot's last copy has run
+  // work lists are planned on the host and read from there by a kernel: host copies of the tables the
+  // records need, and pinned staging slots (one per layer up to a budget) with an event each that tells
+  // when the slot has last been read
   std::vector<int64_t> store_off_host;   // [L][B][Hkv]
   std::vector<int32_t> cap_pad_host;     // [B]
   std::vector<int32_t> plan_rounds, plan_begin, plan_first, plan_count;   // scratch of the planner
   // One block of pinned host memory, cut into two rings of staging slots.  Every slot has an event that tells
-  // when the last copy out of it has run, so a slot is rewritten only after the device has read it.
+  // when the device has last read it (a list by launch_fetch, the small tables by a copy), so a slot is
+  // rewritten only after that.
   char* pinned = nullptr;
   size_t pinned_bytes = 0;
   struct Ring {
@@ -243,7 +244,7 @@ static void release_host_staging(rlkv_cache_t* cache) {
   cache->pinned = nullptr;
 }
 
-// The next slot of a ring, once the copy that last read it has run (it has, unless the host is a whole
+// The next slot of a ring, once the kernel or copy that last read it has run (it has, unless the host is a whole
 // round of slots ahead of the device); nullptr on a HIP error.
 static char* ring_take(rlkv_cache::Ring& r, int* slot) {
   *slot = r.next;
@@ -252,7 +253,7 @@ static char* ring_take(rlkv_cache::Ring& r, int* slot) {
   r.busy[*slot] = 0;
   return r.base + (size_t)*slot * r.slot_bytes;
 }
-// Marks the slot as read by the copies queued on `s` so far.
+// Marks the slot as read by what is queued on `s` so far.
 static bool ring_sent(rlkv_cache::Ring& r, int slot, hipStream_t s) {
   if (hipEventRecord(r.events[slot], s) != hipSuccess) return false;
   r.busy[slot] = 1;
@@ -483,7 +484,7 @@ rlkv_status_t rlkv_cache_destroy(rlkv_cache_t* cache) {
   rlkv_status_t st = RLKV_OK;
   drop_profile_events(cache);
   (void)hipSetDevice(cache->cfg.device);
-  (void)wait_for_cache(cache);           // a copy out of the pinned staging may still be queued
+  (void)wait_for_cache(cache);           // something that reads the pinned staging may still be queued
   release_host_staging(cache);
   if (cache->owns_arena && cache->arena) {
     if (hipFree(cache->arena) != hipSuccess) st = RLKV_ERR_HIP;

@@ -26,12 +26,13 @@ constexpr int kWorklistSlack = 32; // tokens a work list stays valid for after i
 // kernels with wave-uniform (scalar) loads.  A workgroup's record embeds the record of its
 // first pair, so one load level separates the kernel start from the first K/V tile load.
 // The list of a layer is one block of device memory, [ListHeader][WgDesc x n_wg][PairDesc x n_pairs], written by
-// a single copy out of a pinned staging slot of the same layout.
+// one kernel (launch_fetch) that reads a pinned staging slot of the same layout.
 struct ListHeader {      // 64 bytes
-  int32_t grow;          // tokens every active sequence has gained since the list was planned.  The copy that
-                         // brings a new list sets it to 0; the kernels that append advance it (the merge kernel
-                         // behind a fused step by 1, a uniform multi-token append by its token count), so that a
-                         // decode launch needs no per-step argument and a captured step can be replayed
+  int32_t grow;          // tokens every active sequence has gained since the list was planned.  A new list brings
+                         // 0; a fused step advances it by 1 (the merge kernel behind it, or, under a list of whole
+                         // pairs that has none, the attention kernel itself), a uniform multi-token append by its
+                         // token count, so that a decode launch needs no per-step argument and a captured step can
+                         // be replayed
   int32_t whole;         // 1: every share is one whole pair (plan_whole_pairs)
   int32_t pad[14];
 };

@@ -1,6 +1,6 @@
 // Host side of the work list: where the end-to-end sequence of scheduling units is cut into one
-// contiguous share per workgroup.  Runs on the host from the library's mirror of the lengths (the
-// records are then copied to the device), so a rebuild costs the GPU a small copy and no kernel.
+// contiguous share per workgroup.  Runs on the host from the library's mirror of the lengths; the
+// records are then read out of pinned memory by a small kernel (4 us, no copy engine).
 //
 // Cost model (paper Sec. 4.3: the residual cost of a compressed head is its sW/L tokens, so a
 // share's cost is what it reads plus what it restarts): kRoundCost per round of tiles plus
@@ -22,7 +22,7 @@ namespace rlkv {
 // seg_first / seg_count non-null also records the shares.
 static int deal_rounds(const int32_t* rounds, int n_pairs, int cap, int32_t* wg_begin, int32_t* seg_first,
                        int32_t* seg_count, bool single = false) {
-  const int per_fresh = single ? 1 : cap / kRoundCost;                  // rounds a workgroup takes of a pair it does not start
+  const int per_fresh = single ? 1 : cap / kRoundCost;     // rounds a workgroup takes of a pair it does not start
   int w = 0, used = 0, us = 0;                             // us: first unit of the pair in the end-to-end numbering
   for (int p = 0; p < n_pairs; ++p) {
     const int r = rounds[p];
