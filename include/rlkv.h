@@ -296,7 +296,7 @@ rlkv_status_t rlkv_pool_shuffle(rlkv_cache_t* cache, uint64_t seed);
 /* How rlkv_prefill_attention runs one chunk of a layer that does not blend (no gate below 1), exposed
  * for tests and tools (it touches no device).  The attention kernel has a form with two 16-column groups
  * of queries per wavefront and one with a single group (half the chunk positions per workgroup, less
- * efficient; the form that blends).  Long workgroups are those of full heads: 256 / group_size chunk
+ * efficient).  Long workgroups are those of full heads: 256 / group_size chunk
  * positions each.  When twice their number still fits n_compute_units, each one's unmasked tiles are
  * divided among as many workgroups (2..8) as fit one round over the compute units, provided the
  * shortest cached context leaves every share min_share_tiles 32-key tiles and the shares fit the
@@ -366,7 +366,7 @@ int32_t rlkv_plan_list_whole(int32_t kernel, int32_t dtype, int32_t group, int32
                              const int32_t* lengths /* host */, const uint8_t* active /* host */);
 
 /* Shares that every full-head workgroup of a prefill chunk (128 / group chunk positions) is divided into in the
- * single-group form of the kernel, the one that blends and the one rlkv_plan_prefill_form calls narrow: as many (at most 8) as
+ * single-group form of the kernel (the one rlkv_plan_prefill_form calls narrow; small chunks of blending layers take it too): as many (at most 8) as
  * fit one round over the compute units and the scratch slots and leave every share min_share_tiles tiles; 1 = undivided.
  * Exposed for tests and tools.  -1 on an invalid argument (min_share_tiles < 1 among them). */
 int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,

@@ -265,10 +265,14 @@ constexpr int kPrefillBlock = kPrefillWaves * 64;
 // wavefront owns NG 16-column groups of the workgroup's (position, head) columns, flattened
 // position-major across the whole workgroup.
 //
-// GATED (some full head of the layer has an Eq. 1 gate below 1): a wavefront owns one column group
-// instead of two, and its second accumulator set holds the local attention (sink + recent
-// positions) of the same columns; the scores of a tile are computed once for both, and the output
-// is gate * causal + (1 - gate) * local.
+// MIX (some full head of the layer has an Eq. 1 gate below 1: out = gate * causal + (1 - gate) * local): the causal
+// positions are the local ones and the rest, so a blending head's tiles are walked in two passes that share one set of
+// accumulators - first what is local (sinks and recent band), whose finished result is put aside in LDS, then the rest, on
+// top of it.  Every key is thus folded in once, a tile at the edge of the two in both passes, and the registers are those of a
+// plain head.  (Two accumulator sets side by side left room for one column group per wavefront, which makes the hot loop wait
+// for LDS - 16 KiB of operands per wavefront and tile for 16 columns - and folded every local tile in twice, in the general
+// loop: 8 sequences of 1000 to 4000 tokens in chunks of 1024, 28 query and 4 KV heads, 984 -> 775 us with the two passes,
+// 880 us with one column group per wavefront.)
 //
 // Two loops.  The hot one takes the tiles that every query of the workgroup sees whole: those of a
 // full head that lie wholly before the workgroup's first query (nearly all of a prefill's work),
@@ -278,7 +282,7 @@ constexpr int kPrefillBlock = kPrefillWaves * 64;
 // through registers) and read from there as MFMA operands; no masks.  The general one takes everything else (partly filled
 // tiles, a compressed head's ring, the causal diagonal and the band's edge, the sink and band tiles
 // of a gated head), each wavefront on its own, with per-slot positions and masks.
-template <bool PAGED, bool GATED>
+template <bool PAGED, int NG, bool MIX>
 __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView dv, int layer,
                                                                      SeqOrder order,
                                                                      const int32_t* __restrict__ len_in,
@@ -289,9 +293,14 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
                                                                      int staging_tiles, float* __restrict__ split_out,
                                                                      PrefillHeads heads) {
   // LDS: the K halves of four tiles (filled by loads that go from memory straight into LDS, two tiles ahead)
-  // and the V halves of two (through registers: V is converted on the way).
-  __shared__ uint4 sm_k[4][kTileBytes / 32];
+  // and the V halves of two (through registers: V is converted on the way); MIX: the local results, every lane its own.  With
+  // two column groups these leave room for two K halves, which use up the 160 KiB of a CU: tiles are then asked for one ahead.
+  constexpr int kKeySlots = MIX && NG == 2 ? 2 : 4;
+  __shared__ uint4 sm_k[kKeySlots == 2 ? 1 : kKeySlots][kTileBytes / 32];
+  __shared__ uint4 sm_k1[kKeySlots == 2 ? kTileBytes / 32 : 1];          // (an array of its own: the compiler would have reads of the
+                                                                          // one slot wait for the loads into the other)
   __shared__ uint4 sm_v[2][kTileBytes / 32];
+  __shared__ floatx4 sm_local[MIX ? kPrefillWaves : 1][MIX ? NG * 8 : 1][64];
   // Workgroups are handed out in grid order, and each XCD takes the rows dealt to it (prefill_deal) in
   // order: the long ones go first - the pairs of full heads before those of compressed heads, long
   // sequences before short ones, and within a pair the later query blocks (more keys under the
@@ -305,12 +314,11 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   pair_of_grid_row(dv, order, layer, by, heads, b, h, full, t);
   const int pair = b * dv.n_kv_heads + h;
   const int block_x = gridDim.x - 1 - bx;
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int hd = lane & 15;     // score layout: column; operand layouts: row / column
-  const int kb = lane >> 4;     // k-group of the operand layouts; slot quad of the score layout
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int tid = threadIdx.x, lane = tid & 63;
+  int hd = lane & 15;           // score layout: column; operand layouts: row / column
+  int kb = lane >> 4;           // k-group of the operand layouts; slot quad of the score layout
   const int G = dv.group, S = dv.sink, R = dv.recent;
-  constexpr int NG = GATED ? 1 : 2;                      // column groups of queries per wavefront
-  constexpr int LOCAL = NG;                              // index of the first local accumulator set (GATED)
   constexpr int kWaveCols = 16 * NG;
   // Columns are at most 256 and groups at most 16, so that col / G is exact as a product with the reciprocal rounded up.
   const int inv_g = heads.inv_group;
@@ -326,8 +334,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   if (!full && blockIdx.z > 0) return;       // a compressed head's workgroup is short: never divided
   const bool split = full && Z > 1;
   const bool wide = dv.v_wide[layer] != 0;   // (asked for early: read in front of the hot loop)
-  const float gate = (GATED && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
-  const bool mix = GATED && full && gate < 1.f;          // this head blends causal and local attention
+  const float gate = (MIX && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
+  const bool mix = MIX && full && gate < 1.f;            // this head blends causal and local attention
 
   // This wavefront's columns: kWaveCols of the workgroup's flattened (position, head) pairs.
   const int col0 = wave * kWaveCols;
@@ -381,66 +389,100 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // the workgroup's first query.  Compressed head: the store's complete sink tiles, and the staging
   // tiles wholly before the first query that also lie wholly inside the recent band of the last one
   // (a chunk is usually longer than the band, so these are most of what such a head attends over).
-  // A blending head also feeds its local accumulators from the tiles that hold sink positions or
-  // reach into the recent band of that first query: those take the general loop.  (A softmax scale
-  // that is not positive, unusual, takes the general loop throughout.)
+  // A blending head's first pass (kLocal): the complete sink tiles of the store, and the store and staging tiles wholly before
+  // the first query and wholly inside the recent band of the last one; its second pass (kRest): the tiles wholly behind the
+  // sinks and wholly before the band of the first query.  (A softmax scale that is not positive, unusual, takes the
+  // general loop throughout.)
   const bool hot = scale_log2 > 0.f;
-  int hs_lo = 0, hs_hi = 0;                  // hot store tiles [hs_lo, hs_hi)
-  int stg_lo = 0, stg_hi = 0;                // hot staging tiles [stg_lo, stg_hi)
-  if (hot) {
-    stg_hi = c_wg / kTile;
-    if (full) {
-      hs_hi = n_st / kTile;
-    } else {
-      hs_hi = (S < n_st ? S : n_st) / kTile;
-      const int band_first = c_last - R + 1;               // first chunk index the last query still sees
-      stg_lo = band_first > 0 ? (band_first + kTile - 1) / kTile : 0;
-      if (stg_lo > stg_hi) stg_lo = stg_hi;
-    }
-  }
-  if (mix) {
-    const int sink_slots = S < n_st ? S : n_st;
-    const int band_first = n_old + c_wg - R + 1;         // first position of the first query's band
-    hs_lo = (sink_slots + kTile - 1) / kTile;
-    if (hs_lo > hs_hi) hs_lo = hs_hi;
-    const int before_band = band_first > 0 ? band_first / kTile : 0;
-    if (hs_hi > before_band) hs_hi = before_band;
-    if (hs_hi < hs_lo) hs_hi = hs_lo;
-    const int before_band_stage = c_wg - R + 1 > 0 ? (c_wg - R + 1) / kTile : 0;
-    if (stg_hi > before_band_stage) stg_hi = before_band_stage;
-    if (sink_in_chunk > 0) stg_hi = 0;                   // the chunk itself still holds sink positions
-  }
-  const int hot_store = hs_hi - hs_lo;
-  const int n_plain_all = hot_store + stg_hi - stg_lo;
-  // (a divided workgroup: share z of Z of them; the last share also takes the general tiles)
-  const int plain_lo = split ? (int)((int64_t)n_plain_all * z / Z) : 0;
-  const int n_plain = split ? (int)((int64_t)n_plain_all * (z + 1) / Z) - plain_lo : n_plain_all;
-  auto plain_address = [&](int i0) -> const char* {
-    const int i = i0 + plain_lo;
-    return i < hot_store ? store.at(hs_lo + i) : stage + (int64_t)(stg_lo + i - hot_store) * kTileBytes;
-  };
+  const int stg_whole = hot ? c_wg / kTile : 0;          // staging tiles wholly before the first query
+  const int band_first = c_last - R + 1;                 // first chunk index that the last query's band holds
 
-  // General tiles of this wavefront: store tiles [0, n_store), then staging tiles [0, n_stage).
-  int n_store;
-  if (full) {
-    n_store = (n_st + kTile - 1) / kTile;
-  } else {
-    // the ring matters only while the wavefront's first query still reaches positions before the chunk
-    const int reach = c0 < R ? n_st : (S < n_st ? S : n_st);
-    n_store = (reach + kTile - 1) / kTile;
-  }
-  const int n_stage = c_hi / kTile + 1;
-  const int total = busy && (!split || z == Z - 1) ? n_store + n_stage : 0;
+  // General tiles of this wavefront: store tiles [0, n_store), then staging tiles [0, n_stage), without those that are hot or
+  // of no use to it.
   const int band_lo = c0 - R + 1;            // first chunk index inside the recent band of the wavefront's first query
-  // The first tile at or behind x that is not a hot one and that some query of the wavefront may see.  Ranges are hopped
-  // over, not walked: at 16 384 cached tokens the walk over a full head's 512 hot tiles took longer than the tiles here.
-  const int sink_tiles = !full && sink_in_chunk > 0 ? (sink_in_chunk + kTile - 1) / kTile : 0;   // staging tiles with sink positions
-  const int band_tile = !full && band_lo > 0 ? band_lo / kTile : 0;                              // the band's first staging tile
+  const int sink_tiles = sink_in_chunk > 0 ? (sink_in_chunk + kTile - 1) / kTile : 0;            // staging tiles with sink positions
+  const int band_tile = band_lo > 0 ? band_lo / kTile : 0;                                       // the band's first staging tile
+
+  // What a pass takes.  kWhole: a head that does not blend, its one pass.
+  enum { kLocal, kRest, kWhole };
+  int hs_lo, hs_hi;                          // hot store tiles [hs_lo, hs_hi)
+  int hb_lo, hb_hi;                          // kLocal: further ones, those of the band
+  int stg_lo, stg_hi;                        // hot staging tiles [stg_lo, stg_hi)
+  int n_store, n_stage;                      // general tiles: ranges, ...
+  int skip_lo = 0, skip_hi = 0;              // ... store tiles (beside the hot ones) and ...
+  int skip_stg_lo = 0, skip_stg_hi = 0;      // ... staging tiles that it passes over
+  auto plan_pass = [&](int pass) {
+    hs_lo = hs_hi = hb_lo = hb_hi = stg_lo = stg_hi = 0;
+    n_store = (n_st + kTile - 1) / kTile;
+    n_stage = c_hi / kTile + 1;
+    if (!MIX || pass == kWhole) {
+      stg_hi = stg_whole;
+      if (full) {
+        if (hot) hs_hi = n_st / kTile;
+      } else {
+        if (hot) {
+          hs_hi = (S < n_st ? S : n_st) / kTile;
+          stg_lo = band_first > 0 ? (band_first + kTile - 1) / kTile : 0;
+          if (stg_lo > stg_hi) stg_lo = stg_hi;
+        }
+        // the ring matters only while the wavefront's first query still reaches positions before the chunk
+        const int reach = c0 < R ? n_st : (S < n_st ? S : n_st);
+        n_store = (reach + kTile - 1) / kTile;
+        skip_stg_lo = sink_tiles;
+        skip_stg_hi = band_tile;
+      }
+      return;
+    }
+    const int sink_slots = S < n_st ? S : n_st;
+    const int sinks_up = (sink_slots + kTile - 1) / kTile;
+    if (pass == kLocal) {
+      const int band = n_old + band_lo;                  // first position of the wavefront's band
+      if (hot) {
+        hs_hi = sink_slots / kTile;
+        const int band_whole = n_old + band_first > 0 ? (n_old + band_first + kTile - 1) / kTile : 0;
+        hb_hi = n_st / kTile;
+        hb_lo = band_whole > hs_hi ? band_whole : hs_hi;
+        if (hb_lo > hb_hi) hb_lo = hb_hi;
+        stg_hi = stg_whole;
+        stg_lo = band_first > 0 ? (band_first + kTile - 1) / kTile : 0;
+        if (stg_lo > stg_hi) stg_lo = stg_hi;
+      }
+      skip_lo = sinks_up;                                // between the sinks and the band
+      skip_hi = band > 0 ? band / kTile : 0;
+      if (skip_hi > n_store) skip_hi = n_store;
+      skip_stg_lo = sink_tiles;
+      skip_stg_hi = band_tile;
+    } else {
+      const int rest = c_hi - R;                         // last chunk index outside the band of the wavefront's last query
+      const int rest_tiles = n_old + rest >= 0 ? (n_old + rest) / kTile + 1 : 0;
+      if (rest_tiles < n_store) n_store = rest_tiles;
+      n_stage = rest >= 0 ? rest / kTile + 1 : 0;
+      if (hot) {
+        const int before = n_old + c_wg - R + 1;         // first position of the first query's band
+        hs_lo = sinks_up;
+        hs_hi = before > 0 ? before / kTile : 0;
+        if (hs_hi > n_st / kTile) hs_hi = n_st / kTile;
+        if (hs_hi < hs_lo) hs_hi = hs_lo;
+        stg_lo = sink_tiles;                             // (while the chunk itself still holds sink positions)
+        stg_hi = c_wg - R + 1 > 0 ? (c_wg - R + 1) / kTile : 0;
+        if (stg_hi < stg_lo) stg_hi = stg_lo;
+      }
+      skip_lo = 0;                                       // nothing but sinks
+      skip_hi = sink_slots / kTile < n_store ? sink_slots / kTile : n_store;
+      skip_stg_lo = 0;
+      skip_stg_hi = sink_in_chunk > 0 ? sink_in_chunk / kTile : 0;
+    }
+  };
+  // The first general tile at or behind x.  Ranges are hopped over, not walked: at 16 384 cached tokens the walk over a full
+  // head's 512 hot tiles took longer than the tiles here.
   auto next_needed = [&](int x) {
+    if (MIX && x >= skip_lo && x < skip_hi) x = skip_hi;
     if (x >= hs_lo && x < hs_hi) x = hs_hi;
+    if (MIX && x >= skip_lo && x < skip_hi) x = skip_hi;
+    if (MIX && x >= hb_lo && x < hb_hi) x = hb_hi;
     if (x < n_store) return x;
     int j = x - n_store;
-    if (j >= sink_tiles && j < band_tile) j = band_tile;
+    if (j >= skip_stg_lo && j < skip_stg_hi) j = skip_stg_hi;
     if (j >= stg_lo && j < stg_hi) j = stg_hi;
     return j + n_store;
   };
@@ -450,9 +492,9 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 
   Frag ones;
   ones.u = make_uint4(0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u);      // eight bf16 1.0
-  GroupState st[2];             // NG causal sets; GATED: st[1] is the local set of group 0
+  GroupState st[NG];
 #pragma unroll
-  for (int k = 0; k < 2; ++k) {
+  for (int k = 0; k < NG; ++k) {
     set_reference(st[k], -INFINITY, 1.f);
     st[k].l = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -464,12 +506,30 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // those two are applied to the scores up front (general loop) instead.
   const float exp_scale = scale_log2 > 0.f ? scale_log2 : 1.f;
 
+  // One pass, or two of a blending head (of a divided workgroup, the last share takes what is local).
+  int pass = !mix ? kWhole : split && z != Z - 1 ? kRest : kLocal;
+  auto walk = [&](auto local_tag) {
+  constexpr bool LOCAL_PASS = decltype(local_tag)::value;
+  plan_pass(pass);
+  const int hot_store = hs_hi - hs_lo, hot_band = MIX ? hb_hi - hb_lo : 0;
+  const int n_plain_all = hot_store + hot_band + stg_hi - stg_lo;
+  // (a divided workgroup: share z of Z of them; the last share also takes the general tiles)
+  const bool divide = split && pass != kLocal;
+  const int plain_lo = divide ? (int)((int64_t)n_plain_all * z / Z) : 0;
+  const int n_plain = divide ? (int)((int64_t)n_plain_all * (z + 1) / Z) - plain_lo : n_plain_all;
+  auto plain_address = [&](int i0) -> const char* {
+    const int i = i0 + plain_lo;
+    if (MIX && i >= hot_store && i < hot_store + hot_band) return store.at(hb_lo + i - hot_store);
+    return i < hot_store ? store.at(hs_lo + i) : stage + (int64_t)(stg_lo + i - hot_store - hot_band) * kTileBytes;
+  };
+  const int total = busy && (!split || z == Z - 1) ? n_store + n_stage : 0;
+
   // ---- hot loop: the whole workgroup, tiles through LDS ---------------------------------------
   // Thread i moves 16 bytes of the tile's K half and 16 of its V half.  The loop exists in two forms.
   // The usual one (HALF) puts V into LDS as fp16 and sends the weights to the matrix cores as one
   // fp16 operand.  The other one, for a layer whose v_wide flag is up (some V value beyond the fp16
-  // range has been appended since the cache was last empty; unusual), takes V as stored, with
-  // two-part bf16 weights.
+  // range has been appended since the cache was last empty; unusual) and for the local pass of a blending head, takes V as
+  // stored, with two-part bf16 weights.
   auto hot_loop = [&](auto half_tag) {
     constexpr bool HALF = decltype(half_tag)::value;
     uint4 next_v = make_uint4(0, 0, 0, 0);      // the next tile's V as fp16, when the loop body has converted it already
@@ -491,11 +551,13 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     // halves of a tile are asked for two tiles ahead; the compiler makes every wavefront wait for its loads into
     // LDS before the next barrier (the K half therefore has one iteration to arrive), the V half, which
     // passes through registers to be converted, is waited for where it is used, an iteration later.
-    auto fetch = [&](int x, int slot, uint4& v16) {
-      const __amdgpu_buffer_rsrc_t rsrc =
-          __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(plain_address(x)), 0, kTileBytes, 0x00020000);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(&sm_k[slot & 3][wave * 64]), 16,
-                                               thread_off, 0, 0, 0);
+    auto resource = [&](int x) {
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(plain_address(x)), 0, kTileBytes, 0x00020000);
+    };
+    auto fetch_k = [&](const __amdgpu_buffer_rsrc_t& rsrc, uint4* slot) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(slot + wave * 64), 16, thread_off, 0, 0, 0);
+    };
+    auto fetch_v = [&](const __amdgpu_buffer_rsrc_t& rsrc, uint4& v16) {
       const u32x4 vv = __builtin_amdgcn_raw_buffer_load_b128(rsrc, thread_off, 8192, 0);
       v16 = make_uint4(vv[0], vv[1], vv[2], vv[3]);
     };
@@ -504,19 +566,34 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     // One tile.  c1 holds this thread's 16 bytes of V of tile x + 1, asked for an iteration ago; the loads of
     // tile x + 2 are issued here, K into LDS, V into f1.  Two iterations ahead, in two register sets that
     // swap roles: the workgroups of a pair walk its tiles at about the same time, so most of these loads find
-    // their line still on its way from HBM, and one iteration (about a microsecond) does not cover that.
-    auto step = [&](int x, uint4& c1, uint4& f1) {
+    // their line still on its way from HBM, and one iteration (about a microsecond) does not cover that.  (Two key slots: tile
+    // x + 1, V into c1 too.)
+    auto step = [&](auto odd_tag, int x, uint4& c1, uint4& f1) {
+      constexpr bool ODD = decltype(odd_tag)::value;
+      if (kKeySlots == 2) __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt 0: this wavefront's part of tile x's K half is in LDS
       __syncthreads();          // tile x is complete in its buffers; nobody reads the buffers written next any more
-      const uint4* kbuf = sm_k[x & 3];
+      const uint4* kbuf = kKeySlots == 2 ? (ODD ? sm_k1 : sm_k[0]) : sm_k[x & (kKeySlots - 1)];
       const uint4* vbuf = sm_v[x & 1];
       TileRegs tr;
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)                      // (also by a wavefront without queries: no branch here)
 #pragma unroll
         for (int s = 0; s < 4; ++s) tr.k[hf][s].u = kbuf[(hf * 4 + s) * 64 + lane];
+      auto read_v = [&]() {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) tr.v[j].u = vbuf[j * 64 + lane];
-      fetch(x + 2 < n_plain ? x + 2 : n_plain - 1, x + 2, f1);   // (past the end: the last tile again, unused)
+        for (int j = 0; j < 8; ++j) tr.v[j].u = vbuf[j * 64 + lane];
+      };
+      if (kKeySlots == 4) read_v();             // (two slots: behind the scores, for the registers)
+      // (past the end: the last tile again, unused)
+      if constexpr (kKeySlots == 4) {
+        const __amdgpu_buffer_rsrc_t rsrc = resource(x + 2 < n_plain ? x + 2 : n_plain - 1);
+        fetch_k(rsrc, sm_k[(x + 2) & 3]);
+        fetch_v(rsrc, f1);
+      } else {                                   // (the other key slot was last read before this barrier)
+        const __amdgpu_buffer_rsrc_t rsrc = resource(x + 1 < n_plain ? x + 1 : x);
+        fetch_k(rsrc, ODD ? sm_k[0] : sm_k1);
+        fetch_v(rsrc, c1);
+      }
       if (busy) {
         float sc[NG][8], mx[NG];
         bool grow = false;
@@ -526,6 +603,10 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           // (every lane holds its column's reference: the test needs the lane's own scores only)
           mx[cg] = max8(sc[cg]);
           grow |= mx[cg] > st[cg].thr;
+        }
+        if (kKeySlots == 2) {
+          __builtin_amdgcn_sched_barrier(0);
+          read_v();
         }
         if (__any(grow)) {
           // a maximum moved by more than the slack (rare): new references, accumulators rescaled
@@ -602,6 +683,34 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           __builtin_amdgcn_sched_barrier(0);
           next_v = make_uint4(hw[0], hw[1], hw[2], hw[3]);
           next_ready = true;
+        } else if constexpr (!HALF && NG == 2) {
+          // (the same for two-part weights)
+          const float ref0 = st[0].ref, ref1 = st[1].ref;
+          float p[8];
+          Frag hi, lo;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][e], exp_scale, -ref0));
+          split_weights(p, hi, lo);
+          __builtin_amdgcn_sched_barrier(0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, ones_op.v, st[0].l, 0, 0, 0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, ones_op.v, st[0].l, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            __builtin_amdgcn_sched_barrier(0);
+            p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][j], exp_scale, -ref1));
+            __builtin_amdgcn_sched_barrier(0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, tr.v[j].v, st[0].o[j], 0, 0, 0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, tr.v[j].v, st[0].o[j], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          split_weights(p, hi, lo);
+          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, ones_op.v, st[1].l, 0, 0, 0);
+          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, ones_op.v, st[1].l, 0, 0, 0);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, tr.v[j].v, st[1].o[j], 0, 0, 0);
+            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, tr.v[j].v, st[1].o[j], 0, 0, 0);
+          }
         } else
 #pragma unroll
         for (int cg = 0; cg < NG; ++cg) {
@@ -632,20 +741,23 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
       put(x + 1, c1);           // (after the last tile: a copy of it into the buffer nobody reads any more)
     };
     uint4 a1, b1;
-    fetch(0, 0, a1);
+    fetch_k(resource(0), sm_k[0]);
+    fetch_v(resource(0), a1);
     put(0, a1);
-    fetch(1 < n_plain ? 1 : 0, 1, a1);
+    if (kKeySlots == 4) fetch_k(resource(1 < n_plain ? 1 : 0), sm_k[kKeySlots == 4 ? 1 : 0]);
+    if (kKeySlots == 4) fetch_v(resource(1 < n_plain ? 1 : 0), a1);
     for (int x = 0; x < n_plain; x += 2) {
-      step(x, a1, b1);
-      if (x + 1 < n_plain) step(x + 1, b1, a1);
+      step(std::false_type{}, x, a1, b1);
+      if (x + 1 < n_plain) step(std::true_type{}, x + 1, kKeySlots == 2 ? a1 : b1, a1);
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt 0: no load into LDS is left in flight behind the loop
   };
   if (n_plain > 0) {
-    if (!wide) hot_loop(std::true_type{});
+    if constexpr (LOCAL_PASS) hot_loop(std::false_type{});
+    else if (!wide) hot_loop(std::true_type{});
     else hot_loop(std::false_type{});
   }
-  if (!busy) return;            // no barrier lies ahead
+  if (!busy) return;
 
   // ---- general loop: this wavefront alone, tiles straight from memory -------------------------
   // One tile: mask the scores of each column group and fold the tile into its softmax state.
@@ -678,9 +790,11 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     // positions this tile can hold (store tiles of a compressed head: anything before the chunk)
     const int p_first = ring ? 0 : base;
     const int p_last = ring ? n_old - 1 : base + kTile - 1;
-    auto masked = [&](int cg, bool local, const float (&raw)[8], float (&sc)[8]) {
+    const bool local = !full || LOCAL_PASS;                     // only local positions count; or
+    const bool rest = MIX && !LOCAL_PASS && pass == kRest;                     // only those that are not; or all
+    auto masked = [&](int cg, const float (&raw)[8], float (&sc)[8]) {
       const int i = qpos[cg];
-      if (ring || (local && p_first < S && p_last >= S)) {
+      if (ring || ((local || rest) && p_first < S && p_last >= S)) {
         int p[8];
         if (ring) {
 #pragma unroll
@@ -691,17 +805,19 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          const int on = (slot0 + offset(e) < held) & (p[e] <= i) & (!local | (p[e] < S) | (i - p[e] < R));
+          const int near = (p[e] < S) | (i - p[e] < R);
+          const int on = (slot0 + offset(e) < held) & (p[e] <= i) & (MIX ? (local & near) | (rest & (near ^ 1)) : near);
           sc[e] = on ? raw[e] : -INFINITY;
         }
         return;
       }
-      const int own = i - base - kb * 4;                        // offset of the query's own position
-      const int top = complete ? own : min(own, held - 1 - slot0);
+      const int own = i - base - kb * 4;                        // offset of the query's own position, ...
+      const int end = rest ? own - R : own;                     // ... of the last one that counts
+      const int top = complete ? end : min(end, held - 1 - slot0);
       if (local && p_first >= S && g_hi[cg] - p_first >= R) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) sc[e] = offset(e) <= top && offset(e) > own - R ? raw[e] : -INFINITY;
-      } else if (!complete || p_last > g_lo[cg]) {
+      } else if (!complete || p_last > (rest ? g_lo[cg] - R : g_lo[cg])) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) sc[e] = offset(e) <= top ? raw[e] : -INFINITY;
       } else {
@@ -716,8 +832,9 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     float raw[NG][8];
 #pragma unroll
     for (int cg = 0; cg < NG; ++cg) {
-      // (not: wholly above the causal diagonal, or wholly before the recent band)
-      sees[cg] = g_on[cg] && p_first <= g_hi[cg] && (full || p_first < S || p_last >= g_lo[cg] - R + 1);
+      // (not: wholly above the causal diagonal, or wholly before the recent band; of the rest: wholly sinks or in the band)
+      sees[cg] = g_on[cg] && p_first <= (rest ? g_hi[cg] - R : g_hi[cg]) &&
+                 (local ? p_first < S || p_last >= g_lo[cg] - R + 1 : !rest || p_last >= S);
       if (!sees[cg]) continue;
       raw_scores(tr, qb[cg], raw[cg]);
       if (!hot) {
@@ -730,13 +847,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     for (int cg = 0; cg < NG; ++cg) {
       if (!sees[cg]) continue;
       float sc[8];
-      masked(cg, !full, raw[cg], sc);
+      masked(cg, raw[cg], sc);
       group_update(tr, sc, exp_scale, st[cg], kb, ones);
-      if (GATED && mix && (p_first < S || p_last >= g_lo[cg] - R + 1)) {
-        // the same scores under the local mask, into the group's second accumulator set
-        masked(cg, true, raw[cg], sc);
-        group_update(tr, sc, exp_scale, st[GATED ? LOCAL : 0], kb, ones);
-      }
     }
     load_v_cached(tr, refill, lane);
   };
@@ -757,12 +869,35 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     }
   }
 
+  };
+  if constexpr (MIX) {
+    if (pass == kLocal) {
+      walk(std::true_type{});
+      // what is local is complete: its result is put aside, and the rest goes on top of its accumulators
+      pass = kRest;
+      if (busy) {
+#pragma unroll
+        for (int cg = 0; cg < NG; ++cg) {
+          floatx4 inv;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) inv[r] = 1.f / st[cg].l[r];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) sm_local[wave][cg * 8 + j][lane] = st[cg].o[j] * inv;
+        }
+      }
+      __syncthreads();          // nobody reads the tile buffers any more
+    }
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63; hd = lane & 15; kb = lane >> 4;
+  }
+  walk(std::false_type{});
+  if (!busy) return;            // no barrier lies ahead
+
   if (split) {
     float* slot = split_out + (((int64_t)by * gridDim.x + bx) * Z + z) * kSplitSlotFloats;
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {            // two column groups; GATED: one and its local set, as columns 128 and up
-      if (GATED && k == LOCAL && !mix) break;
-      const int first = col0 + (GATED ? kSplitCols / 2 : 16) * k;
+    for (int k = 0; k < NG; ++k) {
+      const int first = col0 + 16 * k;
       if (kb == 0) slot[kSplitCols * kHeadDim + first + hd] = st[k].m;      // the lane's own column
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -770,6 +905,11 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
         if (hd == 0) slot[kSplitCols * (kHeadDim + 1) + col] = st[k].l[r];
 #pragma unroll
         for (int j = 0; j < 8; ++j) slot[col * kHeadDim + j * 16 + hd] = st[k].o[j][r];
+        if (MIX && mix && z == Z - 1) {        // the local results, as columns 128 and up (one column group)
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            slot[(kSplitCols / 2 + col) * kHeadDim + j * 16 + hd] = sm_local[MIX ? wave : 0][MIX ? k * 8 + j : 0][lane][r];
+        }
       }
     }
     return;
@@ -780,25 +920,36 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // two-byte stores changed nothing: the stores are not waited for.)
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) {
+    uint16_t* dst[4];
+    bool on[4];
+    float inv[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int col = col0 + 16 * cg + kb * 4 + r;
       const int cl = div_g(col), hh = col - cl * G;
-      if (c_wg + cl <= c_last) {
-        uint16_t* dst = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + hd;
-        const float inv = 1.f / st[cg].l[r];
-        const float inv_local = mix ? 1.f / st[GATED ? LOCAL : 0].l[r] : 0.f;
+      on[r] = c_wg + cl <= c_last;
+      dst[r] = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + hd;
+      inv[r] = 1.f / st[cg].l[r];
+    }
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) {
-          float res[2];
+    for (int j = 0; j < 8; j += 2) {
+      floatx4 near[2];
+      if (MIX && mix) {
 #pragma unroll
-          for (int k = 0; k < 2; ++k) {
-            res[k] = st[cg].o[j + k][r] * inv;
-            if (GATED && mix) res[k] = gate * res[k] + (1.f - gate) * (st[GATED ? LOCAL : 0].o[j + k][r] * inv_local);
-          }
-          const uint32_t two = bf16_pair(res[0], res[1]);
-          dst[j * 16] = (uint16_t)two;
-          dst[j * 16 + 16] = (uint16_t)(two >> 16);
+        for (int k = 0; k < 2; ++k) near[k] = sm_local[MIX ? wave : 0][MIX ? cg * 8 + j + k : 0][lane];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float res[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          res[k] = st[cg].o[j + k][r] * inv[r];
+          if (MIX && mix) res[k] = gate * res[k] + (1.f - gate) * near[k][r];
+        }
+        const uint32_t two = bf16_pair(res[0], res[1]);
+        if (on[r]) {
+          dst[r][j * 16] = (uint16_t)two;
+          dst[r][j * 16 + 16] = (uint16_t)(two >> 16);
         }
       }
     }
@@ -808,8 +959,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 // Combines the shares of a divided workgroup: weights 2^(m_z - max m) on each share's accumulators and
 // normaliser (every share's weights carry the same 2^kWeightShift, which cancels).  A share that saw no
 // key has m = -inf and counts for nothing; the last share always holds the query's own position.
-// GATED: a block has 128 columns, and a blending head's local sets are columns 128 and up.
-template <bool GATED>
+// MIX: a block has 128 columns, and a blending head's local results are columns 128 and up of its last share.
+template <bool MIX>
 __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, SeqOrder order, const float* __restrict__ split_out,
                                                                    int Z, uint16_t* __restrict__ out, int stride_tokens,
                                                                    PrefillHeads heads) {
@@ -818,11 +969,11 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
   int t;
   pair_of_grid_row(dv, order, layer, blockIdx.y, heads, b, h, full, t);
   const int G = dv.group;
-  const int wg_positions = (GATED ? kSplitCols / 2 : kSplitCols) / G;
+  const int wg_positions = (MIX ? kSplitCols / 2 : kSplitCols) / G;
   const int c_wg = (gridDim.x - 1 - blockIdx.x) * wg_positions;
   if (c_wg >= t) return;
-  const float gate = GATED ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
-  const bool mix = GATED && gate < 1.f;
+  const float gate = MIX ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
+  const bool mix = MIX && gate < 1.f;
   const int c_last = (c_wg + wg_positions < t ? c_wg + wg_positions : t) - 1;
   const float* slot0 = split_out + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * Z * kSplitSlotFloats;
   // eight columns per workgroup, four per thread: the loads behind the four outputs are independent, so
@@ -831,42 +982,34 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
   constexpr int kPer = kMergeColsPerGroup / 2;
   int col[kPer];
   bool on[kPer];
-  float res[kPer];
+  float local[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
     col[i] = blockIdx.z * kMergeColsPerGroup + 2 * i + (threadIdx.x >> 7);
     on[i] = c_wg + col[i] / G <= c_last;
-    res[i] = 0.f;
+    local[i] = mix && on[i] ? slot0[(int64_t)(Z - 1) * kSplitSlotFloats + (kSplitCols / 2 + col[i]) * kHeadDim + d] : 0.f;
   }
-  for (int set = 0; set < (mix ? 2 : 1); ++set) {
-    const int shift = set * (kSplitCols / 2);
-    float M[kPer], num[kPer], den[kPer];
+  float M[kPer], num[kPer], den[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    M[i] = -INFINITY;
+    num[i] = den[i] = 0.f;
+  }
+  for (int zz = 0; zz < Z; ++zz) {
+    const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+      if (on[i]) M[i] = fmaxf(M[i], sl[kSplitCols * kHeadDim + col[i]]);
+  }
+  for (int zz = 0; zz < Z; ++zz) {
+    const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      M[i] = -INFINITY;
-      num[i] = den[i] = 0.f;
-    }
-    for (int zz = 0; zz < Z; ++zz) {
-      const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
-#pragma unroll
-      for (int i = 0; i < kPer; ++i)
-        if (on[i]) M[i] = fmaxf(M[i], sl[kSplitCols * kHeadDim + shift + col[i]]);
-    }
-    for (int zz = 0; zz < Z; ++zz) {
-      const float* sl = slot0 + (int64_t)zz * kSplitSlotFloats;
-#pragma unroll
-      for (int i = 0; i < kPer; ++i) {
-        if (!on[i]) continue;
-        const float m = sl[kSplitCols * kHeadDim + shift + col[i]];
-        const float w = m == -INFINITY ? 0.f : exp2f(m - M[i]);
-        num[i] += w * sl[(shift + col[i]) * kHeadDim + d];
-        den[i] += w * sl[kSplitCols * (kHeadDim + 1) + shift + col[i]];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const float r = num[i] / den[i];
-      res[i] = !mix ? r : set == 0 ? gate * r : res[i] + (1.f - gate) * r;
+      if (!on[i]) continue;
+      const float m = sl[kSplitCols * kHeadDim + col[i]];
+      const float w = m == -INFINITY ? 0.f : exp2f(m - M[i]);
+      num[i] += w * sl[col[i] * kHeadDim + d];
+      den[i] += w * sl[kSplitCols * (kHeadDim + 1) + col[i]];
     }
   }
 #pragma unroll
@@ -874,13 +1017,14 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
     if (!on[i]) continue;
     const int cl = col[i] / G, hh = col[i] - cl * G;
     const int64_t orow = ((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl;
-    out[orow * kHeadDim + d] = f32_to_bf16_rne(res[i]);
+    const float r = num[i] / den[i];
+    out[orow * kHeadDim + d] = f32_to_bf16_rne(mix ? gate * r + (1.f - gate) * local[i] : r);
   }
 }
 
 }  // namespace
 
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
                                const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
                                float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int split_rows, int dealt_rows, const uint8_t* mask_row, hipStream_t stream,
@@ -902,21 +1046,22 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
   hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, (const uint16_t*)k,
                      (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
-  if (n_split < 1 || !split_out) n_split = 1;
-  const int per_block = kPrefillWaves * 16 * (gated ? 1 : 2) / dv.group;      // chunk positions per workgroup
+  if (n_split < 1 || !split_out || (mix && !narrow)) n_split = 1;
+  const int per_block = kPrefillWaves * 16 * (narrow ? 1 : 2) / dv.group;     // chunk positions per workgroup
   const int gx = (max_tokens + per_block - 1) / per_block;
   const dim3 grid(gx, dv.n_pairs, n_split), block(kPrefillBlock);
-#define RLKV_LAUNCH(PG, GT)                                                                                          \
-  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, GT>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
+#define RLKV_LAUNCH(PG, NGR, MX)                                                                                       \
+  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, NGR, MX>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
                         staging_tiles, split_out, heads)
-  if (dv.page_shift >= 0) { if (gated) RLKV_LAUNCH(true, true); else RLKV_LAUNCH(true, false); }
-  else                    { if (gated) RLKV_LAUNCH(false, true); else RLKV_LAUNCH(false, false); }
+#define RLKV_PICK(PG) do { if (narrow) RLKV_LAUNCH(PG, 1, true); else if (mix) RLKV_LAUNCH(PG, 2, true); else RLKV_LAUNCH(PG, 2, false); } while (0)
+  if (dv.page_shift >= 0) RLKV_PICK(true); else RLKV_PICK(false);
+#undef RLKV_PICK
 #undef RLKV_LAUNCH
   if (hipError_t e = hipGetLastError()) return e;
   if (n_split > 1 && split_rows > 0) {
-    const dim3 mgrid(gx, split_rows, kSplitCols / (gated ? 2 : 1) / kMergeColsPerGroup), mblock(kSplitCols);
-    if (gated)
+    const dim3 mgrid(gx, split_rows, kSplitCols / (narrow ? 2 : 1) / kMergeColsPerGroup), mblock(kSplitCols);
+    if (narrow)
       hipLaunchKernelGGL(prefill_merge_kernel<true>, mgrid, mblock, 0, stream, dv, layer, order, (const float*)split_out, n_split,
                          (uint16_t*)out, stride_tokens, heads);
     else

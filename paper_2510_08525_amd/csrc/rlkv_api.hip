@@ -624,18 +624,19 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     const bool record = (size_t)cache->prof_used * 2 + 1 < cache->prof_events.size();
     hipEvent_t e0 = record ? cache->prof_events[2 * cache->prof_used] : nullptr;
     hipEvent_t e1 = record ? cache->prof_events[2 * cache->prof_used + 1] : nullptr;
-    // The kernel form and the division of long workgroups: rlkv_plan_prefill_form (a blending layer always takes
-    // the single-group form); the single-group form is divided by plan_narrow_split.
+    // The kernel form and the division of long workgroups: rlkv_plan_prefill_form, of a blending layer plan_blend_narrow;
+    // the single-group form is divided by plan_narrow_split.
     // Measured on the Qwen shape, one sequence: dividing beats the narrow form from about 85 tiles per share on
     // (the shares' accumulators go through memory and a merge kernel follows).
     const int set_tiles = cache->cfg.prefill_min_share_tiles;      // 0: the defaults
-    bool narrow = cache->layer_gated[layer] != 0;
+    const bool mix = cache->layer_gated[layer] != 0;
+    bool narrow = false;
     int n_split = 1, n_full = 0, split_rows = 0;      // split_rows: grid rows of full heads that have a chunk (they come first)
     {
       const int H = cache->cfg.n_kv_heads;
       for (int h = 0; h < H; ++h) n_full += cache->mask[(size_t)layer * H + h] ? 1 : 0;
     }
-    if (!narrow) {
+    if (!mix) {
       int32_t nw = 0, ns = 1;
       if (rlkv_plan_prefill_form(cache->n_cu, cache->cfg.n_q_heads, cache->cfg.n_kv_heads, n_full, B, n_tokens, lh,
                                  set_tiles > 0 ? set_tiles : kShareTiles, cache->allow_narrow ? 1 : 0, &nw, &ns) != 0)
@@ -643,9 +644,10 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       narrow = nw != 0;
       n_split = ns;
     }
-    // (Shares of that form pay from about 26 tiles on, 40 where a share leaves two accumulator sets.  One sequence of 3000 / 6000
+    // (Shares of that form pay from about 26 tiles on, 40 where heads blend (their last share takes both passes).  One sequence of 3000 / 6000
     // tokens, 28 query and 4 KV heads, 2 full, chunks of 512 / 1024, whole / shares of 40 / 30 / 20 / 12 tiles: 277 / 263 / 251 /
     // 255 / 271, 480 / 436 / 437 / 407 / 443 us; blending, two of 4000 and 5000: 623 / 588 / 594 / 607 / 621 us.)
+    if (mix) narrow = plan_blend_narrow(cache->n_cu, cache->dv.group, n_full, B, n_tokens);
     if (narrow) {
       const int tiles = set_tiles > 0 ? set_tiles : cache->layer_gated[layer] ? kShareTilesBlend : kShareTilesNarrow;
       n_split = plan_narrow_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, tiles);
@@ -656,7 +658,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       if (rlkv_plan_prefill_rows(n_full, B, n_tokens, lh, &dealt_rows, &heavy) != 0) return RLKV_ERR_INVALID_ARG;
       split_rows = heavy;
     }
-    if (launch_prefill_mfma(cache->dv, layer, narrow, seqs, order, len_of(cache->dv, par, layer), prefill->q,
+    if (launch_prefill_mfma(cache->dv, layer, narrow, mix, seqs, order, len_of(cache->dv, par, layer), prefill->q,
                             k, v, prefill->out, stride,
                             max_tok, prefill->softmax_scale * 1.44269504088896340736f, cache->arena + cache->plan.staging,
                             cache->plan.staging_tiles, n_split,

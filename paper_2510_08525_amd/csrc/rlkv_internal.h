@@ -225,8 +225,8 @@ hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_
                           const void* v_new, const uint32_t* merge_words, int most_partials);
 // Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):
 // stages the chunk's K/V as tiles in `staging` (staging_tiles tiles per pair), then attends.
-// `gated`: the kernel form with one column group of queries per wavefront, the only one that can blend
-// (Eq. 1: causal and local attention of a full head with a gate below 1).
+// `narrow`: the kernel form with one column group of queries per wavefront instead of two.  `mix`: some full head of the layer
+// blends (Eq. 1: causal and local attention of a full head with a gate below 1).
 // `n_split` > 1: the unmasked tiles of every full head's workgroup are divided among
 // n_split workgroups, which leave their shares in `split_out` (kPrefillSplitSlotBytes per divided
 // workgroup; at most kPrefillSplitSlots: split_rows (the grid's first rows: full heads of sequences
@@ -234,7 +234,7 @@ hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_
 constexpr int kPrefillSplitSlots = 1024;
 constexpr int kPrefillArgHeads = 64;      // KV heads of a layer whose class lists travel in the prefill kernels' arguments
 constexpr size_t kPrefillSplitSlotBytes = 256 * (size_t)(kHeadDim + 2) * sizeof(float);
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
                                const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
                                float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int split_rows, int dealt_rows,
@@ -242,8 +242,9 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool gated, cons
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 
 // Fewest 32-key tiles a share of a divided prefill workgroup has, where cfg.prefill_min_share_tiles does not say: in the
-// form with two column groups per wavefront, in the single-group form, and in that form with two accumulator sets.
+// form with two column groups per wavefront, in the single-group form, and in that form where heads blend.
 constexpr int kShareTiles = 80, kShareTilesNarrow = 26, kShareTilesBlend = 40;
+bool plan_blend_narrow(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens);
 int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
                       const int32_t* cached, int min_share_tiles);
 

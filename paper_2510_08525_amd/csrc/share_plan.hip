@@ -202,6 +202,20 @@ extern "C" int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_h
 
 namespace rlkv {
 
+// Whether a chunk of a layer with blending heads takes the form with one column group per wavefront (128 columns to a workgroup) or
+// two (256).  A workgroup of 128 columns takes about 0.6 of the time of one of 256 (8 sequences of 1000 to 4000 tokens, chunks 1, 2, 3: 44 / 71, 65 / 104, 79 / 130 us), so the wide form is the
+// better one unless it fills its last round of workgroups so much worse.
+bool plan_blend_narrow(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens) {
+  int64_t rounds[2];
+  for (int form = 0; form < 2; ++form) {
+    const int per_block = (form ? 128 : 256) / group;
+    int64_t blocks = 0;
+    for (int b = 0; b < batch; ++b) blocks += (n_tokens[b] + per_block - 1) / per_block;
+    rounds[form] = (blocks * n_full_heads + n_compute_units - 1) / n_compute_units;
+  }
+  return 3 * rounds[1] < 5 * rounds[0];
+}
+
 // Shares that every full-head workgroup of a chunk is divided into in the form with one column group per wavefront (128 columns
 // to a workgroup).  As above: only where the shares still fit the CUs in one round.
 int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens,
