@@ -327,13 +327,21 @@ int32_t rlkv_plan_prefill_rows(int32_t n_full_heads, int32_t batch, const int32_
                                const int32_t* cached /* host */, int32_t* dealt_rows /* host */,
                                int32_t* heavy_rows /* host */);
 
-/* The (x, y) block of a prefill attention launch that the workgroup with linear index
- * blockIdx.x + grid_x * blockIdx.y works on, as the kernel computes it from the two counts of
- * rlkv_plan_prefill_rows; exposed for tests (it touches no device).  The hardware deals workgroups to the 8
- * XCDs in turn by that index; the map is a bijection of the grid under which every dealt row, and every whole
- * group of 8 light rows, is served by one XCD.  Returns 0, or -1 on an invalid argument. */
+/* The (x, y) block of grid_y rows of grid_x blocks that a workgroup of a prefill attention launch works on where all rows are
+ * alike, from its linear index and the two counts of rlkv_plan_prefill_rows; exposed for tests (it touches no device).
+ * The hardware deals workgroups to the 8 XCDs in turn by that index; the map is a bijection of the grid under which every
+ * dealt row, and every whole group of 8 light rows, is served by one XCD.  Returns 0, or -1 on an invalid argument. */
 int32_t rlkv_plan_prefill_block(int32_t linear_index, int32_t grid_x, int32_t grid_y, int32_t dealt_rows,
                                 int32_t heavy_rows, int32_t* block_x /* host */, int32_t* block_y /* host */);
+
+/* What the workgroup with this linear index works on in an undivided prefill attention launch over sequences of any chunk
+ * lengths, as the kernel computes it; exposed for tests (it touches no device).  Only blocks that hold queries have a workgroup.
+ *   per_block  : chunk positions per block;  n_tokens : host [n_seqs], chunk lengths (> 0) in the launch's order, at most 128
+ *   dealt_rows : as rlkv_plan_prefill_rows returns it (rows of fewer blocks than the longest chunk's are not dealt by rows)
+ *   item       : host [4], out: 1 = full head, place of the sequence, number of the head in its class, block
+ * Returns 0, 1 where linear_index is past the launch's last workgroup, or -1 on an invalid argument. */
+int32_t rlkv_plan_prefill_item(int32_t linear_index, int32_t per_block, int32_t n_full_heads, int32_t n_compressed_heads,
+                               int32_t n_seqs, const int32_t* n_tokens /* host */, int32_t dealt_rows, int32_t* item /* host */);
 
 /* The host-side plan of the split-K work list, exposed for tests and tools (it touches no device).
  * The scheduling units of all pairs are laid end to end - per pair one unit that marks its start,

@@ -83,6 +83,7 @@ def load_library():
         "rlkv_plan_prefill_form": (i32, [i32, i32, i32, i32, i32, vp, vp, i32, i32, vp, vp]),
         "rlkv_plan_prefill_rows": (i32, [i32, i32, vp, vp, vp, vp]),
         "rlkv_plan_prefill_block": (i32, [i32, i32, i32, i32, i32, vp, vp]),
+        "rlkv_plan_prefill_item": (i32, [i32] * 5 + [vp, i32, vp]),
         "rlkv_cache_kernel": (i32, [vp]),
         "rlkv_pool_pages_free": (ctypes.c_int64, [vp]),
         "rlkv_pool_shuffle": (i32, [vp, ctypes.c_uint64]),
@@ -99,7 +100,7 @@ EXPORTED_SYMBOLS = (
     "rlkv_cache_required_bytes", "rlkv_cache_create", "rlkv_cache_destroy", "rlkv_cache_reset",
     "rlkv_append", "rlkv_append_ragged", "rlkv_decode_attention", "rlkv_decode_attention_noalloc", "rlkv_set_active", "rlkv_set_gates", "rlkv_append_decode", "rlkv_append_decode_prepare", "rlkv_append_decode_launch", "rlkv_worklists_built", "rlkv_prefill_attention", "rlkv_profile_enable",
     "rlkv_profile_collect", "rlkv_get_lengths",
-    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_narrow_split", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_cache_kernel", "rlkv_pool_pages_free",
+    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_narrow_split", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_plan_prefill_item", "rlkv_cache_kernel", "rlkv_pool_pages_free",
     "rlkv_pool_shuffle", "rlkv_status_string",
 )
 
@@ -308,6 +309,17 @@ def rlkv_plan_prefill_block(linear_index: int, grid_x: int, grid_y: int, dealt_r
     if rc != 0:
         raise RlkvError(RLKV_ERR_INVALID_ARG, "rlkv_plan_prefill_block")
     return bx.value, by.value
+
+
+def rlkv_plan_prefill_item(linear_index: int, per_block: int, n_full_heads: int, n_compressed_heads: int, n_tokens, dealt_rows: int):
+    """Returns (full, place, head, block), or None past the launch's last workgroup."""
+    t = np.ascontiguousarray(np.asarray(n_tokens, dtype=np.int32).reshape(-1))
+    item = np.zeros(4, dtype=np.int32)
+    rc = load_library().rlkv_plan_prefill_item(linear_index, per_block, n_full_heads, n_compressed_heads, t.size, t.ctypes.data,
+                                               dealt_rows, item.ctypes.data)
+    if rc < 0:
+        raise RlkvError(RLKV_ERR_INVALID_ARG, "rlkv_plan_prefill_item")
+    return None if rc else (bool(item[0]), int(item[1]), int(item[2]), int(item[3]))
 
 
 def rlkv_cache_kernel(handle: int) -> int:

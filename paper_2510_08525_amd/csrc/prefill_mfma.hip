@@ -207,48 +207,40 @@ __global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int 
   if (wide) dv.v_wide[layer] = 1;          // seen by the attention kernel that follows on the stream
 }
 
-// Grid row y of the prefill kernels -> (sequence, KV head): the pairs of full heads first, then those of
-// compressed heads, each class by descending sequence length (the host-sorted order behind the counts).
-// The heads of each class come with the kernel arguments (heads.n_full >= 0; one load instead of two loops of
-// dependent loads over the layer's mask at the start of every workgroup), unless the layer has more heads
-// than fit there.
-struct PrefillHeads {
-  int32_t n_full;                          // full heads of the layer; -1: not given, read the mask
-  int32_t heavy_rows;                      // leading grid rows that are full heads of sequences with a chunk
+// The items of a launch (see prefill_deal.h) and the heads of either class.  The heads come with the kernel arguments (one load
+// instead of a loop of dependent loads over the layer's mask at the start of every workgroup), unless the layer has more than
+// fit there.
+struct PrefillGrid {
+  PrefillItems items;
+  int32_t n_heads[2];                      // full, compressed heads of the layer
+  int32_t n_seqs;                          // sequences that have a chunk
+  int32_t ragged;                          // 1: a sequence's blocks are those `first` gives it; 0: all have items.gx (those
+                                           // without queries do nothing)
+  int32_t n_split;                         // shares of every heavy item (1 = undivided; else dealt in plain order, ragged = 0)
   int32_t inv_group;                       // 65536 / group, rounded up
-  int32_t dealt_rows;                      // of those, the leading ones that go one row per XCD (see prefill_deal)
+  int32_t heads_given;                     // 1: `head` holds the heads
   int32_t head[2][kPrefillArgHeads];       // [0]: the full heads in ascending order, [1]: the compressed ones
+  int32_t first[kArgSeqs + 1];             // blocks of the sequences before each place in the order
 };
-__device__ __forceinline__ void pair_of_grid_row(const DeviceView& dv, const SeqOrder& order, int layer, int y, const PrefillHeads& heads,
-                                                 int& b, int& h, bool& full, int& tokens) {
-  if (heads.n_full >= 0) {
-    const int n_full_pairs = dv.batch * heads.n_full;
-    full = y < n_full_pairs;
-    const int per_seq = full ? heads.n_full : dv.n_kv_heads - heads.n_full;
-    const int yy = full ? y : y - n_full_pairs;
-    seq_in_order(dv, order, yy / per_seq, b, tokens);
-    h = heads.head[full ? 0 : 1][yy % per_seq];
+// Place in the sequence order and number in its class -> (sequence, KV head), chunk length.
+__device__ __forceinline__ void pair_of_place(const DeviceView& dv, const SeqOrder& order, int layer, const PrefillGrid& grid, int place, int head,
+                                              bool full, int& b, int& h, int& tokens) {
+  seq_in_order(dv, order, place, b, tokens);
+  if (grid.heads_given) {
+    h = grid.head[full ? 0 : 1][head];
     return;
   }
-  int n_full_heads = 0;
-  for (int i = 0; i < dv.n_kv_heads; ++i) n_full_heads += dv.full_mask[layer * dv.n_kv_heads + i] ? 1 : 0;
-  const int n_full_pairs = dv.batch * n_full_heads;
-  const bool want_full = y < n_full_pairs;
-  const int per_seq = want_full ? n_full_heads : dv.n_kv_heads - n_full_heads;
-  const int yy = want_full ? y : y - n_full_pairs;
-  seq_in_order(dv, order, yy / per_seq, b, tokens);
   h = 0;
-  for (int i = 0, k = yy % per_seq; i < dv.n_kv_heads; ++i) {
-    if ((dv.full_mask[layer * dv.n_kv_heads + i] != 0) == want_full) {
+  for (int i = 0, k = head; i < dv.n_kv_heads; ++i) {
+    if ((dv.full_mask[layer * dv.n_kv_heads + i] != 0) == full) {
       if (k == 0) { h = i; break; }
       --k;
     }
   }
-  full = want_full;
 }
 
 // Split prefill (few long workgroups: one or two sequences, few full heads): the unmasked tiles of a
-// full head's workgroup are divided among gridDim.z workgroups, each of which leaves its 256 columns'
+// full head's workgroup are divided among n_split workgroups, each of which leaves its 256 columns'
 // unnormalised accumulators, normalisers and reference maxima in a slot of scratch memory
 // ([256][128] O, then [256] m, then [256] l, fp32); prefill_merge_kernel combines them.
 constexpr int kSplitCols = 256;
@@ -291,7 +283,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
                                                                      float scale_log2,
                                                                      const char* __restrict__ staging,
                                                                      int staging_tiles, float* __restrict__ split_out,
-                                                                     PrefillHeads heads) {
+                                                                     PrefillGrid grid) {
   // LDS: the K halves of four tiles (filled by loads that go from memory straight into LDS, two tiles ahead)
   // and the V halves of two (through registers: V is converted on the way); MIX: the local results, every lane its own.  With
   // two column groups these leave room for two K halves, which use up the 160 KiB of a CU: tiles are then asked for one ahead.
@@ -301,19 +293,30 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
                                                                           // one slot wait for the loads into the other)
   __shared__ uint4 sm_v[2][kTileBytes / 32];
   __shared__ floatx4 sm_local[MIX ? kPrefillWaves : 1][MIX ? NG * 8 : 1][64];
-  // Workgroups are handed out in grid order, and each XCD takes the rows dealt to it (prefill_deal) in
+  // Workgroups are handed out in the order of their index, and each XCD takes the items dealt to it (prefill_item) in
   // order: the long ones go first - the pairs of full heads before those of compressed heads, long
   // sequences before short ones, and within a pair the later query blocks (more keys under the
   // causal mask) before the earlier ones - so that the short ones fill the end.
-  int b, h;
+  int index, place, head, from_end, share = 0;
   bool full;
-  int bx = blockIdx.x, by = blockIdx.y;
-  if (gridDim.z == 1) prefill_deal((int)(blockIdx.x + gridDim.x * blockIdx.y), (int)gridDim.x, (int)gridDim.y, heads.dealt_rows,
-                                    heads.heavy_rows, bx, by);   // (a divided launch keeps the plain order: its merge kernel indexes by it)
-  int t;                                   // chunk length of the sequence
-  pair_of_grid_row(dv, order, layer, by, heads, b, h, full, t);
+  const int Z = grid.n_split, gx = grid.items.gx;
+  if (Z == 1) {
+    full = prefill_item(blockIdx.x, grid.items, index);
+  } else {                                 // (plain order, the first share of everything, then the others of the heavy items)
+    index = blockIdx.x;
+    const int heavy = grid.n_seqs * grid.n_heads[0] * gx, all = heavy + grid.n_seqs * grid.n_heads[1] * gx;
+    if (index >= all) {
+      share = (index - all) / heavy;
+      index -= all + share++ * heavy;
+    }
+    full = index < heavy;
+    if (!full) index -= heavy;
+  }
+  prefill_place(index, grid.n_heads[full ? 0 : 1], gx, grid.ragged != 0, grid.first, grid.n_seqs, place, head, from_end);
+  int b, h, t;                             // t: chunk length of the sequence
+  pair_of_place(dv, order, layer, grid, place, head, full, b, h, t);
   const int pair = b * dv.n_kv_heads + h;
-  const int block_x = gridDim.x - 1 - bx;
+  const int block_x = (grid.ragged ? grid.first[place + 1] - grid.first[place] : gx) - 1 - from_end;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int tid = threadIdx.x, lane = tid & 63;
   int hd = lane & 15;           // score layout: column; operand layouts: row / column
@@ -321,17 +324,15 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   const int G = dv.group, S = dv.sink, R = dv.recent;
   constexpr int kWaveCols = 16 * NG;
   // Columns are at most 256 and groups at most 16, so that col / G is exact as a product with the reciprocal rounded up.
-  const int inv_g = heads.inv_group;
+  const int inv_g = grid.inv_group;
   auto div_g = [&](int col) { return (col * inv_g) >> 16; };
   const int wg_positions = div_g(kPrefillWaves * kWaveCols);   // chunk positions per workgroup
   const int n_old = len_in[b];             // positions cached before the chunk
   const int c_wg = block_x * wg_positions; // the workgroup's first chunk index
   if (c_wg >= t) return;
   const int c_last = (c_wg + wg_positions < t ? c_wg + wg_positions : t) - 1;   // its last one
-  // share z of Z of a divided workgroup; grid plane 0, handed out first, holds the last share, the longest one
-  // (it also takes the masked tiles)
-  const int Z = gridDim.z, z = Z - 1 - (int)blockIdx.z;
-  if (!full && blockIdx.z > 0) return;       // a compressed head's workgroup is short: never divided
+  // share z of Z of a divided workgroup; the last share, the longest one (it also takes the masked tiles), is handed out first
+  const int z = Z - 1 - share;
   const bool split = full && Z > 1;
   const bool wide = dv.v_wide[layer] != 0;   // (asked for early: read in front of the hot loop)
   const float gate = (MIX && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
@@ -894,7 +895,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   if (!busy) return;            // no barrier lies ahead
 
   if (split) {
-    float* slot = split_out + (((int64_t)by * gridDim.x + bx) * Z + z) * kSplitSlotFloats;
+    float* slot = split_out + ((int64_t)index * Z + z) * kSplitSlotFloats;
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
       const int first = col0 + 16 * k;
@@ -963,11 +964,9 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 template <bool MIX>
 __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, SeqOrder order, const float* __restrict__ split_out,
                                                                    int Z, uint16_t* __restrict__ out, int stride_tokens,
-                                                                   PrefillHeads heads) {
-  int b, h;
-  bool full;
-  int t;
-  pair_of_grid_row(dv, order, layer, blockIdx.y, heads, b, h, full, t);
+                                                                   PrefillGrid grid) {
+  int b, h, t;
+  pair_of_place(dv, order, layer, grid, blockIdx.y / grid.n_heads[0], blockIdx.y % grid.n_heads[0], true, b, h, t);
   const int G = dv.group;
   const int wg_positions = (MIX ? kSplitCols / 2 : kSplitCols) / G;
   const int c_wg = (gridDim.x - 1 - blockIdx.x) * wg_positions;
@@ -1024,49 +1023,49 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
 
 }  // namespace
 
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
-                               const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
-                               float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
-                               int split_rows, int dealt_rows, const uint8_t* mask_row, hipStream_t stream,
-                               hipEvent_t ev_start, hipEvent_t ev_stop) {
-  PrefillHeads heads;
-  heads.n_full = -1;
-  heads.inv_group = (65536 + dv.group - 1) / dv.group;
-  heads.heavy_rows = split_rows;
-  heads.dealt_rows = dealt_rows;
-  if (mask_row && dv.n_kv_heads <= kPrefillArgHeads) {
-    int nf = 0, nc = 0;
-    for (int i = 0; i < dv.n_kv_heads; ++i) {
-      if (mask_row[i]) heads.head[0][nf++] = i;
-      else heads.head[1][nc++] = i;
-    }
-    heads.n_full = nf;
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, int n_seqs,
+                               const int32_t* len_in, const void* q, const void* k, const void* v, void* out, int stride_tokens,
+                               int max_tokens, float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
+                               int dealt_rows, const uint8_t* mask_row, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (n_split < 1 || !split_out || (mix && !narrow)) n_split = 1;
+  const int per_block = kPrefillWaves * 16 * (narrow ? 1 : 2) / dv.group;     // chunk positions per workgroup
+  const int gx = (max_tokens + per_block - 1) / per_block;
+  PrefillGrid grid;
+  grid.n_heads[0] = grid.n_heads[1] = 0;
+  grid.heads_given = dv.n_kv_heads <= kPrefillArgHeads;
+  for (int i = 0; i < dv.n_kv_heads; ++i) {
+    const int cls = mask_row[i] ? 0 : 1;
+    if (grid.heads_given) grid.head[cls][grid.n_heads[cls]] = i;
+    ++grid.n_heads[cls];
   }
+  grid.n_seqs = n_seqs;
+  grid.n_split = n_split;
+  grid.inv_group = (65536 + dv.group - 1) / dv.group;
+  const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, grid.n_heads, dealt_rows,
+                                           &grid.items, &grid.ragged, grid.first);
   const int tiles = (max_tokens + kTile - 1) / kTile;
   hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, (const uint16_t*)k,
                      (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
-  if (n_split < 1 || !split_out || (mix && !narrow)) n_split = 1;
-  const int per_block = kPrefillWaves * 16 * (narrow ? 1 : 2) / dv.group;     // chunk positions per workgroup
-  const int gx = (max_tokens + per_block - 1) / per_block;
-  const dim3 grid(gx, dv.n_pairs, n_split), block(kPrefillBlock);
-#define RLKV_LAUNCH(PG, NGR, MX)                                                                                       \
-  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, NGR, MX>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
+  const int64_t heavy_rows = (int64_t)n_seqs * grid.n_heads[0];
+  const dim3 blocks((uint32_t)(items + (n_split - 1) * heavy_rows * gx)), block(kPrefillBlock);
+#define RLKV_LAUNCH(PG, NGR, MX)                                                                                          \
+  hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, NGR, MX>), blocks, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
-                        staging_tiles, split_out, heads)
+                        staging_tiles, split_out, grid)
 #define RLKV_PICK(PG) do { if (narrow) RLKV_LAUNCH(PG, 1, true); else if (mix) RLKV_LAUNCH(PG, 2, true); else RLKV_LAUNCH(PG, 2, false); } while (0)
   if (dv.page_shift >= 0) RLKV_PICK(true); else RLKV_PICK(false);
 #undef RLKV_PICK
 #undef RLKV_LAUNCH
   if (hipError_t e = hipGetLastError()) return e;
-  if (n_split > 1 && split_rows > 0) {
-    const dim3 mgrid(gx, split_rows, kSplitCols / (narrow ? 2 : 1) / kMergeColsPerGroup), mblock(kSplitCols);
+  if (n_split > 1 && heavy_rows > 0) {
+    const dim3 mgrid(gx, (uint32_t)heavy_rows, kSplitCols / (narrow ? 2 : 1) / kMergeColsPerGroup), mblock(kSplitCols);
     if (narrow)
       hipLaunchKernelGGL(prefill_merge_kernel<true>, mgrid, mblock, 0, stream, dv, layer, order, (const float*)split_out, n_split,
-                         (uint16_t*)out, stride_tokens, heads);
+                         (uint16_t*)out, stride_tokens, grid);
     else
       hipLaunchKernelGGL(prefill_merge_kernel<false>, mgrid, mblock, 0, stream, dv, layer, order, (const float*)split_out, n_split,
-                         (uint16_t*)out, stride_tokens, heads);
+                         (uint16_t*)out, stride_tokens, grid);
   }
   return hipGetLastError();
 }

@@ -631,7 +631,8 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     const int set_tiles = cache->cfg.prefill_min_share_tiles;      // 0: the defaults
     const bool mix = cache->layer_gated[layer] != 0;
     bool narrow = false;
-    int n_split = 1, n_full = 0, split_rows = 0;      // split_rows: grid rows of full heads that have a chunk (they come first)
+    int n_split = 1, n_full = 0, n_seqs = 0;
+    for (int b = 0; b < B; ++b) n_seqs += n_tokens[b] > 0;
     {
       const int H = cache->cfg.n_kv_heads;
       for (int h = 0; h < H; ++h) n_full += cache->mask[(size_t)layer * H + h] ? 1 : 0;
@@ -656,13 +657,12 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     {
       int32_t heavy = 0;
       if (rlkv_plan_prefill_rows(n_full, B, n_tokens, lh, &dealt_rows, &heavy) != 0) return RLKV_ERR_INVALID_ARG;
-      split_rows = heavy;
     }
-    if (launch_prefill_mfma(cache->dv, layer, narrow, mix, seqs, order, len_of(cache->dv, par, layer), prefill->q,
+    if (launch_prefill_mfma(cache->dv, layer, narrow, mix, seqs, order, n_seqs, len_of(cache->dv, par, layer), prefill->q,
                             k, v, prefill->out, stride,
                             max_tok, prefill->softmax_scale * 1.44269504088896340736f, cache->arena + cache->plan.staging,
                             cache->plan.staging_tiles, n_split,
-                            reinterpret_cast<float*>(cache->arena + cache->plan.prefill_split), split_rows, dealt_rows,
+                            reinterpret_cast<float*>(cache->arena + cache->plan.prefill_split), dealt_rows,
                             cache->mask.data() + (size_t)layer * cache->cfg.n_kv_heads, s, e0,
                             e1) != hipSuccess)
       return RLKV_ERR_HIP;

@@ -229,17 +229,22 @@ hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_
 // blends (Eq. 1: causal and local attention of a full head with a gate below 1).
 // `n_split` > 1: the unmasked tiles of every full head's workgroup are divided among
 // n_split workgroups, which leave their shares in `split_out` (kPrefillSplitSlotBytes per divided
-// workgroup; at most kPrefillSplitSlots: split_rows (the grid's first rows: full heads of sequences
-// that have a chunk) x blocks x n_split) for a merge kernel that follows.
+// workgroup; at most kPrefillSplitSlots: full heads of the sequences that have a chunk x blocks x n_split) for a merge
+// kernel that follows.  `n_seqs`: sequences that have a chunk, the first ones of the order.
 constexpr int kPrefillSplitSlots = 1024;
 constexpr int kPrefillArgHeads = 64;      // KV heads of a layer whose class lists travel in the prefill kernels' arguments
 constexpr size_t kPrefillSplitSlotBytes = 256 * (size_t)(kHeadDim + 2) * sizeof(float);
-hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, const int32_t* len_in, const void* q,
-                               const void* k, const void* v, void* out, int stride_tokens, int max_tokens,
-                               float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
-                               int split_rows, int dealt_rows,
-                               const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
+hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, int n_seqs,
+                               const int32_t* len_in, const void* q, const void* k, const void* v, void* out, int stride_tokens,
+                               int max_tokens, float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
+                               int dealt_rows, const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+// The items of an undivided launch (prefill_deal.h) with `per_block` chunk positions to a block: `tokens` [n_seqs] the chunk lengths
+// in the grid's order, or null (not at hand: every sequence has gx blocks); dealt_rows: heavy rows that may go one row
+// per XCD (rlkv_plan_prefill_rows).  Fills items, ragged and, where that is 1, first [n_seqs + 1]; returns the number of items.
+struct PrefillItems;
+int64_t plan_prefill_items(int per_block, int n_seqs, const int32_t* tokens, int gx, const int32_t (&n_heads)[2], int dealt_rows,
+                           PrefillItems* items, int32_t* ragged, int32_t* first);
 
 // Fewest 32-key tiles a share of a divided prefill workgroup has, where cfg.prefill_min_share_tiles does not say: in the
 // form with two column groups per wavefront, in the single-group form, and in that form where heads blend.

@@ -240,6 +240,31 @@ int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batc
   return n_split;
 }
 
+int64_t plan_prefill_items(int per_block, int n_seqs, const int32_t* tokens, int gx, const int32_t (&n_heads)[2], int dealt_rows,
+                           PrefillItems* items, int32_t* ragged, int32_t* first) {
+  int64_t blocks = (int64_t)n_seqs * gx;
+  int whole = n_seqs;                                // leading sequences with gx blocks
+  *ragged = 0;
+  if (tokens) {
+    whole = 0;
+    while (whole < n_seqs && (tokens[whole] + per_block - 1) / per_block == gx) ++whole;
+    if (whole < n_seqs) {
+      *ragged = 1;
+      blocks = 0;
+      for (int i = 0; i < n_seqs; ++i) {
+        first[i] = (int32_t)blocks;
+        blocks += (tokens[i] + per_block - 1) / per_block;
+      }
+      first[n_seqs] = (int32_t)blocks;
+    }
+  }
+  items->gx = gx;
+  items->dealt[0] = std::min(dealt_rows, whole * n_heads[0]) / 8 * 8;
+  items->dealt[1] = whole * n_heads[1] / 8 * 8;
+  items->rest = (int32_t)(blocks * n_heads[0] - (int64_t)items->dealt[0] * gx);
+  return blocks * (n_heads[0] + n_heads[1]);
+}
+
 }  // namespace rlkv
 
 extern "C" int32_t rlkv_plan_prefill_rows(int32_t n_full_heads, int32_t batch, const int32_t* n_tokens,
@@ -273,10 +298,39 @@ extern "C" int32_t rlkv_plan_prefill_block(int32_t linear_index, int32_t grid_x,
   if (!block_x || !block_y || grid_x < 1 || grid_y < 1 || linear_index < 0 ||
       (int64_t)linear_index >= (int64_t)grid_x * grid_y)
     return -1;
-  int bx = 0, by = 0;
-  rlkv::prefill_deal(linear_index, grid_x, grid_y, dealt_rows, heavy_rows, bx, by);
-  *block_x = bx;
-  *block_y = by;
+  // rows of grid_x blocks each, the heavy ones first
+  const int heavy = heavy_rows < grid_y ? std::max(heavy_rows, 0) : grid_y;
+  const int dealt = std::min(std::max(dealt_rows, 0), heavy) / 8 * 8;
+  const rlkv::PrefillItems items{grid_x, {dealt, (grid_y - heavy) / 8 * 8}, (heavy - dealt) * grid_x};
+  int index = 0;
+  if (!rlkv::prefill_item(linear_index, items, index)) index += heavy * grid_x;
+  *block_x = index % grid_x;
+  *block_y = index / grid_x;
+  return 0;
+}
+
+extern "C" int32_t rlkv_plan_prefill_item(int32_t linear_index, int32_t per_block, int32_t n_full_heads, int32_t n_compressed_heads,
+                                          int32_t n_seqs, const int32_t* n_tokens, int32_t dealt_rows, int32_t* item) {
+  if (!n_tokens || !item || per_block < 1 || n_full_heads < 0 || n_compressed_heads < 0 || n_seqs < 1 || n_seqs > rlkv::kArgSeqs ||
+      dealt_rows < 0 || linear_index < 0)
+    return -1;
+  int32_t longest = 0;
+  for (int i = 0; i < n_seqs; ++i) {
+    if (n_tokens[i] < 1) return -1;
+    longest = std::max(longest, n_tokens[i]);
+  }
+  const int32_t n_heads[2] = {n_full_heads, n_compressed_heads};
+  rlkv::PrefillItems items;
+  int32_t ragged = 0, first[rlkv::kArgSeqs + 1];
+  const int gx = (longest + per_block - 1) / per_block;
+  if (linear_index >= rlkv::plan_prefill_items(per_block, n_seqs, n_tokens, gx, n_heads, dealt_rows, &items, &ragged, first)) return 1;
+  int index = 0, place = 0, head = 0, block = 0;
+  const bool full = rlkv::prefill_item(linear_index, items, index);
+  rlkv::prefill_place(index, n_heads[full ? 0 : 1], gx, ragged != 0, first, n_seqs, place, head, block);
+  item[0] = full;
+  item[1] = place;
+  item[2] = head;
+  item[3] = (ragged ? first[place + 1] - first[place] : gx) - 1 - block;
   return 0;
 }
 
