@@ -23,8 +23,9 @@ HIPCC_FLAGS = [
 ]
 
 
-# per-file additions: the prefill kernel's maxima need no NaN quieting (see the comment there)
-EXTRA_FLAGS = {"prefill_mfma.hip": ["-fno-honor-nans"]}
+# Per-file additions: the prefill kernel's maxima need no NaN quieting (see the comment there), and its hot loop wants to begin on
+# a cache line: the same instructions a few bytes further on took 0.8 % longer (16 x 16 384 tokens, 15.68 against 15.57 ms).
+EXTRA_FLAGS = {"prefill_mfma.hip": ["-fno-honor-nans", "-falign-loops=64"]}
 
 
 def _hipcc() -> str:

@@ -11,6 +11,7 @@
 // copies that row only (tiled layout: through LDS, tile_rows.h).  A multi-token append therefore writes survivors only and gives
 // the same store as the same tokens appended one at a time, whatever the write order.
 #include <string.h>
+#include <type_traits>
 
 #include "rlkv_internal.h"
 #include "tile_rows.h"
@@ -41,13 +42,30 @@ __device__ inline int source_position(bool full, int slot, int len_old, int len_
   return (p >= len_old && p < len_new) ? p : -1;
 }
 
-template <int KERNEL, typename T>
+// The compressed heads of a layer, in the arguments of an append that is for them only (n < 0: not given, all heads).
+struct NoRings {};
+struct RingHeads {
+  int32_t n;
+  int32_t head[kPrefillArgHeads];
+};
+
+// RINGS: compressed heads only (ragged); the full heads and the lengths have been seen to.
+template <int KERNEL, typename T, bool RINGS>
 __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer, const int32_t* __restrict__ len_in,
                                                         int32_t* __restrict__ len_out, const T* __restrict__ k_new,
                                                         const T* __restrict__ v_new, int n_uniform,
-                                                        int stride_tokens, int ragged, SeqCounts seqs) {
-  const int pair = blockIdx.y;
-  const int b = pair / dv.n_kv_heads, h = pair % dv.n_kv_heads;
+                                                        int stride_tokens, int ragged, SeqCounts seqs,
+                                                        std::conditional_t<RINGS, RingHeads, NoRings> rings) {
+  int b, h;
+  if constexpr (RINGS) {
+    const int per_seq = rings.n >= 0 ? rings.n : dv.n_kv_heads;
+    b = blockIdx.y / per_seq;
+    h = blockIdx.y - b * per_seq;
+    if (rings.n >= 0) h = rings.head[h];
+  } else {
+    b = blockIdx.y / dv.n_kv_heads;
+    h = blockIdx.y % dv.n_kv_heads;
+  }
   const int job = blockIdx.x;
   const int S = dv.sink, R = dv.recent;
   // a uniform append skips inactive slots; a ragged append states its counts explicitly
@@ -55,14 +73,14 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
   // lengths are double buffered: read the current copy, the block of (job 0, head 0) writes
   // the advanced length of its sequence to the other copy
   const int len_old = len_in[b];
-  if (job == 0 && h == 0 && threadIdx.x == 0) len_out[b] = len_old + n_tok;
+  if (!RINGS && job == 0 && h == 0 && threadIdx.x == 0) len_out[b] = len_old + n_tok;
   // a uniform append keeps the layer's work list valid: every active sequence has grown by the same count
-  if (!ragged && job == 0 && pair == 0 && threadIdx.x == 0) list_header(dv, layer)->grow += n_uniform;
+  if (!RINGS && !ragged && job == 0 && blockIdx.y == 0 && threadIdx.x == 0) list_header(dv, layer)->grow += n_uniform;
   const int len_new = len_old + n_tok;
   const bool full = dv.full_mask[layer * dv.n_kv_heads + h] != 0;
 
   int tile = -1;
-  if (n_tok > 0) {
+  if (n_tok > 0 && !(RINGS && full)) {
     if (full) {
       const TileRange t = tiles_of(len_old, len_new);
       if (job < t.count) tile = t.first + job;
@@ -113,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
         if (slot_pos && p >= 0) slot_pos[slot] = p;
       }
       __syncthreads();
-      const bool wide = rows_to_tile<false>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
+      const bool wide = rows_to_tile<false, true>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
       if (wide) dv.v_wide[layer] = 1;        // the prefill kernel takes this layer's V as bf16 from now on
     } else {
       // K and V rows: one 16-byte chunk per unit
@@ -213,15 +231,35 @@ hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in,
   const int jobs = max_tokens <= 1 ? 1 : (max_tokens + 3 * (kTile - 2)) / kTile + 3;
   const dim3 grid(jobs, dv.n_pairs), block(kBlock);
   if (dv.dtype == RLKV_F32) {
-    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, float>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const float*)k, (const float*)v, n_tokens_uniform, stride_tokens, ragged, sq);
+    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, float, false>), grid, block, 0, stream, dv, layer,
+                       len_in, len_out, (const float*)k, (const float*)v, n_tokens_uniform, stride_tokens, ragged, sq, NoRings{});
   } else if (dv.kernel == RLKV_KERNEL_MFMA) {
-    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, sq);
+    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t, false>), grid, block, 0, stream, dv, layer,
+                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, sq, NoRings{});
   } else {
-    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, uint16_t>), grid, block, 0, stream, dv, layer,
-                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, sq);
+    hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_VALU, uint16_t, false>), grid, block, 0, stream, dv, layer,
+                       len_in, len_out, (const uint16_t*)k, (const uint16_t*)v, n_tokens_uniform, stride_tokens, ragged, sq, NoRings{});
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_append_rings(const DeviceView& dv, int layer, const int32_t* len_in, const void* k, const void* v, int stride_tokens,
+                               const SeqCounts& seqs, int max_tokens, const uint8_t* mask_row, hipStream_t stream) {
+  RingHeads rings = {};
+  int n = 0;
+  for (int h = 0; h < dv.n_kv_heads; ++h) {
+    if (mask_row[h]) continue;
+    if (n < kPrefillArgHeads) rings.head[n] = h;
+    ++n;
+  }
+  if (n == 0) return hipSuccess;
+  rings.n = n <= kPrefillArgHeads ? n : -1;
+  const int rows = n <= kPrefillArgHeads ? n : dv.n_kv_heads;
+  // Tiles a compressed pair can touch (launch_append), and no more than its three ranges have.
+  const int slots = max_tokens < dv.window ? max_tokens : dv.window;
+  const int jobs = (slots + 3 * (kTile - 2)) / kTile + 3;
+  hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t, true>), dim3(jobs, dv.batch * rows), dim3(kBlock), 0, stream, dv, layer,
+                     len_in, (int32_t*)nullptr, (const uint16_t*)k, (const uint16_t*)v, 0, stride_tokens, 1, seqs, rings);
   return hipGetLastError();
 }
 

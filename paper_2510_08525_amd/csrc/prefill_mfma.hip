@@ -7,12 +7,13 @@
 // tiles its mask rows can touch and masks inside the tile.
 //
 // Keys and values come from two places, both in the tiled MFMA-operand layout:
-//   - the store: positions before the chunk (all of them for a full head; for a compressed head
-//     the sink slots and, while the chunk's first R queries still reach back, the ring slots,
-//     whose positions are read from the slot table);
-//   - a staging buffer holding the chunk's own K/V, tiled by stage_chunk_kernel.  A compressed
-//     head's ring cannot hold a chunk longer than R, and early queries of the chunk need keys that
-//     later ones evict, so the chunk is attended from the staging buffer and appended afterwards.
+//   - the store.  Of a full head it holds every position, the chunk's own included: place_chunk_kernel
+//     appends them first.  Of a compressed head it holds positions before the chunk: the sink slots and,
+//     while the chunk's first R queries still reach back, the ring slots, whose positions are read from
+//     the slot table;
+//   - of a compressed head, a staging buffer with the chunk's own K/V, tiled by place_chunk_kernel.  Its
+//     ring cannot hold a chunk longer than R, and early queries of the chunk need keys that later ones
+//     evict, so the chunk is attended from the staging buffer and appended afterwards.
 //
 // Work split and the two loops of a wavefront: see the comment on prefill_mfma_kernel below.
 // Scores use the same instruction and operand layouts as the decode kernel; a column of the score
@@ -188,22 +189,47 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
   }
 }
 
-// Copies the chunk's K/V rows (row-major [batch][n_kv_heads][stride][128]) into tiles of the MFMA
-// layout: staging tile t of a pair holds chunk rows 32 t .. 32 t + 31; rows past the sequence's
-// count are written as zeros, so a staged tile never holds stale bits.
-__global__ __launch_bounds__(kBlock) void stage_chunk_kernel(DeviceView dv, int layer, SeqCounts seqs, const uint16_t* __restrict__ k_new,
+// Brings the chunk's K/V rows (row-major [batch][n_kv_heads][stride][128]) into tiles of the MFMA layout, and the lengths
+// forward (len_in -> len_out).  A full head's rows go where they stay, into its store: every query sees what it needs there, and
+// nothing is evicted.  A compressed head's go to the staging buffer: staging tile t of a pair holds chunk rows 32 t .. 32 t + 31;
+// rows past the sequence's count are written as zeros, so a staged tile never holds stale bits.
+// Bound: HBM, as tile_rows.h.  (Every head staged here and appended behind the attention launch took a second pass over the
+// full heads' rows: 8 sequences of 1000 to 4000 tokens
+// that blend, chunks of 1024: 700 -> 666 us; a prompt of 333 tokens and 32 decode steps: 291 -> 274 us; 16 x 16 384 tokens, half the
+// heads full: 15.65 -> 15.57 ms.)
+__global__ __launch_bounds__(kBlock) void place_chunk_kernel(DeviceView dv, int layer, SeqCounts seqs, const int32_t* __restrict__ len_in,
+                                                             int32_t* __restrict__ len_out, const uint16_t* __restrict__ k_new,
                                                              const uint16_t* __restrict__ v_new, int stride_tokens,
                                                              char* __restrict__ staging, int staging_tiles) {
-  const int pair = blockIdx.y, tile = blockIdx.x;
-  const int b = pair / dv.n_kv_heads;
+  const int pair = blockIdx.y;
+  const int b = pair / dv.n_kv_heads, h = pair % dv.n_kv_heads;
   const int t = tokens_of_seq(dv, seqs, b);
-  if (tile * kTile >= t) return;
-  char* tile_base = staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes;
-  const int64_t src_head = (int64_t)pair * stride_tokens;
+  const int n_old = len_in[b];
+  if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) len_out[b] = n_old + t;
+  if (t == 0) return;
+  const bool full = dv.full_mask[layer * dv.n_kv_heads + h] != 0;
+  const int tile = (full ? n_old / kTile : 0) + blockIdx.x;
+  const int first = tile * kTile - (full ? n_old : 0);         // chunk row of slot 0 (a full head's first tile: may lie before the chunk)
+  if (first >= t) return;
+  const int64_t src_head = (int64_t)pair * stride_tokens * kHeadDim;
   __shared__ TileRowsLds lds;
-  if (threadIdx.x < kTile) lds.src[threadIdx.x] = tile * kTile + threadIdx.x < t ? tile * kTile + (int)threadIdx.x : -1;
+  if (threadIdx.x < kTile) {
+    const int row = first + threadIdx.x;
+    lds.src[threadIdx.x] = row >= 0 && row < t ? row : -1;
+  }
   __syncthreads();
-  const bool wide = rows_to_tile<true>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
+  bool wide;
+  if (full) {
+    char* tile_base = dv.kv_base + dv.store_off[((int64_t)layer * dv.batch + b) * dv.n_kv_heads + h];
+    if (dv.page_shift >= 0)
+      tile_base += dv.block_table[(int64_t)b * dv.table_stride + (tile >> dv.page_shift)] * dv.page_bytes +
+                   (int64_t)(tile & dv.page_mask) * kTileBytes;
+    else
+      tile_base += (int64_t)tile * kTileBytes;
+    wide = rows_to_tile<false, false>(lds, k_new + src_head, v_new + src_head, tile_base);
+  } else {
+    wide = rows_to_tile<true, false>(lds, k_new + src_head, v_new + src_head, staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes);
+  }
   if (wide) dv.v_wide[layer] = 1;          // seen by the attention kernel that follows on the stream
 }
 
@@ -382,20 +408,21 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   const int32_t* slot_pos = nullptr;
   if (!full) slot_pos = dv.slot_pos + dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window;
 
-  const int n_st = full ? n_old : (n_old < dv.window ? n_old : dv.window);     // store slots that hold data
+  // store slots that hold data: of a full head the chunk's too, of a compressed one what was cached before it
+  const int n_st = full ? n_old + t : (n_old < dv.window ? n_old : dv.window);
   const int sink_in_chunk = S - n_old;       // chunk indices below this are sink positions
 
   // Hot tiles (same for all wavefronts of the workgroup): tiles in which every slot counts for every
-  // query of the workgroup.  Full head: the store's complete tiles and the staging tiles wholly before
-  // the workgroup's first query.  Compressed head: the store's complete sink tiles, and the staging
+  // query of the workgroup.  Full head: the store's tiles up to the workgroup's first query.
+  // Compressed head: the store's complete sink tiles, and the staging
   // tiles wholly before the first query that also lie wholly inside the recent band of the last one
   // (a chunk is usually longer than the band, so these are most of what such a head attends over).
-  // A blending head's first pass (kLocal): the complete sink tiles of the store, and the store and staging tiles wholly before
-  // the first query and wholly inside the recent band of the last one; its second pass (kRest): the tiles wholly behind the
+  // A blending head's first pass (kLocal): of the tiles up to the first query the complete sink tiles and those
+  // wholly inside the recent band of the last one; its second pass (kRest): the tiles wholly behind the
   // sinks and wholly before the band of the first query.  (A softmax scale that is not positive, unusual, takes the
   // general loop throughout.)
   const bool hot = scale_log2 > 0.f;
-  const int stg_whole = hot ? c_wg / kTile : 0;          // staging tiles wholly before the first query
+  const int q_first = n_old + c_wg;                      // position of the workgroup's first query
   const int band_first = c_last - R + 1;                 // first chunk index that the last query's band holds
 
   // General tiles of this wavefront: store tiles [0, n_store), then staging tiles [0, n_stage), without those that are hot or
@@ -414,64 +441,50 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   int skip_stg_lo = 0, skip_stg_hi = 0;      // ... staging tiles that it passes over
   auto plan_pass = [&](int pass) {
     hs_lo = hs_hi = hb_lo = hb_hi = stg_lo = stg_hi = 0;
-    n_store = (n_st + kTile - 1) / kTile;
-    n_stage = c_hi / kTile + 1;
-    if (!MIX || pass == kWhole) {
-      stg_hi = stg_whole;
-      if (full) {
-        if (hot) hs_hi = n_st / kTile;
-      } else {
-        if (hot) {
-          hs_hi = (S < n_st ? S : n_st) / kTile;
-          stg_lo = band_first > 0 ? (band_first + kTile - 1) / kTile : 0;
-          if (stg_lo > stg_hi) stg_lo = stg_hi;
-        }
-        // the ring matters only while the wavefront's first query still reaches positions before the chunk
-        const int reach = c0 < R ? n_st : (S < n_st ? S : n_st);
-        n_store = (reach + kTile - 1) / kTile;
-        skip_stg_lo = sink_tiles;
-        skip_stg_hi = band_tile;
-      }
-      return;
-    }
-    const int sink_slots = S < n_st ? S : n_st;
-    const int sinks_up = (sink_slots + kTile - 1) / kTile;
-    if (pass == kLocal) {
-      const int band = n_old + band_lo;                  // first position of the wavefront's band
+    if (!full) {
+      n_stage = c_hi / kTile + 1;
       if (hot) {
-        hs_hi = sink_slots / kTile;
-        const int band_whole = n_old + band_first > 0 ? (n_old + band_first + kTile - 1) / kTile : 0;
-        hb_hi = n_st / kTile;
-        hb_lo = band_whole > hs_hi ? band_whole : hs_hi;
-        if (hb_lo > hb_hi) hb_lo = hb_hi;
-        stg_hi = stg_whole;
+        hs_hi = (S < n_st ? S : n_st) / kTile;
+        stg_hi = c_wg / kTile;                           // staging tiles wholly before the first query
         stg_lo = band_first > 0 ? (band_first + kTile - 1) / kTile : 0;
         if (stg_lo > stg_hi) stg_lo = stg_hi;
       }
-      skip_lo = sinks_up;                                // between the sinks and the band
-      skip_hi = band > 0 ? band / kTile : 0;
-      if (skip_hi > n_store) skip_hi = n_store;
+      // the ring matters only while the wavefront's first query still reaches positions before the chunk
+      const int reach = c0 < R ? n_st : (S < n_st ? S : n_st);
+      n_store = (reach + kTile - 1) / kTile;
       skip_stg_lo = sink_tiles;
       skip_stg_hi = band_tile;
+      return;
+    }
+    n_store = (n_old + c_hi) / kTile + 1;
+    n_stage = 0;
+    const int seen = hot ? (q_first + 1) / kTile : 0;    // store tiles that the first query sees whole
+    if (!MIX || pass == kWhole) {
+      hs_hi = seen;
+      return;
+    }
+    const int sinks_up = (S + kTile - 1) / kTile;
+    if (pass == kLocal) {
+      const int band = n_old + band_lo;                  // first position of the wavefront's band
+      const int band_whole = n_old + band_first > 0 ? (n_old + band_first + kTile - 1) / kTile : 0;
+      hs_hi = S / kTile < seen ? S / kTile : seen;
+      hb_hi = seen;
+      hb_lo = band_whole > hs_hi ? band_whole : hs_hi;
+      if (hb_lo > hb_hi) hb_lo = hb_hi;
+      skip_lo = sinks_up;                                // between the sinks and the band
+      skip_hi = band > 0 ? band / kTile : 0;
     } else {
-      const int rest = c_hi - R;                         // last chunk index outside the band of the wavefront's last query
-      const int rest_tiles = n_old + rest >= 0 ? (n_old + rest) / kTile + 1 : 0;
+      const int rest = n_old + c_hi - R;                 // last position outside the band of the wavefront's last query
+      const int rest_tiles = rest >= 0 ? rest / kTile + 1 : 0;
       if (rest_tiles < n_store) n_store = rest_tiles;
-      n_stage = rest >= 0 ? rest / kTile + 1 : 0;
       if (hot) {
-        const int before = n_old + c_wg - R + 1;         // first position of the first query's band
+        const int before = q_first - R + 1;              // first position of the first query's band
         hs_lo = sinks_up;
         hs_hi = before > 0 ? before / kTile : 0;
-        if (hs_hi > n_st / kTile) hs_hi = n_st / kTile;
         if (hs_hi < hs_lo) hs_hi = hs_lo;
-        stg_lo = sink_tiles;                             // (while the chunk itself still holds sink positions)
-        stg_hi = c_wg - R + 1 > 0 ? (c_wg - R + 1) / kTile : 0;
-        if (stg_hi < stg_lo) stg_hi = stg_lo;
       }
       skip_lo = 0;                                       // nothing but sinks
-      skip_hi = sink_slots / kTile < n_store ? sink_slots / kTile : n_store;
-      skip_stg_lo = 0;
-      skip_stg_hi = sink_in_chunk > 0 ? sink_in_chunk / kTile : 0;
+      skip_hi = S / kTile < n_store ? S / kTile : n_store;
     }
   };
   // The first general tile at or behind x.  Ranges are hopped over, not walked: at 16 384 cached tokens the walk over a full
@@ -1024,7 +1037,7 @@ __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv
 }  // namespace
 
 hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, int n_seqs,
-                               const int32_t* len_in, const void* q, const void* k, const void* v, void* out, int stride_tokens,
+                               const int32_t* len_in, int32_t* len_out, const void* q, const void* k, const void* v, void* out, int stride_tokens,
                                int max_tokens, float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int dealt_rows, const uint8_t* mask_row, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (n_split < 1 || !split_out || (mix && !narrow)) n_split = 1;
@@ -1043,9 +1056,9 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   grid.inv_group = (65536 + dv.group - 1) / dv.group;
   const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, grid.n_heads, dealt_rows,
                                            &grid.items, &grid.ragged, grid.first);
-  const int tiles = (max_tokens + kTile - 1) / kTile;
-  hipLaunchKernelGGL(stage_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, (const uint16_t*)k,
-                     (const uint16_t*)v, stride_tokens, staging, staging_tiles);
+  const int tiles = (max_tokens + kTile - 2) / kTile + 1;      // (a full head's chunk may start anywhere in a tile)
+  hipLaunchKernelGGL(place_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, len_in, len_out,
+                     (const uint16_t*)k, (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
   const int64_t heavy_rows = (int64_t)n_seqs * grid.n_heads[0];
   const dim3 blocks((uint32_t)(items + (n_split - 1) * heavy_rows * gx)), block(kPrefillBlock);

@@ -554,7 +554,7 @@ static rlkv_status_t reserve_pages(rlkv_cache_t* cache, const std::vector<int32_
 }
 
 // What rlkv_prefill_attention adds to a ragged append: attention of the chunk's queries, run after
-// every capacity check has passed and before the chunk's rows go into the stores.
+// every capacity check has passed; the full heads' rows go into the stores before it, the compressed heads' behind it.
 struct PrefillArgs {
   const void* q;
   void* out;
@@ -658,8 +658,8 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       int32_t heavy = 0;
       if (rlkv_plan_prefill_rows(n_full, B, n_tokens, lh, &dealt_rows, &heavy) != 0) return RLKV_ERR_INVALID_ARG;
     }
-    if (launch_prefill_mfma(cache->dv, layer, narrow, mix, seqs, order, n_seqs, len_of(cache->dv, par, layer), prefill->q,
-                            k, v, prefill->out, stride,
+    if (launch_prefill_mfma(cache->dv, layer, narrow, mix, seqs, order, n_seqs, len_of(cache->dv, par, layer),
+                            len_of(cache->dv, par ^ 1, layer), prefill->q, k, v, prefill->out, stride,
                             max_tok, prefill->softmax_scale * 1.44269504088896340736f, cache->arena + cache->plan.staging,
                             cache->plan.staging_tiles, n_split,
                             reinterpret_cast<float*>(cache->arena + cache->plan.prefill_split), dealt_rows,
@@ -668,8 +668,10 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
       return RLKV_ERR_HIP;
     if (record) ++cache->prof_used;
   }
-  if (launch_append(cache->dv, layer, len_of(cache->dv, par, layer), len_of(cache->dv, par ^ 1, layer), k, v,
-                    uniform, stride, n_tokens ? &seqs : nullptr, max_tok, s) != hipSuccess)
+  if (prefill ? launch_append_rings(cache->dv, layer, len_of(cache->dv, par, layer), k, v, stride, seqs, max_tok,
+                                    cache->mask.data() + (size_t)layer * cache->cfg.n_kv_heads, s) != hipSuccess
+              : launch_append(cache->dv, layer, len_of(cache->dv, par, layer), len_of(cache->dv, par ^ 1, layer), k, v,
+                              uniform, stride, n_tokens ? &seqs : nullptr, max_tok, s) != hipSuccess)
     return RLKV_ERR_HIP;
   cache->parity[layer] = par ^ 1;
   for (int b = 0; b < B; ++b) lh[b] += tokens_of(b);

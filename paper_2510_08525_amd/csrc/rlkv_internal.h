@@ -182,6 +182,10 @@ __host__ __device__ inline int32_t* len_of(const DeviceView& dv, int parity, int
 hipError_t launch_append(const DeviceView& dv, int layer, const int32_t* len_in, int32_t* len_out,
                          const void* k, const void* v, int n_tokens_uniform, int stride_tokens, const SeqCounts* seqs,
                          int max_tokens, hipStream_t stream);
+// Appends a chunk's K/V to the compressed heads of a layer of the tiled layout (behind launch_prefill_mfma, which has appended the
+// full heads' and written the lengths).  mask_row (host, [n_kv_heads]): the layer's mask.
+hipError_t launch_append_rings(const DeviceView& dv, int layer, const int32_t* len_in, const void* k, const void* v, int stride_tokens,
+                               const SeqCounts& seqs, int max_tokens, const uint8_t* mask_row, hipStream_t stream);
 // Copies `bytes` (a multiple of 8) from pinned host memory to the device by a kernel that reads them over the bus.
 hipError_t launch_fetch(void* dst, const void* pinned_src, size_t bytes, hipStream_t stream);
 // Writes n values of host memory to `dst` through kernel arguments.
@@ -224,7 +228,9 @@ constexpr int kMergeArgPairs = 512;
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
                           const void* v_new, const uint32_t* merge_words, int most_partials);
 // Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):
-// stages the chunk's K/V as tiles in `staging` (staging_tiles tiles per pair), then attends.
+// appends the chunk's K/V of the full heads and stages those of the compressed heads as tiles in `staging` (staging_tiles tiles per
+// pair), writes the advanced lengths to len_out, then attends.  Where the layer has compressed heads, launch_append_rings with the
+// same chunk follows.
 // `narrow`: the kernel form with one column group of queries per wavefront instead of two.  `mix`: some full head of the layer
 // blends (Eq. 1: causal and local attention of a full head with a gate below 1).
 // `n_split` > 1: the unmasked tiles of every full head's workgroup are divided among
@@ -235,7 +241,7 @@ constexpr int kPrefillSplitSlots = 1024;
 constexpr int kPrefillArgHeads = 64;      // KV heads of a layer whose class lists travel in the prefill kernels' arguments
 constexpr size_t kPrefillSplitSlotBytes = 256 * (size_t)(kHeadDim + 2) * sizeof(float);
 hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, bool mix, const SeqCounts& seqs, const SeqOrder& order, int n_seqs,
-                               const int32_t* len_in, const void* q, const void* k, const void* v, void* out, int stride_tokens,
+                               const int32_t* len_in, int32_t* len_out, const void* q, const void* k, const void* v, void* out, int stride_tokens,
                                int max_tokens, float scale_log2, char* staging, int staging_tiles, int n_split, float* split_out,
                                int dealt_rows, const uint8_t* mask_row /* host, [n_kv_heads]: the layer's mask */,
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);

@@ -1,5 +1,5 @@
 // Row-major K/V rows -> one 32-slot tile of the MFMA-operand layout (rlkv_internal.h), by one workgroup.  Used by the
-// multi-token append and by the staging of a prefill chunk.
+// multi-token append and by the placing of a prefill chunk.
 //
 // Bound: HBM, 16 KiB read and 16 KiB written per tile.  Both sides of the copy want whole lines and the layouts differ
 // (the tile's V is transposed in 2-byte elements), so a tile passes through LDS: rows come in with 16-byte loads, K and
@@ -23,8 +23,8 @@ struct TileRowsLds {
 
 __device__ __forceinline__ bool any_beyond_fp16(uint32_t two) { return bf16_beyond_fp16(two) || bf16_beyond_fp16(two >> 16); }
 
-// (NT: past the caches.  An append's tiles are not read before the next decode step: import of 32 prompts 211.2 -> 208.6 us.  A
-// staged tile is read by the attention launch behind it.)
+// (NT: past the caches.  An append's tiles are not read before the next decode step: import of 32 prompts 211.2 -> 208.6 us.  The
+// tiles of a prefill chunk are read by the attention launch behind them.)
 typedef uint32_t row_x4 __attribute__((ext_vector_type(4)));
 template <bool NT> __device__ __forceinline__ uint4 row_load(const uint16_t* p) {
   if (!NT) return *reinterpret_cast<const uint4*>(p);
@@ -40,7 +40,7 @@ template <bool NT> __device__ __forceinline__ void tile_store(char* p, const uin
 // lds.src is filled and visible to the workgroup.  k_rows / v_rows: row 0 of the pair (row r at r * kHeadDim).  ZERO: slots
 // without a source row are written as zeros; otherwise they keep what they hold.  Returns whether this thread moved a V
 // value beyond the fp16 range.
-template <bool ZERO>
+template <bool ZERO, bool NT>
 __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* __restrict__ k_rows,
                                              const uint16_t* __restrict__ v_rows, char* __restrict__ tile_base) {
   constexpr int kUnits = kTile * 16 / kBlock;            // 16-byte units of K (and of V) per thread
@@ -52,10 +52,10 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
     const int u = tid + i * kBlock, row = lds.src[u >> 4], chunk = u & 15;
     kv[i] = vv[i] = make_uint4(0, 0, 0, 0);
     if (row >= 0) {
-      kv[i] = row_load<!ZERO>(k_rows + (int64_t)row * kHeadDim + chunk * 8);
+      kv[i] = row_load<NT>(k_rows + (int64_t)row * kHeadDim + chunk * 8);
       const uint16_t* v = v_rows + (int64_t)row * kHeadDim + chunk * 8;
       if (v_aligned) {
-        vv[i] = row_load<!ZERO>(v);
+        vv[i] = row_load<NT>(v);
       } else {
         vv[i] = make_uint4(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16, v[4] | (uint32_t)v[5] << 16,
                            v[6] | (uint32_t)v[7] << 16);
@@ -75,7 +75,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
   for (int i = 0; i < kUnits; ++i) {                     // K: unit u of the tile = [half][chunk][slot % 16]
     const int u = tid + i * kBlock, hf = u >> 8, chunk = (u >> 4) & 15, s16 = u & 15;
     if (ZERO || lds.src[hf * 16 + s16] >= 0)
-      tile_store<!ZERO>(tile_base + u * 16, lds.k[hf * 256 + chunk * 16 + ((s16 + chunk) & 15)]);
+      tile_store<NT>(tile_base + u * 16, lds.k[hf * 256 + chunk * 16 + ((s16 + chunk) & 15)]);
   }
 #pragma unroll
   for (int i = 0; i < kUnits; ++i) {                     // V: unit u = [d / 16][kb][d % 16], eight slots of one d
@@ -90,7 +90,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
     }
     char* dst = tile_base + kTileBytes / 2 + u * 16;
     if (ZERO || have == 0xffu) {
-      tile_store<!ZERO>(dst, make_uint4(val[0] | val[1] << 16, val[2] | val[3] << 16, val[4] | val[5] << 16, val[6] | val[7] << 16));
+      tile_store<NT>(dst, make_uint4(val[0] | val[1] << 16, val[2] | val[3] << 16, val[4] | val[5] << 16, val[6] | val[7] << 16));
     } else {
 #pragma unroll
       for (int e = 0; e < 8; ++e)
