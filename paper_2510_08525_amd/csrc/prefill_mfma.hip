@@ -112,13 +112,17 @@ constexpr float kWeightShift = 6.f;
 // cores as in the decode kernel, a bf16 head plus a bf16 remainder (~16 mantissa bits; a single
 // bf16 weight measurably misses the 1e-2 bar).  This kernel is bound by its vector instruction count, so the
 // normaliser is accumulated by the matrix cores too, from the same two parts against a tile of
-// ones: it then arrives in the accumulator layout and needs no cross-lane sums.
+// ones: it needs no cross-lane sums.  V is the first operand of the products and the weights the second, so that a
+// lane's accumulators, its scores, its normaliser and its reference all belong to its own column: rescaling takes no
+// lane shuffles, and a lane's four outputs of a product lie side by side (8-byte stores; with the operands the other way
+// round an output row was written in 2-byte stores, four times as many: one prompt of 32 500 tokens 4404 -> 4375 us, 16 x 16 384
+// 16.23 -> 16.18 ms, blending 8 x 1000 .. 4000 679 -> 678 us)
 struct GroupState {
   float m;          // reference maximum of column lane%16 (log2 domain; same in all four k-groups)
   float ref;        // what the exponent subtracts: m (0 while m is -inf) minus kWeightShift
   float thr;        // a raw score above this makes the reference move: (m + slack) / scale
-  floatx4 l;        // normaliser of columns 4*(lane/16) + r (accumulator layout)
-  floatx4 o[8];     // O[column 4*(lane/16) + r][d = 16*j + lane%16]
+  floatx4 l;        // normaliser of column lane%16 (four equal rows)
+  floatx4 o[8];     // O[column lane%16][d = 16*j + 4*(lane/16) + r]
 };
 
 // This file is compiled with -fno-honor-nans: fmaxf would otherwise first quiet a possible signalling
@@ -132,10 +136,18 @@ __device__ __forceinline__ float max8(const float (&v)[8]) {
 // The reference maximum only moves when a score outgrows it by more than 2^kSlack; what depends on it
 // is kept beside it, so that a tile costs one comparison and no arithmetic on the reference.
 constexpr float kSlack = 8.f;
+// (the reciprocal by its instruction, off by an ulp: a division here was 20 instructions for a threshold that has slack)
 __device__ __forceinline__ void set_reference(GroupState& st, float m_new, float scale) {
   st.m = m_new;
   st.ref = (m_new == -INFINITY ? 0.f : m_new) - kWeightShift;
-  st.thr = (m_new + kSlack) / scale;       // -inf while no key has been seen: any score moves it
+  st.thr = (m_new + kSlack) * __builtin_amdgcn_rcpf(scale);       // -inf while no key has been seen: any score moves it
+}
+
+// Accumulators and normaliser of the lane's column times `a`.
+__device__ __forceinline__ void rescale(GroupState& st, float a) {
+  st.l *= a;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) st.o[j] *= a;
 }
 
 // Maximum over the four lanes that hold the same column (lane, lane^16, lane^32, lane^48), with
@@ -151,7 +163,7 @@ __device__ __forceinline__ float column_max(float v) {
 // Folds the masked raw scores `sc` of one tile (-inf = does not count) into the group's state;
 // `scale` (> 0, log2 domain) is applied inside the exponent's fused multiply-add.
 __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc)[8], float scale, GroupState& st,
-                                             int kb, const Frag& ones) {
+                                             const Frag& ones) {
   // The reference maximum only moves when some column's scores outgrow it by more than 2^kSlack:
   // until then the weights are simply larger than 1 (fp32 accumulators and the two-part bf16 split
   // are relative, so nothing is lost) and the accumulators need no rescaling.  Every lane holds its
@@ -164,28 +176,19 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
     // a column that has seen no key yet still has a zero accumulator: factor 1
     const float alpha = st.m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - m_new);
     set_reference(st, m_new, scale);
-    if (__any(alpha != 1.f)) {
-      // the accumulators hold columns 4*kb + r: fetch their factors from lanes 0..15
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float a = __shfl(alpha, kb * 4 + r);
-        st.l[r] *= a;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) st.o[j][r] *= a;
-      }
-    }
+    if (__any(alpha != 1.f)) rescale(st, alpha);
   }
   float p[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[e], scale, -st.ref));
   Frag phi, plo;
   split_weights(p, phi, plo);
-  st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi.v, ones.v, st.l, 0, 0, 0);
-  st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo.v, ones.v, st.l, 0, 0, 0);
+  st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, phi.v, st.l, 0, 0, 0);
+  st.l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones.v, plo.v, st.l, 0, 0, 0);
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi.v, t.v[j].v, st.o[j], 0, 0, 0);
-    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo.v, t.v[j].v, st.o[j], 0, 0, 0);
+    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[j].v, phi.v, st.o[j], 0, 0, 0);
+    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[j].v, plo.v, st.o[j], 0, 0, 0);
   }
 }
 
@@ -629,13 +632,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
             const float m_new = fmaxf(st[cg].m, column_max(mx[cg]) * exp_scale);
             const float alpha = st[cg].m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st[cg].m - m_new);
             set_reference(st[cg], m_new, exp_scale);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float a = __shfl(alpha, kb * 4 + r);
-              st[cg].l[r] *= a;
-#pragma unroll
-              for (int j = 0; j < 8; ++j) st[cg].o[j][r] *= a;
-            }
+            rescale(st[cg], alpha);
           }
         }
         if constexpr (HALF && NG == 2) {
@@ -651,18 +648,18 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][e], exp_scale, -ref0));
           half_weights(p, ph0);
           __builtin_amdgcn_sched_barrier(0);
-          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph0.h, ones_op.h, st[0].l, 0, 0, 0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones_op.h, ph0.h, st[0].l, 0, 0, 0);
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             __builtin_amdgcn_sched_barrier(0);
             p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][j], exp_scale, -ref1));
             __builtin_amdgcn_sched_barrier(0);
-            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph0.h, tr.v[j].h, st[0].o[j], 0, 0, 0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr.v[j].h, ph0.h, st[0].o[j], 0, 0, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
           half_weights(p, ph1);
           __builtin_amdgcn_sched_barrier(0);
-          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph1.h, ones_op.h, st[1].l, 0, 0, 0);
+          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones_op.h, ph1.h, st[1].l, 0, 0, 0);
           uint32_t hw[4];
           const uint32_t gw[4] = {c1.x, c1.y, c1.z, c1.w};
 #pragma unroll
@@ -670,7 +667,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
             __builtin_amdgcn_sched_barrier(0);
             if (j < 4) hw[j] = bf16x2_to_f16x2(gw[j]);
             __builtin_amdgcn_sched_barrier(0);
-            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph1.h, tr.v[j].h, st[1].o[j], 0, 0, 0);
+            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr.v[j].h, ph1.h, st[1].o[j], 0, 0, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
           next_v = make_uint4(hw[0], hw[1], hw[2], hw[3]);
@@ -684,7 +681,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][e], exp_scale, -ref0));
           half_weights(p, ph0);
           __builtin_amdgcn_sched_barrier(0);
-          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph0.h, ones_op.h, st[0].l, 0, 0, 0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones_op.h, ph0.h, st[0].l, 0, 0, 0);
           uint32_t hw[4];
           const uint32_t gw[4] = {c1.x, c1.y, c1.z, c1.w};
 #pragma unroll
@@ -692,7 +689,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
             __builtin_amdgcn_sched_barrier(0);
             if (j < 4) hw[j] = bf16x2_to_f16x2(gw[j]);
             __builtin_amdgcn_sched_barrier(0);
-            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph0.h, tr.v[j].h, st[0].o[j], 0, 0, 0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr.v[j].h, ph0.h, st[0].o[j], 0, 0, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
           next_v = make_uint4(hw[0], hw[1], hw[2], hw[3]);
@@ -706,24 +703,24 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[0][e], exp_scale, -ref0));
           split_weights(p, hi, lo);
           __builtin_amdgcn_sched_barrier(0);
-          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, ones_op.v, st[0].l, 0, 0, 0);
-          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, ones_op.v, st[0].l, 0, 0, 0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, hi.v, st[0].l, 0, 0, 0);
+          st[0].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, lo.v, st[0].l, 0, 0, 0);
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
             __builtin_amdgcn_sched_barrier(0);
             p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[1][j], exp_scale, -ref1));
             __builtin_amdgcn_sched_barrier(0);
-            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, tr.v[j].v, st[0].o[j], 0, 0, 0);
-            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, tr.v[j].v, st[0].o[j], 0, 0, 0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, hi.v, st[0].o[j], 0, 0, 0);
+            st[0].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, lo.v, st[0].o[j], 0, 0, 0);
           }
           __builtin_amdgcn_sched_barrier(0);
           split_weights(p, hi, lo);
-          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, ones_op.v, st[1].l, 0, 0, 0);
-          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, ones_op.v, st[1].l, 0, 0, 0);
+          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, hi.v, st[1].l, 0, 0, 0);
+          st[1].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, lo.v, st[1].l, 0, 0, 0);
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi.v, tr.v[j].v, st[1].o[j], 0, 0, 0);
-            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo.v, tr.v[j].v, st[1].o[j], 0, 0, 0);
+            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, hi.v, st[1].o[j], 0, 0, 0);
+            st[1].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, lo.v, st[1].o[j], 0, 0, 0);
           }
         } else
 #pragma unroll
@@ -735,19 +732,19 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           if (HALF) {
             Frag ph;
             half_weights(p, ph);
-            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph.h, ones_op.h, st[cg].l, 0, 0, 0);
+            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones_op.h, ph.h, st[cg].l, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < 8; ++j)
-              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ph.h, tr.v[j].h, st[cg].o[j], 0, 0, 0);
+              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(tr.v[j].h, ph.h, st[cg].o[j], 0, 0, 0);
           } else {
             Frag phi, plo;
             split_weights(p, phi, plo);
-            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi.v, ones_op.v, st[cg].l, 0, 0, 0);
-            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo.v, ones_op.v, st[cg].l, 0, 0, 0);
+            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, phi.v, st[cg].l, 0, 0, 0);
+            st[cg].l = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_op.v, plo.v, st[cg].l, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi.v, tr.v[j].v, st[cg].o[j], 0, 0, 0);
-              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo.v, tr.v[j].v, st[cg].o[j], 0, 0, 0);
+              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, phi.v, st[cg].o[j], 0, 0, 0);
+              st[cg].o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tr.v[j].v, plo.v, st[cg].o[j], 0, 0, 0);
             }
           }
         }
@@ -862,7 +859,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
       if (!sees[cg]) continue;
       float sc[8];
       masked(cg, raw[cg], sc);
-      group_update(tr, sc, exp_scale, st[cg], kb, ones);
+      group_update(tr, sc, exp_scale, st[cg], ones);
     }
     load_v_cached(tr, refill, lane);
   };
@@ -892,9 +889,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
       if (busy) {
 #pragma unroll
         for (int cg = 0; cg < NG; ++cg) {
-          floatx4 inv;
-#pragma unroll
-          for (int r = 0; r < 4; ++r) inv[r] = 1.f / st[cg].l[r];
+          const float inv = 1.f / st[cg].l[0];
 #pragma unroll
           for (int j = 0; j < 8; ++j) sm_local[wave][cg * 8 + j][lane] = st[cg].o[j] * inv;
         }
@@ -911,60 +906,43 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     float* slot = split_out + ((int64_t)index * Z + z) * kSplitSlotFloats;
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
-      const int first = col0 + 16 * k;
-      if (kb == 0) slot[kSplitCols * kHeadDim + first + hd] = st[k].m;      // the lane's own column
+      const int col = col0 + 16 * k + hd;                // the lane's own column
+      if (kb == 0) {
+        slot[kSplitCols * kHeadDim + col] = st[k].m;
+        slot[kSplitCols * (kHeadDim + 1) + col] = st[k].l[0];
+      }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int col = first + kb * 4 + r;
-        if (hd == 0) slot[kSplitCols * (kHeadDim + 1) + col] = st[k].l[r];
+      for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(slot + col * kHeadDim + j * 16 + kb * 4) = st[k].o[j];
+      if (MIX && mix && z == Z - 1) {          // the local results, as columns 128 and up (one column group)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) slot[col * kHeadDim + j * 16 + hd] = st[k].o[j][r];
-        if (MIX && mix && z == Z - 1) {        // the local results, as columns 128 and up (one column group)
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            slot[(kSplitCols / 2 + col) * kHeadDim + j * 16 + hd] = sm_local[MIX ? wave : 0][MIX ? k * 8 + j : 0][lane][r];
-        }
+        for (int j = 0; j < 8; ++j)
+          *reinterpret_cast<floatx4*>(slot + (kSplitCols / 2 + col) * kHeadDim + j * 16 + kb * 4) = sm_local[MIX ? wave : 0][MIX ? k * 8 + j : 0][lane];
       }
     }
     return;
   }
-  // out[b][head][c][d] = O / l (blended with the local result for a gated head); the accumulator
-  // rows of group cg are its columns 4 kb + r.  (Bound: vector instructions; rounded by the packed conversion, two values
-  // at a time: 1.4 us per workgroup, against 3.3 us with the rounding written out.  Whole rows through LDS instead of these
-  // two-byte stores changed nothing: the stores are not waited for.)
+  // out[b][head][c][d] = O / l (blended with the local result for a gated head)
+  const bool out_aligned = (reinterpret_cast<uintptr_t>(out) & 7) == 0;      // (a caller's may start at any element)
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) {
-    uint16_t* dst[4];
-    bool on[4];
-    float inv[4];
+    const int col = col0 + 16 * cg + hd;
+    const int cl = div_g(col), hh = col - cl * G;
+    uint16_t* dst = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + kb * 4;
+    const bool on = c_wg + cl <= c_last;
+    const float inv = 1.f / st[cg].l[0];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int col = col0 + 16 * cg + kb * 4 + r;
-      const int cl = div_g(col), hh = col - cl * G;
-      on[r] = c_wg + cl <= c_last;
-      dst[r] = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + hd;
-      inv[r] = 1.f / st[cg].l[r];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; j += 2) {
-      floatx4 near[2];
-      if (MIX && mix) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) near[k] = sm_local[MIX ? wave : 0][MIX ? cg * 8 + j + k : 0][lane];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        float res[2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          res[k] = st[cg].o[j + k][r] * inv[r];
-          if (MIX && mix) res[k] = gate * res[k] + (1.f - gate) * near[k][r];
-        }
-        const uint32_t two = bf16_pair(res[0], res[1]);
-        if (on[r]) {
-          dst[r][j * 16] = (uint16_t)two;
-          dst[r][j * 16 + 16] = (uint16_t)(two >> 16);
-        }
+    for (int j = 0; j < 8; ++j) {
+      floatx4 res = st[cg].o[j] * inv;
+      if (MIX && mix) res = gate * res + (1.f - gate) * sm_local[MIX ? wave : 0][MIX ? cg * 8 + j : 0][lane];
+      const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
+      if (!on) continue;
+      if (out_aligned) {
+        *reinterpret_cast<uint2*>(dst + j * 16) = four;
+      } else {
+        dst[j * 16] = (uint16_t)four.x;
+        dst[j * 16 + 1] = (uint16_t)(four.x >> 16);
+        dst[j * 16 + 2] = (uint16_t)four.y;
+        dst[j * 16 + 3] = (uint16_t)(four.y >> 16);
       }
     }
   }
