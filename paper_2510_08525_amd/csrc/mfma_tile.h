@@ -48,11 +48,38 @@ __device__ __forceinline__ float exp2_or_zero(float m, float ref) {
   return m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - ref);
 }
 
-// Online-softmax state of one wavefront for one (pair, share) segment.
+// Two fp32 values rounded to bf16 (to nearest even), the first in the low half.
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 r = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, r);
+}
+
+// A value of the four lanes that hold the same column (lane, lane^16, lane^32, lane^48) against the lane 16 (32) away, with the
+// gfx950 row swaps instead of LDS permutes: the two results of a swap are the lane's own value and the other's, in either order.
+struct TwoValues { float a, b; };
+__device__ __forceinline__ TwoValues swap16(float v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+__device__ __forceinline__ TwoValues swap32(float v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+}
+// Maximum over these four lanes.
+__device__ __forceinline__ float column_max(float v) {
+  const TwoValues x = swap32(v);
+  const TwoValues y = swap16(fmaxf(x.a, x.b));
+  return fmaxf(y.a, y.b);
+}
+
+// Online-softmax state of one wavefront for one (pair, share) segment.  All of a lane's is of its own column, head lane%16.
 struct Softmax {
-  float m;          // running maximum of head lane%16 (log2 domain; same in all four k-groups)
+  float m;          // running maximum (log2 domain; same in all four k-groups)
   float l;          // this lane's share of the normaliser
-  floatx4 o[8];     // O[head 4*(lane/16) + r][d = 16*j + lane%16]
+  floatx4 o[8];     // O[d = 16*j + 4*(lane/16) + r]
 };
 
 // Raw scores of one 32-slot tile: lane l receives head l%16, slots 4*(l/16)..+3 of each half.
@@ -69,15 +96,14 @@ __device__ __forceinline__ void tile_scores(const TileRegs& t, const Frag (&qb)[
 
 // Online-softmax update of `st` with the masked scores `sc` of one tile (-inf = does not count;
 // layout as tile_scores leaves them) and accumulation of P.V.  The 16 columns of the score tile
-// are heads (decode) or (query position, head) pairs (prefill); lane l tracks column l%16.  P is
-// split into a bf16 head and a bf16 remainder so the weights carry ~16 mantissa bits.
-__device__ __forceinline__ void softmax_pv(const TileRegs& t, const float (&sc)[8], Softmax& st, int kb) {
+// are heads; lane l tracks column l%16.  P is
+// split into a bf16 head and a bf16 remainder so the weights carry ~16 mantissa bits.  V is the first operand of the products: the
+// accumulators then stand in the lanes of their own head, as scores and maxima do, and rescaling needs no lane shuffles.
+__device__ __forceinline__ void softmax_pv(const TileRegs& t, const float (&sc)[8], Softmax& st) {
   float mx = sc[0];
 #pragma unroll
   for (int e = 1; e < 8; ++e) mx = fmaxf(mx, sc[e]);
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
-  const float m_new = fmaxf(st.m, mx);
+  const float m_new = fmaxf(st.m, column_max(mx));
   const float m_ref = m_new == -INFINITY ? 0.f : m_new;
   const float alpha = __builtin_amdgcn_exp2f(st.m - m_ref);
   st.m = m_new;
@@ -95,18 +121,13 @@ __device__ __forceinline__ void softmax_pv(const TileRegs& t, const float (&sc)[
     plo[e] = (__bf16)(p[e] - (float)phi[e]);
   }
   if (__any(alpha != 1.f)) {
-    // the output accumulator holds heads 4*kb + r: fetch their factors from lanes 0..15
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const float a = __shfl(alpha, kb * 4 + r);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) st.o[j][r] *= a;
-    }
+    for (int j = 0; j < 8; ++j) st.o[j] *= alpha;
   }
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
-    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(phi, t.v[j].v, st.o[j], 0, 0, 0);
-    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(plo, t.v[j].v, st.o[j], 0, 0, 0);
+    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[j].v, phi, st.o[j], 0, 0, 0);
+    st.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.v[j].v, plo, st.o[j], 0, 0, 0);
   }
 }
 

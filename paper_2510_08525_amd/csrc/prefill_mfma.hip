@@ -57,13 +57,6 @@ __device__ __forceinline__ void raw_scores(const TileRegs& t, const Frag (&qb)[4
   for (int e = 0; e < 8; ++e) raw[e] = e < 4 ? s0[e] : s1[e - 4];
 }
 
-// Two fp32 values rounded to bf16 (to nearest even), the first in the low half.
-__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  const bf16x2 r = {(__bf16)a, (__bf16)b};
-  return __builtin_bit_cast(uint32_t, r);
-}
-
 // Eight fp32 weights as two bf16 operands: the head keeps the top 16 bits of each weight
 // (truncated, one byte permute per pair), the remainder p - head is exact in fp32 and is rounded
 // to bf16; together they carry ~16 mantissa bits.
@@ -128,7 +121,6 @@ struct GroupState {
 // This file is compiled with -fno-honor-nans: fmaxf would otherwise first quiet a possible signalling
 // NaN in every operand (three instructions per maximum); scores are never NaN here, and -inf (a masked
 // score, an empty running maximum) is still honoured.
-__device__ __forceinline__ float max2(float a, float b) { return fmaxf(a, b); }
 __device__ __forceinline__ float max8(const float (&v)[8]) {
   return fmaxf(fmaxf(fmaxf(fmaxf(v[0], v[1]), v[2]), fmaxf(fmaxf(v[3], v[4]), v[5])), fmaxf(v[6], v[7]));
 }
@@ -148,16 +140,6 @@ __device__ __forceinline__ void rescale(GroupState& st, float a) {
   st.l *= a;
 #pragma unroll
   for (int j = 0; j < 8; ++j) st.o[j] *= a;
-}
-
-// Maximum over the four lanes that hold the same column (lane, lane^16, lane^32, lane^48), with
-// the gfx950 row swaps instead of LDS permutes.
-__device__ __forceinline__ float column_max(float v) {
-  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  u32x2 a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = max2(__uint_as_float(a[0]), __uint_as_float(a[1]));
-  u32x2 b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return max2(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // Folds the masked raw scores `sc` of one tile (-inf = does not count) into the group's state;
