@@ -55,20 +55,24 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
   return __builtin_bit_cast(uint32_t, r);
 }
 
-// A value of the four lanes that hold the same column (lane, lane^16, lane^32, lane^48) against the lane 16 (32) away, with the
-// gfx950 row swaps instead of LDS permutes: the two results of a swap are the lane's own value and the other's, in either order.
+// Lanes that hold the same column (lane, lane^16, lane^32, lane^48) exchange values with the gfx950 row swaps instead of LDS permutes.
+// swap16 / swap32: the lane's own value and that of the lane 16 / 32 away, in either order.
 struct TwoValues { float a, b; };
-__device__ __forceinline__ TwoValues swap16(float v) {
+// Two values dealt out over the pair of lanes: the even lane group (lower half) is left with both lanes' x, the odd one (upper
+// half) with both lanes' y, so that a sum of either takes one addition in either lane.
+__device__ __forceinline__ TwoValues deal16(float x, float y) {
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
-__device__ __forceinline__ TwoValues swap32(float v) {
+__device__ __forceinline__ TwoValues deal32(float x, float y) {
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   return {__uint_as_float(r[0]), __uint_as_float(r[1])};
 }
-// Maximum over these four lanes.
+__device__ __forceinline__ TwoValues swap16(float v) { return deal16(v, v); }
+__device__ __forceinline__ TwoValues swap32(float v) { return deal32(v, v); }
+// Maximum over the four lanes.
 __device__ __forceinline__ float column_max(float v) {
   const TwoValues x = swap32(v);
   const TwoValues y = swap16(fmaxf(x.a, x.b));
