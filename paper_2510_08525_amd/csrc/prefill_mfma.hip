@@ -529,7 +529,11 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // fp16 operand.  The other one, for a layer whose v_wide flag is up (some V value beyond the fp16
   // range has been appended since the cache was last empty; unusual) and for the local pass of a blending head, takes V as
   // stored, with two-part bf16 weights.
+  // (MIX: the second wavefront of every SIMD goes first where both could issue, which keeps the two out of step: one's exponentials beside
+  // the other's products.  8 x 1000 .. 4000 tokens that blend 663 -> 659 us; in the one-group form one of 3074 tokens in chunks of 512 241.5 ->
+  // 239.1, 8 x 291 .. 868 79.7 -> 78.0, 5 x 2735 .. 3469 734 -> 728.  The two-group form of plain heads: 0.3 % slower with it.)
   auto hot_loop = [&](auto half_tag) {
+    if (MIX && wave >= kPrefillWaves / 2) __builtin_amdgcn_s_setprio(1);
     constexpr bool HALF = decltype(half_tag)::value;
     uint4 next_v = make_uint4(0, 0, 0, 0);      // the next tile's V as fp16, when the loop body has converted it already
     bool next_ready = false;
