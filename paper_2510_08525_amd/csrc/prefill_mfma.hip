@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // the other's products.  8 x 1000 .. 4000 tokens that blend 663 -> 659 us; in the one-group form one of 3074 tokens in chunks of 512 241.5 ->
   // 239.1, 8 x 291 .. 868 79.7 -> 78.0, 5 x 2735 .. 3469 734 -> 728.  The two-group form of plain heads: 0.3 % slower with it.)
   auto hot_loop = [&](auto half_tag) {
-    if (MIX && wave >= kPrefillWaves / 2) __builtin_amdgcn_s_setprio(1);
+    if ((MIX || NG == 1) && wave >= kPrefillWaves / 2) __builtin_amdgcn_s_setprio(1);
     constexpr bool HALF = decltype(half_tag)::value;
     uint4 next_v = make_uint4(0, 0, 0, 0);      // the next tile's V as fp16, when the loop body has converted it already
     bool next_ready = false;
@@ -1030,9 +1030,13 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, NGR, MX>), blocks, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
                         staging_tiles, split_out, grid)
-#define RLKV_PICK(PG) do { if (narrow) RLKV_LAUNCH(PG, 1, true); else if (mix) RLKV_LAUNCH(PG, 2, true); else RLKV_LAUNCH(PG, 2, false); } while (0)
+  // (Layers that do not blend in an instance of their own in either form: the one-group form, which used to carry the blending code
+  // along, 8 x 291 .. 868 tokens 77.9 -> 76.2 us, 5 x 2735 .. 3469 728 -> 706, one of 3074 in chunks of 512 239.1 -> 240.3.)
+#define RLKV_FORM(PG, NGR) do { if (mix) RLKV_LAUNCH(PG, NGR, true); else RLKV_LAUNCH(PG, NGR, false); } while (0)
+#define RLKV_PICK(PG) do { if (narrow) RLKV_FORM(PG, 1); else RLKV_FORM(PG, 2); } while (0)
   if (dv.page_shift >= 0) RLKV_PICK(true); else RLKV_PICK(false);
 #undef RLKV_PICK
+#undef RLKV_FORM
 #undef RLKV_LAUNCH
   if (hipError_t e = hipGetLastError()) return e;
   if (n_split > 1 && heavy_rows > 0) {
