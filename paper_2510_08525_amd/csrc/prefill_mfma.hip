@@ -128,11 +128,12 @@ __device__ __forceinline__ float max8(const float (&v)[8]) {
 // The reference maximum only moves when a score outgrows it by more than 2^kSlack; what depends on it
 // is kept beside it, so that a tile costs one comparison and no arithmetic on the reference.
 constexpr float kSlack = 8.f;
-// (the reciprocal by its instruction, off by an ulp: a division here was 20 instructions for a threshold that has slack)
-__device__ __forceinline__ void set_reference(GroupState& st, float m_new, float scale) {
+// (the reciprocal of the scale comes from the host: a division here was 20 instructions for a threshold that has slack, and the
+// reciprocal's instruction gives 0 for scales beyond 2^126, whose reciprocal is a subnormal)
+__device__ __forceinline__ void set_reference(GroupState& st, float m_new, float inv_scale) {
   st.m = m_new;
   st.ref = (m_new == -INFINITY ? 0.f : m_new) - kWeightShift;
-  st.thr = (m_new + kSlack) * __builtin_amdgcn_rcpf(scale);       // -inf while no key has been seen: any score moves it
+  st.thr = (m_new + kSlack) * inv_scale;       // -inf while no key has been seen: any score moves it
 }
 
 // Accumulators and normaliser of the lane's column times `a`.
@@ -144,7 +145,7 @@ __device__ __forceinline__ void rescale(GroupState& st, float a) {
 
 // Folds the masked raw scores `sc` of one tile (-inf = does not count) into the group's state;
 // `scale` (> 0, log2 domain) is applied inside the exponent's fused multiply-add.
-__device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc)[8], float scale, GroupState& st,
+__device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc)[8], float scale, float inv_scale, GroupState& st,
                                              const Frag& ones) {
   // The reference maximum only moves when some column's scores outgrow it by more than 2^kSlack:
   // until then the weights are simply larger than 1 (fp32 accumulators and the two-part bf16 split
@@ -157,7 +158,7 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
     const float m_new = fmaxf(st.m, mx);
     // a column that has seen no key yet still has a zero accumulator: factor 1
     const float alpha = st.m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st.m - m_new);
-    set_reference(st, m_new, scale);
+    set_reference(st, m_new, inv_scale);
     if (__any(alpha != 1.f)) rescale(st, alpha);
   }
   float p[8];
@@ -229,6 +230,7 @@ struct PrefillGrid {
                                            // without queries do nothing)
   int32_t n_split;                         // shares of every heavy item (1 = undivided; else dealt in plain order, ragged = 0)
   int32_t inv_group;                       // 65536 / group, rounded up
+  float inv_scale;                         // 1 / scale_log2; 1 where that is not positive
   int32_t heads_given;                     // 1: `head` holds the heads
   int32_t head[2][kPrefillArgHeads];       // [0]: the full heads in ascending order, [1]: the compressed ones
   int32_t first[kArgSeqs + 1];             // blocks of the sequences before each place in the order
@@ -504,6 +506,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // running maximum into a minimum, and zero times the -inf of a masked score is not a number, so
   // those two are applied to the scores up front (general loop) instead.
   const float exp_scale = scale_log2 > 0.f ? scale_log2 : 1.f;
+  const float inv_scale = grid.inv_scale;
 
   // One pass, or two of a blending head (of a divided workgroup, the last share takes what is local).
   int pass = !mix ? kWhole : split && z != Z - 1 ? kRest : kLocal;
@@ -617,7 +620,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
           for (int cg = 0; cg < NG; ++cg) {
             const float m_new = fmaxf(st[cg].m, column_max(mx[cg]) * exp_scale);
             const float alpha = st[cg].m == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(st[cg].m - m_new);
-            set_reference(st[cg], m_new, exp_scale);
+            set_reference(st[cg], m_new, inv_scale);
             rescale(st[cg], alpha);
           }
         }
@@ -845,7 +848,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
       if (!sees[cg]) continue;
       float sc[8];
       masked(cg, raw[cg], sc);
-      group_update(tr, sc, exp_scale, st[cg], ones);
+      group_update(tr, sc, exp_scale, inv_scale, st[cg], ones);
     }
     load_v_cached(tr, refill, lane);
   };
@@ -1018,6 +1021,7 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   grid.n_seqs = n_seqs;
   grid.n_split = n_split;
   grid.inv_group = (65536 + dv.group - 1) / dv.group;
+  grid.inv_scale = scale_log2 > 0.f ? 1.f / scale_log2 : 1.f;
   const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, grid.n_heads, dealt_rows,
                                            &grid.items, &grid.ragged, grid.first);
   const int tiles = (max_tokens + kTile - 2) / kTile + 1;      // (a full head's chunk may start anywhere in a tile)
