@@ -6,17 +6,31 @@
 
 namespace rlkv {
 
+// n / d for 0 <= n < 2^31, inv = quotient_inverse(d): the product is at most n / d and less than 1/2 + 1/2 below it, so one
+// correction makes it exact.  (Six scalar instructions; a division is about thirty vector ones, one behind the other.)
+__host__ __device__ inline uint32_t quotient_inverse(int d) { return 0xffffffffu / (uint32_t)(d > 0 ? d : 1); }
+__host__ __device__ inline int quotient(int n, int d, uint32_t inv) {
+  const int q = (int)(((uint64_t)(uint32_t)n * inv) >> 32);
+  return n - q * d >= d ? q + 1 : q;
+}
+
 // The items of a launch: the heavy ones (full heads of the sequences that have a chunk) and the light ones (compressed heads),
 // each class numbered sequence by sequence (long to short), within a sequence head by head (a row: the query blocks of one
 // sequence and head), within a row block by block.  Sequences have up to `gx` blocks; only blocks that hold queries are items
-// (unless `gx` is taken for all, see PrefillGrid::ragged), because the hardware deals workgroups not only to the 8 XCDs but also to the
+// (unless `gx` is taken for all, `ragged` 0), because the hardware deals workgroups not only to the 8 XCDs but also to the
 // 4 shader engines of each strictly in turn, and an engine whose turn it is keeps the others waiting: with 488 of 928
 // workgroups empty, engines of 8 CUs had 12 to 18 that were not, three rounds of work instead of two.
 struct PrefillItems {
   int32_t gx;
   int32_t dealt[2];      // [heavy, light] rows, from the first on, that go one row per XCD: a multiple of 8, of gx blocks each
   int32_t rest;          // heavy items that do not
+  int32_t heads[2];      // full, compressed heads of the layer
+  int32_t n_seqs;        // sequences that have a chunk
+  int32_t ragged;        // 1: a sequence's blocks are those `first` gives it; 0: all have gx (those without queries do nothing)
+  uint32_t inv_gx, inv_heads[2], inv_seq[2];     // quotient_inverse of gx, heads and heads * gx
 };
+// Blocks of the sequences before each place in the order ([n_seqs + 1], then INT32_MAX), looked at where `ragged` is 1.
+constexpr int kFirstEntries = 129;
 
 // Workgroups are dealt to the 8 XCDs in turn by their linear index, and each XCD has an L2 of its own.  All the
 // workgroups of a row read the same tiles, so whole rows are kept on one XCD where that leaves the XCDs equally loaded.
@@ -26,41 +40,50 @@ struct PrefillItems {
 // a bijection for any counts.  Returns whether workgroup `lin` has a heavy item, and its number in the class.
 __host__ __device__ inline bool prefill_item(int lin, const PrefillItems& p, int& index) {
   const int k = lin & 7;
-  int i = lin >> 3;
   const int c_a = (p.dealt[0] >> 3) * p.gx, c_c = (p.dealt[1] >> 3) * p.gx;     // items of whole rows per XCD of either class
   const int c_b = (p.rest - k + 7) >> 3;                // how many of the heavy ones dealt one by one come to this XCD
-  if (i < c_a) { const int row = i / p.gx; index = (row * 8 + k) * p.gx + (i - row * p.gx); return true; }
-  i -= c_a;
-  if (i < c_b) { index = p.dealt[0] * p.gx + i * 8 + k; return true; }
-  i -= c_b;
-  if (i < c_c) { const int row = i / p.gx; index = (row * 8 + k) * p.gx + (i - row * p.gx); return false; }
-  i -= c_c;
-  index = p.dealt[1] * p.gx + (c_b + i) * 8 + k - p.rest;     // the dealt list goes on with the light items left over
-  return false;
+  const int i = lin >> 3;
+  const bool heavy = i < c_a + c_b;
+  const int i_class = heavy ? i : i - c_a - c_b;        // the XCD's items of the class before it
+  const bool by_rows = i_class < (heavy ? c_a : c_c);
+  const int row = quotient(i_class, p.gx, p.inv_gx);
+  const int of_rows = (row * 8 + k) * p.gx + (i_class - row * p.gx);
+  const int one_by_one = heavy ? p.dealt[0] * p.gx + (i - c_a) * 8 + k
+                               : p.dealt[1] * p.gx + (i - c_a - c_c) * 8 + k - p.rest;   // the dealt list goes on with the light items left over
+  index = by_rows ? of_rows : one_by_one;
+  return heavy;
+}
+
+// Place of the sequence whose blocks hold block x: first[place] <= x < first[place + 1].  `first16`: first[0 .. 15], so that up to
+// 16 sequences take no further load, more of them one (a search by halves waited for a load at every step).
+typedef int32_t FirstSixteen __attribute__((ext_vector_type(16), aligned(4)));   // (one scalar load)
+__host__ __device__ inline int place_of_block(int x, int n_seqs, const int32_t* first, const FirstSixteen& first16) {
+  FirstSixteen lead = first16;
+  int place = 0;
+  if (n_seqs > 16) {
+#pragma unroll
+    for (int j = 16; j < kFirstEntries - 1; j += 16) place += first[j] <= x ? 16 : 0;
+    lead = *reinterpret_cast<const FirstSixteen*>(first + place);
+  }
+#pragma unroll
+  for (int j = 1; j < 16; ++j) place += lead[j] <= x ? 1 : 0;
+  return place;
 }
 
 // Item `index` of a class with `heads` heads a sequence: the sequence's place in the order, the head's number in its class and
 // the block counted from the row's end (later query blocks have more keys under the causal mask and go first).
-// `first` [n_seqs + 1]: blocks of the sequences before each place; `ragged` 0: not looked at, every sequence has gx.
-__host__ __device__ inline void prefill_place(int index, int heads, int gx, bool ragged, const int32_t* first, int n_seqs, int& place,
-                                              int& head, int& block) {
-  int at = 0, blocks = gx;
-  if (ragged) {
-    const int x = index / heads;                        // first[place] <= x < first[place + 1]
-    int lo = 0, hi = n_seqs;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (first[mid] <= x) lo = mid; else hi = mid;
-    }
-    place = lo;
-    at = first[lo];
-    blocks = first[lo + 1] - at;
-  } else {
-    place = index / (heads * gx);
-    at = place * gx;
-  }
+// Even launch: every sequence has gx blocks.
+__host__ __device__ inline void even_place(int index, bool full, const PrefillItems& p, int& place, int& head, int& block) {
+  const int per_seq = (full ? p.heads[0] : p.heads[1]) * p.gx;
+  place = quotient(index, per_seq, full ? p.inv_seq[0] : p.inv_seq[1]);
+  const int r = index - place * per_seq;
+  head = quotient(r, p.gx, p.inv_gx);
+  block = r - head * p.gx;
+}
+// Ragged launch, `at` = first[place], `blocks` those of the sequence.
+__host__ __device__ inline void ragged_place(int index, int heads, int at, int blocks, int& head, int& block) {
   const int r = index - at * heads;
-  head = r / blocks;
+  head = (int)((uint32_t)r / (uint32_t)blocks);
   block = r - head * blocks;
 }
 

@@ -30,7 +30,6 @@
 namespace rlkv {
 namespace {
 
-
 // Tiles re-read by many query blocks: ordinary (cached) loads.
 __device__ __forceinline__ void load_k_cached(TileRegs& r, const char* tile_base, int lane) {
   const char* kb = tile_base + lane * 16;
@@ -224,32 +223,32 @@ __global__ __launch_bounds__(kBlock) void place_chunk_kernel(DeviceView dv, int 
 // fit there.
 struct PrefillGrid {
   PrefillItems items;
-  int32_t n_heads[2];                      // full, compressed heads of the layer
-  int32_t n_seqs;                          // sequences that have a chunk
-  int32_t ragged;                          // 1: a sequence's blocks are those `first` gives it; 0: all have items.gx (those
-                                           // without queries do nothing)
-  int32_t n_split;                         // shares of every heavy item (1 = undivided; else dealt in plain order, ragged = 0)
+  int32_t n_split;                         // shares of every heavy item (1 = undivided; else dealt in plain order, not ragged)
   int32_t inv_group;                       // 65536 / group, rounded up
   float inv_scale;                         // 1 / scale_log2; 1 where that is not positive
   int32_t heads_given;                     // 1: `head` holds the heads
-  int32_t head[2][kPrefillArgHeads];       // [0]: the full heads in ascending order, [1]: the compressed ones
-  int32_t first[kArgSeqs + 1];             // blocks of the sequences before each place in the order
+  uint64_t head[2][kPrefillArgHeads / 8];  // [0]: the full heads in ascending order, [1]: the compressed ones, 8 bits each
+  int32_t first[kFirstEntries];
 };
-// Place in the sequence order and number in its class -> (sequence, KV head), chunk length.
-__device__ __forceinline__ void pair_of_place(const DeviceView& dv, const SeqOrder& order, int layer, const PrefillGrid& grid, int place, int head,
-                                              bool full, int& b, int& h, int& tokens) {
-  seq_in_order(dv, order, place, b, tokens);
+// A table entry that no workgroup of the launch writes, the same in all lanes: a scalar load (behind an asm statement the compiler
+// takes an ordinary pointer's memory for possibly changed and loads lane by lane).
+template <typename T> __device__ __forceinline__ T table_entry(const T* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
+
+// Number in its class -> KV head.  first8: the class's first word of grid.head.
+__device__ __forceinline__ int head_of_class(const DeviceView& dv, int layer, const PrefillGrid& grid, uint64_t first8, int head, bool full) {
   if (grid.heads_given) {
-    h = grid.head[full ? 0 : 1][head];
-    return;
+    if (head >= 8) first8 = grid.head[full ? 0 : 1][head >> 3];
+    return (int)(first8 >> ((head & 7) * 8)) & 255;
   }
-  h = 0;
   for (int i = 0, k = head; i < dv.n_kv_heads; ++i) {
     if ((dv.full_mask[layer * dv.n_kv_heads + i] != 0) == full) {
-      if (k == 0) { h = i; break; }
+      if (k == 0) return i;
       --k;
     }
   }
+  return 0;
 }
 
 // Split prefill (few long workgroups: one or two sequences, few full heads): the unmasked tiles of a
@@ -310,14 +309,25 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // order: the long ones go first - the pairs of full heads before those of compressed heads, long
   // sequences before short ones, and within a pair the later query blocks (more keys under the
   // causal mask) before the earlier ones - so that the short ones fill the end.
-  int index, place, head, from_end, share = 0;
+  // Bound, for a short chunk: latency.  What it takes to find the workgroup's own is asked for in as few turns as there are dependent
+  // loads: these arguments, the sequence, its tables.  (Each waited for where it was first looked at, about a dozen in a
+  // row: two prompts of 200 and 300 tokens 25.1 us, now 24.6; two of 210 and 514 27.0, now 26.4; 32 query, 8 KV heads and 12, 4.)
+  // The empty statements use the values, so that their loads are issued side by side here.
+  PrefillItems items = grid.items;
+  uint64_t head8[2] = {grid.head[0][0], grid.head[1][0]};
+  const FirstSixteen lead = *reinterpret_cast<const FirstSixteen*>(grid.first);
+  asm volatile("" : "+s"(items.gx), "+s"(items.heads[0]), "+s"(items.heads[1]), "+s"(items.inv_heads[0]), "+s"(items.inv_heads[1]),
+                    "+s"(items.inv_seq[0]), "+s"(items.inv_seq[1]), "+s"(head8[0]), "+s"(head8[1])
+                  : "s"(lead), "s"(dv.batch), "s"(dv.n_kv_heads), "s"(dv.store_off), "s"(len_in), "s"(order.in_args), "s"(grid.n_split),
+                    "s"(stride_tokens), "s"(grid.heads_given), "s"(grid.inv_group));
+  int index, place, head, from_end, blocks, b, t, share = 0;      // t: chunk length of the sequence
   bool full;
-  const int Z = grid.n_split, gx = grid.items.gx;
+  const int Z = grid.n_split;
   if (Z == 1) {
-    full = prefill_item(blockIdx.x, grid.items, index);
+    full = prefill_item(blockIdx.x, items, index);
   } else {                                 // (plain order, the first share of everything, then the others of the heavy items)
     index = blockIdx.x;
-    const int heavy = grid.n_seqs * grid.n_heads[0] * gx, all = heavy + grid.n_seqs * grid.n_heads[1] * gx;
+    const int heavy = items.n_seqs * items.heads[0] * items.gx, all = heavy + items.n_seqs * items.heads[1] * items.gx;
     if (index >= all) {
       share = (index - all) / heavy;
       index -= all + share++ * heavy;
@@ -325,11 +335,31 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     full = index < heavy;
     if (!full) index -= heavy;
   }
-  prefill_place(index, grid.n_heads[full ? 0 : 1], gx, grid.ragged != 0, grid.first, grid.n_seqs, place, head, from_end);
-  int b, h, t;                             // t: chunk length of the sequence
-  pair_of_place(dv, order, layer, grid, place, head, full, b, h, t);
+  if (items.ragged) {                      // (the order is in the arguments)
+    const int heads = full ? items.heads[0] : items.heads[1];
+    place = place_of_block(quotient(index, heads, full ? items.inv_heads[0] : items.inv_heads[1]), items.n_seqs, grid.first, lead);
+    int at = grid.first[place], next = grid.first[place + 1];
+    b = order.seq[place];
+    t = order.tok[place];
+    asm volatile("" : "+s"(at), "+s"(next), "+s"(b), "+s"(t));
+    blocks = next - at;
+    ragged_place(index, heads, at, blocks, head, from_end);
+  } else {
+    even_place(index, full, items, place, head, from_end);
+    blocks = items.gx;
+    seq_in_order(dv, order, place, b, t);
+  }
+  const int h = __builtin_amdgcn_readfirstlane(head_of_class(dv, layer, grid, full ? head8[0] : head8[1], head, full));
   const int pair = b * dv.n_kv_heads + h;
-  const int block_x = (grid.ragged ? grid.first[place + 1] - grid.first[place] : gx) - 1 - from_end;
+  const int block_x = blocks - 1 - from_end;
+  const int layer_head = layer * dv.n_kv_heads + h;
+  int n_old = table_entry(len_in + b);     // positions cached before the chunk
+  int64_t store_at = table_entry(dv.store_off + ((int64_t)layer * dv.batch + b) * dv.n_kv_heads + h);
+  int64_t slots_at = table_entry(dv.slotpos_off + layer_head);
+  int32_t v_wide = table_entry(dv.v_wide + layer);
+  float gate = MIX ? table_entry(dv.gate + layer_head) : 1.f;
+  asm volatile("" : "+s"(n_old), "+s"(store_at), "+s"(slots_at), "+s"(v_wide));
+  if (MIX) asm volatile("" : "+s"(gate));
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   int tid = threadIdx.x, lane = tid & 63;
   int hd = lane & 15;           // score layout: column; operand layouts: row / column
@@ -340,15 +370,13 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   const int inv_g = grid.inv_group;
   auto div_g = [&](int col) { return (col * inv_g) >> 16; };
   const int wg_positions = div_g(kPrefillWaves * kWaveCols);   // chunk positions per workgroup
-  const int n_old = len_in[b];             // positions cached before the chunk
   const int c_wg = block_x * wg_positions; // the workgroup's first chunk index
   if (c_wg >= t) return;
   const int c_last = (c_wg + wg_positions < t ? c_wg + wg_positions : t) - 1;   // its last one
   // share z of Z of a divided workgroup; the last share, the longest one (it also takes the masked tiles), is handed out first
   const int z = Z - 1 - share;
   const bool split = full && Z > 1;
-  const bool wide = dv.v_wide[layer] != 0;   // (asked for early: read in front of the hot loop)
-  const float gate = (MIX && full) ? dv.gate[layer * dv.n_kv_heads + h] : 1.f;
+  const bool wide = v_wide != 0;
   const bool mix = MIX && full && gate < 1.f;            // this head blends causal and local attention
 
   // This wavefront's columns: kWaveCols of the workgroup's flattened (position, head) pairs.
@@ -382,7 +410,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   }
 
   TileMap<PAGED> store;
-  store.base = dv.kv_base + dv.store_off[((int64_t)layer * dv.batch + b) * dv.n_kv_heads + h];
+  store.base = dv.kv_base + store_at;
   store.paged = PAGED && full;
   if (PAGED) {
     store.row = dv.block_table + (int64_t)b * dv.table_stride;
@@ -393,7 +421,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   }
   const char* stage = staging + (int64_t)pair * staging_tiles * kTileBytes;
   const int32_t* slot_pos = nullptr;
-  if (!full) slot_pos = dv.slot_pos + dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window;
+  if (!full) slot_pos = dv.slot_pos + slots_at + (int64_t)b * dv.window;
 
   // store slots that hold data: of a full head the chunk's too, of a compressed one what was cached before it
   const int n_st = full ? n_old + t : (n_old < dv.window ? n_old : dv.window);
@@ -945,8 +973,10 @@ template <bool MIX>
 __global__ __launch_bounds__(kSplitCols) void prefill_merge_kernel(DeviceView dv, int layer, SeqOrder order, const float* __restrict__ split_out,
                                                                    int Z, uint16_t* __restrict__ out, int stride_tokens,
                                                                    PrefillGrid grid) {
-  int b, h, t;
-  pair_of_place(dv, order, layer, grid, blockIdx.y / grid.n_heads[0], blockIdx.y % grid.n_heads[0], true, b, h, t);
+  const int place = quotient(blockIdx.y, grid.items.heads[0], grid.items.inv_heads[0]);
+  int b, t;
+  seq_in_order(dv, order, place, b, t);
+  const int h = head_of_class(dv, layer, grid, grid.head[0][0], blockIdx.y - place * grid.items.heads[0], true);
   const int G = dv.group;
   const int wg_positions = (MIX ? kSplitCols / 2 : kSplitCols) / G;
   const int c_wg = (gridDim.x - 1 - blockIdx.x) * wg_positions;
@@ -1010,25 +1040,24 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   if (n_split < 1 || !split_out || (mix && !narrow)) n_split = 1;
   const int per_block = kPrefillWaves * 16 * (narrow ? 1 : 2) / dv.group;     // chunk positions per workgroup
   const int gx = (max_tokens + per_block - 1) / per_block;
-  PrefillGrid grid;
-  grid.n_heads[0] = grid.n_heads[1] = 0;
+  PrefillGrid grid = {};
+  int32_t n_heads[2] = {0, 0};
   grid.heads_given = dv.n_kv_heads <= kPrefillArgHeads;
   for (int i = 0; i < dv.n_kv_heads; ++i) {
     const int cls = mask_row[i] ? 0 : 1;
-    if (grid.heads_given) grid.head[cls][grid.n_heads[cls]] = i;
-    ++grid.n_heads[cls];
+    if (grid.heads_given) grid.head[cls][n_heads[cls] >> 3] |= (uint64_t)i << ((n_heads[cls] & 7) * 8);
+    ++n_heads[cls];
   }
-  grid.n_seqs = n_seqs;
   grid.n_split = n_split;
   grid.inv_group = (65536 + dv.group - 1) / dv.group;
   grid.inv_scale = scale_log2 > 0.f ? 1.f / scale_log2 : 1.f;
-  const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, grid.n_heads, dealt_rows,
-                                           &grid.items, &grid.ragged, grid.first);
+  const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, n_heads, dealt_rows,
+                                           &grid.items, grid.first);
   const int tiles = (max_tokens + kTile - 2) / kTile + 1;      // (a full head's chunk may start anywhere in a tile)
   hipLaunchKernelGGL(place_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, len_in, len_out,
                      (const uint16_t*)k, (const uint16_t*)v, stride_tokens, staging, staging_tiles);
   if (hipError_t e = hipGetLastError()) return e;
-  const int64_t heavy_rows = (int64_t)n_seqs * grid.n_heads[0];
+  const int64_t heavy_rows = (int64_t)n_seqs * n_heads[0];
   const dim3 blocks((uint32_t)(items + (n_split - 1) * heavy_rows * gx)), block(kPrefillBlock);
 #define RLKV_LAUNCH(PG, NGR, MX)                                                                                          \
   hipExtLaunchKernelGGL((prefill_mfma_kernel<PG, NGR, MX>), blocks, block, 0, stream, ev_start, ev_stop, 0, dv, layer, order, len_in, \

@@ -129,6 +129,9 @@ __device__ inline void seq_in_order(const DeviceView& dv, const SeqOrder& order,
   if (order.in_args) {
     b = order.seq[i];
     tokens = order.tok[i];
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(b), "+s"(tokens));          // (both asked for here: not through a pointer that is this one or the other)
+#endif
   } else {
     b = dv.append_cnt[dv.batch + i];
     tokens = dv.append_cnt[b];
@@ -247,10 +250,10 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
                                hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 // The items of an undivided launch (prefill_deal.h) with `per_block` chunk positions to a block: `tokens` [n_seqs] the chunk lengths
 // in the grid's order, or null (not at hand: every sequence has gx blocks); dealt_rows: heavy rows that may go one row
-// per XCD (rlkv_plan_prefill_rows).  Fills items, ragged and, where that is 1, first [n_seqs + 1]; returns the number of items.
+// per XCD (rlkv_plan_prefill_rows).  Fills items and, where items->ragged is 1, first [kFirstEntries]; returns the number of items.
 struct PrefillItems;
 int64_t plan_prefill_items(int per_block, int n_seqs, const int32_t* tokens, int gx, const int32_t (&n_heads)[2], int dealt_rows,
-                           PrefillItems* items, int32_t* ragged, int32_t* first);
+                           PrefillItems* items, int32_t* first);
 
 // Fewest 32-key tiles a share of a divided prefill workgroup has, where cfg.prefill_min_share_tiles does not say: in the
 // form with two column groups per wavefront, in the single-group form, and in that form where heads blend.

@@ -9,6 +9,8 @@
 // per-workgroup timestamps.  A pair that continues from the previous workgroup pays no start.
 // The plan is the in-order greedy deal at the smallest capacity that needs no more workgroups than
 // the grid has; greedy is optimal for a contiguous partition once the capacity is fixed.
+#include <string.h>
+
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -241,24 +243,32 @@ int plan_narrow_split(int n_compute_units, int group, int n_full_heads, int batc
 }
 
 int64_t plan_prefill_items(int per_block, int n_seqs, const int32_t* tokens, int gx, const int32_t (&n_heads)[2], int dealt_rows,
-                           PrefillItems* items, int32_t* ragged, int32_t* first) {
+                           PrefillItems* items, int32_t* first) {
   int64_t blocks = (int64_t)n_seqs * gx;
   int whole = n_seqs;                                // leading sequences with gx blocks
-  *ragged = 0;
+  items->ragged = 0;
   if (tokens) {
     whole = 0;
     while (whole < n_seqs && (tokens[whole] + per_block - 1) / per_block == gx) ++whole;
     if (whole < n_seqs) {
-      *ragged = 1;
+      items->ragged = 1;
       blocks = 0;
       for (int i = 0; i < n_seqs; ++i) {
         first[i] = (int32_t)blocks;
         blocks += (tokens[i] + per_block - 1) / per_block;
       }
       first[n_seqs] = (int32_t)blocks;
+      std::fill(first + n_seqs + 1, first + kFirstEntries, INT32_MAX);
     }
   }
   items->gx = gx;
+  items->n_seqs = n_seqs;
+  items->inv_gx = quotient_inverse(gx);
+  for (int c = 0; c < 2; ++c) {
+    items->heads[c] = n_heads[c];
+    items->inv_heads[c] = quotient_inverse(n_heads[c]);
+    items->inv_seq[c] = quotient_inverse(n_heads[c] * gx);
+  }
   items->dealt[0] = std::min(dealt_rows, whole * n_heads[0]) / 8 * 8;
   items->dealt[1] = whole * n_heads[1] / 8 * 8;
   items->rest = (int32_t)(blocks * n_heads[0] - (int64_t)items->dealt[0] * gx);
@@ -301,7 +311,12 @@ extern "C" int32_t rlkv_plan_prefill_block(int32_t linear_index, int32_t grid_x,
   // rows of grid_x blocks each, the heavy ones first
   const int heavy = heavy_rows < grid_y ? std::max(heavy_rows, 0) : grid_y;
   const int dealt = std::min(std::max(dealt_rows, 0), heavy) / 8 * 8;
-  const rlkv::PrefillItems items{grid_x, {dealt, (grid_y - heavy) / 8 * 8}, (heavy - dealt) * grid_x};
+  rlkv::PrefillItems items = {};
+  items.gx = grid_x;
+  items.dealt[0] = dealt;
+  items.dealt[1] = (grid_y - heavy) / 8 * 8;
+  items.rest = (heavy - dealt) * grid_x;
+  items.inv_gx = rlkv::quotient_inverse(grid_x);
   int index = 0;
   if (!rlkv::prefill_item(linear_index, items, index)) index += heavy * grid_x;
   *block_x = index % grid_x;
@@ -321,16 +336,25 @@ extern "C" int32_t rlkv_plan_prefill_item(int32_t linear_index, int32_t per_bloc
   }
   const int32_t n_heads[2] = {n_full_heads, n_compressed_heads};
   rlkv::PrefillItems items;
-  int32_t ragged = 0, first[rlkv::kArgSeqs + 1];
+  int32_t first[rlkv::kFirstEntries];
   const int gx = (longest + per_block - 1) / per_block;
-  if (linear_index >= rlkv::plan_prefill_items(per_block, n_seqs, n_tokens, gx, n_heads, dealt_rows, &items, &ragged, first)) return 1;
-  int index = 0, place = 0, head = 0, block = 0;
+  if (linear_index >= rlkv::plan_prefill_items(per_block, n_seqs, n_tokens, gx, n_heads, dealt_rows, &items, first)) return 1;
+  int index = 0, place = 0, head = 0, block = 0, blocks = gx;
   const bool full = rlkv::prefill_item(linear_index, items, index);
-  rlkv::prefill_place(index, n_heads[full ? 0 : 1], gx, ragged != 0, first, n_seqs, place, head, block);
+  if (items.ragged) {
+    const int c = full ? 0 : 1;
+    rlkv::FirstSixteen lead;
+    memcpy(&lead, first, sizeof(lead));
+    place = rlkv::place_of_block(rlkv::quotient(index, items.heads[c], items.inv_heads[c]), n_seqs, first, lead);
+    blocks = first[place + 1] - first[place];
+    rlkv::ragged_place(index, items.heads[c], first[place], blocks, head, block);
+  } else {
+    rlkv::even_place(index, full, items, place, head, block);
+  }
   item[0] = full;
   item[1] = place;
   item[2] = head;
-  item[3] = (ragged ? first[place + 1] - first[place] : gx) - 1 - block;
+  item[3] = blocks - 1 - block;
   return 0;
 }
 

@@ -55,6 +55,36 @@ def test_every_block_with_queries_is_one_workgroups(seed):
         assert engines.max() - engines.min() <= 2
 
 
+@pytest.mark.parametrize("seed", range(4))
+def test_blocks_of_large_grids(seed):
+    """Quotients by the sizes of a launch are taken as products with their inverses: exact up to the last index of the largest
+    grids, and around every multiple."""
+    rng = np.random.default_rng(seed)
+    for _ in range(200):
+        gx = int(rng.choice([1, 2, 3, 7, 13, 455, 4096, 65535, 65536, int(rng.integers(1, 65537))]))
+        gy = int(rng.integers(1, min(65535, (2 ** 31 - 1) // gx) + 1))
+        heavy = int(rng.integers(0, gy + 1))
+        dealt = 8 * int(rng.integers(0, heavy // 8 + 1))
+        rows_h, rows_l, n_b = dealt // 8, (gy - heavy) // 8, (heavy - dealt) * gx
+        last = gx * gy - 1
+        near = int(rng.integers(0, gy)) * gx
+        for lin in {0, last, max(0, last - 7), *(min(last, max(0, near * 8 + d)) for d in (-1, 0, 7, 8)), int(rng.integers(0, last + 1))}:
+            k, i = lin % 8, lin // 8
+            c_a, c_b, c_c = rows_h * gx, (n_b - k + 7) // 8, rows_l * gx
+            if i < c_a:
+                want = (i % gx, i // gx * 8 + k)
+            elif i < c_a + c_b:
+                w = (i - c_a) * 8 + k
+                want = (w % gx, dealt + w // gx)
+            elif i < c_a + c_b + c_c:
+                j = i - c_a - c_b
+                want = (j % gx, heavy + j // gx * 8 + k)
+            else:
+                w = (i - c_a - c_c) * 8 + k - n_b
+                want = (w % gx, heavy + 8 * rows_l + w // gx)
+            assert rl.rlkv_plan_prefill_block(lin, gx, gy, dealt, heavy) == want, (lin, gx, gy, dealt, heavy)
+
+
 def test_rejects_bad_arguments():
     for bad in [(0, 0, 1, 0, [5], 0), (-1, 36, 1, 0, [5], 0), (0, 36, -1, 0, [5], 0), (0, 36, 1, 0, [0], 0), (0, 36, 1, 0, [5], -8),
                 (0, 36, 1, 0, [5] * 129, 0)]:
