@@ -30,6 +30,8 @@
 namespace rlkv {
 namespace {
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
 // Tiles re-read by many query blocks: ordinary (cached) loads.
 __device__ __forceinline__ void load_k_cached(TileRegs& r, const char* tile_base, int lane) {
   const char* kb = tile_base + lane * 16;
@@ -100,15 +102,22 @@ __device__ __forceinline__ void half_weights(const float (&p)[8], Frag& ph) {
 // the normaliser): it keeps fp16 weights as small as 2^-30 of the reference maximum representable.
 constexpr float kWeightShift = 6.f;
 
+// What the wavefront's lanes have written to LDS is there for its other lanes (its LDS instructions run in order: the compiler only
+// has to keep that order).
+__device__ __forceinline__ void wave_exchange() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Online-softmax state of one 16-column group.  In the general loop the weights go to the matrix
 // cores as in the decode kernel, a bf16 head plus a bf16 remainder (~16 mantissa bits; a single
 // bf16 weight measurably misses the 1e-2 bar).  This kernel is bound by its vector instruction count, so the
 // normaliser is accumulated by the matrix cores too, from the same two parts against a tile of
 // ones: it needs no cross-lane sums.  V is the first operand of the products and the weights the second, so that a
 // lane's accumulators, its scores, its normaliser and its reference all belong to its own column: rescaling takes no
-// lane shuffles, and a lane's four outputs of a product lie side by side (8-byte stores; with the operands the other way
-// round an output row was written in 2-byte stores, four times as many: one prompt of 32 500 tokens 4404 -> 4375 us, 16 x 16 384
-// 16.23 -> 16.18 ms, blending 8 x 1000 .. 4000 679 -> 678 us)
+// lane shuffles, and a lane's four outputs of a product lie side by side.  (With the operands the other way round one prompt
+// of 32 500 tokens took 4404 us, against 4375, 16 x 16 384 16.23 ms, against 16.18.)
 struct GroupState {
   float m;          // reference maximum of column lane%16 (log2 domain; same in all four k-groups)
   float ref;        // what the exponent subtracts: m (0 while m is -inf) minus kWeightShift
@@ -305,6 +314,10 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
                                                                           // one slot wait for the loads into the other)
   __shared__ uint4 sm_v[2][kTileBytes / 32];
   __shared__ floatx4 sm_local[MIX ? kPrefillWaves : 1][MIX ? NG * 8 : 1][64];
+  // Where a wavefront turns its outputs into rows: 4 KiB for each column group in its part of the local results, or, group by group,
+  // in its eighth of the K halves (kKeySlots == 4).
+  constexpr bool kOutInLocal = kKeySlots == 2;
+  constexpr int kOutChunks = kOutInLocal ? 512 : 0;           // 16-byte units from one group's place to the next
   // Workgroups are handed out in the order of their index, and each XCD takes the items dealt to it (prefill_item) in
   // order: the long ones go first - the pairs of full heads before those of compressed heads, long
   // sequences before short ones, and within a pair the later query blocks (more keys under the
@@ -322,7 +335,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
                     "s"(stride_tokens), "s"(grid.heads_given), "s"(grid.inv_group));
   int index, place, head, from_end, blocks, b, t, share = 0;      // t: chunk length of the sequence
   bool full;
-  const int Z = grid.n_split;
+  const int Z = kKeySlots == 2 ? 1 : grid.n_split;               // (the form of two column groups that blends is not divided)
   if (Z == 1) {
     full = prefill_item(blockIdx.x, items, index);
   } else {                                 // (plain order, the first share of everything, then the others of the heavy items)
@@ -784,6 +797,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     if constexpr (LOCAL_PASS) hot_loop(std::false_type{});
     else if (!wide) hot_loop(std::true_type{});
     else hot_loop(std::false_type{});
+    if (!kOutInLocal && !LOCAL_PASS) __syncthreads();          // the outputs take the place of the K halves
   }
   if (!busy) return;
 
@@ -919,6 +933,13 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   walk(std::false_type{});
   if (!busy) return;            // no barrier lies ahead
 
+  // Accumulators and outputs leave through LDS: a lane holds four values in a row of its own column, and 16 neighbouring lanes
+  // belong to 16 rows, so they are turned into whole rows first, 16 lanes each.  (Stored from where they are, every
+  // instruction is 64 requests of 8 or 16 bytes: the launch over 16 chunks of 300 tokens, 32 query and 8 KV heads, 49.1 us, now
+  // 44.9; 14 of 142 .. 289 35.2, now 31.2; a prompt of 3074 in chunks of 512, divided, 241 us in all, now 236; blending, 8 x 1000 ..
+  // 4000, 666, now 648.)  16-byte chunk c of row r lies at chunk c ^ r, which spreads both sides over all banks.  (Values keep their
+  // type on the way: cast to integers here, the accumulators were copied between registers in every step of the hot loop, 8 %.)
+  u32x4* rows = kOutInLocal ? reinterpret_cast<u32x4*>(sm_local[MIX ? wave : 0]) : reinterpret_cast<u32x4*>(&sm_k[0][0]) + wave * 256;
   if (split) {
     float* slot = split_out + ((int64_t)index * Z + z) * kSplitSlotFloats;
 #pragma unroll
@@ -929,7 +950,17 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
         slot[kSplitCols * (kHeadDim + 1) + col] = st[k].l[0];
       }
 #pragma unroll
-      for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(slot + col * kHeadDim + j * 16 + kb * 4) = st[k].o[j];
+      for (int half = 0; half < 2; ++half) {             // 64 of a row's 128 values at a time
+#pragma unroll
+        for (int j = 0; j < 4; ++j) reinterpret_cast<floatx4*>(rows)[hd * 16 + ((j * 4 + kb) ^ hd)] = st[k].o[half * 4 + j];
+        wave_exchange();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int row = i * 4 + kb;
+          *reinterpret_cast<u32x4*>(slot + (col0 + 16 * k + row) * kHeadDim + half * 64 + hd * 4) = rows[row * 16 + (hd ^ row)];
+        }
+        wave_exchange();
+      }
       if (MIX && mix && z == Z - 1) {          // the local results, as columns 128 and up (one column group)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -939,27 +970,37 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
     return;
   }
   // out[b][head][c][d] = O / l (blended with the local result for a gated head)
-  const bool out_aligned = (reinterpret_cast<uintptr_t>(out) & 7) == 0;      // (a caller's may start at any element)
+  const uintptr_t out_bits = reinterpret_cast<uintptr_t>(out);               // (a caller's may start at any element)
 #pragma unroll
   for (int cg = 0; cg < NG; ++cg) {
-    const int col = col0 + 16 * cg + hd;
-    const int cl = div_g(col), hh = col - cl * G;
-    uint16_t* dst = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + kb * 4;
-    const bool on = c_wg + cl <= c_last;
+    u32x4* mine = rows + cg * kOutChunks;
     const float inv = 1.f / st[cg].l[0];
+    u32x2 four[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       floatx4 res = st[cg].o[j] * inv;
       if (MIX && mix) res = gate * res + (1.f - gate) * sm_local[MIX ? wave : 0][MIX ? cg * 8 + j : 0][lane];
-      const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
-      if (!on) continue;
-      if (out_aligned) {
-        *reinterpret_cast<uint2*>(dst + j * 16) = four;
+      four[j] = u32x2{bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3])};
+    }
+    wave_exchange();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) reinterpret_cast<u32x2*>(mine + hd * 16 + ((j * 2 + (kb >> 1)) ^ hd))[kb & 1] = four[j];
+    wave_exchange();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = i * 4 + kb, col = col0 + 16 * cg + row;
+      const int cl = div_g(col), hh = col - cl * G;
+      const u32x4 w = mine[row * 16 + (hd ^ row)];
+      uint16_t* dst = out + (((int64_t)b * dv.n_q_heads + h * G + hh) * stride_tokens + c_wg + cl) * kHeadDim + hd * 8;
+      if (c_wg + cl > c_last) continue;
+      if ((out_bits & 15) == 0) {
+        *reinterpret_cast<u32x4*>(dst) = w;
+      } else if ((out_bits & 7) == 0) {
+        reinterpret_cast<u32x2*>(dst)[0] = u32x2{w[0], w[1]};
+        reinterpret_cast<u32x2*>(dst)[1] = u32x2{w[2], w[3]};
       } else {
-        dst[j * 16] = (uint16_t)four.x;
-        dst[j * 16 + 1] = (uint16_t)(four.x >> 16);
-        dst[j * 16 + 2] = (uint16_t)four.y;
-        dst[j * 16 + 3] = (uint16_t)(four.y >> 16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dst[e] = (uint16_t)(w[e >> 1] >> (e & 1) * 16);
       }
     }
   }
