@@ -124,14 +124,16 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
     if constexpr (KERNEL == RLKV_KERNEL_MFMA) {
       // which appended row ends in each slot: once per slot, then the rows go through LDS into the tile
       __shared__ TileRowsLds lds;
+      __shared__ int32_t src[kTile];
       if (threadIdx.x < kTile) {
         const int slot = tile * kTile + threadIdx.x;
         const int p = source_position(full, slot, len_old, len_new, S, R);
-        lds.src[threadIdx.x] = p < 0 ? -1 : p - len_old;
+        src[threadIdx.x] = p < 0 ? -1 : p - len_old;
         if (slot_pos && p >= 0) slot_pos[slot] = p;
       }
       __syncthreads();
-      const bool wide = rows_to_tile<false, true>(lds, k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
+      const bool wide = rows_to_tile<false, true>(lds, [&](int slot) { return src[slot]; }, k_new + src_head * kHeadDim,
+                                                  v_new + src_head * kHeadDim, tile_base);
       if (wide) dv.v_wide[layer] = 1;        // the prefill kernel takes this layer's V as bf16 from now on
     } else {
       // K and V rows: one 16-byte chunk per unit

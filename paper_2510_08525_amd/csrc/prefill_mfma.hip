@@ -183,6 +183,12 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
   }
 }
 
+// A table entry that no workgroup of the launch writes, the same in all lanes: a scalar load (behind an asm statement the compiler
+// takes an ordinary pointer's memory for possibly changed and loads lane by lane).
+template <typename T> __device__ __forceinline__ T table_entry(const T* p) {
+  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // Brings the chunk's K/V rows (row-major [batch][n_kv_heads][stride][128]) into tiles of the MFMA layout, and the lengths
 // forward (len_in -> len_out).  A full head's rows go where they stay, into its store: every query sees what it needs there, and
 // nothing is evicted.  A compressed head's go to the staging buffer: staging tile t of a pair holds chunk rows 32 t .. 32 t + 31;
@@ -194,35 +200,37 @@ __device__ __forceinline__ void group_update(const TileRegs& t, const float (&sc
 __global__ __launch_bounds__(kBlock) void place_chunk_kernel(DeviceView dv, int layer, SeqCounts seqs, const int32_t* __restrict__ len_in,
                                                              int32_t* __restrict__ len_out, const uint16_t* __restrict__ k_new,
                                                              const uint16_t* __restrict__ v_new, int stride_tokens,
-                                                             char* __restrict__ staging, int staging_tiles) {
-  const int pair = blockIdx.y;
-  const int b = pair / dv.n_kv_heads, h = pair % dv.n_kv_heads;
-  const int t = tokens_of_seq(dv, seqs, b);
-  const int n_old = len_in[b];
+                                                             char* __restrict__ staging, int staging_tiles,
+                                                             uint64_t full_heads /* one bit a head; layers of up to kPrefillArgHeads */) {
+  // (what has to be known before the first row is asked for, in two turns: the arguments, the tables)
+  asm volatile("" :: "s"(dv.n_kv_heads), "s"(dv.n_pairs), "s"(dv.append_cnt), "s"(dv.store_off), "s"(dv.kv_base), "s"(dv.page_shift), "s"(layer),
+                     "s"(seqs.in_args), "s"(len_in), "s"(len_out), "s"(k_new), "s"(v_new), "s"(stride_tokens), "s"(staging),
+                     "s"(staging_tiles), "s"(full_heads));
+  const int h = blockIdx.y, b = blockIdx.z, pair = b * dv.n_kv_heads + h;
+  int t = seqs.in_args ? seqs.tok[b] : table_entry(dv.append_cnt + b);
+  int n_old = table_entry(len_in + b);
+  int64_t store_at = table_entry(dv.store_off + (int64_t)layer * dv.n_pairs + pair);
+  asm volatile("" : "+s"(t), "+s"(n_old), "+s"(store_at));
   if (blockIdx.x == 0 && h == 0 && threadIdx.x == 0) len_out[b] = n_old + t;
   if (t == 0) return;
-  const bool full = dv.full_mask[layer * dv.n_kv_heads + h] != 0;
+  const bool full = dv.n_kv_heads <= kPrefillArgHeads ? (full_heads >> h & 1) != 0 : dv.full_mask[layer * dv.n_kv_heads + h] != 0;
   const int tile = (full ? n_old / kTile : 0) + blockIdx.x;
   const int first = tile * kTile - (full ? n_old : 0);         // chunk row of slot 0 (a full head's first tile: may lie before the chunk)
   if (first >= t) return;
   const int64_t src_head = (int64_t)pair * stride_tokens * kHeadDim;
   __shared__ TileRowsLds lds;
-  if (threadIdx.x < kTile) {
-    const int row = first + threadIdx.x;
-    lds.src[threadIdx.x] = row >= 0 && row < t ? row : -1;
-  }
-  __syncthreads();
+  auto row_of = [&](int slot) { return first + slot >= 0 && first + slot < t ? first + slot : -1; };
   bool wide;
   if (full) {
-    char* tile_base = dv.kv_base + dv.store_off[((int64_t)layer * dv.batch + b) * dv.n_kv_heads + h];
+    char* tile_base = dv.kv_base + store_at;
     if (dv.page_shift >= 0)
       tile_base += dv.block_table[(int64_t)b * dv.table_stride + (tile >> dv.page_shift)] * dv.page_bytes +
                    (int64_t)(tile & dv.page_mask) * kTileBytes;
     else
       tile_base += (int64_t)tile * kTileBytes;
-    wide = rows_to_tile<false, false>(lds, k_new + src_head, v_new + src_head, tile_base);
+    wide = rows_to_tile<false, false>(lds, row_of, k_new + src_head, v_new + src_head, tile_base);
   } else {
-    wide = rows_to_tile<true, false>(lds, k_new + src_head, v_new + src_head, staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes);
+    wide = rows_to_tile<true, false>(lds, row_of, k_new + src_head, v_new + src_head, staging + ((int64_t)pair * staging_tiles + tile) * kTileBytes);
   }
   if (wide) dv.v_wide[layer] = 1;          // seen by the attention kernel that follows on the stream
 }
@@ -239,12 +247,6 @@ struct PrefillGrid {
   uint64_t head[2][kPrefillArgHeads / 8];  // [0]: the full heads in ascending order, [1]: the compressed ones, 8 bits each
   int32_t first[kFirstEntries];
 };
-// A table entry that no workgroup of the launch writes, the same in all lanes: a scalar load (behind an asm statement the compiler
-// takes an ordinary pointer's memory for possibly changed and loads lane by lane).
-template <typename T> __device__ __forceinline__ T table_entry(const T* p) {
-  return *reinterpret_cast<const __attribute__((address_space(4))) T*>(reinterpret_cast<uintptr_t>(p));
-}
-
 // Number in its class -> KV head.  first8: the class's first word of grid.head.
 __device__ __forceinline__ int head_of_class(const DeviceView& dv, int layer, const PrefillGrid& grid, uint64_t first8, int head, bool full) {
   if (grid.heads_given) {
@@ -1084,8 +1086,10 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   PrefillGrid grid = {};
   int32_t n_heads[2] = {0, 0};
   grid.heads_given = dv.n_kv_heads <= kPrefillArgHeads;
+  uint64_t full_heads = 0;
   for (int i = 0; i < dv.n_kv_heads; ++i) {
     const int cls = mask_row[i] ? 0 : 1;
+    if (grid.heads_given) full_heads |= (uint64_t)(cls == 0) << i;
     if (grid.heads_given) grid.head[cls][n_heads[cls] >> 3] |= (uint64_t)i << ((n_heads[cls] & 7) * 8);
     ++n_heads[cls];
   }
@@ -1095,8 +1099,8 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
   const int64_t items = plan_prefill_items(per_block, n_seqs, order.in_args && n_split == 1 ? order.tok : nullptr, gx, n_heads, dealt_rows,
                                            &grid.items, grid.first);
   const int tiles = (max_tokens + kTile - 2) / kTile + 1;      // (a full head's chunk may start anywhere in a tile)
-  hipLaunchKernelGGL(place_chunk_kernel, dim3(tiles, dv.n_pairs), dim3(kBlock), 0, stream, dv, layer, seqs, len_in, len_out,
-                     (const uint16_t*)k, (const uint16_t*)v, stride_tokens, staging, staging_tiles);
+  hipLaunchKernelGGL(place_chunk_kernel, dim3(tiles, dv.n_kv_heads, dv.batch), dim3(kBlock), 0, stream, dv, layer, seqs, len_in, len_out,
+                     (const uint16_t*)k, (const uint16_t*)v, stride_tokens, staging, staging_tiles, full_heads);
   if (hipError_t e = hipGetLastError()) return e;
   const int64_t heavy_rows = (int64_t)n_seqs * n_heads[0];
   const dim3 blocks((uint32_t)(items + (n_split - 1) * heavy_rows * gx)), block(kPrefillBlock);

@@ -18,7 +18,6 @@ constexpr int kTileRowStride = 272;      // bytes of a V row in LDS: 16 more tha
 struct TileRowsLds {
   uint4 k[kTile * 16];                   // the tile's K image; the 16 units of a chunk rotated by the chunk (bank conflicts)
   alignas(16) char v[kTile * kTileRowStride];
-  int32_t src[kTile];                    // source row of every slot, -1 = the slot is not written (filled by the caller)
 };
 
 __device__ __forceinline__ bool any_beyond_fp16(uint32_t two) { return bf16_beyond_fp16(two) || bf16_beyond_fp16(two >> 16); }
@@ -37,11 +36,11 @@ template <bool NT> __device__ __forceinline__ void tile_store(char* p, const uin
   __builtin_nontemporal_store(v, reinterpret_cast<row_x4*>(p));
 }
 
-// lds.src is filled and visible to the workgroup.  k_rows / v_rows: row 0 of the pair (row r at r * kHeadDim).  ZERO: slots
+// row_of(slot): the slot's source row, -1 = none.  k_rows / v_rows: row 0 of the pair (row r at r * kHeadDim).  ZERO: slots
 // without a source row are written as zeros; otherwise they keep what they hold.  Returns whether this thread moved a V
 // value beyond the fp16 range.
-template <bool ZERO, bool NT>
-__device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* __restrict__ k_rows,
+template <bool ZERO, bool NT, typename RowOf>
+__device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const RowOf& row_of, const uint16_t* __restrict__ k_rows,
                                              const uint16_t* __restrict__ v_rows, char* __restrict__ tile_base) {
   constexpr int kUnits = kTile * 16 / kBlock;            // 16-byte units of K (and of V) per thread
   const int tid = threadIdx.x;
@@ -49,7 +48,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
   uint4 kv[kUnits], vv[kUnits];
 #pragma unroll
   for (int i = 0; i < kUnits; ++i) {
-    const int u = tid + i * kBlock, row = lds.src[u >> 4], chunk = u & 15;
+    const int u = tid + i * kBlock, row = row_of(u >> 4), chunk = u & 15;
     kv[i] = vv[i] = make_uint4(0, 0, 0, 0);
     if (row >= 0) {
       kv[i] = row_load<NT>(k_rows + (int64_t)row * kHeadDim + chunk * 8);
@@ -74,7 +73,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
 #pragma unroll
   for (int i = 0; i < kUnits; ++i) {                     // K: unit u of the tile = [half][chunk][slot % 16]
     const int u = tid + i * kBlock, hf = u >> 8, chunk = (u >> 4) & 15, s16 = u & 15;
-    if (ZERO || lds.src[hf * 16 + s16] >= 0)
+    if (ZERO || row_of(hf * 16 + s16) >= 0)
       tile_store<NT>(tile_base + u * 16, lds.k[hf * 256 + chunk * 16 + ((s16 + chunk) & 15)]);
   }
 #pragma unroll
@@ -86,7 +85,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const uint16_t* _
     for (int e = 0; e < 8; ++e) {
       const int slot = (e >> 2) * 16 + kb * 4 + (e & 3);
       val[e] = *reinterpret_cast<const uint16_t*>(lds.v + slot * kTileRowStride + d * 2);
-      if (!ZERO) have |= lds.src[slot] >= 0 ? 1u << e : 0u;
+      if (!ZERO) have |= row_of(slot) >= 0 ? 1u << e : 0u;
     }
     char* dst = tile_base + kTileBytes / 2 + u * 16;
     if (ZERO || have == 0xffu) {
