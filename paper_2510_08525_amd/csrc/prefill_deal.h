@@ -54,22 +54,6 @@ __host__ __device__ inline bool prefill_item(int lin, const PrefillItems& p, int
   return heavy;
 }
 
-// Place of the sequence whose blocks hold block x: first[place] <= x < first[place + 1].  `first16`: first[0 .. 15], so that up to
-// 16 sequences take no further load, more of them one (a search by halves waited for a load at every step).
-typedef int32_t FirstSixteen __attribute__((ext_vector_type(16), aligned(4)));   // (one scalar load)
-__host__ __device__ inline int place_of_block(int x, int n_seqs, const int32_t* first, const FirstSixteen& first16) {
-  FirstSixteen lead = first16;
-  int place = 0;
-  if (n_seqs > 16) {
-#pragma unroll
-    for (int j = 16; j < kFirstEntries - 1; j += 16) place += first[j] <= x ? 16 : 0;
-    lead = *reinterpret_cast<const FirstSixteen*>(first + place);
-  }
-#pragma unroll
-  for (int j = 1; j < 16; ++j) place += lead[j] <= x ? 1 : 0;
-  return place;
-}
-
 // Item `index` of a class with `heads` heads a sequence: the sequence's place in the order, the head's number in its class and
 // the block counted from the row's end (later query blocks have more keys under the causal mask and go first).
 // Even launch: every sequence has gx blocks.
@@ -80,11 +64,22 @@ __host__ __device__ inline void even_place(int index, bool full, const PrefillIt
   head = quotient(r, p.gx, p.inv_gx);
   block = r - head * p.gx;
 }
-// Ragged launch, `at` = first[place], `blocks` those of the sequence.
+// Ragged launch: index / heads is a block of the sequence with first[place] <= it < first[place + 1]; `at` = first[place],
+// `blocks` those of the sequence.  The head is a quotient below 2^16: in fp32, taken a little low (the reciprocal is good to
+// 2^-22), it is the right one or one less.
 __host__ __device__ inline void ragged_place(int index, int heads, int at, int blocks, int& head, int& block) {
   const int r = index - at * heads;
-  head = (int)((uint32_t)r / (uint32_t)blocks);
+#ifdef __HIP_DEVICE_COMPILE__
+  const float inv = __builtin_amdgcn_rcpf((float)blocks);
+  head = __builtin_amdgcn_readfirstlane((int)((float)r * (inv * (1.f - 0x1p-20f))));
+#else
+  head = (int)((float)r * (1.f / (float)blocks * (1.f - 0x1p-20f)));
+#endif
   block = r - head * blocks;
+  if (block >= blocks) {
+    ++head;
+    block -= blocks;
+  }
 }
 
 }  // namespace rlkv

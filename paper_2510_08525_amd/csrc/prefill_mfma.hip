@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   __shared__ uint4 sm_k1[kKeySlots == 2 ? kTileBytes / 32 : 1];          // (an array of its own: the compiler would have reads of the
                                                                           // one slot wait for the loads into the other)
   __shared__ uint4 sm_v[2][kTileBytes / 32];
-  __shared__ floatx4 sm_local[MIX ? kPrefillWaves : 1][MIX ? NG * 8 : 1][64];
+  __shared__ floatx4 sm_local[MIX ? kPrefillWaves : 1][MIX ? NG * 8 : 1][MIX ? 64 : 1];
   // Where a wavefront turns its outputs into rows: 4 KiB for each column group in its part of the local results, or, group by group,
   // in its eighth of the K halves (kKeySlots == 4).
   constexpr bool kOutInLocal = kKeySlots == 2;
@@ -325,16 +325,22 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // sequences before short ones, and within a pair the later query blocks (more keys under the
   // causal mask) before the earlier ones - so that the short ones fill the end.
   // Bound, for a short chunk: latency.  What it takes to find the workgroup's own is asked for in as few turns as there are dependent
-  // loads: these arguments, the sequence, its tables.  (Each waited for where it was first looked at, about a dozen in a
-  // row: two prompts of 200 and 300 tokens 25.1 us, now 24.6; two of 210 and 514 27.0, now 26.4; 32 query, 8 KV heads and 12, 4.)
-  // The empty statements use the values, so that their loads are issued side by side here.
+  // loads, the arguments and then the sequence's tables, and in little code: it runs once, and a cold line of it costs as much as a
+  // load.  The sequences' words of the arguments therefore come to the lanes of two registers, and are picked out of
+  // them.  (Each argument waited for where it was first looked at, a dozen in a row, a search by halves and divisions: two prompts of 200
+  // and 300 tokens, 32 query and 8 KV heads, 25.1 us; side by side, with a search in scalar registers, 24.6; like this 24.2.)
+  // The empty statement uses the values, so that their loads are issued side by side here.
   PrefillItems items = grid.items;
   uint64_t head8[2] = {grid.head[0][0], grid.head[1][0]};
-  const FirstSixteen lead = *reinterpret_cast<const FirstSixteen*>(grid.first);
+  const int lane0 = threadIdx.x & 63;
+  const int32_t first_lo = grid.first[lane0], first_hi = grid.first[lane0 + 64];
+  const int32_t seq_lo = order.seq[lane0], seq_hi = order.seq[lane0 + 64], tok_lo = order.tok[lane0], tok_hi = order.tok[lane0 + 64];
   asm volatile("" : "+s"(items.gx), "+s"(items.heads[0]), "+s"(items.heads[1]), "+s"(items.inv_heads[0]), "+s"(items.inv_heads[1]),
                     "+s"(items.inv_seq[0]), "+s"(items.inv_seq[1]), "+s"(head8[0]), "+s"(head8[1])
-                  : "s"(lead), "s"(dv.batch), "s"(dv.n_kv_heads), "s"(dv.store_off), "s"(len_in), "s"(order.in_args), "s"(grid.n_split),
+                  : "s"(dv.batch), "s"(dv.n_kv_heads), "s"(dv.store_off), "s"(len_in), "s"(order.in_args), "s"(grid.n_split),
                     "s"(stride_tokens), "s"(grid.heads_given), "s"(grid.inv_group));
+  static_assert(kArgSeqs == 128 && kFirstEntries == kArgSeqs + 1);
+  auto of_place = [](int32_t lo, int32_t hi, int place) { return __builtin_amdgcn_readlane(place < 64 ? lo : hi, place & 63); };
   int index, place, head, from_end, blocks, b, t, share = 0;      // t: chunk length of the sequence
   bool full;
   const int Z = kKeySlots == 2 ? 1 : grid.n_split;               // (the form of two column groups that blends is not divided)
@@ -352,16 +358,19 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   }
   if (items.ragged) {                      // (the order is in the arguments)
     const int heads = full ? items.heads[0] : items.heads[1];
-    place = place_of_block(quotient(index, heads, full ? items.inv_heads[0] : items.inv_heads[1]), items.n_seqs, grid.first, lead);
-    int at = grid.first[place], next = grid.first[place + 1];
-    b = order.seq[place];
-    t = order.tok[place];
-    asm volatile("" : "+s"(at), "+s"(next), "+s"(b), "+s"(t));
-    blocks = next - at;
+    const int x = quotient(index, heads, full ? items.inv_heads[0] : items.inv_heads[1]);
+    place = __popcll(__ballot(first_lo <= x)) + __popcll(__ballot(first_hi <= x)) - 1;
+    const int at = of_place(first_lo, first_hi, place);
+    blocks = (place + 1 < kArgSeqs ? of_place(first_lo, first_hi, place + 1) : grid.first[kArgSeqs]) - at;
     ragged_place(index, heads, at, blocks, head, from_end);
   } else {
     even_place(index, full, items, place, head, from_end);
     blocks = items.gx;
+  }
+  if (order.in_args) {
+    b = of_place(seq_lo, seq_hi, place);
+    t = of_place(tok_lo, tok_hi, place);
+  } else {
     seq_in_order(dv, order, place, b, t);
   }
   const int h = __builtin_amdgcn_readfirstlane(head_of_class(dv, layer, grid, full ? head8[0] : head8[1], head, full));
@@ -966,7 +975,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
       if (MIX && mix && z == Z - 1) {          // the local results, as columns 128 and up (one column group)
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          *reinterpret_cast<floatx4*>(slot + (kSplitCols / 2 + col) * kHeadDim + j * 16 + kb * 4) = sm_local[MIX ? wave : 0][MIX ? k * 8 + j : 0][lane];
+          *reinterpret_cast<floatx4*>(slot + (kSplitCols / 2 + col) * kHeadDim + j * 16 + kb * 4) = sm_local[MIX ? wave : 0][MIX ? k * 8 + j : 0][MIX ? lane : 0];
       }
     }
     return;
@@ -981,7 +990,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       floatx4 res = st[cg].o[j] * inv;
-      if (MIX && mix) res = gate * res + (1.f - gate) * sm_local[MIX ? wave : 0][MIX ? cg * 8 + j : 0][lane];
+      if (MIX && mix) res = gate * res + (1.f - gate) * sm_local[MIX ? wave : 0][MIX ? cg * 8 + j : 0][MIX ? lane : 0];
       four[j] = u32x2{bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3])};
     }
     wave_exchange();

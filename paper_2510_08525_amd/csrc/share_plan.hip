@@ -9,8 +9,6 @@
 // per-workgroup timestamps.  A pair that continues from the previous workgroup pays no start.
 // The plan is the in-order greedy deal at the smallest capacity that needs no more workgroups than
 // the grid has; greedy is optimal for a contiguous partition once the capacity is fixed.
-#include <string.h>
-
 #include <algorithm>
 #include <cmath>
 #include <vector>
@@ -343,9 +341,8 @@ extern "C" int32_t rlkv_plan_prefill_item(int32_t linear_index, int32_t per_bloc
   const bool full = rlkv::prefill_item(linear_index, items, index);
   if (items.ragged) {
     const int c = full ? 0 : 1;
-    rlkv::FirstSixteen lead;
-    memcpy(&lead, first, sizeof(lead));
-    place = rlkv::place_of_block(rlkv::quotient(index, items.heads[c], items.inv_heads[c]), n_seqs, first, lead);
+    const int x = rlkv::quotient(index, items.heads[c], items.inv_heads[c]);
+    while (first[place + 1] <= x) ++place;
     blocks = first[place + 1] - first[place];
     rlkv::ragged_place(index, items.heads[c], first[place], blocks, head, block);
   } else {

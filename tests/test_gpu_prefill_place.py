@@ -61,6 +61,21 @@ def test_more_compressed_heads_than_travel_in_the_arguments(gpu_device, n_compre
     c.close()
 
 
+@pytest.mark.parametrize("B", [64, 65, 128, 129])
+def test_batches_around_those_that_travel_in_the_arguments(gpu_device, B):
+    """Chunks of unlike lengths, a few without tokens: the order of up to 64 sequences comes to the lanes of one register, of up to
+    128 to those of two, of more through memory."""
+    c = Case(Hq=8, Hkv=2, B=B, S=4, R=20, mask=[1, 0], cap=150, seed=B, prefill_tokens=100, **KW)
+    rng = np.random.default_rng(B)
+    for step in range(2):
+        counts = rng.integers(1, [100, 50][step], size=B)
+        counts[rng.integers(0, B, size=step)] = 0
+        counts[-1] = [99, 1][step]
+        c.check_prefill(counts, step, f"chunk {step}")
+    np.testing.assert_array_equal(c.cache.lengths(0), c.n.astype(np.int32))
+    c.close()
+
+
 @pytest.mark.parametrize("offset", [0, 1, 2, 4, 8])
 def test_output_that_starts_at_any_element(gpu_device, offset):
     """Output rows go out in 8-byte stores where the caller's buffer lies on 8 bytes, else in 2-byte ones: the same bits."""
