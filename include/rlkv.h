@@ -87,8 +87,8 @@ typedef struct {
                                       default 80, in the single-group form 26 and, for a layer that
                                       blends, 40                                                 */
   int32_t prefill_two_group_only;  /* 1: rlkv_prefill_attention never picks its single-group kernel form
-                                      for a layer that does not blend (tests run small shapes through
-                                      the form the large ones take); default 0                   */
+                                      (tests run small shapes through the form the large ones take);
+                                      default 0                                                  */
 } rlkv_config_t;
 
 /* Paged full heads (Sec. 4.3: a standard paged cache for the full heads beside the fixed-size
@@ -342,6 +342,14 @@ int32_t rlkv_plan_prefill_block(int32_t linear_index, int32_t grid_x, int32_t gr
  * Returns 0, 1 where linear_index is past the launch's last workgroup, or -1 on an invalid argument. */
 int32_t rlkv_plan_prefill_item(int32_t linear_index, int32_t per_block, int32_t n_full_heads, int32_t n_compressed_heads,
                                int32_t n_seqs, const int32_t* n_tokens /* host */, int32_t dealt_rows, int32_t* item /* host */);
+
+/* The form of the attention kernel for a chunk of a layer that blends, exposed for tests: 1 = single group (128 / group chunk
+ * positions per workgroup), 0 = two groups (256 / group; always with allow_narrow = 0), -1 on an invalid argument.  A workgroup of the
+ * single-group form takes about 0.6 of the time of one of the other, so the form whose rounds of workgroups over the compute
+ * units take less is chosen.
+ *   n_tokens : host [batch], chunk lengths (>= 0) */
+int32_t rlkv_plan_blend_form(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
+                             const int32_t* n_tokens /* host */, int32_t allow_narrow);
 
 /* The host-side plan of the split-K work list, exposed for tests and tools (it touches no device).
  * The scheduling units of all pairs are laid end to end - per pair one unit that marks its start,

@@ -80,6 +80,7 @@ def load_library():
         "rlkv_plan_whole_pairs": (i32, [vp, i32, i32, vp, vp, vp]),
         "rlkv_plan_list_whole": (i32, [i32] * 10 + [vp, vp]),
         "rlkv_plan_narrow_split": (i32, [i32, i32, i32, i32, vp, vp, i32]),
+        "rlkv_plan_blend_form": (i32, [i32, i32, i32, i32, vp, i32]),
         "rlkv_plan_prefill_form": (i32, [i32, i32, i32, i32, i32, vp, vp, i32, i32, vp, vp]),
         "rlkv_plan_prefill_rows": (i32, [i32, i32, vp, vp, vp, vp]),
         "rlkv_plan_prefill_block": (i32, [i32, i32, i32, i32, i32, vp, vp]),
@@ -100,7 +101,7 @@ EXPORTED_SYMBOLS = (
     "rlkv_cache_required_bytes", "rlkv_cache_create", "rlkv_cache_destroy", "rlkv_cache_reset",
     "rlkv_append", "rlkv_append_ragged", "rlkv_decode_attention", "rlkv_decode_attention_noalloc", "rlkv_set_active", "rlkv_set_gates", "rlkv_append_decode", "rlkv_append_decode_prepare", "rlkv_append_decode_launch", "rlkv_worklists_built", "rlkv_prefill_attention", "rlkv_profile_enable",
     "rlkv_profile_collect", "rlkv_get_lengths",
-    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_narrow_split", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_plan_prefill_item", "rlkv_cache_kernel", "rlkv_pool_pages_free",
+    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_narrow_split", "rlkv_plan_blend_form", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_plan_prefill_item", "rlkv_cache_kernel", "rlkv_pool_pages_free",
     "rlkv_pool_shuffle", "rlkv_status_string",
 )
 
@@ -282,6 +283,15 @@ def rlkv_plan_prefill_form(n_compute_units: int, n_q_heads: int, n_kv_heads: int
     if rc != 0:
         raise RlkvError(RLKV_ERR_INVALID_ARG, "rlkv_plan_prefill_form")
     return bool(narrow[0]), int(n_split[0])
+
+
+def rlkv_plan_blend_form(n_compute_units: int, group: int, n_full_heads: int, n_tokens, allow_narrow: bool = True) -> bool:
+    """Whether a chunk of a layer that blends takes the kernel form with one column group per wavefront."""
+    t = np.ascontiguousarray(np.asarray(n_tokens, dtype=np.int32).reshape(-1))
+    rc = load_library().rlkv_plan_blend_form(n_compute_units, group, n_full_heads, t.size, t.ctypes.data, 1 if allow_narrow else 0)
+    if rc < 0:
+        raise RlkvError(RLKV_ERR_INVALID_ARG, "rlkv_plan_blend_form")
+    return bool(rc)
 
 
 def rlkv_plan_prefill_rows(n_full_heads: int, n_tokens, cached):

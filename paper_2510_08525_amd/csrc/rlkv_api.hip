@@ -172,7 +172,7 @@ struct rlkv_cache {
   std::vector<uint8_t> layer_gated; // [L] some full head of the layer has a gate below 1
   std::vector<uint32_t> merge_words; // [L][pairs] (first partial slot << 12) | partials of the layer's work list; empty if too many pairs
   int n_cu;                         // compute units of the device
-  bool allow_narrow;                // prefill may pick the one-group kernel form for a layer that does not blend
+  bool allow_narrow;                // prefill may pick the one-group kernel form
   DeviceView dv;
   Plan plan;
   char* arena;
@@ -648,7 +648,7 @@ static rlkv_status_t append_impl(rlkv_cache_t* cache, int32_t layer, const void*
     // (Shares of that form pay from about 26 tiles on, 40 where heads blend (their last share takes both passes).  One sequence of 3000 / 6000
     // tokens, 28 query and 4 KV heads, 2 full, chunks of 512 / 1024, whole / shares of 40 / 30 / 20 / 12 tiles: 277 / 263 / 251 /
     // 255 / 271, 480 / 436 / 437 / 407 / 443 us; blending, two of 4000 and 5000: 623 / 588 / 594 / 607 / 621 us.)
-    if (mix) narrow = plan_blend_narrow(cache->n_cu, cache->dv.group, n_full, B, n_tokens);
+    if (mix) narrow = cache->allow_narrow && plan_blend_narrow(cache->n_cu, cache->dv.group, n_full, B, n_tokens);
     if (narrow) {
       const int tiles = set_tiles > 0 ? set_tiles : cache->layer_gated[layer] ? kShareTilesBlend : kShareTilesNarrow;
       n_split = plan_narrow_split(cache->n_cu, cache->dv.group, n_full, B, n_tokens, lh, tiles);

@@ -381,6 +381,14 @@ extern "C" int32_t rlkv_plan_list_whole(int32_t kernel, int32_t dtype, int32_t g
                                  lengths, active);
 }
 
+extern "C" int32_t rlkv_plan_blend_form(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
+                                        const int32_t* n_tokens, int32_t allow_narrow) {
+  if (!n_tokens || n_compute_units < 1 || group < 1 || group > rlkv::kMaxGroup || n_full_heads < 0 || batch < 1) return -1;
+  for (int b = 0; b < batch; ++b)
+    if (n_tokens[b] < 0) return -1;
+  return allow_narrow && rlkv::plan_blend_narrow(n_compute_units, group, n_full_heads, batch, n_tokens);
+}
+
 extern "C" int32_t rlkv_plan_narrow_split(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
                                           const int32_t* n_tokens, const int32_t* cached, int32_t min_share_tiles) {
   if (!n_tokens || !cached || n_compute_units < 1 || group < 1 || group > rlkv::kMaxGroup || n_full_heads < 0 || batch < 1 ||

@@ -277,7 +277,7 @@ def test_prefill_with_chunks_longer_than_the_recent_band(gpu_device, Hq, Hkv, ma
     c.check_decode(0, "decode after the prefill", fused=True)
     c.check_prefill([100, 512], 5, "chunk after a decode step")
     c.check_indices()
-    # the same heads in the kernel form for blending layers (one column group per wavefront)
+    # the same heads in a blending layer
     g = np.where(np.asarray(mask) == 1, 0.25, 1.0).astype(np.float32)
     c.cache.set_gates(g)
     c.check_prefill([256, 100], 6, "chunk in a blending layer", gates=g)
