@@ -317,8 +317,8 @@ int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_heads, int32
  * The rows of full heads of sequences that have a chunk come first ("heavy" rows, sequences ordered by
  * cached + chunk length, longest first), and of those the leading groups of 8 rows whose work differs by less
  * than 15 % within the group are dealt one row per XCD; the heavy rows after them are dealt workgroup by
- * workgroup, so that ragged chunks leave no XCD idle.  (Rows of compressed heads are light and always dealt
- * by rows.)  Work of a row: chunk tokens x (cached + chunk / 2 + 600).
+ * workgroup, so that ragged chunks leave no XCD idle.  (Rows of compressed heads are light and dealt by rows where the
+ * sequence's chunk has the launch's full number of blocks, in groups of 8 from the first on.)  Work of a row: chunk tokens x (cached + chunk / 2 + 600).
  *   n_tokens, cached : host [batch], chunk length and positions already cached per sequence
  *   dealt_rows       : host, out: leading heavy rows dealt one row per XCD (a multiple of 8)
  *   heavy_rows       : host, out: rows of full heads of sequences with a chunk

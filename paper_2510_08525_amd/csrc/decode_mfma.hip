@@ -15,8 +15,8 @@
 // the merge.  P is split into a bf16 head and a bf16 remainder (two MFMAs per V block) so
 // the weights carry ~16 mantissa bits; the matrix cores are idle most of the time anyway.
 //
-// The kernel is latency-lean at its start: a workgroup learns its share and its first store
-// from one wave-uniform record and at once issues the loads of Q and of its first tile.
+// At its start a workgroup learns its share and its first store from one wave-uniform record and issues the loads of Q, and
+// then of its first tile (four wavefronts, plain: once Q has arrived; the fused forms: once the new row is in the store).
 // Each wavefront keeps one tile (16 KiB) in flight behind the one it works on; with one
 // workgroup per CU that is 64 KiB in flight per CU, which measurement shows is where this
 // part's HBM streams best (more in flight lowers the achieved bandwidth).
@@ -241,12 +241,13 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
     int tile = WAVES > kRound && wave >= stride ? tile_hi : tile_lo + wave;
     TileRegs ra, rb;
     if (tile < tile_hi) load_tile(ra, store.at(tile), lane);
-    // address of the tile after this one; looked up one iteration ahead so that a block-table
-    // read never sits between a wavefront and its next loads
+    // address of the tile after this one, looked up one iteration ahead.  (Paged: the compiled loop reads the table entry through
+    // a vector load and waits for it, and with it for every load before it, at the lookup.)
     const char* next_base = store.at(tile + stride);
     // the next pair's record, for the (rare) share that crosses a pair boundary
     PairDesc pd_next = pd;
-    if (seg_end < u_end) pd_next = pairs[pi + 1];     // fetched early, looked at after the segment
+    // (the compiler moves it to scalar registers here, which waits for the loads before it, the first tile's included)
+    if (seg_end < u_end) pd_next = pairs[pi + 1];
 
     // Eq. 1 gate: a full head with gate < 1 also accumulates its local attention (sink + recent
     // positions) over the same tiles; out = gate * full + (1 - gate) * local.
@@ -260,10 +261,11 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
 #pragma unroll
       for (int j = 0; j < 8; ++j) st[k].o[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    // Two register images that swap roles, and the last tile of the segment outside the steady state:
-    // inside it the loads of the next tile are unconditional, so the work on the current one waits for
-    // its own loads only and the next tile's stay in flight beside it.  (With one loop and a conditional
-    // load the compiler has to wait for every load in flight before the work, the next tile's included.)
+    // Two register images that swap roles, and the last tile of the segment outside the steady state: inside it the loads of the
+    // next tile are unconditional.  As compiled, the second half of the loop waits for its own tile only, the next tile's 16 loads in
+    // flight beside it (`vmcnt(16)`); between the second half and the first the image is copied from one set of registers
+    // to the other with 8 loads left, and the next tile is asked for with 2 left (fused: 0), since its addresses take registers
+    // that loads still fill.  (With one loop and a conditional load every half waited for all loads, the next tile's included.)
     auto work = [&](TileRegs& t, int tl) {
       process_tile<GATED>(t, qb, st[0], st[GATED ? 1 : 0], two_sets, tl, n_eff, scale_log2, kb, keep_lo, keep_from,
                           [] {});
@@ -273,7 +275,8 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
       // eight wavefronts and two accumulator sets need, and faster where the next tile's address comes out of a table.
       // (Gated, 16 sequences of 3000 .. 5000 tokens: 30.8 us against 32.2 with a copy per tile from the image in flight,
       // 63 with two images; paged, 24 of 2000 .. 20 000: 46.9 against 51.4 us with two images.  Contiguous stores: the
-      // same for a plain launch, a 28-layer fused step 1170 against 1165 us.)
+      // same for a plain launch, a 28-layer fused step 1170 against 1165 us.)  As compiled, all of these loops but the fused one
+      // that blends wait for V too before the scores, which need K only.
       for (; tile + stride < tile_hi; tile += stride) {
         const char* refill = next_base;
         next_base = store.at(tile + 2 * stride);

@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
     const int tile_lo = r_lo * kRound;
     const bool whole_pair = u == ps && seg_end == pe;
     PairDesc pd_next = pd;
-    if (seg_end < u_end) pd_next = pairs[pi + 1];     // fetched early, looked at after the segment
+    if (seg_end < u_end) pd_next = pairs[pi + 1];     // (moved to scalar registers here, which waits for it)
 
     const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
     const int n_old = pd.n_build + grow;

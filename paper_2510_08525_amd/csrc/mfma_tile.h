@@ -138,7 +138,8 @@ __device__ __forceinline__ void softmax_pv(const TileRegs& t, const float (&sc)[
 // Where the tiles of one pair's store live.  Contiguous store: tile t at base + t * 16 KiB.
 // Paged full head (PAGED; Sec. 4.3): base is the head's pool and the sequence's block-table row
 // names the page of every run of 2^shift tiles.  The tile index is the same in all lanes of a
-// wavefront, so the table entry comes through a scalar load.
+// wavefront; the entry nevertheless comes through a vector load (in a kernel that stores, the compiler takes the table for
+// possibly changed) and the address is a lane's own value.
 template <bool PAGED>
 struct TileMap {
   char* base;

@@ -283,8 +283,8 @@ constexpr int kPrefillBlock = kPrefillWaves * 64;
 // MIX (some full head of the layer has an Eq. 1 gate below 1: out = gate * causal + (1 - gate) * local): the causal
 // positions are the local ones and the rest, so a blending head's tiles are walked in two passes that share one set of
 // accumulators - first what is local (sinks and recent band), whose finished result is put aside in LDS, then the rest, on
-// top of it.  Every key is thus folded in once, a tile at the edge of the two in both passes, and the registers are those of a
-// plain head.  (Two accumulator sets side by side left room for one column group per wavefront, which makes the hot loop wait
+// top of it.  Every key is thus folded in once, a tile at the edge of the two in both passes.  (The form with two column groups takes
+// all 256 registers and spills 4 more, 7 if paged: a Q operand, read back in the loop that takes V as stored.)  (Two accumulator sets side by side left room for one column group per wavefront, which makes the hot loop wait
 // for LDS - 16 KiB of operands per wavefront and tile for 16 columns - and folded every local tile in twice, in the general
 // loop: 8 sequences of 1000 to 4000 tokens in chunks of 1024, 28 query and 4 KV heads, 984 -> 775 us with the two passes,
 // 880 us with one column group per wavefront.)
@@ -294,9 +294,10 @@ constexpr int kPrefillBlock = kPrefillWaves * 64;
 // and for a compressed head its complete sink tiles and the chunk tiles before the first query
 // that no query's recent band has left yet.  The eight wavefronts walk them together, every tile is
 // fetched from memory once per workgroup into LDS (one barrier per tile; K straight into LDS, V
-// through registers) and read from there as MFMA operands; no masks.  The general one takes everything else (partly filled
-// tiles, a compressed head's ring, the causal diagonal and the band's edge, the sink and band tiles
-// of a gated head), each wavefront on its own, with per-slot positions and masks.
+// through registers) and read from there as MFMA operands; no masks.  Of a blending head it takes, in the first pass, the complete
+// sink tiles and those wholly inside the recent band of all queries, in the second those wholly between.  The general one takes
+// everything else (partly filled tiles, a compressed head's ring, the causal diagonal, the tiles at the end of the sinks and at the
+// band's edge), each wavefront on its own, with per-slot positions and masks.
 template <bool PAGED, int NG, bool MIX>
 __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView dv, int layer,
                                                                      SeqOrder order,
@@ -588,6 +589,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // the other's products.  8 x 1000 .. 4000 tokens that blend 663 -> 659 us; in the one-group form one of 3074 tokens in chunks of 512 241.5 ->
   // 239.1, 8 x 291 .. 868 79.7 -> 78.0, 5 x 2735 .. 3469 734 -> 728.  The two-group form of plain heads: 0.3 % slower with it.)
   auto hot_loop = [&](auto half_tag) {
+    // (It stays raised behind the loop, through the general tiles and the output.)
     if ((MIX || NG == 1) && wave >= kPrefillWaves / 2) __builtin_amdgcn_s_setprio(1);
     constexpr bool HALF = decltype(half_tag)::value;
     uint4 next_v = make_uint4(0, 0, 0, 0);      // the next tile's V as fp16, when the loop body has converted it already

@@ -203,8 +203,10 @@ extern "C" int32_t rlkv_plan_prefill_form(int32_t n_compute_units, int32_t n_q_h
 namespace rlkv {
 
 // Whether a chunk of a layer with blending heads takes the form with one column group per wavefront (128 columns to a workgroup) or
-// two (256).  A workgroup of 128 columns takes about 0.6 of the time of one of 256 (8 sequences of 1000 to 4000 tokens, chunks 1, 2, 3: 44 / 71, 65 / 104, 79 / 130 us), so the wide form is the
-// better one unless it fills its last round of workgroups so much worse.
+// two (256).  A workgroup of 128 columns takes about 0.6 of the time of one of 256, by three chunks of one batch (8 sequences of 1000
+// to 4000 tokens, 28 query and 4 KV heads, chunks 1, 2, 3 of 1024: 44 / 71, 65 / 104, 79 / 130 us), so the wide form is the better one
+// unless it fills its last round of workgroups so much worse.  (Dividing a half-empty round, which only the narrow form can, is not
+// weighed.)
 bool plan_blend_narrow(int n_compute_units, int group, int n_full_heads, int batch, const int32_t* n_tokens) {
   int64_t rounds[2];
   for (int form = 0; form < 2; ++form) {

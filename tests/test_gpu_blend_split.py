@@ -1,5 +1,6 @@
-"""Blending prefill (Eq. 1) of few long sequences: every full head's workgroup divided into 2 to 8 shares, two accumulator
-sets each, merged and blended by the kernel that follows."""
+"""Blending prefill (Eq. 1) of few long sequences: every full head's workgroup divided into 2 to 8 shares of the keys outside the
+local positions; the last share takes those too and leaves their result beside its accumulators; merged and blended by the kernel
+that follows."""
 import numpy as np
 import pytest
 
