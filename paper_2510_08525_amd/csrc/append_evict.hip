@@ -57,11 +57,11 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
                                                         int stride_tokens, int ragged, SeqCounts seqs,
                                                         std::conditional_t<RINGS, RingHeads, NoRings> rings) {
   int b, h;
+  bool given = false;                  // the head comes from the list: it is a compressed one
   if constexpr (RINGS) {
-    const int per_seq = rings.n >= 0 ? rings.n : dv.n_kv_heads;
-    b = blockIdx.y / per_seq;
-    h = blockIdx.y - b * per_seq;
-    if (rings.n >= 0) h = rings.head[h];
+    given = rings.n >= 0;
+    b = blockIdx.z;
+    h = given ? rings.head[blockIdx.y] : (int)blockIdx.y;
   } else {
     b = blockIdx.y / dv.n_kv_heads;
     h = blockIdx.y % dv.n_kv_heads;
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
   // a uniform append keeps the layer's work list valid: every active sequence has grown by the same count
   if (!RINGS && !ragged && job == 0 && blockIdx.y == 0 && threadIdx.x == 0) list_header(dv, layer)->grow += n_uniform;
   const int len_new = len_old + n_tok;
-  const bool full = dv.full_mask[layer * dv.n_kv_heads + h] != 0;
+  const bool full = !given && dv.full_mask[layer * dv.n_kv_heads + h] != 0;
 
   int tile = -1;
   if (n_tok > 0 && !(RINGS && full)) {
@@ -132,8 +132,8 @@ __global__ __launch_bounds__(kBlock) void append_kernel(DeviceView dv, int layer
         if (slot_pos && p >= 0) slot_pos[slot] = p;
       }
       __syncthreads();
-      const bool wide = rows_to_tile<false, true>(lds, [&](int slot) { return src[slot]; }, k_new + src_head * kHeadDim,
-                                                  v_new + src_head * kHeadDim, tile_base);
+      const bool wide = rows_to_tile<true>(lds, [&](int slot) { return src[slot]; }, [&](int slot) { return src[slot] < 0; },
+                                           k_new + src_head * kHeadDim, v_new + src_head * kHeadDim, tile_base);
       if (wide) dv.v_wide[layer] = 1;        // the prefill kernel takes this layer's V as bf16 from now on
     } else {
       // K and V rows: one 16-byte chunk per unit
@@ -260,7 +260,7 @@ hipError_t launch_append_rings(const DeviceView& dv, int layer, const int32_t* l
   // Tiles a compressed pair can touch (launch_append), and no more than its three ranges have.
   const int slots = max_tokens < dv.window ? max_tokens : dv.window;
   const int jobs = (slots + 3 * (kTile - 2)) / kTile + 3;
-  hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t, true>), dim3(jobs, dv.batch * rows), dim3(kBlock), 0, stream, dv, layer,
+  hipLaunchKernelGGL((append_kernel<RLKV_KERNEL_MFMA, uint16_t, true>), dim3(jobs, rows, dv.batch), dim3(kBlock), 0, stream, dv, layer,
                      len_in, (int32_t*)nullptr, (const uint16_t*)k, (const uint16_t*)v, 0, stride_tokens, 1, seqs, rings);
   return hipGetLastError();
 }

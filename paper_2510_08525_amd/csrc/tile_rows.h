@@ -36,11 +36,11 @@ template <bool NT> __device__ __forceinline__ void tile_store(char* p, const uin
   __builtin_nontemporal_store(v, reinterpret_cast<row_x4*>(p));
 }
 
-// row_of(slot): the slot's source row, -1 = none.  k_rows / v_rows: row 0 of the pair (row r at r * kHeadDim).  ZERO: slots
-// without a source row are written as zeros; otherwise they keep what they hold.  Returns whether this thread moved a V
+// row_of(slot): the slot's source row, -1 = none.  keep(slot): the slot keeps what it holds (it has no source row); the others
+// without one are written as zeros.  k_rows / v_rows: row 0 of the pair (row r at r * kHeadDim).  Returns whether this thread moved a V
 // value beyond the fp16 range.
-template <bool ZERO, bool NT, typename RowOf>
-__device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const RowOf& row_of, const uint16_t* __restrict__ k_rows,
+template <bool NT, typename RowOf, typename Keep>
+__device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const RowOf& row_of, const Keep& keep, const uint16_t* __restrict__ k_rows,
                                              const uint16_t* __restrict__ v_rows, char* __restrict__ tile_base) {
   constexpr int kUnits = kTile * 16 / kBlock;            // 16-byte units of K (and of V) per thread
   const int tid = threadIdx.x;
@@ -73,7 +73,7 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const RowOf& row_
 #pragma unroll
   for (int i = 0; i < kUnits; ++i) {                     // K: unit u of the tile = [half][chunk][slot % 16]
     const int u = tid + i * kBlock, hf = u >> 8, chunk = (u >> 4) & 15, s16 = u & 15;
-    if (ZERO || row_of(hf * 16 + s16) >= 0)
+    if (!keep(hf * 16 + s16))
       tile_store<NT>(tile_base + u * 16, lds.k[hf * 256 + chunk * 16 + ((s16 + chunk) & 15)]);
   }
 #pragma unroll
@@ -85,10 +85,10 @@ __device__ __forceinline__ bool rows_to_tile(TileRowsLds& lds, const RowOf& row_
     for (int e = 0; e < 8; ++e) {
       const int slot = (e >> 2) * 16 + kb * 4 + (e & 3);
       val[e] = *reinterpret_cast<const uint16_t*>(lds.v + slot * kTileRowStride + d * 2);
-      if (!ZERO) have |= row_of(slot) >= 0 ? 1u << e : 0u;
+      have |= keep(slot) ? 0u : 1u << e;
     }
     char* dst = tile_base + kTileBytes / 2 + u * 16;
-    if (ZERO || have == 0xffu) {
+    if (have == 0xffu) {
       tile_store<NT>(dst, make_uint4(val[0] | val[1] << 16, val[2] | val[3] << 16, val[4] | val[5] << 16, val[6] | val[7] << 16));
     } else {
 #pragma unroll
