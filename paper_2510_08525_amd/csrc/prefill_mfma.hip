@@ -330,8 +330,8 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // Bound, for a short chunk: latency.  What it takes to find the workgroup's own is asked for in as few turns as there are dependent
   // loads, the arguments and then the sequence's tables, and in little code: it runs once, and a cold line of it costs as much as a
   // load.  The sequences' words of the arguments therefore come to the lanes of two registers, and are picked out of
-  // them.  (Each argument waited for where it was first looked at, a dozen in a row, a search by halves and divisions: two prompts of 200
-  // and 300 tokens, 32 query and 8 KV heads, 25.1 us; side by side, with a search in scalar registers, 24.6; like this 24.2.)
+  // them.  (Each argument waited for where it was first looked at, a dozen in a row, a search by halves and divisions: two prompts of 212
+  // and 250 tokens, 32 query and 8 KV heads, 25.1 us; side by side, with a search in scalar registers, 24.6; like this 24.2.)
   // The empty statement uses the values, so that their loads are issued side by side here.
   PrefillItems items = grid.items;
   uint64_t head8[2] = {grid.head[0][0], grid.head[1][0]};
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // range has been appended since the cache was last empty; unusual) and for the local pass of a blending head, takes V as
   // stored, with two-part bf16 weights.
   // (MIX: the second wavefront of every SIMD goes first where both could issue, which keeps the two out of step: one's exponentials beside
-  // the other's products.  8 x 1000 .. 4000 tokens that blend 663 -> 659 us; in the one-group form one of 3074 tokens in chunks of 512 241.5 ->
+  // the other's products.  8 x 1000 .. 4000 tokens that blend 663 -> 659 us; in the one-group form one of 2670 tokens in chunks of 512 241.5 ->
   // 239.1, 8 x 291 .. 868 79.7 -> 78.0, 5 x 2735 .. 3469 734 -> 728.  The two-group form of plain heads: 0.3 % slower with it.)
   auto hot_loop = [&](auto half_tag) {
     // (It stays raised behind the loop, through the general tiles and the output.)
@@ -951,7 +951,7 @@ __global__ __launch_bounds__(kPrefillBlock) void prefill_mfma_kernel(DeviceView 
   // Accumulators and outputs leave through LDS: a lane holds four values in a row of its own column, and 16 neighbouring lanes
   // belong to 16 rows, so they are turned into whole rows first, 16 lanes each.  (Stored from where they are, every
   // instruction is 64 requests of 8 or 16 bytes: the launch over 16 chunks of 300 tokens, 32 query and 8 KV heads, 49.1 us, now
-  // 44.9; 14 of 142 .. 289 35.2, now 31.2; a prompt of 3074 in chunks of 512, divided, 241 us in all, now 236; blending, 8 x 1000 ..
+  // 44.9; 14 of 142 .. 289 35.2, now 31.2; a prompt of 2670 in chunks of 512, divided, 241 us in all, now 236; blending, 8 x 1000 ..
   // 4000, 666, now 648.)  16-byte chunk c of row r lies at chunk c ^ r, which spreads both sides over all banks.  (Values keep their
   // type on the way: cast to integers here, the accumulators were copied between registers in every step of the hot loop, 8 %.)
   u32x4* rows = kOutInLocal ? reinterpret_cast<u32x4*>(sm_local[MIX ? wave : 0]) : reinterpret_cast<u32x4*>(&sm_k[0][0]) + wave * 256;
@@ -1122,7 +1122,7 @@ hipError_t launch_prefill_mfma(const DeviceView& dv, int layer, bool narrow, boo
                         (const uint16_t*)q, (uint16_t*)out, stride_tokens, scale_log2, (const char*)staging,       \
                         staging_tiles, split_out, grid)
   // (Layers that do not blend in an instance of their own in either form: the one-group form, which used to carry the blending code
-  // along, 8 x 291 .. 868 tokens 77.9 -> 76.2 us, 5 x 2735 .. 3469 728 -> 706, one of 3074 in chunks of 512 239.1 -> 240.3.)
+  // along, 8 x 291 .. 868 tokens 77.9 -> 76.2 us, 5 x 2735 .. 3469 728 -> 706, one of 2670 in chunks of 512 239.1 -> 240.3.)
 #define RLKV_FORM(PG, NGR) do { if (mix) RLKV_LAUNCH(PG, NGR, true); else RLKV_LAUNCH(PG, NGR, false); } while (0)
 #define RLKV_PICK(PG) do { if (narrow) RLKV_FORM(PG, 1); else RLKV_FORM(PG, 2); } while (0)
   if (dv.page_shift >= 0) RLKV_PICK(true); else RLKV_PICK(false);
