@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import harness
 import paper_2510_08525_amd as rl
 from harness import Case
 from inputs import synth
@@ -92,4 +93,32 @@ def test_output_that_starts_at_any_element(gpu_device, offset):
     torch.cuda.synchronize()
     assert torch.equal(want, got)
     assert not room[:offset].any() and not room[offset + want.numel():].any()
+    c.close()
+
+
+@pytest.mark.parametrize("gated", [False, True], ids=["plain", "blending"])
+@pytest.mark.parametrize("form", [0, 1], ids=["form by size", "two-group form"])
+def test_every_form_writes_the_same_rows_at_any_element(gpu_device, form, gated, monkeypatch):
+    """A wavefront's outputs pass through LDS, in each form through another part of it: the rows of the last, partly filled block,
+    of the first one and of heads of either class, at offsets of 0, 2, 8 and 16 bytes, against the oracle and bit for bit."""
+    monkeypatch.setattr(harness, "TUNING", {"prefill_two_group_only": form})
+    B, Hq, Hkv, T = 2, 21, 3, 75
+    c = Case(Hq=Hq, Hkv=Hkv, B=B, S=4, R=20, mask=[1, 0, 1], cap=T, seed=8, prefill_tokens=T, **KW)
+    g = None
+    if gated:
+        g = np.asarray([0.5, 1.0, 1.0], dtype=np.float32)
+        c.cache.set_gates(g)
+    c.check_prefill([T, T - 6], 0, "aligned", gates=g)
+    q = synth.normal(8, synth.T_Q, 0, range(B), range(Hq), 100000, T, 128, dtype=torch.float32).to(torch.bfloat16).to(c.device)
+    want = c.last_out
+    c.n[:] = 0
+    k, v = rows(c, [T, T - 6])
+    for offset in (0, 1, 4, 8):
+        room = torch.full((want.numel() + 16,), 7.0, dtype=torch.bfloat16, device=c.device)
+        got = room[offset:offset + want.numel()].view(want.shape)
+        c.cache.reset()
+        c.cache.prefill_attention(0, q, k, v, [T, T - 6], got, c.scale)
+        torch.cuda.synchronize()
+        assert torch.equal(want, got), offset
+        assert (room[:offset] == 7.0).all() and (room[offset + want.numel():] == 7.0).all()
     c.close()
