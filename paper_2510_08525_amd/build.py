@@ -25,7 +25,11 @@ HIPCC_FLAGS = [
 
 # Per-file additions: the prefill kernel's maxima need no NaN quieting (see the comment there), and its hot loop wants to begin on
 # a cache line: the same instructions a few bytes further on took 0.8 % longer (16 x 16 384 tokens, 15.68 against 15.57 ms).
-EXTRA_FLAGS = {"prefill_mfma.hip": ["-fno-honor-nans", "-falign-loops=64"]}
+# The first 14 words of a kernel's arguments in scalar registers before its first instruction: of kernels whose start is a chain of
+# memory latencies (see decode_mfma.hip).
+PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
+EXTRA_FLAGS = {"decode_mfma.hip": PRELOAD, "worklist_combine.hip": PRELOAD,
+               "prefill_mfma.hip": ["-fno-honor-nans", "-falign-loops=64"]}
 
 
 def _hipcc() -> str:

@@ -9,17 +9,23 @@
 //                           A = V^T tile (k runs over the 32 slots of a tile), B = P^T
 // The score accumulator leaves lane l holding head l%16 and slots 4*(l/16)..+3 of each
 // 16-slot half, which is exactly the B-operand register layout, so P never moves between
-// lanes; O comes out as O^T, each head in the lanes that hold its scores.  The stores are laid out (see rlkv_internal.h) so that every 128-bit load per lane
-// is one contiguous kilobyte per wavefront and lands directly in operand registers: no
+// lanes; O comes out as O^T, each head in the lanes that hold its scores.  The stores are laid out (see rlkv_internal.h) so that
+// every 128-bit load per lane is one contiguous kilobyte per wavefront and lands directly in operand registers: no
 // LDS staging, no transposes, and the wavefronts of a workgroup run independently until
 // the merge.  P is split into a bf16 head and a bf16 remainder (two MFMAs per V block) so
 // the weights carry ~16 mantissa bits; the matrix cores are idle most of the time anyway.
 //
-// At its start a workgroup learns its share and its first store from one wave-uniform record and issues the loads of Q, and
-// then of its first tile (four wavefronts, plain: once Q has arrived; the fused forms: once the new row is in the store).
-// Each wavefront keeps one tile (16 KiB) in flight behind the one it works on; with one
-// workgroup per CU that is 64 KiB in flight per CU, which measurement shows is where this
-// part's HBM streams best (more in flight lowers the achieved bandwidth).
+// Start: the address of the list, and whatever else the first loads need, is in scalar registers before the first instruction
+// (kernel arguments loaded ahead, see kShapeGroup); the workgroup's record is one scalar load of 64 bytes, and the other arguments
+// come in its shadow; then the new row's loads, Q's and the first tile's go out together.  (Compiled from one struct of arguments and
+// plain pointers, the same start was five to six round trips to memory in a row.)
+// Loop: eight wavefronts, two per SIMD, whatever the list; one register image each, K refilled behind the scores and V behind the
+// products, every wait for its own registers only.  That last needs care: with a FLAT store possibly in flight - the output through a
+// generic pointer - the compiler turns every wait for a load into one for all of them.
+// Measured, before / now, us a call: one sequence of 333 tokens and 32 steps (32 query, 8 KV heads) 246 / 229, the launch by itself
+// 7.1 / 5.6; 8 x 8192 40.3 / 38.6; 16 gated of 3000 .. 5000 28.8 / 25.1; 24 paged of 2000 .. 20 000 46.6 / 42.5; a 28-layer step of
+// 16 x 16 384 1152 / 1088; 32 of 4000 .. 32 000 184.2 / 181.9; 64 of 16 000 .. 64 000 783 / 777.
+// Four wavefronts with two register images, exact waits: 185.5 for the 32, 1132 for the step; with one image 185.7 and 1120.
 //
 // Gated heads (GATED = true; paper Sec. 3.1, Eq. 1): a full head with gate g < 1 returns
 // g * full + (1 - g) * local attention.  The local positions (first S, last R) are a subset of
@@ -29,8 +35,8 @@
 // Fused single-token append (FUSED = true): the kernel also performs this step's append.
 // Every sequence grows by one position; the wavefront that owns the tile holding the new
 // slot of a pair writes the new K/V row into the store (sink slot, ring slot - evicting
-// position p - R - or next row of a full head) before it loads that tile; each lane writes
-// exactly the bytes it later loads, so no other wavefront ever depends on the write.  No
+// position p - R - or next row of a full head); each lane writes exactly the bytes it later loads, so no other wavefront ever
+// depends on the write, and where the tile is the first one, asked for already, the row goes into its registers as well.  No
 // workgroup reads a length from the table: a pair's length is its length when the work list was
 // planned plus the list's growth counter (ListHeader::grow), which no workgroup writes while another
 // one reads it, so the kernel needs no grid-wide fence: under a list of shares every workgroup reads
@@ -42,6 +48,26 @@
 
 namespace rlkv {
 namespace {
+
+// The first 14 words of a kernel's arguments are loaded into scalar registers before its first instruction (the build asks for
+// it, -amdgpu-kernarg-preload-count): they are what a workgroup needs to ask for its record.  The others are loaded beside the record.
+constexpr uint32_t kShapeGroup = 31, kShapeInTurn = 32, kShapeMore = 64;   // of `shape`; kShapeMore: another layer's list follows
+constexpr int kShapeWgs = 8;                                               // workgroups << 8
+constexpr int kWaves = 8, kThreads = kWaves * 64;
+struct DecodeRest {
+  uint16_t* out;
+  float scale_log2;
+  int32_t n_kv_heads;
+  float *part_o, *part_m, *part_l;
+  int64_t part_set_o, part_set_ml;
+  int64_t list_stride;
+  int32_t pair_off, batch;
+  int32_t *len0, *len1;          // both copies of the layer's lengths
+  int32_t *slot_pos, *v_wide;    // (v_wide: of this layer)
+  const int32_t* block_table;
+  int64_t page_bytes;
+  int32_t page_shift, page_mask, table_stride;
+};
 
 // Online-softmax update and P.V accumulation of one tile into `st`.  A slot counts if it
 // lies in the valid prefix [0, n_eff) and, for the local attention of a gated head (LOCAL),
@@ -76,6 +102,25 @@ __device__ __forceinline__ void tile_accumulate(TileRegs& t, const float (&raw)[
   softmax_pv(t, sc, st);
 }
 
+// N = 4 / 8 lanes of every 16 hold something in each of 16 / N registers: the first N lanes keep a, the next N get b's, and so on.
+template <int N>
+__device__ __forceinline__ floatx4 pack_lanes(const floatx4& a, const floatx4& b, const floatx4& c, const floatx4& d) {
+  floatx4 p;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    int x = __float_as_int(a[e]);
+    if (N == 4) {
+      x = __builtin_amdgcn_update_dpp(x, __float_as_int(b[e]), 0x114, 0xf, 0x2, false);      // row_shr:4, lanes 4 .. 7 of a row
+      x = __builtin_amdgcn_update_dpp(x, __float_as_int(c[e]), 0x118, 0xf, 0x4, false);
+      x = __builtin_amdgcn_update_dpp(x, __float_as_int(d[e]), 0x11c, 0xf, 0x8, false);
+    } else {
+      x = __builtin_amdgcn_update_dpp(x, __float_as_int(b[e]), 0x118, 0xf, 0xc, false);      // row_shr:8, lanes 8 .. 15
+    }
+    p[e] = __int_as_float(x);
+  }
+  return p;
+}
+
 // One tile of a head: full attention into st_full and, for a gated head (Eq. 1), the local
 // attention into st_local when the tile touches the sink or the recent range.  The scores
 // are computed once; the full update runs first because its V clearing (slots past the
@@ -93,61 +138,52 @@ __device__ __forceinline__ void process_tile(TileRegs& t, const Frag (&qb)[4], S
     tile_accumulate<true>(t, raw, st_local, tile, n_eff, kb, keep_lo, keep_from);
 }
 
-// The gated variant carries two accumulator sets: it is built for one wavefront per SIMD (the
-// configuration the library launches), which leaves it 512 registers.
-//
-// WAVES = 8 (kWholeWaves): the form for lists of whole pairs (share_plan.hip), two wavefronts per SIMD.  A launch whose
-// `grow` is -1 (one whose growth only the device knows, or a recorded decode call, replayed under other lists) takes the growth from
-// the list's header, and if the list is not of whole pairs, the upper four wavefronts have no tiles and every pair is worked as the
-// four-wavefront form does, to the bit.
-// Bound: a whole-pair launch is a chain of latencies (record, first tiles, merge, store) plus its longest pair at what
-// one CU can draw.  Decode call of 1 / 8 / 32 sequences of 300 tokens, 32 query and 8 KV heads: 7.4 / 7.4 / 8.3 us against
-// 10.6 / 10.5 / 10.7 us of shares and merge launch; 32 of 1500 tokens: 21.9 against 23.9 us.  (Four wavefronts with a tile
-// in flight behind the one in work need 450 registers; two per SIMD cover each other instead.)
-template <bool FUSED, bool GATED, bool PAGED, int WAVES>
-__global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView dv, int layer,
+// (A launch whose `grow_known` is -1 - one whose growth only the device knows, or a recorded call, replayed under other lists - takes
+// the growth from the list's header.)
+// Bound: HBM; a launch over short contexts is a chain of latencies: record, first tile (a CU takes 64 bytes a clock: eight tiles are
+// 2048), scores to products, merge.
+template <bool FUSED, bool GATED, bool PAGED>
+__global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __restrict__ list, char* __restrict__ kv_base,
                                                                 const uint16_t* __restrict__ q,
-                                                                uint16_t* __restrict__ out, float scale_log2,
                                                                 const uint16_t* __restrict__ k_new,
-                                                                const uint16_t* __restrict__ v_new, int grow_known,
-                                                                int in_turn) {
+                                                                const uint16_t* __restrict__ v_new, uint32_t shape,
+                                                                int grow_known, int window, int recent, DecodeRest r) {
   constexpr int kRow = kHeadDim + 4;                   // (the 16 heads of a store fall into different banks)
-  __shared__ floatx4 sm_o[WAVES][kMaxGroup][kRow / 4];
-  __shared__ float sm_m[WAVES][kMaxGroup];
-  __shared__ float sm_l[WAVES][kMaxGroup];
-  constexpr int kThreads = WAVES * 64;
+  __shared__ floatx4 sm_o[kWaves][kMaxGroup][kRow / 4];
+  __shared__ float2 sm_ml[kMaxGroup][kWaves];
 
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of
   // shares so that its L2 and TLBs see one compact slice of the stores.
-  const int n_wg = gridDim.x;
-  // (Not where half of the shares or more are empty, `in_turn`: the others would sit on few XCDs.)
+  const int n_wg = shape >> kShapeWgs;
+  // (Not where half of the shares or more are empty: the others would sit on few XCDs.)
+  const bool in_turn = (shape & kShapeInTurn) != 0;
   const int wg = (n_wg & 7) == 0 && !in_turn ? (blockIdx.x & 7) * (n_wg >> 3) + (blockIdx.x >> 3) : blockIdx.x;
-  const WgDesc* __restrict__ wdp = wg_desc_of(dv, layer) + wg;
-  // tokens since the list was planned: asked for beside the record, or (eight wavefronts) known to the host
-  int grow = grow_known, stride = WAVES;               // stride: wavefronts that share a segment's tiles
-  if (WAVES == kRound) {
-    grow = list_header(dv, layer)->grow;
-  } else if (grow_known < 0) {
-    grow = list_header(dv, layer)->grow;
-    if (!list_header(dv, layer)->whole) stride = kRound;
-  } else if (FUSED && blockIdx.x == 0 && threadIdx.x == 0) {
-    list_header(dv, layer)->grow = grow + 1;           // (no workgroup of this launch reads it)
-  }
-  const int u_begin = wdp->u_begin, u_end = wdp->u_end;
-  // The record this workgroup will start the next layer's launch with: asked for now, so that it is in
-  // L2 by then (its record is the first thing a workgroup waits for).  Looked at only at the very end.
-  uint32_t warm = 0;
-  if (threadIdx.x == 0 && layer + 1 < dv.n_layers)
-    warm = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(wdp) + dv.list_stride);
-  if (u_begin >= u_end) return;
-  int pi = wdp->first_pair;
-  PairDesc pd = wdp->first;
-  const PairDesc* __restrict__ pairs = pair_desc_of(dv, layer);
+  WgDesc wd = load_wg(list, wg);
+  // tokens since the list was planned: known to the host, or asked for beside the record
+  int grow = grow_known;
+  if (grow_known < 0) grow = load_const<int32_t>(list);
+  // (the other arguments in the shadow of the record: left alone the compiler asks for each where it is first used)
+  typedef __attribute__((address_space(1))) uint16_t GlobalOut;   // (a generic pointer would make flat stores of them: with one
+  GlobalOut* out = (GlobalOut*)r.out;                             // in flight every wait for a load waits for all)
+  asm volatile("" : "+s"(out), "+s"(r.scale_log2), "+s"(r.n_kv_heads), "+s"(r.list_stride), "+s"(r.pair_off));
+  if (PAGED) asm volatile("" : "+s"(r.block_table), "+s"(r.page_bytes), "+s"(r.page_shift), "+s"(r.page_mask), "+s"(r.table_stride));
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int u_begin = wd.u_begin, u_end = wd.u_end;
+  // (no workgroup of this launch reads the counter)
+  const bool advance = FUSED && grow_known >= 0 && blockIdx.x == 0 && tid == 0;
+  if (u_begin >= u_end) {
+    if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
+    return;
+  }
+  int pi = wd.first_pair, b = wd.seq, h = wd.head;
+  PairDesc pd = wd.first;
+  const char* pairs = list + r.pair_off;
+  uint32_t warm = 0;
+
   const int hd = lane & 15;     // score layout: head; operand layouts: row / column
   const int kb = lane >> 4;     // k-group of the operand layouts; slot quad of the score layout
-  const int G = dv.group;
+  const int G = shape & kShapeGroup;
 
   for (int u = u_begin; u < u_end;) {
     // segment = the units [u, seg_end) of pair pi = tiles [tile_lo, tile_hi) of its store
@@ -158,101 +194,42 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
     const int r_hi = seg_end - ps > kPairOverheadUnits ? seg_end - ps - kPairOverheadUnits : 0;
     const int tile_lo = r_lo * kRound;
     const bool whole_pair = u == ps && seg_end == pe;
-    const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
     const int n_old = pd.n_build + grow;
     const int n = FUSED ? n_old + 1 : n_old;
-    const bool full = pd.full != 0;
-    const int n_eff = full ? n : (n < dv.window ? n : dv.window);
+    const bool full = pd.ring < 0;
+    const int n_eff = full ? n : (n < window ? n : window);
     TileMap<PAGED> store;
-    store.base = dv.kv_base + pd.koff;
+    store.base = kv_base + pd.koff;
     store.paged = PAGED && full;
     if (PAGED) {
-      store.row = dv.block_table + (int64_t)b * dv.table_stride;
-      store.page_bytes = dv.page_bytes;
-      store.shift = dv.page_shift;
-      store.mask = dv.page_mask;
-      store.last = dv.table_stride - 1;
+      store.row = r.block_table + (int64_t)b * r.table_stride;
+      store.page_bytes = r.page_bytes;
+      store.shift = r.page_shift;
+      store.mask = r.page_mask;
+      store.last = r.table_stride - 1;
     }
     // the list was built with room to grow: tiles past the valid prefix are still empty
     const int tiles_valid = (n_eff + kTile - 1) / kTile;
     const int tile_hi = r_hi * kRound < tiles_valid ? r_hi * kRound : tiles_valid;
+    int tile = tile_lo + wave;
 
+    // This step's append: position n_old goes to slot_new (sink / ring / next row of a full head).  The wavefront that will read the
+    // tile with the new slot writes the row (`mine`): its loads go out first, its stores behind the first tile's loads.
+    const int sink = window - recent;
+    int slot_new = 0, tile_new = 0;
+    bool mine = false;
     if (FUSED) {
-      // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads
-      // either during this launch)
-      if (h == 0 && tile_lo == 0 && tid == 0) { len_of(dv, 0, layer)[b] = n; len_of(dv, 1, layer)[b] = n; }
-      // position n_old goes to slot_new (sink / ring / next row of a full head)
-      const int slot_new = (full || n_old < dv.sink) ? n_old : dv.sink + (n_old - dv.sink) % dv.recent;
-      const int tile_new = slot_new >> 5;
-      if (tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & (stride - 1)) == wave) {
-        // This wavefront will read the tile that holds the new slot: it writes the row first.
-        // Every 16-byte unit below is written by the lane that later loads it, so program
-        // order makes the loads see the new row.
-        const int st = slot_new & 31, hf = st >> 4;
-        char* tile_base = store.at(tile_new);
-        const int64_t src = ((int64_t)b * dv.n_kv_heads + h) * kHeadDim;
-        // (all loads of the new row first, then the stores: one memory latency instead of two in a row
-        // for the one wavefront per pair that does this, and whose workgroup waits for it at the merge)
-        const bool k_lane = hd == (st & 15);            // K: the lanes that hold row slot % 16
-        const bool v_lane = kb == ((st & 15) >> 2);     // V: the lanes that hold this slot's k-group
-        uint4 kn[4];
-        uint16_t vn[8];
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-          kn[s] = k_lane ? *reinterpret_cast<const uint4*>(k_new + src + (s * 4 + kb) * 8) : make_uint4(0, 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) vn[j] = v_lane ? v_new[src + j * 16 + hd] : (uint16_t)0;
-        if (k_lane) {
-#pragma unroll
-          for (int s = 0; s < 4; ++s) *reinterpret_cast<uint4*>(tile_base + hf * 4096 + s * 1024 + lane * 16) = kn[s];
-        }
-        if (v_lane) {
-          const int e = hf * 4 + (st & 3);
-#pragma unroll
-          for (int j = 0; j < 8; ++j)
-            *reinterpret_cast<uint16_t*>(tile_base + 8192 + j * 1024 + lane * 16 + e * 2) = vn[j];
-        }
-        if (WAVES > kRound) {
-          // (no merge kernel follows a list of whole pairs: the fp16 range test is made here; in the four-wavefront
-          // form it cost the launch 2 us)
-          bool wide = false;
-#pragma unroll
-          for (int j = 0; j < 8; ++j) wide |= bf16_beyond_fp16(vn[j]);
-          if (wide) dv.v_wide[layer] = 1;
-        }
-        if (lane == 0 && !full)
-          dv.slot_pos[dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window + slot_new] = n_old;
-      }
+      slot_new = (full || n_old < sink) ? n_old : sink + (n_old - sink) % recent;
+      tile_new = slot_new >> 5;
+      mine = tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & (kWaves - 1)) == wave;
     }
-
-    // Q as the B operand of the score MFMA: column = head, k-group kb, step s
-    Frag qb[4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      if (hd < G) {
-        const int64_t qrow = (int64_t)b * dv.n_q_heads + h * G + hd;
-        qb[s].u = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) +
-                                                  (qrow * kHeadDim + s * 32 + kb * 8) * 2);
-      } else {
-        qb[s].u = make_uint4(0, 0, 0, 0);
-      }
-    }
-    // each wavefront keeps one tile in flight behind the one it is working on
-    int tile = WAVES > kRound && wave >= stride ? tile_hi : tile_lo + wave;
-    TileRegs ra, rb;
-    if (tile < tile_hi) load_tile(ra, store.at(tile), lane);
-    // address of the tile after this one, looked up one iteration ahead.  (Paged: the compiled loop reads the table entry through
-    // a vector load and waits for it, and with it for every load before it, at the lookup.)
-    const char* next_base = store.at(tile + stride);
     // the next pair's record, for the (rare) share that crosses a pair boundary
     PairDesc pd_next = pd;
-    // (the compiler moves it to scalar registers here, which waits for the loads before it, the first tile's included)
-    if (seg_end < u_end) pd_next = pairs[pi + 1];
-
+    auto fetch_next = [&]() { if (seg_end < u_end) pd_next = load_pair(pairs, pi + 1); };
     // Eq. 1 gate: a full head with gate < 1 also accumulates its local attention (sink + recent
     // positions) over the same tiles; out = gate * full + (1 - gate) * local.
     const bool two_sets = GATED && full && pd.gate < 1.f;
-    const int keep_lo = dv.sink, keep_from = n - dv.recent;          // local: slot < S or slot >= n - R
+    const int keep_lo = sink, keep_from = n - recent;                 // local: slot < S or slot >= n - R
     Softmax st[GATED ? 2 : 1];
 #pragma unroll
     for (int k = 0; k < (GATED ? 2 : 1); ++k) {
@@ -261,54 +238,98 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
 #pragma unroll
       for (int j = 0; j < 8; ++j) st[k].o[j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
-    // Two register images that swap roles, and the last tile of the segment outside the steady state: inside it the loads of the
-    // next tile are unconditional.  As compiled, the second half of the loop waits for its own tile only, the next tile's 16 loads in
-    // flight beside it (`vmcnt(16)`); between the second half and the first the image is copied from one set of registers
-    // to the other with 8 loads left, and the next tile is asked for with 2 left (fused: 0), since its addresses take registers
-    // that loads still fill.  (With one loop and a conditional load every half waited for all loads, the next tile's included.)
-    auto work = [&](TileRegs& t, int tl) {
-      process_tile<GATED>(t, qb, st[0], st[GATED ? 1 : 0], two_sets, tl, n_eff, scale_log2, kb, keep_lo, keep_from,
-                          [] {});
-    };
-    if constexpr (WAVES > kRound || GATED || PAGED) {
-      // One image, refilled as it is used up - K behind the scores, V behind the products: half the registers, which
-      // eight wavefronts and two accumulator sets need, and faster where the next tile's address comes out of a table.
-      // (Gated, 16 sequences of 3000 .. 5000 tokens: 30.8 us against 32.2 with a copy per tile from the image in flight,
-      // 63 with two images; paged, 24 of 2000 .. 20 000: 46.9 against 51.4 us with two images.  Contiguous stores: the
-      // same for a plain launch, a 28-layer fused step 1170 against 1165 us.)  As compiled, all of these loops but the fused one
-      // that blends wait for V too before the scores, which need K only.
-      for (; tile + stride < tile_hi; tile += stride) {
+    if (tile < tile_hi) {
+      uint4 kn[4];
+      uint32_t vn[8];
+      if (FUSED && mine) {
+        // K: the lanes that hold row slot % 16 need it; V: the lanes that hold this slot's k-group
+        const int64_t src = (int64_t)pi * kHeadDim;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) kn[s] = *reinterpret_cast<const uint4*>(k_new + src + (s * 4 + kb) * 8);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) vn[j] = v_new[src + j * 16 + hd];
+      }
+
+      // Q as the B operand of the score MFMA: column = head, k-group kb, step s (columns past the group repeat its last head;
+      // nobody reads them)
+      Frag qb[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        qb[s].u = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) +
+                                                  (((int64_t)pi * G + (hd < G ? hd : G - 1)) * kHeadDim + s * 32 + kb * 8) * 2);
+      // each wavefront keeps one tile in flight behind the one it is working on
+      TileRegs ra;
+      load_tile(ra, store.at(tile), lane);
+      // address of the tile after this one, looked up one iteration ahead
+      const char* next_base = store.at(tile + kWaves);
+      fetch_next();
+      // The record this workgroup will start the next layer's launch with: asked for now, so that it is in
+      // L2 by then (its record is the first thing a workgroup waits for).  Looked at only at the very end.
+      if (u == u_begin && (shape & kShapeMore) && wave == 0)
+        warm = *reinterpret_cast<const uint32_t*>(list + r.list_stride + sizeof(ListHeader) + (int64_t)wg * (int)sizeof(WgDesc));
+
+      if (FUSED && mine) {
+        // The row goes into the store, every 16-byte unit by the lane that later loads it (so program order makes later loads see
+        // it), and, where the tile is the one that has just been asked for, into its registers: a load behind the stores would
+        // be another memory latency for the wavefront the workgroup waits for at the merge.
+        const int st = slot_new & 31, hf = st >> 4, e = hf * 4 + (st & 3);
+        const bool k_lane = hd == (st & 15), v_lane = kb == ((st & 15) >> 2);
+        if (tile == tile_new) {
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            const uint32_t m = k_lane && hf == half ? 0xffffffffu : 0u;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+              uint4& u4 = ra.k[half][s].u;
+              u4.x = (kn[s].x & m) | (u4.x & ~m); u4.y = (kn[s].y & m) | (u4.y & ~m);
+              u4.z = (kn[s].z & m) | (u4.z & ~m); u4.w = (kn[s].w & m) | (u4.w & ~m);
+            }
+          }
+          uint32_t m[4];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) m[w] = v_lane && (e >> 1) == w ? ((e & 1) ? 0xffff0000u : 0xffffu) : 0u;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const uint32_t two = vn[j] | (vn[j] << 16);
+            uint4& u4 = ra.v[j].u;
+            u4.x = (two & m[0]) | (u4.x & ~m[0]); u4.y = (two & m[1]) | (u4.y & ~m[1]);
+            u4.z = (two & m[2]) | (u4.z & ~m[2]); u4.w = (two & m[3]) | (u4.w & ~m[3]);
+          }
+        }
+        char* tile_base = store.at(tile_new);
+        if (k_lane) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) *reinterpret_cast<uint4*>(tile_base + hf * 4096 + s * 1024 + lane * 16) = kn[s];
+        }
+        if (v_lane) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<uint16_t*>(tile_base + 8192 + j * 1024 + lane * 16 + e * 2) = (uint16_t)vn[j];
+        }
+        bool wide = false;                       // the fp16 range test, for prefill
+#pragma unroll
+        for (int j = 0; j < 8; ++j) wide |= bf16_beyond_fp16(vn[j]);
+        if (wide) *r.v_wide = 1;
+        if (lane == 0 && !full) r.slot_pos[((int64_t)pd.ring * r.batch + b) * window + slot_new] = n_old;
+      }
+
+      // One image, refilled as it is used up: K behind the scores, V behind the products.  Every wait is for its own registers only, the
+      // refills behind them in flight.
+      for (; tile + kWaves < tile_hi; tile += kWaves) {
         const char* refill = next_base;
-        next_base = store.at(tile + 2 * stride);
-        process_tile<GATED>(ra, qb, st[0], st[GATED ? 1 : 0], two_sets, tile, n_eff, scale_log2, kb, keep_lo, keep_from,
+        next_base = store.at(tile + 2 * kWaves);
+        process_tile<GATED>(ra, qb, st[0], st[GATED ? 1 : 0], two_sets, tile, n_eff, r.scale_log2, kb, keep_lo, keep_from,
                             [&] { load_tile_k(ra, refill, lane); });
         load_tile_v(ra, refill, lane);
       }
-      if (tile < tile_hi) work(ra, tile);
-    } else
-    for (;;) {
-      if (tile + stride >= tile_hi) {
-        if (tile < tile_hi) work(ra, tile);
-        break;
-      }
-      load_tile(rb, next_base, lane);
-      next_base = store.at(tile + 2 * stride);
-      work(ra, tile);
-      tile += stride;
-      if (tile + stride >= tile_hi) {
-        work(rb, tile);
-        break;
-      }
-      load_tile(ra, next_base, lane);
-      next_base = store.at(tile + 2 * stride);
-      work(rb, tile);
-      tile += stride;
+      process_tile<GATED>(ra, qb, st[0], st[GATED ? 1 : 0], two_sets, tile, n_eff, r.scale_log2, kb, keep_lo, keep_from, [] {});
+    } else {
+      fetch_next();
     }
 
-    // Merge of the wavefronts: four outputs of a head per thread, so that all of a group of 8 heads are one pass of 256 threads.
-    // (With one output per thread and pass, and O instead of O^T in the accumulators - four times the LDS stores here, shuffles in every
-    // rescaling - a 28-layer step of 16 x 16 384 tokens took 1187 us, now 1153; blending heads, 16 x 3000 .. 5000, 31.1 us, now 28.7;
-    // 24 paged sequences of 2000 .. 20 000 47.1, now 46.6; 32 of 4000 .. 32 000 185, now 185.)
+    // Merge of the wavefronts: four outputs of a head per thread.  The accumulators are packed first, so that a store to LDS is of
+    // 64 lanes where the group is small (of 4 heads, 16 lanes hold a head: eight stores a wavefront, 16 clocks each and more
+    // whatever the lanes, were 1150 clocks of the merge).
     constexpr int kPasses = kMaxGroup * kHeadDim / 4 / kThreads;
     floatx4 held[kPasses];                                             // full-attention results of a whole pair
 #pragma unroll
@@ -318,9 +339,17 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
       const TwoValues l16 = swap16(ss.l);
       const TwoValues l32 = swap32(l16.a + l16.b);
 
-      __syncthreads();   // the previous merge has finished reading LDS
-      if (hd < G) {
-        if (kb == 0) { sm_m[wave][hd] = ss.m; sm_l[wave][hd] = l32.a + l32.b; }
+      if (u != u_begin || set > 0) __syncthreads();   // the previous merge has finished reading LDS
+      if (kb == 0) sm_ml[hd][wave] = make_float2(ss.m, l32.a + l32.b);
+      if (G <= 4) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          sm_o[wave][hd & 3][(t * 4 + (hd >> 2)) * 4 + kb] = pack_lanes<4>(ss.o[t * 4], ss.o[t * 4 + 1], ss.o[t * 4 + 2], ss.o[t * 4 + 3]);
+      } else if (G <= 8) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          sm_o[wave][hd & 7][(t * 2 + (hd >> 3)) * 4 + kb] = pack_lanes<8>(ss.o[t * 2], ss.o[t * 2 + 1], ss.o[t * 2], ss.o[t * 2]);
+      } else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) sm_o[wave][hd][j * 4 + kb] = ss.o[j];
       }
@@ -329,16 +358,22 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
       for (int it = 0; it < kPasses; ++it) {
         const int idx = tid + it * kThreads, g = idx >> 5, d4 = idx & 31;
         if (g >= G) break;
-        float M = sm_m[0][g];
+        float2 ml[kWaves];
+        floatx4 o[kWaves];
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) M = fmaxf(M, sm_m[w][g]);
+        for (int w = 0; w < kWaves; ++w) ml[w] = sm_ml[g][w];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) o[w] = sm_o[w][g][d4];
+        float M = ml[0].x;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) M = fmaxf(M, ml[w].x);
         floatx4 O = floatx4{0.f, 0.f, 0.f, 0.f};
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) {
-          const float sc = exp2_or_zero(sm_m[w][g], M);
-          O += sc * sm_o[w][g][d4];
-          L += sc * sm_l[w][g];
+        for (int w = 0; w < kWaves; ++w) {
+          const float sc = exp2_or_zero(ml[w].x, M);
+          O += sc * o[w];
+          L += sc * ml[w].y;
         }
         if (whole_pair) {
           floatx4 res = O / L;
@@ -346,10 +381,11 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
             if (set == 0) { held[it] = res; continue; }
             res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
-          uint16_t* dst = out + ((int64_t)b * dv.n_q_heads + h * G + g) * kHeadDim + d4 * 4;
+          GlobalOut* dst = out + ((int64_t)pi * G + g) * kHeadDim + d4 * 4;
           const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
-          if ((reinterpret_cast<uintptr_t>(out) & 7) == 0) {            // (a caller's may start at any element)
-            *reinterpret_cast<uint2*>(dst) = four;
+          if (((uintptr_t)out & 7) == 0) {                             // (a caller's may start at any element)
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            *(__attribute__((address_space(1))) u32x2*)dst = u32x2{four.x, four.y};
           } else {
             dst[0] = (uint16_t)four.x;
             dst[1] = (uint16_t)(four.x >> 16);
@@ -358,48 +394,61 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_mfma_kernel(DeviceView d
           }
         } else {
           const int64_t slot = (int64_t)wg + pi;
-          *reinterpret_cast<floatx4*>(dv.part_o + set * dv.part_set_o + (slot * G + g) * kHeadDim + d4 * 4) = O;
+          *reinterpret_cast<floatx4*>(r.part_o + set * r.part_set_o + (slot * G + g) * kHeadDim + d4 * 4) = O;
           if (d4 == 0) {
-            dv.part_m[set * dv.part_set_ml + slot * G + g] = M;
-            dv.part_l[set * dv.part_set_ml + slot * G + g] = L;
+            r.part_m[set * r.part_set_ml + slot * G + g] = M;
+            r.part_l[set * r.part_set_ml + slot * G + g] = L;
           }
         }
       }
     }
+    // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
+    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
     u = seg_end;
-    ++pi;
+    auto step_on = [&]() { ++pi; if (++h == r.n_kv_heads) { h = 0; ++b; } };
+    step_on();
     pd = pd_next;
     if (u < u_end)
-      while (pd.unit_end <= u) pd = pairs[++pi];       // pairs of inactive slots own no units
+      while (pd.unit_end <= u) { step_on(); pd = load_pair(pairs, pi); }       // pairs of inactive slots own no units
   }
+  if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
   asm volatile("" ::"v"(warm));                        // keeps the load above alive
 }
 
 }  // namespace
 
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const void* q, void* out, float scale_log2,
-                              const void* k_new, const void* v_new, bool whole, int grow, bool few, hipStream_t stream,
+                              const void* k_new, const void* v_new, int grow, bool in_turn, hipStream_t stream,
                               hipEvent_t ev_start, hipEvent_t ev_stop) {
   const dim3 grid(dv.n_wg);
+  const char* list = dv.list_base + layer * dv.list_stride;
+  const uint32_t shape = (uint32_t)dv.group | (in_turn ? kShapeInTurn : 0u) | (layer + 1 < dv.n_layers ? kShapeMore : 0u) |
+                         ((uint32_t)dv.n_wg << kShapeWgs);
+  DecodeRest r = {};
+  r.out = (uint16_t*)out; r.scale_log2 = scale_log2; r.n_kv_heads = dv.n_kv_heads;
+  r.pair_off = dv.list_pair_off; r.batch = dv.batch; r.list_stride = dv.list_stride;
+  r.part_o = dv.part_o; r.part_m = dv.part_m; r.part_l = dv.part_l;
+  r.part_set_o = dv.part_set_o; r.part_set_ml = dv.part_set_ml;
+  r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer);
+  r.slot_pos = dv.slot_pos; r.v_wide = dv.v_wide + layer;
+  r.block_table = dv.block_table; r.page_bytes = dv.page_bytes; r.page_shift = dv.page_shift; r.page_mask = dv.page_mask;
+  r.table_stride = dv.table_stride;
   // (the plain launch when no timestamps are asked for: that form can be recorded into a graph)
-#define RLKV_LAUNCH(F, GT, PG, W)                                                                                 \
+#define RLKV_LAUNCH(F, GT, PG)                                                                                    \
   do {                                                                                                            \
-    const dim3 block(W * 64);                                                                                     \
     if (ev_start || ev_stop)                                                                                      \
-      hipExtLaunchKernelGGL((decode_mfma_kernel<F, GT, PG, W>), grid, block, 0, stream, ev_start, ev_stop, 0, dv, \
-                            layer, (const uint16_t*)q, (uint16_t*)out, scale_log2, (const uint16_t*)k_new,       \
-                            (const uint16_t*)v_new, grow, (int)(few && !whole));                                  \
+      hipExtLaunchKernelGGL((decode_mfma_kernel<F, GT, PG>), grid, dim3(kThreads), 0, stream, ev_start, ev_stop, 0, \
+                            list, dv.kv_base, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, \
+                            shape, grow, dv.window, dv.recent, r);                                                \
     else                                                                                                          \
-      hipLaunchKernelGGL((decode_mfma_kernel<F, GT, PG, W>), grid, block, 0, stream, dv, layer,                   \
-                         (const uint16_t*)q, (uint16_t*)out, scale_log2, (const uint16_t*)k_new,                  \
-                         (const uint16_t*)v_new, grow, (int)(few && !whole));                                     \
+      hipLaunchKernelGGL((decode_mfma_kernel<F, GT, PG>), grid, dim3(kThreads), 0, stream, list, dv.kv_base,      \
+                         (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, shape, grow,         \
+                         dv.window, dv.recent, r);                                                                \
   } while (0)
-#define RLKV_WAVES(F, GT, PG) do { if (whole) RLKV_LAUNCH(F, GT, PG, kWholeWaves); else RLKV_LAUNCH(F, GT, PG, kRound); } while (0)
-#define RLKV_PICK(F, GT) do { if (dv.page_shift >= 0) RLKV_WAVES(F, GT, true); else RLKV_WAVES(F, GT, false); } while (0)
+#define RLKV_PICK(F, GT) do { if (dv.page_shift >= 0) RLKV_LAUNCH(F, GT, true); else RLKV_LAUNCH(F, GT, false); } while (0)
   if (k_new) { if (gated) RLKV_PICK(true, true); else RLKV_PICK(true, false); }
   else       { if (gated) RLKV_PICK(false, true); else RLKV_PICK(false, false); }
 #undef RLKV_PICK
-#undef RLKV_WAVES
 #undef RLKV_LAUNCH
   return hipGetLastError();
 }

@@ -136,7 +136,7 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
     const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
     const int n_old = pd.n_build + grow;
     const int n = FUSED ? n_old + 1 : n_old;
-    const bool full = pd.full != 0;
+    const bool full = pd.ring < 0;
     const int n_eff = full ? n : (n < dv.window ? n : dv.window);
     char* kst = dv.kv_base + pd.koff;
     char* vst = kst + (int64_t)pd.cap * dv.row_bytes;
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
           }
         }
         if (lane == 0 && !full)
-          dv.slot_pos[dv.slotpos_off[layer * dv.n_kv_heads + h] + (int64_t)b * dv.window + slot_new] = n_old;
+          dv.slot_pos[((int64_t)pd.ring * dv.batch + b) * dv.window + slot_new] = n_old;
       }
     }
 

@@ -138,8 +138,7 @@ __device__ __forceinline__ void softmax_pv(const TileRegs& t, const float (&sc)[
 // Where the tiles of one pair's store live.  Contiguous store: tile t at base + t * 16 KiB.
 // Paged full head (PAGED; Sec. 4.3): base is the head's pool and the sequence's block-table row
 // names the page of every run of 2^shift tiles.  The tile index is the same in all lanes of a
-// wavefront; the entry nevertheless comes through a vector load (in a kernel that stores, the compiler takes the table for
-// possibly changed) and the address is a lane's own value.
+// wavefront and no attention kernel writes the table: its entry comes by a scalar load, which waits for no load of K or V.
 template <bool PAGED>
 struct TileMap {
   char* base;
@@ -151,7 +150,7 @@ struct TileMap {
     if (PAGED && paged) {
       int idx = __builtin_amdgcn_readfirstlane(tile) >> shift;
       idx = idx < last ? idx : last;      // look-ahead may run past the row: stay inside it
-      return base + row[idx] * page_bytes + (int64_t)(tile & mask) * kTileBytes;
+      return base + load_const<int32_t>(row + idx) * page_bytes + (int64_t)(tile & mask) * kTileBytes;
     }
     return base + (int64_t)tile * kTileBytes;
   }

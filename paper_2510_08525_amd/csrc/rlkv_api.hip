@@ -157,6 +157,7 @@ struct rlkv_cache {
   rlkv_config_t cfg;
   std::vector<uint8_t> mask;        // host copy [L][Hkv]
   std::vector<int32_t> max_len;     // host copy [B]
+  std::vector<int32_t> ring_index;  // [L][Hkv] number of a compressed (layer, head) among all of them
   std::vector<int32_t> len_host;    // host mirror of the lengths [L][B]
   std::vector<int32_t> wl_slack;    // [L] tokens the layer's work list is still valid for; -1 = rebuild
   std::vector<int32_t> list_grow;   // [L] tokens since the layer's work list was planned (steps prepared included)
@@ -304,6 +305,8 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
   const int L = cfg->n_layers, H = cfg->n_kv_heads, B = cfg->batch;
   c->mask.assign(cfg->full_mask, cfg->full_mask + (size_t)L * H);
   c->max_len.assign(cfg->max_len, cfg->max_len + B);
+  c->ring_index.assign((size_t)L * H, 0);
+  for (int i = 0, n = 0; i < L * H; ++i) c->ring_index[i] = c->mask[i] ? 0 : n++;
   c->len_host.assign((size_t)L * B, 0);
   c->wl_slack.assign((size_t)L, -1);
   c->list_grow.assign((size_t)L, 0);
@@ -722,7 +725,6 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   WgDesc* wd = reinterpret_cast<WgDesc*>(base + sizeof(ListHeader));
   PairDesc* pd = reinterpret_cast<PairDesc*>(base + dv.list_pair_off);
   memset(hd, 0, sizeof(ListHeader));          // grow = 0: the lengths in the records are the current ones
-  hd->whole = whole ? 1 : 0;
   int32_t us = 0;
   for (int pi = 0; pi < n_pairs; ++pi) {
     const int b = pi / H, h = pi % H;
@@ -735,7 +737,7 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
     us += rounds[pi] ? rounds[pi] + kPairOverheadUnits : 0;
     d.unit_end = us;
     d.wg_first = seg_first[pi];
-    d.full = full ? 1 : 0;
+    d.ring = full ? -1 : cache->ring_index[(size_t)layer * H + h];
     d.gate = full ? cache->gate[(size_t)layer * H + h] : 1.f;
     d.n_seg = seg_count[pi];
     if (!cache->merge_words.empty())
@@ -750,10 +752,13 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
     if (d.u_begin >= d.u_end) {
       d.first_pair = 0;
       d.u_begin = d.u_end = 0;
-      d.first = PairDesc{0, 0, 0, 0, 0, 0, 0, 1.f, 0};
+      d.seq = d.head = 0;
+      d.first = PairDesc{0, 0, 0, 0, 0, 0, -1, 1.f, 0};
     } else {
       while (pd[pi].unit_end <= d.u_begin) ++pi;      // the pair that holds the share's first unit
       d.first_pair = pi;
+      d.seq = pi / H;
+      d.head = pi % H;
       d.first = pd[pi];
     }
   }
@@ -823,7 +828,7 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   const int grow = !whole || capturing || cache->step_ready[layer] ? -1 : cache->list_grow[layer];
   const bool few = 2 * cache->list_used[layer] <= dv.n_wg && !capturing;
   hipError_t e = dv.kernel == RLKV_KERNEL_MFMA
-                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, whole, grow, few, s, e0, e1)
+                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, grow, few && !whole, s, e0, e1)
                      : launch_decode_valu(dv, layer, q, out, scale_log2, nullptr, nullptr, grow, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
@@ -832,7 +837,7 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   // (the merge kernel of a recorded launch reads the pair records of the list it runs under from memory)
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * dv.n_pairs;
-  if (launch_combine(dv, layer, out, s, 0, nullptr, words, capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
+  if (launch_combine(dv, layer, out, s, 0, words, capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
     return RLKV_ERR_HIP;
   return RLKV_OK;
 }
@@ -984,7 +989,7 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   const int grow = whole && grow_known ? cache->list_grow[layer] - 1 : -1;
   const bool few = !capturing && 2 * cache->list_used[layer] <= cache->dv.n_wg;
   const hipError_t e = tiled ? launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v,
-                                                  whole, grow, few, s, e0, e1)
+                                                  grow, few && !whole, s, e0, e1)
                              : launch_decode_valu(cache->dv, layer, q, out, scale_log2, k, v, grow, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
@@ -993,9 +998,7 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   // from memory instead of taking them as arguments)
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * cache->dv.n_pairs;
-  // (the merge kernel of the tiled layout also looks at the appended V rows, for the fp16 range flag of prefill)
-  if (launch_combine(cache->dv, layer, out, s, 1, tiled ? v : nullptr, words,
-                     capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
+  if (launch_combine(cache->dv, layer, out, s, 1, words, capturing ? 0 : cache->list_partials[layer]) != hipSuccess)
     return RLKV_ERR_HIP;
   return RLKV_OK;
 }

@@ -14,12 +14,11 @@ constexpr int kHeadDim = 128;      // the only head_dim the kernels are written 
 constexpr int kMaxGroup = 16;      // query heads per KV head
 constexpr int kMaxWorkgroups = 2048;  // upper bound of the split-K grid (sizes the scratch)
 constexpr int kBlock = 256;        // threads per workgroup (4 wavefronts)
-constexpr int kRound = 4;          // tiles per scheduling unit: one tile for each wavefront of a workgroup
+constexpr int kRound = 4;          // tiles per scheduling unit (one for each wavefront of a row-major workgroup, half a round of a tiled one)
 constexpr int kPairOverheadUnits = 1;  // units at the head of every pair that carry no tiles (a label for its start)
 constexpr int kRoundCost = 2;          // cost model of the share partition, in half rounds: one round of tiles ...
 constexpr int kPairStartCost = 3;      // ... and the start of a pair (pipeline restart on a new store, Q load,
                                        // merge, output write): about 1.5 rounds, from per-workgroup timestamps
-constexpr int kWholeWaves = 8;         // wavefronts of a workgroup that works one whole pair of the tiled layout
 constexpr int kWorklistSlack = 32; // tokens a work list stays valid for after it was built
 
 // Work-list records, written by the host (share_plan.hip, ensure_worklist) and read by the attention and merge
@@ -33,8 +32,7 @@ struct ListHeader {      // 64 bytes
                          // pairs that has none, the attention kernel itself), a uniform multi-token append by its
                          // token count, so that a decode launch needs no per-step argument and a captured step can
                          // be replayed
-  int32_t whole;         // 1: every share is one whole pair (plan_whole_pairs)
-  int32_t pad[14];
+  int32_t pad[15];
 };
 struct PairDesc {        // 40 bytes
   int64_t koff;          // byte offset of the pair's K store from kv_base
@@ -44,16 +42,20 @@ struct PairDesc {        // 40 bytes
   int32_t unit_end;      // one past its last unit.  The first kPairOverheadUnits units of a pair hold
                          // no tiles; every later unit is kRound consecutive tiles of its store
   int32_t wg_first;      // first workgroup that holds units of the pair; its partial slots are wg + pair index
-  int32_t full;          // 1 = full head, 0 = compressed
+  int32_t ring;          // -1 = full head; of a compressed one its number among the compressed (layer, head)s, which is
+                         // where its slot positions are: slot_pos + (ring * batch + sequence) * window
   float gate;            // Eq. 1 gate of a full head: out = gate * full + (1 - gate) * local; 1 = plain
   int32_t n_seg;         // workgroups that hold units of the pair (wg_first .. wg_first + n_seg - 1)
 };
-struct WgDesc {          // 56 bytes
+struct WgDesc {          // 64 bytes: one line, one scalar load
   int32_t first_pair;    // pair that holds the workgroup's first tile
   int32_t u_begin, u_end;  // the workgroup's share of units [u_begin, u_end); empty if u_begin >= u_end
-  int32_t pad;
+  int32_t seq;           // sequence and head of that pair
   PairDesc first;        // copy of pair_desc[first_pair]
+  int32_t head;
+  int32_t pad;
 };
+static_assert(sizeof(ListHeader) == 64 && sizeof(PairDesc) == 40 && sizeof(WgDesc) == 64, "the kernels load these word by word");
 
 // Everything a kernel needs to find its data; passed by value as a kernel argument.
 struct DeviceView {
@@ -173,6 +175,38 @@ __host__ __device__ inline PairDesc* pair_desc_of(const DeviceView& dv, int laye
   return reinterpret_cast<PairDesc*>(dv.list_base + layer * dv.list_stride + dv.list_pair_off);
 }
 
+// The list of a launch is not written while the launch runs, so it is read through the constant address space: scalar loads, in a
+// kernel that stores too (else the compiler takes it for possibly changed, loads it through vector registers and waits at
+// once, for every load before it as well).
+#define RLKV_CONST const __attribute__((address_space(4)))
+typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
+typedef int32_t i32x8 __attribute__((ext_vector_type(8), aligned(8)));
+typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
+template <typename T>
+__device__ __forceinline__ T load_const(const void* p) { return *(RLKV_CONST T*)(uintptr_t)p; }
+__device__ __forceinline__ PairDesc pair_from_words(const i32x8& a, int gate, int n_seg) {
+  PairDesc d;
+  d.koff = ((int64_t)a[1] << 32) | (uint32_t)a[0];
+  d.cap = a[2]; d.n_build = a[3]; d.unit_start = a[4]; d.unit_end = a[5]; d.wg_first = a[6]; d.ring = a[7];
+  d.gate = __builtin_bit_cast(float, gate); d.n_seg = n_seg;
+  return d;
+}
+__device__ __forceinline__ PairDesc load_pair(const char* pairs, int pi) {
+  const char* at = pairs + (int64_t)pi * (int)sizeof(PairDesc);
+  const i32x8 a = load_const<i32x8>(at);
+  const i32x2 b = load_const<i32x2>(at + 32);
+  return pair_from_words(a, b[0], b[1]);
+}
+__device__ __forceinline__ WgDesc load_wg(const char* list, int wg) {
+  const i32x16 r = load_const<i32x16>(list + sizeof(ListHeader) + (int64_t)wg * (int)sizeof(WgDesc));
+  WgDesc d;
+  d.first_pair = r[0]; d.u_begin = r[1]; d.u_end = r[2]; d.seq = r[3];
+  const i32x8 a = {r[4], r[5], r[6], r[7], r[8], r[9], r[10], r[11]};
+  d.first = pair_from_words(a, r[12], r[13]);
+  d.head = r[14]; d.pad = 0;
+  return d;
+}
+
 // Lengths of `layer` in copy `parity` (0 / 1).
 __host__ __device__ inline int32_t* len_of(const DeviceView& dv, int parity, int layer) {
   return dv.len + ((int64_t)parity * dv.n_layers + layer) * dv.batch;
@@ -218,10 +252,10 @@ bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, 
 hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
                               const void* k_new, const void* v_new, int grow, hipStream_t stream, hipEvent_t ev_start,
                               hipEvent_t ev_stop);
-// `few`: at most half of the list's shares hold units.  `whole`: the eight-wavefront form (right for any list, made for lists of whole pairs; with `grow` >= 0 only for those).
+// `in_turn`: shares go to the XCDs in turn instead of in contiguous runs (a list of shares at most half of which hold units).
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
                               const void* q, void* out, float scale_log2, const void* k_new, const void* v_new,
-                              bool whole, int grow, bool few, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+                              int grow, bool in_turn, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 // merge_words (host, [n_pairs], optional): per pair (first partial slot << 12) | partials, as planned for the
 // work list now on the device; with it and at most kMergeArgPairs pairs the merge kernel takes these from its
 // arguments instead of from the pair records (not for a layer with gates: their records carry more).
@@ -229,7 +263,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
 // advance: tokens to add to the layer's ListHeader::grow (1 behind a fused append + decode launch).
 constexpr int kMergeArgPairs = 512;
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
-                          const void* v_new, const uint32_t* merge_words, int most_partials);
+                          const uint32_t* merge_words, int most_partials);
 // Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):
 // appends the chunk's K/V of the full heads and stages those of the compressed heads as tiles in `staging` (staging_tiles tiles per
 // pair), writes the advanced lengths to len_out, then attends.  Where the layer has compressed heads, launch_append_rings with the

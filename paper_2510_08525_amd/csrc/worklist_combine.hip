@@ -4,6 +4,7 @@
 // (m, l, O) per pair it touches, in slot (workgroup index + pair index).  The workgroups of a pair
 // are consecutive, and this kernel walks them in ascending order, so the result is deterministic.
 #include <string.h>
+#include <type_traits>
 
 #include "rlkv_internal.h"
 
@@ -11,17 +12,20 @@ namespace rlkv {
 namespace {
 
 // One block per (pair, query head of the group), one thread per output dimension.
-// v_new (tiled bf16 caches, after a fused append + decode step): the V rows that step appended.  This
-// kernel has time to spare, so it is the one that looks whether any of them lies beyond the fp16 range
-// and raises the layer's flag for the prefill kernel (a test inside the attention kernel's append
-// cost it 2 us per launch).
+//
+// The kernel is a chain of memory latencies (words or record, partials, output) and little else: what it needs of the partials'
+// place is in its first arguments, which are in registers when it starts (decode_mfma.hip), every load of a pair is asked for before
+// anything is waited for, and the usual case, a handful of partials, has neither LDS nor a barrier.
 //
 // IN_ARGS (a layer without gates, at most kMergeArgPairs pairs): what the kernel needs of a pair's record
 // - its first partial slot and its number of partials - comes as one word per pair among the kernel
-// arguments instead of from the record in memory, which takes one memory latency out of a kernel that
-// is a chain of three of them.
+// arguments instead of from the record in memory, which takes one memory latency out.
 struct MergeWords {
   uint32_t w[kMergeArgPairs];     // (first slot << 12) | partials
+};
+struct NoWords {};
+struct MergeRest {
+  int64_t part_set_o, part_set_ml;
 };
 //
 // MANY (some pair has more than kManyPartials): 32 loads of a pair with more than kFew partials are on their way at a time, the
@@ -30,85 +34,107 @@ struct MergeWords {
 // 18.4 -> 18.2 us; 40 partials in two sets (gates): 19.6 -> 22.9 us, hence the line.  A kernel of its own also because the
 // registers cost the usual form 0.2 us a launch.
 constexpr int kManyPartials = 64;
-constexpr int kFew = 16;
+constexpr int kFew = 16;                 // a DPP row
+
+// Maximum / sum over the 16 lanes of a row, in every lane.
+template <int CTRL>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float row_max(float x) {
+  x = fmaxf(x, row_ror<0x128>(x));
+  x = fmaxf(x, row_ror<0x124>(x));
+  x = fmaxf(x, row_ror<0x122>(x));
+  return fmaxf(x, row_ror<0x121>(x));
+}
+__device__ __forceinline__ float row_sum(float x) {
+  x += row_ror<0x128>(x);
+  x += row_ror<0x124>(x);
+  x += row_ror<0x122>(x);
+  return x + row_ror<0x121>(x);
+}
+
 template <typename T, bool IN_ARGS, bool MANY>
-__global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int layer, T* __restrict__ out,
-                                                           const uint16_t* __restrict__ v_new, MergeWords words,
-                                                           int advance) {
+__global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restrict__ all_o, const float* __restrict__ all_m,
+                                                           const float* __restrict__ all_l, T* __restrict__ out,
+                                                           char* __restrict__ list, int G, int pair_off, int advance,
+                                                           MergeRest r, std::conditional_t<IN_ARGS, MergeWords, NoWords> words) {
   __shared__ float sm_scale[kHeadDim];
   __shared__ float sm_red[2];
   const int pi = blockIdx.x, g = blockIdx.y, d = threadIdx.x;
-  // behind a fused append + decode launch: the list's growth counter follows the lengths (no kernel reads it
-  // while this one runs; the next launch that does comes after it on the stream)
-  if (advance != 0 && pi == 0 && g == 0 && d == 0) list_header(dv, layer)->grow += advance;
-  PairDesc pd;
-  if (IN_ARGS) {
+  int nseg, wg_first, n_sets = 1;
+  float gate = 1.f;
+  if constexpr (IN_ARGS) {
     const uint32_t word = words.w[pi];
-    pd.n_seg = (int32_t)(word & 0xfffu);
-    pd.wg_first = (int32_t)(word >> 12) - pi;
-    pd.full = 0;
-    pd.gate = 1.f;
+    nseg = (int32_t)(word & 0xfffu);
+    wg_first = (int32_t)(word >> 12) - pi;
   } else {
-    pd = pair_desc_of(dv, layer)[pi];
+    const PairDesc pd = load_pair(list + pair_off, pi);
+    nseg = pd.n_seg;
+    wg_first = pd.wg_first;
+    gate = pd.gate;
+    // a gated full head (Eq. 1) has two sets of partials: full attention and local attention
+    if (pd.ring < 0 && gate < 1.f) n_sets = 2;
   }
-  // The two loads of the range test are asked for here, side by side, and looked at (range_test) once the loads
-  // of the partials are on their way too; the empty asm marks the place up to which the compiler must have issued
-  // them (left alone it makes the second wait for the first, and the partials for both).
-  const bool look = v_new != nullptr && g == 0;
-  uint32_t act = 0, vn = 0;
-  if (look) {
-    act = dv.active[pi / dv.n_kv_heads];
-    vn = v_new[(int64_t)pi * kHeadDim + d];
-  }
-  auto range_test = [&]() {
-    asm volatile("" : "+v"(act), "+v"(vn));
-    if (look && act != 0 && bf16_beyond_fp16(vn)) dv.v_wide[layer] = 1;
+  // behind a fused append + decode launch: the list's growth counter follows the lengths (no kernel reads it
+  // while this one runs; the next launch that does comes after it on the stream).  An addition in memory: nothing comes back.
+  if (advance != 0 && pi == 0 && g == 0 && d == 0)
+    (void)__hip_atomic_fetch_add(reinterpret_cast<int32_t*>(list), advance, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (nseg <= 1) return;                // no units (inactive slot), or a single workgroup wrote the final output itself
+  const int64_t slot0 = (int64_t)wg_first + pi;       // partial slots of this pair are consecutive
+  const int64_t at = ((int64_t)pi * G + g) * kHeadDim + d;
+  auto emit = [&](float v) {
+    if constexpr (sizeof(T) == 4) out[at] = v;
+    else out[at] = f32_to_bf16_rne(v);
   };
-  const int nseg = pd.n_seg;
-  if (nseg <= 1) {                      // no units (inactive slot), or a single workgroup wrote the final output itself
-    range_test();
-    return;
-  }
-  const int G = dv.group;
-  const int64_t slot0 = (int64_t)pd.wg_first + pi;       // partial slots of this pair are consecutive
-  // a gated full head (Eq. 1) has two sets of partials: full attention and local attention
-  const int n_sets = (pd.full && pd.gate < 1.f) ? 2 : 1;
-  float r = 0.f;
-  for (int set = 0; set < n_sets; ++set) {
-    const float* part_m = dv.part_m + set * dv.part_set_ml;
-    const float* part_l = dv.part_l + set * dv.part_set_ml;
-    const float* part_o = dv.part_o + set * dv.part_set_o;
-    __syncthreads();
-    if (nseg <= kFew) {
-      // The usual case, a handful of partials: every load is issued before anything is waited for
-      // (this kernel is a chain of memory latencies and little else), one barrier, same ascending
-      // order of accumulation as the general path below.
-      const float* po = part_o + (slot0 * G + g) * kHeadDim + d;
-      float o[kFew];
+  if (nseg <= kFew) {
+    // Lanes 0 .. nseg - 1 of every row hold the partials' (m, l), so that each wavefront has the weights by itself; same ascending
+    // order of accumulation as the general path below.
+    const int mine = d & (kFew - 1), from = mine < nseg ? mine : 0;
+    float o[2][kFew], mw[2], lw[2];
+    auto ask = [&](int set) {
+      const int64_t ml = set * r.part_set_ml + (slot0 + from) * G + g;
+      mw[set] = all_m[ml];
+      lw[set] = all_l[ml];
+      const float* po = all_o + set * r.part_set_o + (slot0 * G + g) * kHeadDim + d;
 #pragma unroll
-      for (int j = 0; j < kFew; ++j) o[j] = j < nseg ? po[(int64_t)j * G * kHeadDim] : 0.f;
-      float mw = -INFINITY, lw = 0.f;
-      if (d < nseg) { mw = part_m[(slot0 + d) * G + g]; lw = part_l[(slot0 + d) * G + g]; }
-      if (set == 0) range_test();
-      if (d < 64) {                       // the first wavefront holds all the (m, l) pairs in lanes 0 .. nseg - 1
-        float M = mw;
+      for (int t = 0; t < kFew; t += 4) {
+        if (t >= nseg) break;
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) M = fmaxf(M, __shfl_xor(M, off));
-        const float sc = mw == -INFINITY ? 0.f : exp2f(mw - M);
-        float ls = sc * lw;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) ls += __shfl_xor(ls, off);
-        if (d < kFew) sm_scale[d] = sc;
-        if (d == 0) sm_red[0] = ls;
+        for (int j = t; j < t + 4; ++j) o[set][j] = po[(int64_t)(j < nseg ? j : 0) * G * kHeadDim];   // (weight 0 beyond nseg)
       }
-      __syncthreads();
+    };
+    auto merged = [&](int set) {
+      const float m = mine < nseg ? mw[set] : -INFINITY;
+      const float M = row_max(m);
+      const float sc = m == -INFINITY ? 0.f : exp2f(m - M);
+      const float L = row_sum(sc * (mine < nseg ? lw[set] : 0.f));
       float acc = 0.f;
 #pragma unroll
-      for (int j = 0; j < kFew; ++j) acc += sm_scale[j] * o[j];      // scale is 0 beyond nseg
-      const float res = acc / sm_red[0];
-      r = n_sets == 1 ? res : (set == 0 ? pd.gate * res : r + (1.f - pd.gate) * res);
-      continue;
+      for (int t = 0; t < kFew; t += 4) {
+        if (t >= nseg) break;
+#pragma unroll
+        for (int j = t; j < t + 4; ++j)
+          acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), j)) * o[set][j];
+      }
+      return acc / L;
+    };
+    ask(0);
+    if (!IN_ARGS && n_sets == 2) {
+      ask(1);
+      const float full = merged(0);
+      emit(gate * full + (1.f - gate) * merged(1));
+    } else {
+      emit(merged(0));
     }
+    return;
+  }
+  float res_all = 0.f;
+  for (int set = 0; set < n_sets; ++set) {
+    const float* part_m = all_m + set * r.part_set_ml;
+    const float* part_l = all_l + set * r.part_set_ml;
+    const float* part_o = all_o + set * r.part_set_o;
+    __syncthreads();
     constexpr int kDeep = MANY ? 32 : 1;
     const float* po = part_o + (slot0 * G + g) * kHeadDim + d;
     float o[kDeep];
@@ -117,7 +143,6 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       for (int j = 0; j < kDeep; ++j) o[j] = first + j < nseg ? po[(int64_t)(first + j) * G * kHeadDim] : 0.f;
     };
     if (MANY) load(0);
-    if (set == 0) range_test();
     // maximum over the partial maxima
     float M = -INFINITY;
     for (int i = d; i < nseg; i += kHeadDim) M = fmaxf(M, part_m[(slot0 + i) * G + g]);
@@ -166,31 +191,32 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(DeviceView dv, int la
       }
     }
     const float res = acc / L;
-    r = n_sets == 1 ? res : (set == 0 ? pd.gate * res : r + (1.f - pd.gate) * res);
+    res_all = n_sets == 1 ? res : (set == 0 ? gate * res : res_all + (1.f - gate) * res);
   }
-  const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
-  const int64_t o = ((int64_t)b * dv.n_q_heads + h * G + g) * kHeadDim + d;
-  if (sizeof(T) == 4) reinterpret_cast<float*>(out)[o] = r;
-  else reinterpret_cast<uint16_t*>(out)[o] = f32_to_bf16_rne(r);
+  emit(res_all);
 }
 
 }  // namespace
 
-hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance, const void* v_new,
+hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
                           const uint32_t* merge_words, int most_partials) {
   const dim3 grid(dv.n_pairs, dv.group), block(kHeadDim);
-  const uint16_t* vn = (dv.dtype != RLKV_F32 && dv.kernel == RLKV_KERNEL_MFMA) ? (const uint16_t*)v_new : nullptr;
-  MergeWords words;
+  char* list = dv.list_base + layer * dv.list_stride;
+  const MergeRest r = {dv.part_set_o, dv.part_set_ml};
   const bool in_args = merge_words != nullptr && dv.n_pairs <= kMergeArgPairs;
-  if (in_args) memcpy(words.w, merge_words, (size_t)dv.n_pairs * sizeof(uint32_t));
-#define RLKV_LAUNCH(T, IA, MN) hipLaunchKernelGGL((combine_kernel<T, IA, MN>), grid, block, 0, stream, dv, layer, (T*)out, vn, words, advance)
-#define RLKV_PICK(T)                                                                                       \
-  do {                                                                                                     \
-    if (most_partials > kManyPartials) { if (in_args) RLKV_LAUNCH(T, true, true); else RLKV_LAUNCH(T, false, true); } \
-    else                      { if (in_args) RLKV_LAUNCH(T, true, false); else RLKV_LAUNCH(T, false, false); } \
-  } while (0)
-  if (dv.dtype == RLKV_F32) RLKV_PICK(float);
-  else RLKV_PICK(uint16_t);
+#define RLKV_LAUNCH(T, IA, MN, W)                                                                                          \
+  hipLaunchKernelGGL((combine_kernel<T, IA, MN>), grid, block, 0, stream, dv.part_o, dv.part_m, dv.part_l, (T*)out, list, \
+                     dv.group, dv.list_pair_off, advance, r, W)
+#define RLKV_PICK(T, IA, W) do { if (most_partials > kManyPartials) RLKV_LAUNCH(T, IA, true, W); else RLKV_LAUNCH(T, IA, false, W); } while (0)
+  if (in_args) {
+    MergeWords words;
+    memcpy(words.w, merge_words, (size_t)dv.n_pairs * sizeof(uint32_t));
+    if (dv.dtype == RLKV_F32) RLKV_PICK(float, true, words);
+    else RLKV_PICK(uint16_t, true, words);
+  } else {
+    if (dv.dtype == RLKV_F32) RLKV_PICK(float, false, NoWords{});
+    else RLKV_PICK(uint16_t, false, NoWords{});
+  }
 #undef RLKV_PICK
 #undef RLKV_LAUNCH
   return hipGetLastError();
