@@ -28,7 +28,7 @@ HIPCC_FLAGS = [
 # The first 14 words of a kernel's arguments in scalar registers before its first instruction: of kernels whose start is a chain of
 # memory latencies (see decode_mfma.hip).
 PRELOAD = ["-mllvm", "-amdgpu-kernarg-preload-count=14"]
-EXTRA_FLAGS = {"decode_mfma.hip": PRELOAD, "worklist_combine.hip": PRELOAD,
+EXTRA_FLAGS = {"decode_mfma.hip": PRELOAD, "decode_valu.hip": PRELOAD, "worklist_combine.hip": PRELOAD,
                "prefill_mfma.hip": ["-fno-honor-nans", "-falign-loops=64"]}
 
 

@@ -1,4 +1,4 @@
-// Split-K decode attention, vector-ALU variant (row-major stores; fp32 and bf16).
+// Split-K decode attention over row-major stores (fp32, and bf16 where it is asked for).
 //
 // For every (sequence, KV head) pair the kernel computes ordinary softmax attention of
 // the G query heads of the group over the rows the store holds (paper Sec. 3.1 Eq. 1 with
@@ -7,119 +7,146 @@
 // attention does not depend on the order of the rows, so ring slots are read in slot
 // order.
 //
-// Mapping: a wavefront reads whole rows with 128-bit loads, 16 lanes per row (a 256-byte bf16 row
-// in one load, a 512-byte fp32 row in two); every lane keeps its 8 elements of Q for all heads of the group, so a
-// K/V row is loaded once per group.  (32 lanes per fp32 row, 4 elements each, took twice the reductions, exponentials and
-// batches per tile.  With one round of tiles per workgroup where the grid allows it, fp32 decode of one sequence of 1000 tokens:
-// 15.7 -> 10.7 us a call, 8 of 5000: 43.2 -> 33.4 us; with the append in the same launch, a step of one sequence of 1000
-// tokens: 18.2 -> 11.2 us.)
-// Dot products are reduced across the lanes of a row with DPP row rotations; each group
-// of lanes that shares a row index runs its own online softmax, and the streams are
-// merged at the end of the segment (lane groups by shuffles, wavefronts through LDS).
+// Mapping: a wavefront works 16 rows at a time, two rows to a load of 32 lanes with 4 columns each, with v_mfma_f32_4x4x1_16b_f32, 16
+// independent blocks (lane quads) of a 4 x 4 outer product each (products and sums in fp32), four query heads to a set:
+//   scores   block b = columns 16 (b % 8) .. + 15 of rows 2n + b / 8; A = 4 rows of K (n = 0 .. 3 or 4 .. 7), B = 4 heads of Q, one
+//            instruction per column.  As loaded, a quad's lanes hold neighbouring columns of one row (lanes of a quad in different rows
+//            take a load four times as long); a 4 x 4 transpose inside the quad gives each of them a row.
+//   output   blocks 0..7 = one row, 8..15 the next: A = V as loaded, B = the weights of 4 heads, one
+//            instruction per column of a lane: lane l holds 16 sums of head l%4, of the even rows or of the odd ones
+// The partial scores of the blocks are dealt out as they are summed: each quarter of the wavefront keeps 4 of the 16 rows.
+// With the vector ALU alone a batch of 16 rows and 4 fp32 heads was 520 instructions and 3300 clocks, which two wavefronts of a SIMD
+// do not share; now 2000, 512 of them of the matrix cores.  References of the running maxima are whole numbers, so that moving a sum
+// from one to another rounds nothing: error against 64 bits over 13 fp32 shapes 1.4e-7 .. 3.1e-7, before 1.5e-7 .. 4.7e-7, and no
+// shape's is larger.
+// Measured, before / now, us: fp32, one sequence of 1000 tokens and 16 steps, 32 query and 8 KV heads, the launch by itself 7.3 / 6.1;
+// 8 x 5000, 28 and 4 heads 38.3 / 30.2, 16 on 1 33.7 / 21.5, 32 and 8 56.2 / 53.0 (at the rate of the memory); one of 60, 16 on 1 14.9 / 8.3;
+// bf16, 16 x 16 384, 28 and 4 144 / 109, 8 x 5000, 32 and 8 32.6 / 30.0.
+#include <type_traits>
+
 #include "mfma_tile.h"
 
 namespace rlkv {
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-template <int CTRL>
-__device__ inline float dpp_mov(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-
-// Sum over the 16 lanes of a DPP row; every lane receives the total.
-__device__ inline float row_sum16(float x) {
-  x += dpp_mov<0x128>(x);  // row_ror:8
-  x += dpp_mov<0x124>(x);  // row_ror:4
-  x += dpp_mov<0x122>(x);  // row_ror:2
-  x += dpp_mov<0x121>(x);  // row_ror:1
-  return x;
-}
-
-// Element types.  `Q` is what a lane keeps of a query row (its column chunk) and `dot` the lane's part of
-// <q, k> for one K row as loaded: fp32 multiplies and adds the unpacked elements; bf16 leaves both rows packed
-// and takes two products per instruction (v_dot2c_f32_bf16: exact products, fp32 accumulation), which spares
-// the unpacking of K and half of the multiply-adds - this kernel is bound by its vector instruction count.
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// Four columns of a row, as loaded.
 template <typename T> struct Elem;
 template <> struct Elem<float> {
-  static constexpr int kChunks = 2;            // 16-byte chunks of a row per lane
-  struct Q { float f[8]; };
-  __device__ static void unpack(const uint4 (&r)[2], float* f) {
+  typedef u32x4 Four;
+  __device__ static void unpack(const Four& r, float* f) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      f[4 * i + 0] = __uint_as_float(r[i].x); f[4 * i + 1] = __uint_as_float(r[i].y);
-      f[4 * i + 2] = __uint_as_float(r[i].z); f[4 * i + 3] = __uint_as_float(r[i].w);
-    }
-  }
-  __device__ static Q query(const uint4 (&r)[2]) { Q q; unpack(r, q.f); return q; }
-  __device__ static float dot(const Q& q, const uint4 (&k)[2]) {
-    float kf[8];
-    unpack(k, kf);
-    // (a sum of its own per chunk: one chain over both loses more of the small products behind large ones)
-    float d[2] = {0.f, 0.f};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) d[e >> 2] = fmaf(q.f[e], kf[e], d[e >> 2]);
-    return d[0] + d[1];
+    for (int e = 0; e < 4; ++e) f[e] = __uint_as_float(r[e]);
   }
 };
 template <> struct Elem<uint16_t> {
-  static constexpr int kChunks = 1;
-  struct Q { uint4 packed; };
-  __device__ static void unpack(const uint4 (&rr)[1], float* f) {
-    const uint4& r = rr[0];
-    f[0] = __uint_as_float(r.x << 16); f[1] = __uint_as_float(r.x & 0xffff0000u);
-    f[2] = __uint_as_float(r.y << 16); f[3] = __uint_as_float(r.y & 0xffff0000u);
-    f[4] = __uint_as_float(r.z << 16); f[5] = __uint_as_float(r.z & 0xffff0000u);
-    f[6] = __uint_as_float(r.w << 16); f[7] = __uint_as_float(r.w & 0xffff0000u);
-  }
-  __device__ static Q query(const uint4 (&r)[1]) { return Q{r[0]}; }
-  __device__ static float dot(const Q& q, const uint4 (&kk)[1]) {
-    const uint4& k = kk[0];
-    float d = 0.f;
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.x), __builtin_bit_cast(bf16x2, k.x), d, false);
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.y), __builtin_bit_cast(bf16x2, k.y), d, false);
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.z), __builtin_bit_cast(bf16x2, k.z), d, false);
-    d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, q.packed.w), __builtin_bit_cast(bf16x2, k.w), d, false);
-    return d;
+  typedef uint32_t Four __attribute__((ext_vector_type(2)));
+  __device__ static void unpack(const Four& r, float* f) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = __uint_as_float((e & 1) ? r[e >> 1] & 0xffff0000u : r[e >> 1] << 16);
   }
 };
 
-// FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the tile with the new
-// slot writes the row before it loads the tile, every 16 bytes by the lane that later loads them.
-template <typename T, int GB, bool FUSED>
-__global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, int layer,
-                                                             const T* __restrict__ q, T* __restrict__ out,
-                                                             float scale_log2, const T* __restrict__ k_new,
-                                                             const T* __restrict__ v_new, int grow_known) {
-  constexpr int LPR = 16;                       // lanes per row
-  constexpr int EPL = kHeadDim / LPR;           // elements per lane
-  constexpr int CH = Elem<T>::kChunks;          // 16-byte chunks they come in, 16 chunks apart
-  constexpr int EPC = EPL / CH;                 // elements per chunk
-  constexpr int RPL = 64 / LPR;                 // rows per wavefront load
-  constexpr int U = 4;                          // row loads in flight per K and per V
-  constexpr int kBatches = kTile / (RPL * U);
+// 4 x 4 transpose over the lanes of each quad: lane i of x[k] receives what lane k of x[i] held.
+template <typename Four>
+__device__ __forceinline__ void quad_transpose(Four* x, int lane) {
+  const bool odd = lane & 1, high = lane & 2;
+  // (every lane takes part in an exchange: the empty asm keeps it out of a branch of the lanes that use it)
+  auto other = [](int v, auto ctrl) {
+    int x = __builtin_amdgcn_update_dpp(0, v, decltype(ctrl)::value, 0xf, 0xf, true);
+    asm("" : "+v"(x));
+    return x;
+  };
+  constexpr std::integral_constant<int, 0xb1> xor1;      // quad_perm [1,0,3,2]
+  constexpr std::integral_constant<int, 0x4e> xor2;      // quad_perm [2,3,0,1]
+#pragma unroll
+  for (int w = 0; w < (int)(sizeof(Four) / 4); ++w) {
+    int t[4];
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {
+      const int a = x[k][w], b = x[k + 1][w], ax = other(a, xor1), bx = other(b, xor1);
+      t[k] = odd ? bx : a;
+      t[k + 1] = odd ? b : ax;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int ax = other(t[k], xor2), bx = other(t[k + 2], xor2);
+      x[k][w] = high ? bx : t[k];
+      x[k + 2][w] = high ? t[k + 2] : ax;
+    }
+  }
+}
 
-  __shared__ floatx4 sm_o[4][GB][kHeadDim / 4];
-  __shared__ float sm_m[4][GB];
-  __shared__ float sm_l[4][GB];
+__device__ __forceinline__ floatx4 mfma_4x4(float a, float b, const floatx4& c) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+template <int CTRL>
+__device__ __forceinline__ float row_ror(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+constexpr uint32_t kShapeGroup = 31;           // of `shape`
+constexpr int waves_for(int sets) { return sets > 2 ? 4 : 8; }
+template <typename T>
+struct DecodeRest {
+  T* out;
+  float scale_log2;
+  int32_t n_kv_heads;
+  float *part_o, *part_m, *part_l;
+  int64_t part_set_o, part_set_ml;
+  int32_t pair_off, batch;
+  int32_t *len0, *len1;          // both copies of the layer's lengths
+  int32_t* slot_pos;
+};
+
+// NS: sets of four heads.  FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the batch of
+// rows with the new slot writes the row, every byte by the lane that loads it.
+// Of every tile two wavefronts take a batch of 16 rows each, one register image, K refilled behind the scores and V behind the
+// products; eight wavefronts, two per SIMD, up to group 8, four beyond (Q and the sums of four sets take 128 registers).  The first arguments are in registers when the kernel starts (decode_mfma.hip).
+template <typename T, int NS, bool FUSED>
+__global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(const char* __restrict__ list, char* __restrict__ kv_base,
+                                                             const T* __restrict__ q, const T* __restrict__ k_new,
+                                                             const T* __restrict__ v_new, uint32_t shape, int grow_known,
+                                                             int window, int recent, DecodeRest<T> r) {
+  using E = Elem<T>;
+  typedef typename E::Four Four;
+  constexpr int kWaves = waves_for(NS), kThreads = kWaves * 64;
+  constexpr int kBatch = 16;                    // rows of a batch
+  constexpr int kLoads = kBatch / 2;            // loads of K and of V in a batch, two rows each
+  constexpr int kBatches = kTile / kBatch;      // batches of a tile, one wavefront each
+  constexpr int kStride = kWaves / kBatches;    // tiles a workgroup works at a time
+  constexpr int kRowBytes = kHeadDim * sizeof(T);
+
+  __shared__ floatx4 sm_o[kWaves][NS * 4][kHeadDim / 4];
+  __shared__ float2 sm_ml[NS * 4][kWaves];
 
   const int wg = blockIdx.x;
-  const WgDesc* __restrict__ wdp = wg_desc_of(dv, layer) + wg;
+  const WgDesc wd = load_wg(list, wg);
   // tokens since the list was planned: known to the host, or asked for beside the record
-  const int grow = grow_known >= 0 ? grow_known : list_header(dv, layer)->grow;
-  if (FUSED && grow_known >= 0 && blockIdx.x == 0 && threadIdx.x == 0)
-    list_header(dv, layer)->grow = grow + 1;           // (no workgroup of this launch reads it)
-  const int u_begin = wdp->u_begin, u_end = wdp->u_end;
-  if (u_begin >= u_end) return;
-  int pi = wdp->first_pair;
-  PairDesc pd = wdp->first;
-  const PairDesc* __restrict__ pairs = pair_desc_of(dv, layer);
+  int grow = grow_known;
+  if (grow_known < 0) grow = load_const<int32_t>(list);
+  // (the other arguments in the shadow of the record; `out` as a global pointer, see decode_mfma.hip)
+  typedef __attribute__((address_space(1))) T GlobalOut;
+  GlobalOut* out = (GlobalOut*)r.out;
+  asm volatile("" : "+s"(out), "+s"(r.scale_log2), "+s"(r.n_kv_heads), "+s"(r.pair_off));
 
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int c = lane % LPR, rg = lane / LPR;
-  const int G = dv.group;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int u_begin = wd.u_begin, u_end = wd.u_end;
+  // (no workgroup of this launch reads the counter)
+  const bool advance = FUSED && grow_known >= 0 && blockIdx.x == 0 && tid == 0;
+  if (u_begin >= u_end) {
+    if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
+    return;
+  }
+  int pi = wd.first_pair, b = wd.seq, h = wd.head;
+  PairDesc pd = wd.first;
+  const char* pairs = list + r.pair_off;
+
+  const int hl = lane & 3;                             // head of a set
+  const int half = lane >> 5, off = (lane & 31) * 4 * (int)sizeof(T);        // loads: row of two, and bytes
+  const int s_row = ((lane >> 4) & 1) * 8 + half;      // scores: rows s_row + 2 u, u = 0 .. 3
+  const int G = shape & kShapeGroup;
+  const int sink = window - recent;
+  const int row0 = (wave % kBatches) * kBatch;         // the wavefront's batch of a tile
 
   for (int u = u_begin; u < u_end;) {
     // segment = the units [u, seg_end) of pair pi = tiles [tile_lo, tile_hi) of its store
@@ -128,262 +155,260 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
     // the first unit(s) of a pair carry no tiles (they stand for its fixed cost)
     const int r_lo = u - ps > kPairOverheadUnits ? u - ps - kPairOverheadUnits : 0;
     const int r_hi = seg_end - ps > kPairOverheadUnits ? seg_end - ps - kPairOverheadUnits : 0;
-    const int tile_lo = r_lo * kRound;
+    const int tile_lo = r_lo * wd.round_tiles;
     const bool whole_pair = u == ps && seg_end == pe;
-    PairDesc pd_next = pd;
-    if (seg_end < u_end) pd_next = pairs[pi + 1];     // (moved to scalar registers here, which waits for it)
 
-    const int b = pi / dv.n_kv_heads, h = pi % dv.n_kv_heads;
     const int n_old = pd.n_build + grow;
     const int n = FUSED ? n_old + 1 : n_old;
     const bool full = pd.ring < 0;
-    const int n_eff = full ? n : (n < dv.window ? n : dv.window);
-    char* kst = dv.kv_base + pd.koff;
-    char* vst = kst + (int64_t)pd.cap * dv.row_bytes;
+    const int n_eff = full ? n : (n < window ? n : window);
+    char* kst = kv_base + pd.koff;
+    char* vst = kst + (int64_t)pd.cap * kRowBytes;
     // the list was built with room to grow: tiles past the valid prefix are still empty
     const int tiles_valid = (n_eff + kTile - 1) / kTile;
-    const int tile_hi = r_hi * kRound < tiles_valid ? r_hi * kRound : tiles_valid;
+    const int tile_hi = r_hi * wd.round_tiles < tiles_valid ? r_hi * wd.round_tiles : tiles_valid;
+    const int tile_first = tile_lo + wave / kBatches;
 
+    // This step's append: position n_old goes to slot_new (sink / ring / next row of a full head).  The row is asked for first and
+    // written behind the loads of the wavefront's first batch.
+    int slot_new = 0;
+    bool mine = false;
+    Four kn, vn;
     if (FUSED) {
-      // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads
-      // either during this launch)
-      if (h == 0 && tile_lo == 0 && tid == 0) { len_of(dv, 0, layer)[b] = n; len_of(dv, 1, layer)[b] = n; }
-      const int slot_new = (full || n_old < dv.sink) ? n_old : dv.sink + (n_old - dv.sink) % dv.recent;
+      slot_new = (full || n_old < sink) ? n_old : sink + (n_old - sink) % recent;
       const int tile_new = slot_new / kTile;
-      if (tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & 3) == wave) {
-        if (rg == slot_new % RPL) {                        // the lanes that load row slot_new below
-          const int64_t src = ((int64_t)b * dv.n_kv_heads + h) * dv.row_bytes + c * 16;
-          const int64_t dst = (int64_t)slot_new * dv.row_bytes + c * 16;
-          uint4 kn[CH], vn[CH];
-#pragma unroll
-          for (int i = 0; i < CH; ++i) {
-            kn[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(k_new) + src + i * LPR * 16);
-            vn[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(v_new) + src + i * LPR * 16);
-          }
-#pragma unroll
-          for (int i = 0; i < CH; ++i) {
-            *reinterpret_cast<uint4*>(kst + dst + i * LPR * 16) = kn[i];
-            *reinterpret_cast<uint4*>(vst + dst + i * LPR * 16) = vn[i];
-          }
-        }
-        if (lane == 0 && !full)
-          dv.slot_pos[((int64_t)pd.ring * dv.batch + b) * dv.window + slot_new] = n_old;
+      mine = tile_new >= tile_lo && tile_new < tile_hi && (tile_new - tile_lo) % kStride == wave / kBatches &&
+             slot_new % kTile / kBatch * kBatch == row0;
+      if (mine) {
+        kn = *reinterpret_cast<const Four*>(reinterpret_cast<const char*>(k_new) + (int64_t)pi * kRowBytes + off);
+        vn = *reinterpret_cast<const Four*>(reinterpret_cast<const char*>(v_new) + (int64_t)pi * kRowBytes + off);
       }
     }
+    // Q: the block's 16 columns of head hl of every set (past the group: its last head again; nobody reads what comes of it)
+    float qf[NS][16];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int g = s * 4 + hl < G ? s * 4 + hl : G - 1;
+      const Four* src = reinterpret_cast<const Four*>(reinterpret_cast<const char*>(q) + ((int64_t)pi * G + g) * kRowBytes) + ((lane >> 2) & 7) * 4;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) E::unpack(src[k], qf[s] + 4 * k);
+    }
 
-    for (int gb = 0; gb < G; gb += GB) {
-      const int gcount = G - gb < GB ? G - gb : GB;
-      typename Elem<T>::Q qf[GB];
+    // Eq. 1 gate: a full head with gate < 1 takes a second, local pass over the tiles of this
+    // segment that hold sink or recent positions; out = gate * full + (1 - gate) * local.
+    const bool two_pass = full && pd.gate < 1.f;
+    const int keep_lo = sink, keep_from = n - recent;              // local pass: row < S or row >= n - R
+    const int sink_tiles = (keep_lo + kTile - 1) / kTile;
+    const int recent_tile0 = keep_from > 0 ? keep_from / kTile : 0;
+    constexpr int kPasses = (NS * 4 * kHeadDim / 4 + kThreads - 1) / kThreads;
+    floatx4 held[kPasses];                                         // full-pass results of a whole-pair segment
+    for (int pass = 0; pass < (two_pass ? 2 : 1); ++pass) {
+      float m[NS], l[NS];
+      floatx4 acc[NS][4];                              // [set][column of four]: D row i = columns 4 * (4 * (block % 8) + i) + e
 #pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        uint4 r[CH];
+      for (int s = 0; s < NS; ++s) {
+        m[s] = -INFINITY;
+        l[s] = 0.f;
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-          r[i] = make_uint4(0, 0, 0, 0);                   // (no such head: zeros, in either element type)
-          if (g < gcount) {
-            const int64_t qrow = (int64_t)b * dv.n_q_heads + h * G + gb + g;
-            r[i] = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(q) + qrow * dv.row_bytes + (i * LPR + c) * 16);
-          }
-        }
-        qf[g] = Elem<T>::query(r);
+        for (int e = 0; e < 4; ++e) acc[s][e] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
 
-      // Eq. 1 gate: a full head with gate < 1 takes a second, local pass over the tiles of this
-      // segment that hold sink or recent positions; out = gate * full + (1 - gate) * local.
-      const bool two_pass = full && pd.gate < 1.f;
-      const int keep_lo = dv.sink, keep_from = n - dv.recent;        // local pass: row < S or row >= n - R
-      const int sink_tiles = (keep_lo + kTile - 1) / kTile;
-      const int recent_tile0 = keep_from > 0 ? keep_from / kTile : 0;
-      constexpr int kPasses = (GB * kHeadDim / 4 + kBlock - 1) / kBlock;
-      floatx4 held[kPasses];                                         // full-pass results of a whole-pair segment
-      for (int pass = 0; pass < (two_pass ? 2 : 1); ++pass) {
-      float m[GB], l[GB], acc[GB][EPL];
+      struct Rows { Four k[kLoads], v[kLoads]; };
+      auto counts = [&](int tok) { return (tok < n_eff) & ((pass == 0) | (tok < keep_lo) | (tok >= keep_from)); };   // (no short circuits)
+      // rows are read once per step: stream them past the caches
+      auto load = [&](Four (&dst)[kLoads], const char* st, int tile) {
 #pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        m[g] = -INFINITY;
-        l[g] = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] = 0.f;
-      }
-
-      // The wavefront's rows in batches of U loads of K and of V.
-      // fp32, and groups beyond 4: one loop, one copy of its body.  bf16 up to group 4: two register images that swap roles, a
-      // batch asked for before the one ahead of it is worked on.  With the images everywhere the body stands four times,
-      // 29 to 43 KB of code at group 8, and half the registers are reached through copies.  Two images / one loop (us per
-      // call): bf16, 8 sequences of 5000 tokens, 32 query and 8 KV heads 22.1 / 27.6, group 16 (one sequence) 35.7 / 32.6; fp32,
-      // group 16, 8 of 5000 95.6 / 84.8, one of 60 23.8 / 19.0; fp32, group 4: one of 1000 tokens, a fused step 11.8 / 11.2.
-      struct Rows { uint4 k[U][CH], v[U][CH]; bool on[U]; };
-      auto load = [&](Rows& r, int tile, int bt) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int tok = tile * kTile + (bt * U + u) * RPL + rg;
-          // (no short circuits: they make a branch around every row's loads)
-          r.on[u] = (tok < n_eff) & ((pass == 0) | (tok < keep_lo) | (tok >= keep_from));
-          const int tc = r.on[u] ? tok : n_eff - 1;          // stay inside the valid prefix
-          const int64_t off = (int64_t)tc * dv.row_bytes + c * 16;
-          // rows are read once per step: stream them past the caches
-#pragma unroll
-          for (int i = 0; i < CH; ++i) {
-            const u32x4 kk = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kst + off + i * LPR * 16));
-            const u32x4 vv = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vst + off + i * LPR * 16));
-            r.k[u][i] = make_uint4(kk.x, kk.y, kk.z, kk.w);
-            r.v[u][i] = make_uint4(vv.x, vv.y, vv.z, vv.w);
-          }
+        for (int t = 0; t < kLoads; ++t) {
+          const int tok = tile * kTile + row0 + t * 2 + half;
+          const int64_t at = (int64_t)(tok < n_eff ? tok : n_eff - 1) * kRowBytes + off;       // stay inside the valid prefix
+          dst[t] = __builtin_nontemporal_load(reinterpret_cast<const Four*>(st + at));
         }
       };
-      auto work = [&](Rows& r) {
-        float s[U][GB];
+      auto work = [&](Rows& rw, int tile, auto scored) {
+        const int tok0 = tile * kTile + row0;
+        const bool ragged = tok0 + kBatch > n_eff || pass == 1;
+        float sc[NS][4];                       // [set][u]: rows s_row + 2 u of the batch
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          // (a row that does not count may be the one another wavefront is writing: nothing of it may reach a sum)
+        for (int part = 0; part < 2; ++part) {
+          Four x[4];
 #pragma unroll
-          for (int i = 0; i < CH; ++i)
-            if (FUSED && !r.on[u]) r.v[u][i] = make_uint4(0, 0, 0, 0);
+          for (int k = 0; k < 4; ++k) x[k] = rw.k[part * 4 + k];
+          quad_transpose(x, lane);
+          float kf[16];
 #pragma unroll
-          for (int g = 0; g < GB; ++g) {
-            float d = Elem<T>::dot(qf[g], r.k[u]);
-            d = row_sum16(d);
-            s[u][g] = r.on[u] ? d * scale_log2 : -INFINITY;
+          for (int k = 0; k < 4; ++k) E::unpack(x[k], kf + 4 * k);
+#pragma unroll
+          for (int s = 0; s < NS; ++s) {
+            floatx4 d[4];                      // (four sums of four columns: one chain loses more of the small products behind large ones)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) d[k] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) d[k] = mfma_4x4(kf[4 * k + e], qf[s][4 * k + e], d[k]);
+            const floatx4 sum = (d[0] + d[1]) + (d[2] + d[3]);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              if (part == 0) {
+                sc[s][u] = sum[u];
+              } else {
+                const TwoValues y = deal16(sc[s][u], sum[u]);
+                float z = y.a + y.b;
+                z += row_ror<0x128>(z);
+                z += row_ror<0x124>(z);
+                sc[s][u] = z;
+              }
+            }
           }
         }
-        float p[U][GB];
+        scored();                        // K's registers are free from here on
+        // The reference is a whole number (log2 domain): what moves a sum from one reference to another, here and in the merges, is a power
+        // of two and rounds nothing.  The scale goes into the exponent's one rounding.
+        bool on[4];
 #pragma unroll
-        for (int g = 0; g < GB; ++g) {
-          float mx = s[0][g];
+        for (int u = 0; u < 4; ++u) on[u] = !ragged || counts(tok0 + s_row + 2 * u);
+        float p[NS][4];
 #pragma unroll
-          for (int u = 1; u < U; ++u) mx = fmaxf(mx, s[u][g]);
-          const float m_new = fmaxf(m[g], mx);
+        for (int s = 0; s < NS; ++s) {
+          float mx = -INFINITY;
+#pragma unroll
+          for (int u = 0; u < 4; ++u) mx = fmaxf(mx, on[u] ? sc[s][u] * r.scale_log2 : -INFINITY);
+          const float m_new = fmaxf(m[s], __builtin_ceilf(column_max(mx)));     // (over the quarters, which hold other rows)
           const float m_ref = m_new == -INFINITY ? 0.f : m_new;
-          const float alpha = __builtin_amdgcn_exp2f(m[g] - m_ref);   // 2^-inf = 0 for a fresh stream
-          m[g] = m_new;
-          float ps_ = 0.f;
+          const float alpha = __builtin_amdgcn_exp2f(m[s] - m_ref);   // 2^-inf = 0 for a fresh stream
+          m[s] = m_new;
+          float sum = 0.f;
 #pragma unroll
-          for (int u = 0; u < U; ++u) {
-            p[u][g] = __builtin_amdgcn_exp2f(s[u][g] - m_ref);
-            ps_ += p[u][g];
+          for (int u = 0; u < 4; ++u) {
+            p[s][u] = on[u] ? __builtin_amdgcn_exp2f(fmaf(sc[s][u], r.scale_log2, -m_ref)) : 0.f;
+            sum += p[s][u];
           }
-          l[g] = l[g] * alpha + ps_;
+          l[s] = l[s] * alpha + sum;
+          if (__any(alpha != 1.f)) {
 #pragma unroll
-          for (int e = 0; e < EPL; ++e) acc[g][e] *= alpha;
+            for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
+          }
+        }
+        // (a row that does not count may be the one another wavefront is writing: nothing of it may reach a sum)
+        if (FUSED && ragged) {
+#pragma unroll
+          for (int t = 0; t < kLoads; ++t)
+            if (!counts(tok0 + t * 2 + half)) rw.v[t] = Four{};
         }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float vf[EPL];
-          Elem<T>::unpack(r.v[u], vf);
+        for (int u = 0; u < 4; ++u) {
+          float vf[2][4];
+          E::unpack(rw.v[u], vf[0]);
+          E::unpack(rw.v[4 + u], vf[1]);
 #pragma unroll
-          for (int g = 0; g < GB; ++g)
+          for (int s = 0; s < NS; ++s) {
+            const TwoValues w = swap16(p[s][u]);       // rows 2u and 2u + 1 in the halves, then 8 + 2u and 9 + 2u
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p[u][g], vf[e], acc[g][e]);
+            for (int e = 0; e < 4; ++e) acc[s][e] = mfma_4x4(vf[0][e], w.a, acc[s][e]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[s][e] = mfma_4x4(vf[1][e], w.b, acc[s][e]);
+          }
         }
       };
-      // the tile at or behind `tile` (in this wavefront's steps of 4) that this pass looks at
+      // the tile at or behind `tile` (in this wavefront's steps) that this pass looks at
       auto settle = [&](int tile) {
-        if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + 3) / 4 * 4;   // hop over the evicted middle
+        if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + kStride - 1) / kStride * kStride;   // hop over the evicted middle
         return tile;
       };
-      if constexpr (GB > 4 || sizeof(T) == 4) {
-        for (int tile = settle(tile_lo + wave); tile < tile_hi; tile = settle(tile + 4)) {
-#pragma unroll 1
-          for (int bt = 0; bt < kBatches; ++bt) {
-            Rows r;
-            load(r, tile, bt);
-            work(r);
+      int tile = settle(tile_first);
+      if (tile < tile_hi) {
+        Rows rw;
+        load(rw.k, kst, tile);
+        load(rw.v, vst, tile);
+        if (FUSED && mine && pass == 0) {
+          // the row goes into the store and, where this is its batch, into the registers: a load behind the stores would be
+          // another memory latency
+          const int in = slot_new % kBatch;
+          const bool lane_new = half == in % 2;
+          if (tile == slot_new / kTile) {
+#pragma unroll
+            for (int t = 0; t < kLoads; ++t)
+              if (lane_new && t == in / 2) { rw.k[t] = kn; rw.v[t] = vn; }
           }
-        }
-      } else {
-        int tile = settle(tile_lo + wave), bt = 0;
-        auto step_on = [&]() { if (++bt == kBatches) { bt = 0; tile = settle(tile + 4); } };
-        if (tile < tile_hi) {
-          Rows ra, rb;
-          load(ra, tile, bt);
-          for (;;) {
-            step_on();
-            if (tile >= tile_hi) { work(ra); break; }
-            load(rb, tile, bt);
-            work(ra);
-            step_on();
-            if (tile >= tile_hi) { work(rb); break; }
-            load(ra, tile, bt);
-            work(rb);
+          if (lane_new) {
+            *reinterpret_cast<Four*>(kst + (int64_t)slot_new * kRowBytes + off) = kn;
+            *reinterpret_cast<Four*>(vst + (int64_t)slot_new * kRowBytes + off) = vn;
           }
+          if (lane == 0 && !full) r.slot_pos[((int64_t)pd.ring * r.batch + b) * window + slot_new] = n_old;
         }
+        for (;;) {
+          const int next = settle(tile + kStride);
+          if (next >= tile_hi) break;
+          work(rw, tile, [&] { load(rw.k, kst, next); });
+          load(rw.v, vst, next);
+          tile = next;
+        }
+        work(rw, tile, [] {});
       }
 
-      // Merge of the wavefront's four lane groups (they hold the same columns), lane groups 16 apart first, then halves.  The columns
-      // are dealt out as they are summed - of a pair of lanes either keeps one half of its columns - so that every lane ends up with
-      // two whole sums.  (Every lane summing all eight of its columns by LDS permutes, and one output per thread and pass
-      // below, took longer by 10 % of a 1000-token prompt and 16 fp32 steps, 205.7 -> 186.6 us; a fp32 decode call, gated, 28 query
-      // and 4 KV heads, 7 x 104 tokens 19.3 -> 15.5 us, one of 33 464 tokens, 16 heads on 1, 41.4 -> 36.9 us; the same sums to the bit.)
-      static_assert(EPL == 8 && LPR == 16);
-      float part[GB][2];
+      // The halves of a wavefront (even and odd rows; one reference) are added as their columns are dealt out over them.
+      if (u != u_begin || pass > 0) __syncthreads();   // the previous merge has finished reading LDS
 #pragma unroll
-      for (int g = 0; g < GB; ++g) {
-        const TwoValues m16 = swap16(m[g]), l16 = swap16(l[g]);
-        const float M16 = fmaxf(m16.a, m16.b);
-        const float a16 = exp2_or_zero(m16.a, M16), b16 = exp2_or_zero(m16.b, M16);
-        float four[4];
+      for (int s = 0; s < NS; ++s) {
+        const TwoValues l16 = swap16(l[s]);
+        const TwoValues l32 = swap32(l16.a + l16.b);
+        if (lane < 4) sm_ml[s * 4 + hl][wave] = make_float2(m[s], l32.a + l32.b);
+        floatx4 o[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const TwoValues x = deal16(acc[g][e], acc[g][e + 4]);
-          four[e] = x.a * a16 + x.b * b16;
-        }
-        const TwoValues m32 = swap32(M16), l32 = swap32(l16.a * a16 + l16.b * b16);
-        m[g] = fmaxf(m32.a, m32.b);
-        const float a32 = exp2_or_zero(m32.a, m[g]), b32 = exp2_or_zero(m32.b, m[g]);
-        l[g] = l32.a * a32 + l32.b * b32;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const TwoValues x = deal32(four[e], four[e + 2]);
-          part[g][e] = x.a * a32 + x.b * b32;
-        }
-      }
-      __syncthreads();   // previous segment's readers are done with the LDS buffers
-      {
-        const int e = (rg & 1) * 4 + (rg >> 1) * 2;        // the lane's two columns are its group's e and e + 1
-        const int at = (e / EPC * LPR + c) * EPC + e % EPC;
-#pragma unroll
-        for (int g = 0; g < GB; ++g) {
-          *reinterpret_cast<float2*>(reinterpret_cast<float*>(sm_o[wave][g]) + at) = make_float2(part[g][0], part[g][1]);
-          if (lane == 0) { sm_m[wave][g] = m[g]; sm_l[wave][g] = l[g]; }
-        }
+          for (int e = 0; e < 4; ++e) {
+            const TwoValues x = deal32(acc[s][e][i], acc[s][e][i + 2]);
+            o[i][e] = x.a + x.b;
+          }
+        // (four columns to an entry: of the lane's block, i and, in the upper half, i + 2)
+        const int at = ((lane >> 2) & 7) * 4 + (lane >> 5) * 2;
+        sm_o[wave][s * 4 + hl][at] = o[0];
+        sm_o[wave][s * 4 + hl][at + 1] = o[1];
       }
       __syncthreads();
-      // merge the four wavefronts, four outputs of a head per thread; emit the final output or a partial for the combine pass
+      // merge the wavefronts, four outputs of a head per thread; emit the final output or a partial for the combine pass
       constexpr int kAlign = 4 * sizeof(T);                // (a caller's output may start at any element)
-      const bool out_aligned = (reinterpret_cast<uintptr_t>(out) & (kAlign - 1)) == 0;
+      const bool out_aligned = ((uintptr_t)out & (kAlign - 1)) == 0;
 #pragma unroll
       for (int it = 0; it < kPasses; ++it) {
-        const int idx = tid + it * kBlock, g = idx >> 5, d4 = idx & 31;
-        if (g >= gcount) break;
-        float M = sm_m[0][g];
+        const int idx = tid + it * kThreads, g = idx >> 5, d4 = idx & 31;
+        if (g >= G) break;
+        float2 ml[kWaves];
+        floatx4 o[kWaves];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) M = fmaxf(M, sm_m[w][g]);
+        for (int w = 0; w < kWaves; ++w) ml[w] = sm_ml[g][w];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) o[w] = sm_o[w][g][d4];
+        float M = ml[0].x;
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) M = fmaxf(M, ml[w].x);
         floatx4 O = floatx4{0.f, 0.f, 0.f, 0.f};
         float L = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const float sc = exp2_or_zero(sm_m[w][g], M);
-          O += sc * sm_o[w][g][d4];
-          L += sc * sm_l[w][g];
+        for (int w = 0; w < kWaves; ++w) {
+          const float sc = exp2_or_zero(ml[w].x, M);
+          O += sc * o[w];
+          L += sc * ml[w].y;
         }
         if (whole_pair) {
-          T* dst = out + ((int64_t)b * dv.n_q_heads + h * G + gb + g) * kHeadDim + d4 * 4;
-          floatx4 r = O / L;
+          GlobalOut* dst = out + ((int64_t)pi * G + g) * kHeadDim + d4 * 4;
+          floatx4 res = O / L;
           if (two_pass) {
-            if (pass == 0) { held[it] = r; continue; }
-            r = pd.gate * held[it] + (1.f - pd.gate) * r;
+            if (pass == 0) { held[it] = res; continue; }
+            res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
           if constexpr (sizeof(T) == 4) {
             if (out_aligned) {
-              *reinterpret_cast<floatx4*>(dst) = r;
+              *(__attribute__((address_space(1))) floatx4*)dst = res;
             } else {
 #pragma unroll
-              for (int e = 0; e < 4; ++e) dst[e] = r[e];
+              for (int e = 0; e < 4; ++e) dst[e] = res[e];
             }
           } else {
-            const uint2 four = make_uint2(bf16_pair(r[0], r[1]), bf16_pair(r[2], r[3]));
+            const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
             if (out_aligned) {
-              *reinterpret_cast<uint2*>(dst) = four;
+              *(__attribute__((address_space(1))) i32x2*)dst = i32x2{(int)four.x, (int)four.y};
             } else {
               dst[0] = (T)four.x;
               dst[1] = (T)(four.x >> 16);
@@ -393,46 +418,55 @@ __global__ __launch_bounds__(kBlock, 1) void decode_valu_kernel(DeviceView dv, i
           }
         } else {
           const int64_t slot = (int64_t)wg + pi;
-          *reinterpret_cast<floatx4*>(dv.part_o + pass * dv.part_set_o + (slot * G + gb + g) * kHeadDim + d4 * 4) = O;
+          *reinterpret_cast<floatx4*>(r.part_o + pass * r.part_set_o + (slot * G + g) * kHeadDim + d4 * 4) = O;
           if (d4 == 0) {
-            dv.part_m[pass * dv.part_set_ml + slot * G + gb + g] = M;
-            dv.part_l[pass * dv.part_set_ml + slot * G + gb + g] = L;
+            r.part_m[pass * r.part_set_ml + slot * G + g] = M;
+            r.part_l[pass * r.part_set_ml + slot * G + g] = L;
           }
         }
       }
-      }   // pass
-    }
+    }   // pass
+    // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
+    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
     u = seg_end;
-    ++pi;
-    pd = pd_next;
-    if (u < u_end)
-      while (pd.unit_end <= u) pd = pairs[++pi];       // pairs of inactive slots own no units
+    auto step_on = [&]() { ++pi; if (++h == r.n_kv_heads) { h = 0; ++b; } };
+    while (u < u_end) {
+      step_on();
+      pd = load_pair(pairs, pi);
+      if (pd.unit_end > u) break;                          // (pairs of inactive slots own no units)
+    }
   }
+  if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
 }
 
 template <typename T, bool FUSED>
 hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2, const void* k_new,
                     const void* v_new, int grow, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
-  const dim3 grid(dv.n_wg), block(kBlock);
+  const dim3 grid(dv.n_wg);
   const T *qp = (const T*)q, *kp = (const T*)k_new, *vp = (const T*)v_new;
-  T* op = (T*)out;
   const int G = dv.group;
+  const char* list = dv.list_base + layer * dv.list_stride;
+  const uint32_t shape = (uint32_t)G;
+  DecodeRest<T> r = {};
+  r.out = (T*)out; r.scale_log2 = scale_log2; r.n_kv_heads = dv.n_kv_heads;
+  r.part_o = dv.part_o; r.part_m = dv.part_m; r.part_l = dv.part_l;
+  r.part_set_o = dv.part_set_o; r.part_set_ml = dv.part_set_ml;
+  r.pair_off = dv.list_pair_off; r.batch = dv.batch;
+  r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer); r.slot_pos = dv.slot_pos;
   // (without events: the plain launch, which a stream capture can record)
-#define RLKV_LAUNCH_VALU(GB)                                                                                         \
+#define RLKV_LAUNCH_ROWS(NS)                                                                                         \
   do {                                                                                                               \
     if (e0 || e1)                                                                                                    \
-      hipExtLaunchKernelGGL((decode_valu_kernel<T, GB, FUSED>), grid, block, 0, stream, e0, e1, 0, dv, layer, qp,   \
-                            op, scale_log2, kp, vp, grow);                                                           \
+      hipExtLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED>), grid, dim3(waves_for(NS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
+                            qp, kp, vp, shape, grow, dv.window, dv.recent, r);                                       \
     else                                                                                                             \
-      hipLaunchKernelGGL((decode_valu_kernel<T, GB, FUSED>), grid, block, 0, stream, dv, layer, qp, op, scale_log2, \
-                         kp, vp, grow);                                                                              \
+      hipLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED>), grid, dim3(waves_for(NS) * 64), 0, stream, list, dv.kv_base, qp, kp, vp,   \
+                         shape, grow, dv.window, dv.recent, r);                                                      \
   } while (0)
-  if (G <= 1) RLKV_LAUNCH_VALU(1);
-  else if (G <= 2) RLKV_LAUNCH_VALU(2);
-  else if (G <= 4) RLKV_LAUNCH_VALU(4);
-  else if (G == 7) RLKV_LAUNCH_VALU(7);
-  else RLKV_LAUNCH_VALU(8);
-#undef RLKV_LAUNCH_VALU
+  if (G <= 4) RLKV_LAUNCH_ROWS(1);
+  else if (G <= 8) RLKV_LAUNCH_ROWS(2);
+  else RLKV_LAUNCH_ROWS(4);
+#undef RLKV_LAUNCH_ROWS
   return hipGetLastError();
 }
 

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "rlkv_internal.h"
@@ -698,12 +699,17 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   const int32_t* lh = cache->len_host.data() + (size_t)layer * B;
   const uint8_t* mask = cache->mask.data() + (size_t)layer * H;
   int32_t* rounds = cache->plan_rounds.data();
-  for (int pi = 0; pi < n_pairs; ++pi) {
-    const int b = pi / H, h = pi % H;
-    const int limit = mask[h] ? cache->cap_pad_host[b] : dv.window;       // what the store can ever hold
-    const int n_fut = lh[b] + kWorklistSlack < limit ? lh[b] + kWorklistSlack : limit;
-    rounds[pi] = cache->active[b] ? (n_fut + kTile * kRound - 1) / (kTile * kRound) : 0;   // inactive slots are not attended
-  }
+  auto count_rounds = [&](int tiles) {           // rounds of that many tiles; what the longest pair has, what all have
+    std::pair<int, int64_t> seen(0, 0);
+    for (int pi = 0; pi < n_pairs; ++pi) {
+      const int b = pi / H, h = pi % H;
+      const int limit = mask[h] ? cache->cap_pad_host[b] : dv.window;       // what the store can ever hold
+      const int n_fut = lh[b] + kWorklistSlack < limit ? lh[b] + kWorklistSlack : limit;
+      rounds[pi] = cache->active[b] ? (n_fut + kTile * tiles - 1) / (kTile * tiles) : 0;   // inactive slots are not attended
+      seen = {std::max(seen.first, rounds[pi]), seen.second + rounds[pi]};
+    }
+    return seen;
+  };
   int32_t* wg_begin = cache->plan_begin.data();
   int32_t* seg_first = cache->plan_first.data();
   int32_t* seg_count = cache->plan_count.data();
@@ -715,8 +721,17 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
     whole = wants_whole_pairs(dv.kernel, dv.dtype, dv.group, cache->layer_gated[layer] != 0, use == ListUse::kStep, n_wg, H, n_full,
                               dv.window, B, lh, cache->active.data());
   }
+  // fp32 rows are twice as long: a short list goes out in half rounds, one per workgroup, where the grid and the merge (32 partials
+  // in one go) take it.  (One of 1000 tokens, 8 heads, half of them compressed: 6.9 -> 6.1 us a launch; a prompt of 500 and one of
+  // 2500, 16 heads on 1, and 8 steps: 151 -> 129 us.)
+  int tiles = kRound;
+  if (!whole && dv.dtype == RLKV_F32) {
+    const auto half = count_rounds(kRound / 2);
+    if (half.second <= n_wg && half.first <= kMergeFew) tiles = kRound / 2;
+  }
+  count_rounds(tiles);
   if (whole) plan_whole_pairs(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
-  else cache->list_used[layer] = plan_shares(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count);
+  else cache->list_used[layer] = plan_shares(rounds, n_pairs, n_wg, wg_begin, seg_first, seg_count, tiles < kRound);
 
   int slot;
   char* base = ring_take(cache->list_ring, &slot);
@@ -748,7 +763,7 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
     WgDesc& d = wd[w];
     d.u_begin = wg_begin[w];
     d.u_end = wg_begin[w + 1];
-    d.pad = 0;
+    d.round_tiles = tiles;
     if (d.u_begin >= d.u_end) {
       d.first_pair = 0;
       d.u_begin = d.u_end = 0;

@@ -53,7 +53,7 @@ struct WgDesc {          // 64 bytes: one line, one scalar load
   int32_t seq;           // sequence and head of that pair
   PairDesc first;        // copy of pair_desc[first_pair]
   int32_t head;
-  int32_t pad;
+  int32_t round_tiles;   // tiles of a unit (row-major stores; kRound otherwise)
 };
 static_assert(sizeof(ListHeader) == 64 && sizeof(PairDesc) == 40 && sizeof(WgDesc) == 64, "the kernels load these word by word");
 
@@ -203,7 +203,7 @@ __device__ __forceinline__ WgDesc load_wg(const char* list, int wg) {
   d.first_pair = r[0]; d.u_begin = r[1]; d.u_end = r[2]; d.seq = r[3];
   const i32x8 a = {r[4], r[5], r[6], r[7], r[8], r[9], r[10], r[11]};
   d.first = pair_from_words(a, r[12], r[13]);
-  d.head = r[14]; d.pad = 0;
+  d.head = r[14]; d.round_tiles = r[15];
   return d;
 }
 
@@ -232,8 +232,9 @@ hipError_t launch_table_update(const DeviceView& dv, const TableUpdates& up, hip
 // Host-side plan of the shares (share_plan.hip): rounds[p] = rounds of tiles of pair p (0 = none).
 // Fills wg_begin[0 .. n_wg] (share w = units [wg_begin[w], wg_begin[w + 1])), seg_first[p] / seg_count[p]
 // (the workgroups that hold units of pair p); returns the number of workgroups used.
+// `singly`: one round per workgroup (which the grid must be able to take), whatever else.
 int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
-                int32_t* seg_count);
+                int32_t* seg_count, bool singly = false);
 // The plan of a list of whole pairs, one workgroup each (n_used of them have rounds; at most n_wg do): pairs spread evenly over
 // the shares, so that few pairs still meet all XCDs.
 void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
@@ -262,6 +263,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
 // most_partials: of any pair of the list (0 where the launch may run under another list; the kernel's form only).
 // advance: tokens to add to the layer's ListHeader::grow (1 behind a fused append + decode launch).
 constexpr int kMergeArgPairs = 512;
+constexpr int kMergeFew = 32;             // partials of a pair that the merge kernel takes in one go
 hipError_t launch_combine(const DeviceView& dv, int layer, void* out, hipStream_t stream, int advance,
                           const uint32_t* merge_words, int most_partials);
 // Prefill attention of one chunk (counts in `seqs`, the same in the grid's order in `order`, lengths before the chunk in len_in):

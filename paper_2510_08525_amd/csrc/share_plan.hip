@@ -53,7 +53,7 @@ static int deal_rounds(const int32_t* rounds, int n_pairs, int cap, int32_t* wg_
 }
 
 int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin, int32_t* seg_first,
-                int32_t* seg_count) {
+                int32_t* seg_count, bool singly) {
   int64_t cost = 0, units = 0, all_rounds = 0;
   int longest = 0;
   for (int p = 0; p < n_pairs; ++p)
@@ -71,7 +71,7 @@ int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin,
   }
   // A list that the grid takes at one round per workgroup: the shortest chain of latencies there is, as long as the merge
   // kernel still takes a pair's partials in one go (16).
-  if (all_rounds <= n_wg && longest <= 16)
+  if (singly || (all_rounds <= n_wg && longest <= 16))
     return deal_rounds(rounds, n_pairs, kPairStartCost + kRoundCost, wg_begin, seg_first, seg_count, true);
   // feasible for sure: the whole list in one workgroup; look upward from the average
   int64_t cap = (cost + n_wg - 1) / n_wg;

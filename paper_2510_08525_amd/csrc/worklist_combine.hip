@@ -6,7 +6,7 @@
 #include <string.h>
 #include <type_traits>
 
-#include "rlkv_internal.h"
+#include "mfma_tile.h"
 
 namespace rlkv {
 namespace {
@@ -34,24 +34,29 @@ struct MergeRest {
 // 18.4 -> 18.2 us; 40 partials in two sets (gates): 19.6 -> 22.9 us, hence the line.  A kernel of its own also because the
 // registers cost the usual form 0.2 us a launch.
 constexpr int kManyPartials = 64;
-constexpr int kFew = 16;                 // a DPP row
+constexpr int kFew = kMergeFew;          // two DPP rows
+static_assert(kFew == 32);
 
-// Maximum / sum over the 16 lanes of a row, in every lane.
+// Maximum / sum over 32 lanes, in every lane of them.
 template <int CTRL>
 __device__ __forceinline__ float row_ror(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
-__device__ __forceinline__ float row_max(float x) {
+__device__ __forceinline__ float max32(float x) {
   x = fmaxf(x, row_ror<0x128>(x));
   x = fmaxf(x, row_ror<0x124>(x));
   x = fmaxf(x, row_ror<0x122>(x));
-  return fmaxf(x, row_ror<0x121>(x));
+  x = fmaxf(x, row_ror<0x121>(x));
+  const TwoValues y = swap16(x);
+  return fmaxf(y.a, y.b);
 }
-__device__ __forceinline__ float row_sum(float x) {
+__device__ __forceinline__ float sum32(float x) {
   x += row_ror<0x128>(x);
   x += row_ror<0x124>(x);
   x += row_ror<0x122>(x);
-  return x + row_ror<0x121>(x);
+  x += row_ror<0x121>(x);
+  const TwoValues y = swap16(x);
+  return y.a + y.b;
 }
 
 template <typename T, bool IN_ARGS, bool MANY>
@@ -88,7 +93,7 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restri
     else out[at] = f32_to_bf16_rne(v);
   };
   if (nseg <= kFew) {
-    // Lanes 0 .. nseg - 1 of every row hold the partials' (m, l), so that each wavefront has the weights by itself; same ascending
+    // Lanes 0 .. nseg - 1 of either half hold the partials' (m, l), so that each wavefront has the weights by itself; same ascending
     // order of accumulation as the general path below.
     const int mine = d & (kFew - 1), from = mine < nseg ? mine : 0;
     float o[2][kFew], mw[2], lw[2];
@@ -106,9 +111,9 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restri
     };
     auto merged = [&](int set) {
       const float m = mine < nseg ? mw[set] : -INFINITY;
-      const float M = row_max(m);
+      const float M = max32(m);
       const float sc = m == -INFINITY ? 0.f : exp2f(m - M);
-      const float L = row_sum(sc * (mine < nseg ? lw[set] : 0.f));
+      const float L = sum32(sc * (mine < nseg ? lw[set] : 0.f));
       float acc = 0.f;
 #pragma unroll
       for (int t = 0; t < kFew; t += 4) {
