@@ -39,12 +39,12 @@
 // depends on the write, and where the tile is the first one, asked for already, the row goes into its registers as well.  No
 // workgroup reads a length from the table: a pair's length is its length when the work list was
 // planned plus the list's growth counter (ListHeader::grow), which no workgroup writes while another
-// one reads it, so the kernel needs no grid-wide fence: under a list of shares every workgroup reads
-// the counter and the merge kernel that follows advances it - no per-step argument, and a captured
-// launch can be replayed; under a list of whole pairs, which has no merge kernel, the count comes as an
+// one reads it, so the kernel needs no grid-wide fence: with a merge kernel behind it every workgroup reads
+// the counter and that kernel advances it - no per-step argument, and a captured
+// launch can be replayed; without one (whole pairs, or partials merged here, share_merge.h) the count comes as an
 // argument, nobody reads the counter, and the first workgroup writes it.  The new lengths are written
 // to both copies of the length table for the kernels that do read it.
-#include "mfma_tile.h"
+#include "share_merge.h"
 
 namespace rlkv {
 namespace {
@@ -58,8 +58,7 @@ struct DecodeRest {
   uint16_t* out;
   float scale_log2;
   int32_t n_kv_heads;
-  float *part_o, *part_m, *part_l;
-  int64_t part_set_o, part_set_ml;
+  Partials part;
   int64_t list_stride;
   int32_t pair_off, batch;
   int32_t *len0, *len1;          // both copies of the layer's lengths
@@ -151,6 +150,8 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
   constexpr int kRow = kHeadDim + 4;                   // (the 16 heads of a store fall into different banks)
   __shared__ floatx4 sm_o[kWaves][kMaxGroup][kRow / 4];
   __shared__ float2 sm_ml[kMaxGroup][kWaves];
+  __shared__ float sm_w[kMaxGroup][kMergeFew];
+  __shared__ LeftPair sm_left[2];                      // (in LDS only to spare registers)
 
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of
   // shares so that its L2 and TLBs see one compact slice of the stores.
@@ -179,11 +180,24 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
   int pi = wd.first_pair, b = wd.seq, h = wd.head;
   PairDesc pd = wd.first;
   const char* pairs = list + r.pair_off;
+  int n_left = 0;
   uint32_t warm = 0;
 
+  const int G = shape & kShapeGroup;
+  auto emit = [&](int pair, int g, int d4, const floatx4& v) {
+    GlobalOut* dst = out + ((int64_t)pair * G + g) * kHeadDim + d4 * 4;
+    const uint2 four = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+    if (((uintptr_t)out & 7) == 0) {                             // (a caller's may start at any element)
+      *(__attribute__((address_space(1))) i32x2*)dst = i32x2{(int)four.x, (int)four.y};
+    } else {
+      dst[0] = (uint16_t)four.x;
+      dst[1] = (uint16_t)(four.x >> 16);
+      dst[2] = (uint16_t)four.y;
+      dst[3] = (uint16_t)(four.y >> 16);
+    }
+  };
   const int hd = lane & 15;     // score layout: head; operand layouts: row / column
   const int kb = lane >> 4;     // k-group of the operand layouts; slot quad of the score layout
-  const int G = shape & kShapeGroup;
 
   for (int u = u_begin; u < u_end;) {
     // segment = the units [u, seg_end) of pair pi = tiles [tile_lo, tile_hi) of its store
@@ -340,6 +354,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
       const TwoValues l32 = swap32(l16.a + l16.b);
 
       if (u != u_begin || set > 0) __syncthreads();   // the previous merge has finished reading LDS
+      if (set == 0 && tid == 0 && !whole_pair) sm_left[n_left] = LeftPair{pi, pd.wg_first, pd.n_seg, two_sets ? pd.gate : 1.f};
       if (kb == 0) sm_ml[hd][wave] = make_float2(ss.m, l32.a + l32.b);
       if (G <= 4) {
 #pragma unroll
@@ -376,32 +391,18 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
           L += sc * ml[w].y;
         }
         if (whole_pair) {
-          floatx4 res = O / L;
+          floatx4 res = quotients(O, L);
           if (two_sets) {
             if (set == 0) { held[it] = res; continue; }
             res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
-          GlobalOut* dst = out + ((int64_t)pi * G + g) * kHeadDim + d4 * 4;
-          const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
-          if (((uintptr_t)out & 7) == 0) {                             // (a caller's may start at any element)
-            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-            *(__attribute__((address_space(1))) u32x2*)dst = u32x2{four.x, four.y};
-          } else {
-            dst[0] = (uint16_t)four.x;
-            dst[1] = (uint16_t)(four.x >> 16);
-            dst[2] = (uint16_t)four.y;
-            dst[3] = (uint16_t)(four.y >> 16);
-          }
+          emit(pi, g, d4, res);
         } else {
-          const int64_t slot = (int64_t)wg + pi;
-          *reinterpret_cast<floatx4*>(r.part_o + set * r.part_set_o + (slot * G + g) * kHeadDim + d4 * 4) = O;
-          if (d4 == 0) {
-            r.part_m[set * r.part_set_ml + slot * G + g] = M;
-            r.part_l[set * r.part_set_ml + slot * G + g] = L;
-          }
+          leave_partial(r.part, set, wg + pi, G, g, d4, O, M, L);
         }
       }
     }
+    if (!whole_pair && r.part.arrived) ++n_left;
     // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
     if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
     u = seg_end;
@@ -411,6 +412,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
     if (u < u_end)
       while (pd.unit_end <= u) { step_on(); pd = load_pair(pairs, pi); }       // pairs of inactive slots own no units
   }
+  finish_pairs<kThreads, GATED>(r.part, sm_left, n_left, G, sm_w, emit);
   if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
   asm volatile("" ::"v"(warm));                        // keeps the load above alive
 }
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
 }  // namespace
 
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const void* q, void* out, float scale_log2,
-                              const void* k_new, const void* v_new, int grow, bool in_turn, hipStream_t stream,
+                              const void* k_new, const void* v_new, int grow, bool merge_here, bool in_turn, hipStream_t stream,
                               hipEvent_t ev_start, hipEvent_t ev_stop) {
   const dim3 grid(dv.n_wg);
   const char* list = dv.list_base + layer * dv.list_stride;
@@ -427,8 +429,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const
   DecodeRest r = {};
   r.out = (uint16_t*)out; r.scale_log2 = scale_log2; r.n_kv_heads = dv.n_kv_heads;
   r.pair_off = dv.list_pair_off; r.batch = dv.batch; r.list_stride = dv.list_stride;
-  r.part_o = dv.part_o; r.part_m = dv.part_m; r.part_l = dv.part_l;
-  r.part_set_o = dv.part_set_o; r.part_set_ml = dv.part_set_ml;
+  r.part = {dv.part_o, dv.part_m, dv.part_l, dv.part_set_o, dv.part_set_ml, merge_here ? dv.arrived + (int64_t)layer * dv.n_pairs * (kMaxGroup / 2) : nullptr};
   r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer);
   r.slot_pos = dv.slot_pos; r.v_wide = dv.v_wide + layer;
   r.block_table = dv.block_table; r.page_bytes = dv.page_bytes; r.page_shift = dv.page_shift; r.page_mask = dv.page_mask;

@@ -24,7 +24,7 @@
 // bf16, 16 x 16 384, 28 and 4 144 / 109, 8 x 5000, 32 and 8 32.6 / 30.0.
 #include <type_traits>
 
-#include "mfma_tile.h"
+#include "share_merge.h"
 
 namespace rlkv {
 namespace {
@@ -79,10 +79,6 @@ __device__ __forceinline__ void quad_transpose(Four* x, int lane) {
 __device__ __forceinline__ floatx4 mfma_4x4(float a, float b, const floatx4& c) {
   return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
 }
-template <int CTRL>
-__device__ __forceinline__ float row_ror(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
 
 constexpr uint32_t kShapeGroup = 31;           // of `shape`
 constexpr int waves_for(int sets) { return sets > 2 ? 4 : 8; }
@@ -91,8 +87,7 @@ struct DecodeRest {
   T* out;
   float scale_log2;
   int32_t n_kv_heads;
-  float *part_o, *part_m, *part_l;
-  int64_t part_set_o, part_set_ml;
+  Partials part;
   int32_t pair_off, batch;
   int32_t *len0, *len1;          // both copies of the layer's lengths
   int32_t* slot_pos;
@@ -118,6 +113,8 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
 
   __shared__ floatx4 sm_o[kWaves][NS * 4][kHeadDim / 4];
   __shared__ float2 sm_ml[NS * 4][kWaves];
+  __shared__ float sm_w[NS * 4][kMergeFew];
+  __shared__ LeftPair sm_left[2];                      // (in LDS only to spare registers)
 
   const int wg = blockIdx.x;
   const WgDesc wd = load_wg(list, wg);
@@ -140,11 +137,35 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
   int pi = wd.first_pair, b = wd.seq, h = wd.head;
   PairDesc pd = wd.first;
   const char* pairs = list + r.pair_off;
+  int n_left = 0;
 
   const int hl = lane & 3;                             // head of a set
   const int half = lane >> 5, off = (lane & 31) * 4 * (int)sizeof(T);        // loads: row of two, and bytes
   const int s_row = ((lane >> 4) & 1) * 8 + half;      // scores: rows s_row + 2 u, u = 0 .. 3
   const int G = shape & kShapeGroup;
+  auto emit = [&](int pair, int g, int d4, const floatx4& v) {
+    constexpr int kAlign = 4 * sizeof(T);                // (a caller's output may start at any element)
+    const bool out_aligned = ((uintptr_t)out & (kAlign - 1)) == 0;
+    GlobalOut* dst = out + ((int64_t)pair * G + g) * kHeadDim + d4 * 4;
+    if constexpr (sizeof(T) == 4) {
+      if (out_aligned) {
+        *(__attribute__((address_space(1))) floatx4*)dst = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[e] = v[e];
+      }
+    } else {
+      const uint2 four = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
+      if (out_aligned) {
+        *(__attribute__((address_space(1))) i32x2*)dst = i32x2{(int)four.x, (int)four.y};
+      } else {
+        dst[0] = (T)four.x;
+        dst[1] = (T)(four.x >> 16);
+        dst[2] = (T)four.y;
+        dst[3] = (T)(four.y >> 16);
+      }
+    }
+  };
   const int sink = window - recent;
   const int row0 = (wave % kBatches) * kBatch;         // the wavefront's batch of a tile
 
@@ -348,6 +369,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
 
       // The halves of a wavefront (even and odd rows; one reference) are added as their columns are dealt out over them.
       if (u != u_begin || pass > 0) __syncthreads();   // the previous merge has finished reading LDS
+      if (pass == 0 && tid == 0 && !whole_pair) sm_left[n_left] = LeftPair{pi, pd.wg_first, pd.n_seg, two_pass ? pd.gate : 1.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         const TwoValues l16 = swap16(l[s]);
@@ -368,8 +390,6 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       }
       __syncthreads();
       // merge the wavefronts, four outputs of a head per thread; emit the final output or a partial for the combine pass
-      constexpr int kAlign = 4 * sizeof(T);                // (a caller's output may start at any element)
-      const bool out_aligned = ((uintptr_t)out & (kAlign - 1)) == 0;
 #pragma unroll
       for (int it = 0; it < kPasses; ++it) {
         const int idx = tid + it * kThreads, g = idx >> 5, d4 = idx & 31;
@@ -392,40 +412,18 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
           L += sc * ml[w].y;
         }
         if (whole_pair) {
-          GlobalOut* dst = out + ((int64_t)pi * G + g) * kHeadDim + d4 * 4;
-          floatx4 res = O / L;
+          floatx4 res = quotients(O, L);
           if (two_pass) {
             if (pass == 0) { held[it] = res; continue; }
             res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
-          if constexpr (sizeof(T) == 4) {
-            if (out_aligned) {
-              *(__attribute__((address_space(1))) floatx4*)dst = res;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) dst[e] = res[e];
-            }
-          } else {
-            const uint2 four = make_uint2(bf16_pair(res[0], res[1]), bf16_pair(res[2], res[3]));
-            if (out_aligned) {
-              *(__attribute__((address_space(1))) i32x2*)dst = i32x2{(int)four.x, (int)four.y};
-            } else {
-              dst[0] = (T)four.x;
-              dst[1] = (T)(four.x >> 16);
-              dst[2] = (T)four.y;
-              dst[3] = (T)(four.y >> 16);
-            }
-          }
+          emit(pi, g, d4, res);
         } else {
-          const int64_t slot = (int64_t)wg + pi;
-          *reinterpret_cast<floatx4*>(r.part_o + pass * r.part_set_o + (slot * G + g) * kHeadDim + d4 * 4) = O;
-          if (d4 == 0) {
-            r.part_m[pass * r.part_set_ml + slot * G + g] = M;
-            r.part_l[pass * r.part_set_ml + slot * G + g] = L;
-          }
+          leave_partial(r.part, pass, wg + pi, G, g, d4, O, M, L);
         }
       }
     }   // pass
+    if (!whole_pair && r.part.arrived) ++n_left;
     // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
     if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
     u = seg_end;
@@ -436,12 +434,13 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       if (pd.unit_end > u) break;                          // (pairs of inactive slots own no units)
     }
   }
+  finish_pairs<kThreads, true>(r.part, sm_left, n_left, G, sm_w, emit);
   if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
 }
 
 template <typename T, bool FUSED>
 hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2, const void* k_new,
-                    const void* v_new, int grow, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
+                    const void* v_new, int grow, bool merge_here, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid(dv.n_wg);
   const T *qp = (const T*)q, *kp = (const T*)k_new, *vp = (const T*)v_new;
   const int G = dv.group;
@@ -449,8 +448,7 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
   const uint32_t shape = (uint32_t)G;
   DecodeRest<T> r = {};
   r.out = (T*)out; r.scale_log2 = scale_log2; r.n_kv_heads = dv.n_kv_heads;
-  r.part_o = dv.part_o; r.part_m = dv.part_m; r.part_l = dv.part_l;
-  r.part_set_o = dv.part_set_o; r.part_set_ml = dv.part_set_ml;
+  r.part = {dv.part_o, dv.part_m, dv.part_l, dv.part_set_o, dv.part_set_ml, merge_here ? dv.arrived + (int64_t)layer * dv.n_pairs * (kMaxGroup / 2) : nullptr};
   r.pair_off = dv.list_pair_off; r.batch = dv.batch;
   r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer); r.slot_pos = dv.slot_pos;
   // (without events: the plain launch, which a stream capture can record)
@@ -473,13 +471,13 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
 }  // namespace
 
 hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
-                              const void* k_new, const void* v_new, int grow, hipStream_t stream, hipEvent_t ev_start,
+                              const void* k_new, const void* v_new, int grow, bool merge_here, hipStream_t stream, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
   if (dv.dtype == RLKV_F32)
-    return k_new ? launch_t<float, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop)
-                 : launch_t<float, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop);
-  return k_new ? launch_t<uint16_t, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop)
-               : launch_t<uint16_t, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, stream, ev_start, ev_stop);
+    return k_new ? launch_t<float, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop)
+                 : launch_t<float, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop);
+  return k_new ? launch_t<uint16_t, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop)
+               : launch_t<uint16_t, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop);
 }
 
 }  // namespace rlkv

@@ -22,7 +22,7 @@ inline int round_up_tile(int x) { return (x + kTile - 1) / kTile * kTile; }
 // Byte offsets of every region inside the arena.
 struct Plan {
   size_t full_mask, active, gate, store_off, cap_pad, slotpos_off, len, v_wide, slot_pos, append_cnt;
-  size_t lists, part_o, part_m, part_l, block_table, staging, prefill_split, kv;
+  size_t lists, arrived, part_o, part_m, part_l, block_table, staging, prefill_split, kv;
   size_t list_stride;        // bytes between the work-list blocks of consecutive layers
   int staging_tiles;         // staging tiles per (sequence, KV head) pair for prefill chunks
   int table_stride;          // block-table entries per sequence (0 = contiguous stores)
@@ -100,6 +100,7 @@ void make_plan(const rlkv_config_t* c, Plan* p) {
   p->append_cnt = take(2 * B * sizeof(int32_t));      // token counts, then the prefill's sequence order
   p->list_stride = list_block_bytes(kMaxWorkgroups, (int)n_pairs);
   p->lists = take(L * p->list_stride);
+  p->arrived = take(L * n_pairs * (kMaxGroup / 2) * sizeof(int32_t));           // (before part_o: zeroed with the lists)
   p->part_o = take(2 * slots * G * kHeadDim * sizeof(float));   // two sets: full / local pass of gated heads
   p->part_m = take(2 * slots * G * sizeof(float));
   p->part_l = take(2 * slots * G * sizeof(float));
@@ -382,6 +383,7 @@ rlkv_status_t rlkv_cache_create(const rlkv_config_t* cfg, rlkv_cache_t** out) {
   dv.list_base = a + p.lists;
   dv.list_stride = (int64_t)p.list_stride;
   dv.list_pair_off = (int32_t)list_pair_offset(n_wg);
+  dv.arrived = reinterpret_cast<int32_t*>(a + p.arrived);
   dv.part_o = reinterpret_cast<float*>(a + p.part_o);
   dv.part_m = reinterpret_cast<float*>(a + p.part_m);
   dv.part_l = reinterpret_cast<float*>(a + p.part_l);
@@ -825,6 +827,21 @@ static bool stream_is_capturing(hipStream_t s) {
   return st != hipStreamCaptureStatusNone;
 }
 
+// Whether the last workgroup of a pair merges its partials (share_merge.h) or a merge launch does, which spreads the heads of every
+// pair over workgroups of their own.  Inside, it costs about 2 us at the end of the attention; the launch costs 4 us of the device's
+// time and 2.8 us of the host's, which is what short lists wait for.  (us a call, merge launch / inside: one sequence of 1500 tokens, 32 on 8
+// heads, 10.7 / 5.9; 4 of 2500 10.3 / 7.5; 8 of 3000, 28 on 4 11.4 / 10.7; 8 x 8192 38.2 / 37.7.  A list of many workgroups and groups beyond 8
+// or blending heads, twice the partials a wavefront has to read: 4 of 6000, 16 on 1 10.2 / 11.3; 32 of 9000 23.4 / 24.5; 16 blending of
+// 3000 .. 5000 25.6 / 26.3; short: one of 2000, 16 on 1 10.1 / 7.4.  Row-major, four wavefronts beyond group 8: prompts of 500 and 2500, 16
+// on 1, and 8 steps 129 / 162.)  Only where the host knows the list's growth: without the merge kernel nobody could advance it while
+// workgroups read it.
+static bool merges_in_launch(const rlkv_cache_t* cache, int32_t layer) {
+  if (cache->list_whole[layer] || cache->list_partials[layer] > kMergeFew) return false;
+  const DeviceView& dv = cache->dv;
+  if (dv.group > 8 && dv.kernel != RLKV_KERNEL_MFMA) return false;
+  return (dv.group <= 8 && !cache->layer_gated[layer]) || (2 * cache->list_used[layer] <= dv.n_wg && cache->list_partials[layer] <= 16);
+}
+
 // Decode attention of one layer with the kernels looking for their tables and partials in `dv` (the cache's own
 // view, or a copy whose partials point elsewhere).
 static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv, int32_t layer, const void* q, void* out,
@@ -840,15 +857,17 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   // have run (as a replay) or not: both take the growth from the list's header.
   const bool capturing = stream_is_capturing(s);
   const bool whole = cache->list_whole[layer] != 0;
-  const int grow = !whole || capturing || cache->step_ready[layer] ? -1 : cache->list_grow[layer];
+  const bool known = !capturing && !cache->step_ready[layer];
+  const bool merge_here = known && merges_in_launch(cache, layer);
+  const int grow = known && (whole || merge_here) ? cache->list_grow[layer] : -1;
   const bool few = 2 * cache->list_used[layer] <= dv.n_wg && !capturing;
   hipError_t e = dv.kernel == RLKV_KERNEL_MFMA
-                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, grow, few && !whole, s, e0, e1)
-                     : launch_decode_valu(dv, layer, q, out, scale_log2, nullptr, nullptr, grow, s, e0, e1);
+                     ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, grow, merge_here, few && !whole, s, e0, e1)
+                     : launch_decode_valu(dv, layer, q, out, scale_log2, nullptr, nullptr, grow, merge_here, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
   ++cache->decode_calls[layer];
-  if (whole && !capturing) return RLKV_OK;       // every pair was finished by its one workgroup
+  if ((whole && !capturing) || merge_here) return RLKV_OK;       // every pair was finished by its one workgroup, or its last
   // (the merge kernel of a recorded launch reads the pair records of the list it runs under from memory)
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])
                               ? nullptr : cache->merge_words.data() + (size_t)layer * dv.n_pairs;
@@ -999,16 +1018,15 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   const bool tiled = cache->dv.kernel == RLKV_KERNEL_MFMA;
   // (a recorded launch takes the form for shares: its replays are prepared)
   const bool whole = !capturing && cache->list_whole[layer] != 0;
-  // (a list of shares has a merge kernel behind it that advances the counter; written by the attention kernel of a
-  // 28-layer step of 16 x 16384 tokens instead, it cost 0.7 us per launch)
-  const int grow = whole && grow_known ? cache->list_grow[layer] - 1 : -1;
+  const bool merge_here = !capturing && grow_known && merges_in_launch(cache, layer);
+  const int grow = grow_known && (whole || merge_here) ? cache->list_grow[layer] - 1 : -1;
   const bool few = !capturing && 2 * cache->list_used[layer] <= cache->dv.n_wg;
   const hipError_t e = tiled ? launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v,
-                                                  grow, few && !whole, s, e0, e1)
-                             : launch_decode_valu(cache->dv, layer, q, out, scale_log2, k, v, grow, s, e0, e1);
+                                                  grow, merge_here, few && !whole, s, e0, e1)
+                             : launch_decode_valu(cache->dv, layer, q, out, scale_log2, k, v, grow, merge_here, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
-  if (grow >= 0) return RLKV_OK;                 // every pair was finished by its one workgroup, the counter is advanced
+  if (grow >= 0) return RLKV_OK;                 // every pair was finished by its one workgroup or its last, the counter is advanced
   // (a recorded launch outlives the work list it was recorded under, so its merge kernel reads the pair records
   // from memory instead of taking them as arguments)
   const uint32_t* words = (capturing || cache->merge_words.empty() || cache->layer_gated[layer])

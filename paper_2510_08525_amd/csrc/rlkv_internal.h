@@ -28,8 +28,8 @@ constexpr int kWorklistSlack = 32; // tokens a work list stays valid for after i
 // one kernel (launch_fetch) that reads a pinned staging slot of the same layout.
 struct ListHeader {      // 64 bytes
   int32_t grow;          // tokens every active sequence has gained since the list was planned.  A new list brings
-                         // 0; a fused step advances it by 1 (the merge kernel behind it, or, under a list of whole
-                         // pairs that has none, the attention kernel itself), a uniform multi-token append by its
+                         // 0; a fused step advances it by 1 (the merge kernel behind it, or, where there is
+                         // none, the attention kernel itself), a uniform multi-token append by its
                          // token count, so that a decode launch needs no per-step argument and a captured step can
                          // be replayed
   int32_t pad[15];
@@ -87,6 +87,8 @@ struct DeviceView {
   float* part_m;                  // [n_wg + n_pairs][group]  (log2 domain maxima)
   float* part_l;                  // [n_wg + n_pairs][group]
   int64_t part_set_o, part_set_ml; // element offsets of the second partial set (local attention of gated heads)
+  int32_t* arrived;               // [n_layers][n_pairs][kMaxGroup / 2] workgroups that have left their partials of a pair's
+                                  // two heads, 0 between launches
   char* kv_base;                  // start of the K/V stores
 
   // Paged full heads (Sec. 4.3).  store_off of a full head is then the offset of its pool, the
@@ -247,16 +249,17 @@ bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, 
 // `gated`: some full head of the layer has a gate below 1 (two passes for those heads).
 // k_new / v_new non-null: fused single-token append (rows [batch][n_kv_heads][1][head_dim]); the advanced
 // lengths are written to both copies of the length table.
-// `grow` (lists of whole pairs): tokens since the layer's list was planned, as the host knows them; a fused launch then also
-// writes the advanced growth counter.  -1 (a launch that may be replayed, or whose count the host does not know): read from the
+// `grow` (lists of whole pairs, and with `merge_here`): tokens since the layer's list was planned, as the host knows them; a fused
+// launch then also writes the advanced growth counter.  `merge_here`: the last workgroup of a pair merges its partials, no merge launch
+// follows.  -1 (a launch that may be replayed, or whose count the host does not know): read from the
 // list's header, and a fused launch must be followed by the merge kernel with advance = 1.
 hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
-                              const void* k_new, const void* v_new, int grow, hipStream_t stream, hipEvent_t ev_start,
+                              const void* k_new, const void* v_new, int grow, bool merge_here, hipStream_t stream, hipEvent_t ev_start,
                               hipEvent_t ev_stop);
 // `in_turn`: shares go to the XCDs in turn instead of in contiguous runs (a list of shares at most half of which hold units).
 hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated,
                               const void* q, void* out, float scale_log2, const void* k_new, const void* v_new,
-                              int grow, bool in_turn, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
+                              int grow, bool merge_here, bool in_turn, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop);
 // merge_words (host, [n_pairs], optional): per pair (first partial slot << 12) | partials, as planned for the
 // work list now on the device; with it and at most kMergeArgPairs pairs the merge kernel takes these from its
 // arguments instead of from the pair records (not for a layer with gates: their records carry more).

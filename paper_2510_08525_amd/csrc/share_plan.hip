@@ -69,8 +69,8 @@ int plan_shares(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_begin,
     for (int p = 0; p < n_pairs; ++p) seg_first[p] = seg_count[p] = 0;
     return 0;
   }
-  // A list that the grid takes at one round per workgroup: the shortest chain of latencies there is, as long as the merge
-  // kernel still takes a pair's partials in one go (16).
+  // A list that the grid takes at one round per workgroup: the shortest chain of latencies there is, as long as a pair has few
+  // partials (16).
   if (singly || (all_rounds <= n_wg && longest <= 16))
     return deal_rounds(rounds, n_pairs, kPairStartCost + kRoundCost, wg_begin, seg_first, seg_count, true);
   // feasible for sure: the whole list in one workgroup; look upward from the average

@@ -6,7 +6,7 @@
 #include <string.h>
 #include <type_traits>
 
-#include "mfma_tile.h"
+#include "share_merge.h"
 
 namespace rlkv {
 namespace {
@@ -36,28 +36,6 @@ struct MergeRest {
 constexpr int kManyPartials = 64;
 constexpr int kFew = kMergeFew;          // two DPP rows
 static_assert(kFew == 32);
-
-// Maximum / sum over 32 lanes, in every lane of them.
-template <int CTRL>
-__device__ __forceinline__ float row_ror(float x) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-__device__ __forceinline__ float max32(float x) {
-  x = fmaxf(x, row_ror<0x128>(x));
-  x = fmaxf(x, row_ror<0x124>(x));
-  x = fmaxf(x, row_ror<0x122>(x));
-  x = fmaxf(x, row_ror<0x121>(x));
-  const TwoValues y = swap16(x);
-  return fmaxf(y.a, y.b);
-}
-__device__ __forceinline__ float sum32(float x) {
-  x += row_ror<0x128>(x);
-  x += row_ror<0x124>(x);
-  x += row_ror<0x122>(x);
-  x += row_ror<0x121>(x);
-  const TwoValues y = swap16(x);
-  return y.a + y.b;
-}
 
 template <typename T, bool IN_ARGS, bool MANY>
 __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restrict__ all_o, const float* __restrict__ all_m,
@@ -112,23 +90,23 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restri
     auto merged = [&](int set) {
       const float m = mine < nseg ? mw[set] : -INFINITY;
       const float M = max32(m);
-      const float sc = m == -INFINITY ? 0.f : exp2f(m - M);
-      const float L = sum32(sc * (mine < nseg ? lw[set] : 0.f));
+      const float sc = exp2_or_zero(m, M);
+      const float L = sum32(product(sc, mine < nseg ? lw[set] : 0.f));
       float acc = 0.f;
 #pragma unroll
       for (int t = 0; t < kFew; t += 4) {
         if (t >= nseg) break;
 #pragma unroll
         for (int j = t; j < t + 4; ++j)
-          acc += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), j)) * o[set][j];
+          acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), j)), o[set][j], acc);
       }
-      return acc / L;
+      return quotients(floatx4{acc, acc, acc, acc}, L)[0];
     };
     ask(0);
     if (!IN_ARGS && n_sets == 2) {
       ask(1);
       const float full = merged(0);
-      emit(gate * full + (1.f - gate) * merged(1));
+      emit(blend(gate, full, merged(1)));
     } else {
       emit(merged(0));
     }
