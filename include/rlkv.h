@@ -372,7 +372,8 @@ int32_t rlkv_plan_whole_pairs(const int32_t* rounds /* host */, int32_t n_pairs,
                               int32_t* wg_begin /* host */, int32_t* seg_first /* host */,
                               int32_t* seg_count /* host */);
 
-/* Which kind of list a layer gets: 1 = whole pairs, 0 = shares, -1 on an invalid argument; exposed for tests.
+/* Which kind of list is the faster one where shares have a merge launch behind them: 1 = whole pairs, 0 = shares, -1 on an invalid
+ * argument; exposed for tests.
  *   kernel (VALU or MFMA), dtype, group, n_kv_heads, n_full_heads, window = sink + recent : the layer
  *   gated   : some full head of it has a gate below 1;  step : planned by rlkv_append_decode (else by a decode call;
  *             rlkv_append_decode_prepare always plans shares)
@@ -380,6 +381,11 @@ int32_t rlkv_plan_whole_pairs(const int32_t* rounds /* host */, int32_t n_pairs,
 int32_t rlkv_plan_list_whole(int32_t kernel, int32_t dtype, int32_t group, int32_t gated, int32_t step, int32_t n_workgroups,
                              int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
                              const int32_t* lengths /* host */, const uint8_t* active /* host */);
+
+/* Which kind of list a layer gets, merges inside the attention launch considered.  Arguments and result as above. */
+int32_t rlkv_plan_list_kind(int32_t kernel, int32_t dtype, int32_t group, int32_t gated, int32_t step, int32_t n_workgroups,
+                            int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
+                            const int32_t* lengths /* host */, const uint8_t* active /* host */);
 
 /* Shares that every full-head workgroup of a prefill chunk (128 / group chunk positions) is divided into in the
  * single-group form of the kernel (the one rlkv_plan_prefill_form calls narrow; small chunks of blending layers take it too): as many (at most 8) as

@@ -720,8 +720,8 @@ static rlkv_status_t ensure_worklist(rlkv_cache_t* cache, int32_t layer, int gro
   if (use != ListUse::kPrepared) {
     int n_full = 0;
     for (int h = 0; h < H; ++h) n_full += mask[h] ? 1 : 0;
-    whole = wants_whole_pairs(dv.kernel, dv.dtype, dv.group, cache->layer_gated[layer] != 0, use == ListUse::kStep, n_wg, H, n_full,
-                              dv.window, B, lh, cache->active.data());
+    whole = list_is_whole(dv.kernel, dv.dtype, dv.group, cache->layer_gated[layer] != 0, use == ListUse::kStep, n_wg, H, n_full,
+                          dv.window, B, lh, cache->active.data());
   }
   // fp32 rows are twice as long: a short list goes out in half rounds, one per workgroup, where the grid and the merge (32 partials
   // in one go) take it.  (One of 1000 tokens, 8 heads, half of them compressed: 6.9 -> 6.1 us a launch; a prompt of 500 and one of

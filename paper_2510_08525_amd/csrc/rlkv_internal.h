@@ -243,7 +243,9 @@ void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_
                       int32_t* seg_count);
 // Whether a list of whole pairs is the faster one for sequences of these lengths (see share_plan.hip).
 bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
-                       int batch, const int32_t* lengths, const uint8_t* active);
+                       int batch, const int32_t* lengths, const uint8_t* active, bool merged_inside);
+bool list_is_whole(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
+                   int batch, const int32_t* lengths, const uint8_t* active);
 // ev_start / ev_stop (both or neither): events that receive the kernel's own begin and end
 // timestamps (the dispatch's completion signal), for the measurement aid.
 // `gated`: some full head of the layer has a gate below 1 (two passes for those heads).

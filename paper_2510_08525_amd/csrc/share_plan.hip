@@ -131,8 +131,9 @@ struct WholeCost {
 constexpr WholeCost kWholeCost[2][2] = {      // [some full head blends][planned by a fused step]
     {{-4.1, 3.9, -4.8, 0.4, 0.4, -1.3}, {-4.1, 3.9, -3.9, 0.4, 0.3, -2.1}},
     {{-2.9, 3.8, -3.9, 0.1, 0.4, -1.8}, {-3.3, 4.0, -3.2, 0.4, 0.8, -5.3}}};
+constexpr double kInsideSaves = 1.2;
 bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
-                       int batch, const int32_t* lengths, const uint8_t* active) {
+                       int batch, const int32_t* lengths, const uint8_t* active, bool merged_inside) {
   int64_t pairs = 0, longest = 0, all = 0;
   for (int b = 0; b < batch; ++b) {
     if (active && !active[b]) continue;
@@ -152,7 +153,31 @@ bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, 
   const WholeCost& c = kWholeCost[gated][step];
   const double diff = c.fixed + (c.longest * longest + c.even * all / n_wg) * 1e-3 + c.alike * std::log2(1.0 + (double)all / longest) +
                       (group > 8 ? c.wide : 0.0) + c.filled * pairs / n_wg;
-  return excess <= 800 && diff <= 0.0;
+  return excess <= 800 && diff + (merged_inside ? kInsideSaves : 0.0) <= 0.0;
+}
+
+// The kind of list a layer gets (true: whole pairs).  wants_whole_pairs was fitted with a merge launch behind the shares; where the
+// tiled kernel merges them itself (merges_in_launch in rlkv_api.hip), they are better by kInsideSaves, and a list of at least
+// three rounds that goes out at one per workgroup and fills at most half of the grid is always the faster one (whole / shares,
+// us: a step of one sequence, 32 on 8 heads, half compressed, 150 tokens 6.9 / 7.2, 230 6.9 / 7.0, 300 7.7 / 7.3, 480 8.6 / 7.0; 8 of
+// 480, 28 on 4 9.6 / 7.5; 4 of 300, 16 on 1 8.1 / 7.3; 4 of 500 that blend, 28 on 4 11.5 / 9.3.  Longer lists: 16 of 800, 32 on 8
+// 13.7 / 12.4, of 500 10.4 / 11.2; 16 of 600, 8 on 8 12.0 / 11.3).
+bool list_is_whole(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
+                   int batch, const int32_t* lengths, const uint8_t* active) {
+  const bool tiled = kernel == RLKV_KERNEL_MFMA;
+  if (tiled) {
+    auto rounds = [&](int64_t n) { return (n + kWorklistSlack + kTile * kRound - 1) / (kTile * kRound); };
+    int64_t most = 0, all = 0;
+    for (int b = 0; b < batch; ++b) {
+      if (active && !active[b]) continue;
+      const int64_t full = rounds(lengths[b]), ring = rounds(std::min(lengths[b], window));
+      most = std::max(most, n_full > 0 ? full : ring);
+      all += n_full * full + (n_kv_heads - n_full) * ring;
+    }
+    if (most >= 3 && most <= 16 && 2 * all <= n_wg) return false;
+  }
+  return wants_whole_pairs(kernel, dtype, group, gated, step, n_wg, n_kv_heads, n_full, window, batch, lengths, active,
+                           tiled && group <= 8 && !gated);
 }
 
 }  // namespace rlkv
@@ -370,17 +395,31 @@ extern "C" int32_t rlkv_plan_whole_pairs(const int32_t* rounds, int32_t n_pairs,
   return used;
 }
 
+static bool list_arguments_valid(int32_t kernel, int32_t dtype, int32_t group, int32_t n_workgroups, int32_t n_kv_heads, int32_t n_full_heads,
+                                 int32_t window, int32_t batch, const int32_t* lengths) {
+  if (!lengths || (kernel != RLKV_KERNEL_VALU && kernel != RLKV_KERNEL_MFMA) || (dtype != RLKV_F32 && dtype != RLKV_BF16)) return false;
+  if (group < 1 || group > rlkv::kMaxGroup || n_workgroups < 1 || n_kv_heads < 1 || n_full_heads < 0 || n_full_heads > n_kv_heads ||
+      window < 1 || batch < 1)
+    return false;
+  for (int b = 0; b < batch; ++b)
+    if (lengths[b] < 0) return false;
+  return true;
+}
+
 extern "C" int32_t rlkv_plan_list_whole(int32_t kernel, int32_t dtype, int32_t group, int32_t gated, int32_t step, int32_t n_workgroups,
                                         int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
                                         const int32_t* lengths, const uint8_t* active) {
-  if (!lengths || (kernel != RLKV_KERNEL_VALU && kernel != RLKV_KERNEL_MFMA) || (dtype != RLKV_F32 && dtype != RLKV_BF16)) return -1;
-  if (group < 1 || group > rlkv::kMaxGroup || n_workgroups < 1 || n_kv_heads < 1 || n_full_heads < 0 || n_full_heads > n_kv_heads ||
-      window < 1 || batch < 1)
-    return -1;
-  for (int b = 0; b < batch; ++b)
-    if (lengths[b] < 0) return -1;
+  if (!list_arguments_valid(kernel, dtype, group, n_workgroups, n_kv_heads, n_full_heads, window, batch, lengths)) return -1;
   return rlkv::wants_whole_pairs(kernel, dtype, group, gated != 0, step != 0, n_workgroups, n_kv_heads, n_full_heads, window, batch,
-                                 lengths, active);
+                                 lengths, active, false);
+}
+
+extern "C" int32_t rlkv_plan_list_kind(int32_t kernel, int32_t dtype, int32_t group, int32_t gated, int32_t step, int32_t n_workgroups,
+                                       int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
+                                       const int32_t* lengths, const uint8_t* active) {
+  if (!list_arguments_valid(kernel, dtype, group, n_workgroups, n_kv_heads, n_full_heads, window, batch, lengths)) return -1;
+  return rlkv::list_is_whole(kernel, dtype, group, gated != 0, step != 0, n_workgroups, n_kv_heads, n_full_heads, window, batch,
+                             lengths, active);
 }
 
 extern "C" int32_t rlkv_plan_blend_form(int32_t n_compute_units, int32_t group, int32_t n_full_heads, int32_t batch,
