@@ -25,6 +25,8 @@
 // Measured, before / now, us a call: one sequence of 333 tokens and 32 steps (32 query, 8 KV heads) 246 / 229, the launch by itself
 // 7.1 / 5.6; 8 x 8192 40.3 / 38.6; 16 gated of 3000 .. 5000 28.8 / 25.1; 24 paged of 2000 .. 20 000 46.6 / 42.5; a 28-layer step of
 // 16 x 16 384 1152 / 1088; 32 of 4000 .. 32 000 184.2 / 181.9; 64 of 16 000 .. 64 000 783 / 777.
+// Arguments and addresses that the loads do not need behind them (late_arguments): a launch after another, decode / step of one sequence, 32
+// and 8 heads, 340 tokens 5.00 / 5.78 -> 4.92 / 5.64, 1030 5.35 / 5.86 -> 5.28 / 5.65.
 // Four wavefronts with two register images, exact waits: 185.5 for the 32, 1132 for the step; with one image 185.7 and 1120.
 //
 // Gated heads (GATED = true; paper Sec. 3.1, Eq. 1): a full head with gate g < 1 returns
@@ -66,6 +68,7 @@ struct DecodeRest {
   const int32_t* block_table;
   int64_t page_bytes;
   int32_t page_shift, page_mask, table_stride;
+  uint32_t recent_inverse;       // inverse_of(recent)
 };
 
 // Online-softmax update and P.V accumulation of one tile into `st`.  A slot counts if it
@@ -163,10 +166,14 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
   // tokens since the list was planned: known to the host, or asked for beside the record
   int grow = grow_known;
   if (grow_known < 0) grow = load_const<int32_t>(list);
-  // (the other arguments in the shadow of the record: left alone the compiler asks for each where it is first used)
-  typedef __attribute__((address_space(1))) uint16_t GlobalOut;   // (a generic pointer would make flat stores of them: with one
-  GlobalOut* out = (GlobalOut*)r.out;                             // in flight every wait for a load waits for all)
-  asm volatile("" : "+s"(out), "+s"(r.scale_log2), "+s"(r.n_kv_heads), "+s"(r.list_stride), "+s"(r.pair_off));
+  // The other arguments: what the loads and scores need is asked for in the shadow of the record, the rest behind the loads
+  // (late_args: left alone the compiler asks for all of it in front of them, and keeps it in lanes of vector registers).
+  asm volatile("" : "+s"(r.scale_log2));
+  if (FUSED) asm volatile("" : "+s"(r.recent_inverse));
+  auto late_args = [] { return late_arguments<DecodeRest>(); };
+  // (a generic pointer would make flat stores of them: with one in flight every wait for a load waits for all)
+  typedef __attribute__((address_space(1))) uint16_t GlobalOut;
+  typedef __attribute__((address_space(1))) int32_t GlobalInt;
   if (PAGED) asm volatile("" : "+s"(r.block_table), "+s"(r.page_bytes), "+s"(r.page_shift), "+s"(r.page_mask), "+s"(r.table_stride));
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -179,12 +186,11 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
   }
   int pi = wd.first_pair, b = wd.seq, h = wd.head;
   PairDesc pd = wd.first;
-  const char* pairs = list + r.pair_off;
   int n_left = 0;
   uint32_t warm = 0;
 
   const int G = shape & kShapeGroup;
-  auto emit = [&](int pair, int g, int d4, const floatx4& v) {
+  auto emit = [&](GlobalOut* out, int pair, int g, int d4, const floatx4& v) {
     GlobalOut* dst = out + ((int64_t)pair * G + g) * kHeadDim + d4 * 4;
     const uint2 four = make_uint2(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]));
     if (((uintptr_t)out & 7) == 0) {                             // (a caller's may start at any element)
@@ -233,13 +239,13 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
     int slot_new = 0, tile_new = 0;
     bool mine = false;
     if (FUSED) {
-      slot_new = (full || n_old < sink) ? n_old : sink + (n_old - sink) % recent;
+      slot_new = (full || n_old < sink) ? n_old : sink + remainder_of(n_old - sink, recent, r.recent_inverse);
       tile_new = slot_new >> 5;
       mine = tile_new >= tile_lo && tile_new < tile_hi && ((tile_new - tile_lo) & (kWaves - 1)) == wave;
     }
     // the next pair's record, for the (rare) share that crosses a pair boundary
     PairDesc pd_next = pd;
-    auto fetch_next = [&]() { if (seg_end < u_end) pd_next = load_pair(pairs, pi + 1); };
+    auto fetch_next = [&]() { if (seg_end < u_end) pd_next = load_pair(list + late_args()->pair_off, pi + 1); };
     // Eq. 1 gate: a full head with gate < 1 also accumulates its local attention (sink + recent
     // positions) over the same tiles; out = gate * full + (1 - gate) * local.
     const bool two_sets = GATED && full && pd.gate < 1.f;
@@ -280,7 +286,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
       // The record this workgroup will start the next layer's launch with: asked for now, so that it is in
       // L2 by then (its record is the first thing a workgroup waits for).  Looked at only at the very end.
       if (u == u_begin && (shape & kShapeMore) && wave == 0)
-        warm = *reinterpret_cast<const uint32_t*>(list + r.list_stride + sizeof(ListHeader) + (int64_t)wg * (int)sizeof(WgDesc));
+        warm = *reinterpret_cast<const uint32_t*>(list + late_args()->list_stride + sizeof(ListHeader) + (int64_t)wg * (int)sizeof(WgDesc));
 
       if (FUSED && mine) {
         // The row goes into the store, every 16-byte unit by the lane that later loads it (so program order makes later loads see
@@ -323,8 +329,9 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
         bool wide = false;                       // the fp16 range test, for prefill
 #pragma unroll
         for (int j = 0; j < 8; ++j) wide |= bf16_beyond_fp16(vn[j]);
-        if (wide) *r.v_wide = 1;
-        if (lane == 0 && !full) r.slot_pos[((int64_t)pd.ring * r.batch + b) * window + slot_new] = n_old;
+        auto* late = late_args();
+        if (wide) *(GlobalInt*)late->v_wide = 1;
+        if (lane == 0 && !full) ((GlobalInt*)late->slot_pos)[((int64_t)pd.ring * late->batch + b) * window + slot_new] = n_old;
       }
 
       // One image, refilled as it is used up: K behind the scores, V behind the products.  Every wait is for its own registers only, the
@@ -346,6 +353,14 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
     // whatever the lanes, were 1150 clocks of the merge).
     constexpr int kPasses = kMaxGroup * kHeadDim / 4 / kThreads;
     floatx4 held[kPasses];                                             // full-attention results of a whole pair
+    // (What the merge computes from the thread's number and reads of the arguments stays behind the loads: the compiler would place it
+    // before the loop, in front of the first of them.)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int hd = tid & 15, kb = (tid >> 4) & 3;
+    auto* late = late_args();
+    const Partials part = partials_at(late->part);
+    GlobalOut* out = (GlobalOut*)late->out;
 #pragma unroll
     for (int set = 0; set < (GATED ? 2 : 1); ++set) {
       if (set == 1 && !two_sets) break;
@@ -396,23 +411,30 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
             if (set == 0) { held[it] = res; continue; }
             res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
-          emit(pi, g, d4, res);
+          emit(out, pi, g, d4, res);
         } else {
-          leave_partial(r.part, set, wg + pi, G, g, d4, O, M, L);
+          leave_partial(part, set, wg + pi, G, g, d4, O, M, L);
         }
       }
     }
-    if (!whole_pair && r.part.arrived) ++n_left;
+    if (!whole_pair && part.arrived) ++n_left;
     // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
-    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
+    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) {
+      ((GlobalInt*)late->len0)[b] = n;
+      ((GlobalInt*)late->len1)[b] = n;
+    }
     u = seg_end;
-    auto step_on = [&]() { ++pi; if (++h == r.n_kv_heads) { h = 0; ++b; } };
+    auto step_on = [&]() { ++pi; if (++h == late->n_kv_heads) { h = 0; ++b; } };
     step_on();
     pd = pd_next;
     if (u < u_end)
-      while (pd.unit_end <= u) { step_on(); pd = load_pair(pairs, pi); }       // pairs of inactive slots own no units
+      while (pd.unit_end <= u) { step_on(); pd = load_pair(list + late->pair_off, pi); }       // pairs of inactive slots own no units
   }
-  finish_pairs<kThreads, GATED>(r.part, sm_left, n_left, G, sm_w, emit);
+  if (n_left > 0) {
+    auto* late = late_args();
+    finish_pairs<kThreads, GATED>(partials_at(late->part), sm_left, n_left, G, sm_w,
+                                  [&](int pair, int g, int d4, const floatx4& v) { emit((GlobalOut*)late->out, pair, g, d4, v); });
+  }
   if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
   asm volatile("" ::"v"(warm));                        // keeps the load above alive
 }
@@ -434,6 +456,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const
   r.slot_pos = dv.slot_pos; r.v_wide = dv.v_wide + layer;
   r.block_table = dv.block_table; r.page_bytes = dv.page_bytes; r.page_shift = dv.page_shift; r.page_mask = dv.page_mask;
   r.table_stride = dv.table_stride;
+  r.recent_inverse = inverse_of(dv.recent);
   // (the plain launch when no timestamps are asked for: that form can be recorded into a graph)
 #define RLKV_LAUNCH(F, GT, PG)                                                                                    \
   do {                                                                                                            \

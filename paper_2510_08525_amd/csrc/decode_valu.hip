@@ -22,6 +22,10 @@
 // Measured, before / now, us: fp32, one sequence of 1000 tokens and 16 steps, 32 query and 8 KV heads, the launch by itself 7.3 / 6.1;
 // 8 x 5000, 28 and 4 heads 38.3 / 30.2, 16 on 1 33.7 / 21.5, 32 and 8 56.2 / 53.0 (at the rate of the memory); one of 60, 16 on 1 14.9 / 8.3;
 // bf16, 16 x 16 384, 28 and 4 144 / 109, 8 x 5000, 32 and 8 32.6 / 30.0.
+// Short lists wait for the start: with the second pass of blending heads in a form of its own (GATED) and whatever the loads do not need
+// behind them (late_arguments), 470 instructions between the record and the first row are 190; a launch after another of a step of one
+// fp32 sequence, 32 and 8 heads, half compressed, 20 / 500 / 1030 tokens 5.6 / 7.6 / 8.1 -> 4.2 / 6.2 / 7.1 us, of a decode call 4.2 / 6.5 /
+// 7.3 -> 3.5 / 6.0 / 6.9.
 #include <type_traits>
 
 #include "share_merge.h"
@@ -91,13 +95,14 @@ struct DecodeRest {
   int32_t pair_off, batch;
   int32_t *len0, *len1;          // both copies of the layer's lengths
   int32_t* slot_pos;
+  uint32_t recent_inverse;       // inverse_of(recent)
 };
 
-// NS: sets of four heads.  FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the batch of
+// GATED: some full head may have a gate below 1.  NS: sets of four heads.  FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the batch of
 // rows with the new slot writes the row, every byte by the lane that loads it.
 // Of every tile two wavefronts take a batch of 16 rows each, one register image, K refilled behind the scores and V behind the
 // products; eight wavefronts, two per SIMD, up to group 8, four beyond (Q and the sums of four sets take 128 registers).  The first arguments are in registers when the kernel starts (decode_mfma.hip).
-template <typename T, int NS, bool FUSED>
+template <typename T, int NS, bool FUSED, bool GATED>
 __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(const char* __restrict__ list, char* __restrict__ kv_base,
                                                              const T* __restrict__ q, const T* __restrict__ k_new,
                                                              const T* __restrict__ v_new, uint32_t shape, int grow_known,
@@ -121,10 +126,12 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
   // tokens since the list was planned: known to the host, or asked for beside the record
   int grow = grow_known;
   if (grow_known < 0) grow = load_const<int32_t>(list);
-  // (the other arguments in the shadow of the record; `out` as a global pointer, see decode_mfma.hip)
+  // (what the loads and scores need of the other arguments in the shadow of the record; global pointers: see decode_mfma.hip)
   typedef __attribute__((address_space(1))) T GlobalOut;
-  GlobalOut* out = (GlobalOut*)r.out;
-  asm volatile("" : "+s"(out), "+s"(r.scale_log2), "+s"(r.n_kv_heads), "+s"(r.pair_off));
+  typedef __attribute__((address_space(1))) int32_t GlobalInt;
+  auto late_args = [] { return late_arguments<DecodeRest<T>>(); };
+  asm volatile("" : "+s"(r.scale_log2));
+  if (FUSED) asm volatile("" : "+s"(r.recent_inverse));
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int u_begin = wd.u_begin, u_end = wd.u_end;
@@ -136,14 +143,13 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
   }
   int pi = wd.first_pair, b = wd.seq, h = wd.head;
   PairDesc pd = wd.first;
-  const char* pairs = list + r.pair_off;
   int n_left = 0;
 
   const int hl = lane & 3;                             // head of a set
   const int half = lane >> 5, off = (lane & 31) * 4 * (int)sizeof(T);        // loads: row of two, and bytes
   const int s_row = ((lane >> 4) & 1) * 8 + half;      // scores: rows s_row + 2 u, u = 0 .. 3
   const int G = shape & kShapeGroup;
-  auto emit = [&](int pair, int g, int d4, const floatx4& v) {
+  auto emit = [&](GlobalOut* out, int pair, int g, int d4, const floatx4& v) {
     constexpr int kAlign = 4 * sizeof(T);                // (a caller's output may start at any element)
     const bool out_aligned = ((uintptr_t)out & (kAlign - 1)) == 0;
     GlobalOut* dst = out + ((int64_t)pair * G + g) * kHeadDim + d4 * 4;
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
     bool mine = false;
     Four kn, vn;
     if (FUSED) {
-      slot_new = (full || n_old < sink) ? n_old : sink + (n_old - sink) % recent;
+      slot_new = (full || n_old < sink) ? n_old : sink + remainder_of(n_old - sink, recent, r.recent_inverse);
       const int tile_new = slot_new / kTile;
       mine = tile_new >= tile_lo && tile_new < tile_hi && (tile_new - tile_lo) % kStride == wave / kBatches &&
              slot_new % kTile / kBatch * kBatch == row0;
@@ -215,14 +221,15 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       for (int k = 0; k < 4; ++k) E::unpack(src[k], qf[s] + 4 * k);
     }
 
-    // Eq. 1 gate: a full head with gate < 1 takes a second, local pass over the tiles of this
+    // Eq. 1 gate (GATED): a full head with gate < 1 takes a second, local pass over the tiles of this
     // segment that hold sink or recent positions; out = gate * full + (1 - gate) * local.
-    const bool two_pass = full && pd.gate < 1.f;
+    const bool two_pass = GATED && full && pd.gate < 1.f;
     const int keep_lo = sink, keep_from = n - recent;              // local pass: row < S or row >= n - R
     const int sink_tiles = (keep_lo + kTile - 1) / kTile;
     const int recent_tile0 = keep_from > 0 ? keep_from / kTile : 0;
     constexpr int kPasses = (NS * 4 * kHeadDim / 4 + kThreads - 1) / kThreads;
     floatx4 held[kPasses];                                         // full-pass results of a whole-pair segment
+#pragma unroll 1
     for (int pass = 0; pass < (two_pass ? 2 : 1); ++pass) {
       float m[NS], l[NS];
       floatx4 acc[NS][4];                              // [set][column of four]: D row i = columns 4 * (4 * (block % 8) + i) + e
@@ -235,19 +242,20 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       }
 
       struct Rows { Four k[kLoads], v[kLoads]; };
-      auto counts = [&](int tok) { return (tok < n_eff) & ((pass == 0) | (tok < keep_lo) | (tok >= keep_from)); };   // (no short circuits)
+      auto counts = [&](int tok) { return (tok < n_eff) & (!GATED | (pass == 0) | (tok < keep_lo) | (tok >= keep_from)); };   // (no short circuits)
       // rows are read once per step: stream them past the caches
       auto load = [&](Four (&dst)[kLoads], const char* st, int tile) {
+        const char* base = st + (int64_t)tile * (kTile * kRowBytes);
+        const int last = n_eff - 1 - tile * kTile;                       // stay inside the valid prefix
 #pragma unroll
         for (int t = 0; t < kLoads; ++t) {
-          const int tok = tile * kTile + row0 + t * 2 + half;
-          const int64_t at = (int64_t)(tok < n_eff ? tok : n_eff - 1) * kRowBytes + off;       // stay inside the valid prefix
-          dst[t] = __builtin_nontemporal_load(reinterpret_cast<const Four*>(st + at));
+          const int row = row0 + t * 2 + half;
+          dst[t] = __builtin_nontemporal_load(reinterpret_cast<const Four*>(base + (uint32_t)((row < last ? row : last) * kRowBytes + off)));
         }
       };
       auto work = [&](Rows& rw, int tile, auto scored) {
         const int tok0 = tile * kTile + row0;
-        const bool ragged = tok0 + kBatch > n_eff || pass == 1;
+        const bool ragged = tok0 + kBatch > n_eff || (GATED && pass == 1);
         float sc[NS][4];                       // [set][u]: rows s_row + 2 u of the batch
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
@@ -333,7 +341,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       };
       // the tile at or behind `tile` (in this wavefront's steps) that this pass looks at
       auto settle = [&](int tile) {
-        if (pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + kStride - 1) / kStride * kStride;   // hop over the evicted middle
+        if (GATED && pass == 1 && tile >= sink_tiles && tile < recent_tile0) tile += (recent_tile0 - tile + kStride - 1) / kStride * kStride;   // hop over the evicted middle
         return tile;
       };
       int tile = settle(tile_first);
@@ -341,21 +349,30 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         Rows rw;
         load(rw.k, kst, tile);
         load(rw.v, vst, tile);
-        if (FUSED && mine && pass == 0) {
+        if (FUSED && mine && (!GATED || pass == 0)) {
           // the row goes into the store and, where this is its batch, into the registers: a load behind the stores would be
           // another memory latency
           const int in = slot_new % kBatch;
           const bool lane_new = half == in % 2;
           if (tile == slot_new / kTile) {
+            int at = lane_new ? in / 2 : -1;
+            asm volatile("" : "+v"(at));                  // (eight comparisons here, not in front of the loads)
 #pragma unroll
-            for (int t = 0; t < kLoads; ++t)
-              if (lane_new && t == in / 2) { rw.k[t] = kn; rw.v[t] = vn; }
+            for (int t = 0; t < kLoads; ++t) {
+              const bool here = at == t;
+#pragma unroll
+              for (int w = 0; w < (int)(sizeof(Four) / 4); ++w) {
+                rw.k[t][w] = here ? kn[w] : rw.k[t][w];
+                rw.v[t][w] = here ? vn[w] : rw.v[t][w];
+              }
+            }
           }
           if (lane_new) {
             *reinterpret_cast<Four*>(kst + (int64_t)slot_new * kRowBytes + off) = kn;
             *reinterpret_cast<Four*>(vst + (int64_t)slot_new * kRowBytes + off) = vn;
           }
-          if (lane == 0 && !full) r.slot_pos[((int64_t)pd.ring * r.batch + b) * window + slot_new] = n_old;
+          auto* late = late_args();
+          if (lane == 0 && !full) ((GlobalInt*)late->slot_pos)[((int64_t)pd.ring * late->batch + b) * window + slot_new] = n_old;
         }
         for (;;) {
           const int next = settle(tile + kStride);
@@ -367,8 +384,15 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         work(rw, tile, [] {});
       }
 
+      // (what follows is computed behind the loads, see late_arguments)
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      const int lane = tid & 63, hl = tid & 3;
+      auto* late = late_args();
+      const Partials part = partials_at(late->part);
+      GlobalOut* out = (GlobalOut*)late->out;
       // The halves of a wavefront (even and odd rows; one reference) are added as their columns are dealt out over them.
-      if (u != u_begin || pass > 0) __syncthreads();   // the previous merge has finished reading LDS
+      if (u != u_begin || (GATED && pass > 0)) __syncthreads();   // the previous merge has finished reading LDS
       if (pass == 0 && tid == 0 && !whole_pair) sm_left[n_left] = LeftPair{pi, pd.wg_first, pd.n_seg, two_pass ? pd.gate : 1.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -413,32 +437,40 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         }
         if (whole_pair) {
           floatx4 res = quotients(O, L);
-          if (two_pass) {
+          if (GATED && two_pass) {
             if (pass == 0) { held[it] = res; continue; }
             res = pd.gate * held[it] + (1.f - pd.gate) * res;
           }
-          emit(pi, g, d4, res);
+          emit(out, pi, g, d4, res);
         } else {
-          leave_partial(r.part, pass, wg + pi, G, g, d4, O, M, L);
+          leave_partial(part, GATED ? pass : 0, wg + pi, G, g, d4, O, M, L);
         }
       }
     }   // pass
-    if (!whole_pair && r.part.arrived) ++n_left;
+    auto* late = late_args();
+    if (!whole_pair && late->part.arrived) ++n_left;
     // whoever owns tile 0 of head 0 publishes the new length, in both copies of the table (nobody reads either during this launch)
-    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) { r.len0[b] = n; r.len1[b] = n; }
+    if (FUSED && h == 0 && tile_lo == 0 && tid == 0) {
+      ((GlobalInt*)late->len0)[b] = n;
+      ((GlobalInt*)late->len1)[b] = n;
+    }
     u = seg_end;
-    auto step_on = [&]() { ++pi; if (++h == r.n_kv_heads) { h = 0; ++b; } };
+    auto step_on = [&]() { ++pi; if (++h == late->n_kv_heads) { h = 0; ++b; } };
     while (u < u_end) {
       step_on();
-      pd = load_pair(pairs, pi);
+      pd = load_pair(list + late->pair_off, pi);
       if (pd.unit_end > u) break;                          // (pairs of inactive slots own no units)
     }
   }
-  finish_pairs<kThreads, true>(r.part, sm_left, n_left, G, sm_w, emit);
+  if (n_left > 0) {
+    auto* late = late_args();
+    finish_pairs<kThreads, GATED>(partials_at(late->part), sm_left, n_left, G, sm_w,
+                                  [&](int pair, int g, int d4, const floatx4& v) { emit((GlobalOut*)late->out, pair, g, d4, v); });
+  }
   if (advance) *reinterpret_cast<int32_t*>(const_cast<char*>(list)) = grow + 1;
 }
 
-template <typename T, bool FUSED>
+template <typename T, bool FUSED, bool GATED>
 hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2, const void* k_new,
                     const void* v_new, int grow, bool merge_here, hipStream_t stream, hipEvent_t e0, hipEvent_t e1) {
   const dim3 grid(dv.n_wg);
@@ -451,14 +483,15 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
   r.part = {dv.part_o, dv.part_m, dv.part_l, dv.part_set_o, dv.part_set_ml, merge_here ? dv.arrived + (int64_t)layer * dv.n_pairs * (kMaxGroup / 2) : nullptr};
   r.pair_off = dv.list_pair_off; r.batch = dv.batch;
   r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer); r.slot_pos = dv.slot_pos;
+  r.recent_inverse = inverse_of(dv.recent);
   // (without events: the plain launch, which a stream capture can record)
 #define RLKV_LAUNCH_ROWS(NS)                                                                                         \
   do {                                                                                                               \
     if (e0 || e1)                                                                                                    \
-      hipExtLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED>), grid, dim3(waves_for(NS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
+      hipExtLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED, GATED>), grid, dim3(waves_for(NS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
                             qp, kp, vp, shape, grow, dv.window, dv.recent, r);                                       \
     else                                                                                                             \
-      hipLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED>), grid, dim3(waves_for(NS) * 64), 0, stream, list, dv.kv_base, qp, kp, vp,   \
+      hipLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED, GATED>), grid, dim3(waves_for(NS) * 64), 0, stream, list, dv.kv_base, qp, kp, vp,   \
                          shape, grow, dv.window, dv.recent, r);                                                      \
   } while (0)
   if (G <= 4) RLKV_LAUNCH_ROWS(1);
@@ -470,14 +503,14 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
 
 }  // namespace
 
-hipError_t launch_decode_valu(const DeviceView& dv, int layer, const void* q, void* out, float scale_log2,
+hipError_t launch_decode_valu(const DeviceView& dv, int layer, bool gated, const void* q, void* out, float scale_log2,
                               const void* k_new, const void* v_new, int grow, bool merge_here, hipStream_t stream, hipEvent_t ev_start,
                               hipEvent_t ev_stop) {
-  if (dv.dtype == RLKV_F32)
-    return k_new ? launch_t<float, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop)
-                 : launch_t<float, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop);
-  return k_new ? launch_t<uint16_t, true>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop)
-               : launch_t<uint16_t, false>(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop);
+#define RLKV_PICK(T, F) \
+  (gated ? launch_t<T, F, true> : launch_t<T, F, false>)(dv, layer, q, out, scale_log2, k_new, v_new, grow, merge_here, stream, ev_start, ev_stop)
+  if (dv.dtype == RLKV_F32) return k_new ? RLKV_PICK(float, true) : RLKV_PICK(float, false);
+  return k_new ? RLKV_PICK(uint16_t, true) : RLKV_PICK(uint16_t, false);
+#undef RLKV_PICK
 }
 
 }  // namespace rlkv

@@ -863,7 +863,7 @@ static rlkv_status_t decode_with_view(rlkv_cache_t* cache, const DeviceView& dv,
   const bool few = 2 * cache->list_used[layer] <= dv.n_wg && !capturing;
   hipError_t e = dv.kernel == RLKV_KERNEL_MFMA
                      ? launch_decode_mfma(dv, layer, gated, q, out, scale_log2, nullptr, nullptr, grow, merge_here, few && !whole, s, e0, e1)
-                     : launch_decode_valu(dv, layer, q, out, scale_log2, nullptr, nullptr, grow, merge_here, s, e0, e1);
+                     : launch_decode_valu(dv, layer, gated || capturing, q, out, scale_log2, nullptr, nullptr, grow, merge_here, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
   ++cache->decode_calls[layer];
@@ -1023,7 +1023,7 @@ static rlkv_status_t launch_step(rlkv_cache_t* cache, int32_t layer, const void*
   const bool few = !capturing && 2 * cache->list_used[layer] <= cache->dv.n_wg;
   const hipError_t e = tiled ? launch_decode_mfma(cache->dv, layer, cache->layer_gated[layer] != 0, q, out, scale_log2, k, v,
                                                   grow, merge_here, few && !whole, s, e0, e1)
-                             : launch_decode_valu(cache->dv, layer, q, out, scale_log2, k, v, grow, merge_here, s, e0, e1);
+                             : launch_decode_valu(cache->dv, layer, cache->layer_gated[layer] != 0 || capturing, q, out, scale_log2, k, v, grow, merge_here, s, e0, e1);
   if (e != hipSuccess) return RLKV_ERR_HIP;
   if (record) ++cache->prof_used;
   if (grow >= 0) return RLKV_OK;                 // every pair was finished by its one workgroup or its last, the counter is advanced
