@@ -47,11 +47,11 @@ typedef enum {
 typedef enum { RLKV_F32 = 0, RLKV_BF16 = 1 } rlkv_dtype_t;
 
 /* Which decode kernel (and with it which in-HBM store layout) a cache uses.
- *   RLKV_KERNEL_VALU : row-major stores [slot][head_dim]; dot products on the vector
- *                      ALU with wavefront DPP reductions.  fp32 and bf16.  The fp32 path, and
- *                      for bf16 the comparison baseline: at a group size of 7 its bf16 form
- *                      is bound by the vector ALU, not by memory, and streams at less than
- *                      60 % of the rate of the MFMA kernel; no paging, no prefill.
+ *   RLKV_KERNEL_VALU : row-major stores [slot][head_dim]; products of fp32 values on the
+ *                      matrix cores, 4 x 4 blocks.  fp32 and bf16.  The fp32 path, and for
+ *                      bf16 the comparison baseline: its operands are brought into order in
+ *                      registers and its instructions are those for fp32, so at a group size
+ *                      of 7 it is slower than the MFMA kernel; no paging, no prefill.
  *   RLKV_KERNEL_MFMA : stores tiled so that a 128-bit load per lane lands directly in
  *                      MFMA operand registers; bf16 only.
  *   RLKV_KERNEL_AUTO : MFMA for bf16, VALU for fp32. */

@@ -57,15 +57,15 @@ struct Partials {
   int32_t* arrived;              // [pairs][kMaxGroup / 2] of the layer, 0 between launches
 };
 
-__device__ __forceinline__ Partials partials_at(const RLKV_CONST Partials& p) { return {p.o, p.m, p.l, p.set_o, p.set_ml, p.arrived}; }
+__device__ __forceinline__ Partials partials_at(RLKV_CONST Partials& p) { return {p.o, p.m, p.l, p.set_o, p.set_ml, p.arrived}; }
 
 // The arguments of an attention kernel beyond the 14 words that are in registers when it starts, asked for where this is called: left
 // alone the compiler asks for all of them, and computes what depends on them or on the thread's number alone, in front of the first loads
 // (of fp32 rows 470 instructions, 90 of them to keep scalars in lanes of vector registers).
 template <typename Rest>
-__device__ __forceinline__ const RLKV_CONST Rest* late_arguments() {
+__device__ __forceinline__ RLKV_CONST Rest* late_arguments() {
   constexpr int kAt = 14 * 4;
-  auto* p = (const RLKV_CONST Rest*)((RLKV_CONST char*)__builtin_amdgcn_kernarg_segment_ptr() + kAt);
+  auto* p = (RLKV_CONST Rest*)((RLKV_CONST char*)__builtin_amdgcn_kernarg_segment_ptr() + kAt);
   asm volatile("" : "+s"(p));
   return p;
 }

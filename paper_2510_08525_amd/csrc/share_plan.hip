@@ -108,7 +108,8 @@ void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_
   while (w <= n_wg) wg_begin[w++] = us;
 }
 
-// Where a list of whole pairs takes over from one of shares.  It saves the merge launch (3.3 us, and the host's time for it)
+// Where a list of whole pairs takes over from one of shares.  It saves the partials and their merge (a launch, or 1 to 2 us at the end
+// of this one, merges_in_launch)
 // and costs the time that the longest pair takes one CU beyond an even share of all rows.
 // Tiled stores: the difference in us, whole pairs minus shares, as a sum over what both depend on; the factors were fitted to 1277
 // pairs of timings (1 to 64 sequences of 100 to 8000 tokens, even and ragged, groups 1 to 16, 1 to 256 pairs), of which this
