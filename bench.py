@@ -425,8 +425,8 @@ def measured_stream_ceiling(device, gib=4, reps=4):
     return {"read_gbps": best, "workgroups": best_wg, "gib": gib}
 
 
-KERNEL_SOURCES = {"decode_mfma_kernel": ("decode_mfma.hip", "mfma_tile.h", "rlkv_internal.h"),
-                  "decode_valu_kernel": ("decode_valu.hip", "rlkv_internal.h")}
+KERNEL_SOURCES = {"decode_mfma_kernel": ("decode_mfma.hip", "share_merge.h", "mfma_tile.h", "rlkv_internal.h"),
+                  "decode_valu_kernel": ("decode_valu.hip", "share_merge.h", "mfma_tile.h", "rlkv_internal.h")}
 
 
 def kernel_source_sha16(kernel_name: str) -> str:
