@@ -1,6 +1,6 @@
 // Split-K decode attention, MFMA variant (tiled bf16 stores).
 //
-// Same operation as the vector-ALU variant (softmax attention of the G query heads of a
+// Same operation as the row-major variant (softmax attention of the G query heads of a
 // group over the rows a store holds; paper Sec. 3.1 Eq. 1 at gate 0/1, Sec. 3.3), with the
 // two contractions on the matrix cores:
 //   scores  S[slot][head] = sum_d K[slot][d] * Q[head][d]   v_mfma_f32_16x16x32_bf16,
@@ -16,13 +16,13 @@
 // the weights carry ~16 mantissa bits; the matrix cores are idle most of the time anyway.
 //
 // Start: the address of the list, and whatever else the first loads need, is in scalar registers before the first instruction
-// (kernel arguments loaded ahead, see kShapeGroup); the workgroup's record is one scalar load of 64 bytes, and the other arguments
-// come in its shadow; then the new row's loads, Q's and the first tile's go out together.  (Compiled from one struct of arguments and
+// (kernel arguments loaded ahead, see kShapeGroup); the workgroup's record is one scalar load of 64 bytes, and what the
+// scores need of the other arguments comes in its shadow; then the new row's loads, Q's and the first tile's go out together.  (Compiled from one struct of arguments and
 // plain pointers, the same start was five to six round trips to memory in a row.)
 // Loop: eight wavefronts, two per SIMD, whatever the list; one register image each, K refilled behind the scores and V behind the
 // products, every wait for its own registers only.  That last needs care: with a FLAT store possibly in flight - the output through a
 // generic pointer - the compiler turns every wait for a load into one for all of them.
-// Measured, before / now, us a call: one sequence of 333 tokens and 32 steps (32 query, 8 KV heads) 246 / 229, the launch by itself
+// Measured, before / now, us a call: one sequence of 333 tokens and 32 steps (32 query, 8 KV heads) 246 / 219, the launch by itself
 // 7.1 / 5.6; 8 x 8192 40.3 / 38.6; 16 gated of 3000 .. 5000 28.8 / 25.1; 24 paged of 2000 .. 20 000 46.6 / 42.5; a 28-layer step of
 // 16 x 16 384 1152 / 1088; 32 of 4000 .. 32 000 184.2 / 181.9; 64 of 16 000 .. 64 000 783 / 777.
 // Arguments and addresses that the loads do not need behind them (late_arguments): a launch after another, decode / step of one sequence, 32

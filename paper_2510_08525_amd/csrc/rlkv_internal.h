@@ -14,7 +14,7 @@ constexpr int kHeadDim = 128;      // the only head_dim the kernels are written 
 constexpr int kMaxGroup = 16;      // query heads per KV head
 constexpr int kMaxWorkgroups = 2048;  // upper bound of the split-K grid (sizes the scratch)
 constexpr int kBlock = 256;        // threads per workgroup (4 wavefronts)
-constexpr int kRound = 4;          // tiles per scheduling unit (one for each wavefront of a row-major workgroup, half a round of a tiled one)
+constexpr int kRound = 4;          // tiles per scheduling unit (what a row-major workgroup works at a time up to group 8, half of that of a tiled one)
 constexpr int kPairOverheadUnits = 1;  // units at the head of every pair that carry no tiles (a label for its start)
 constexpr int kRoundCost = 2;          // cost model of the share partition, in half rounds: one round of tiles ...
 constexpr int kPairStartCost = 3;      // ... and the start of a pair (pipeline restart on a new store, Q load,
@@ -40,7 +40,7 @@ struct PairDesc {        // 40 bytes
   int32_t n_build;       // cached tokens of the sequence when the list was built
   int32_t unit_start;    // first scheduling unit of the pair in the end-to-end numbering
   int32_t unit_end;      // one past its last unit.  The first kPairOverheadUnits units of a pair hold
-                         // no tiles; every later unit is kRound consecutive tiles of its store
+                         // no tiles; every later unit is WgDesc::round_tiles consecutive tiles of its store
   int32_t wg_first;      // first workgroup that holds units of the pair; its partial slots are wg + pair index
   int32_t ring;          // -1 = full head; of a compressed one its number among the compressed (layer, head)s, which is
                          // where its slot positions are: slot_pos + (ring * batch + sequence) * window
@@ -53,7 +53,7 @@ struct WgDesc {          // 64 bytes: one line, one scalar load
   int32_t seq;           // sequence and head of that pair
   PairDesc first;        // copy of pair_desc[first_pair]
   int32_t head;
-  int32_t round_tiles;   // tiles of a unit (row-major stores; kRound otherwise)
+  int32_t round_tiles;   // tiles of a unit (kRound, or half of it: short fp32 lists)
 };
 static_assert(sizeof(ListHeader) == 64 && sizeof(PairDesc) == 40 && sizeof(WgDesc) == 64, "the kernels load these word by word");
 
