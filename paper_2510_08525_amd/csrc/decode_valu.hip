@@ -292,7 +292,9 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         }
         scored();                        // K's registers are free from here on
         // The reference is a whole number (log2 domain): what moves a sum from one reference to another, here and in the merges, is a power
-        // of two and rounds nothing.  The scale goes into the exponent's one rounding.
+        // of two and rounds nothing.  The scale goes into the exponent's one rounding, up to references of 2^24.  From there on the products
+        // are whole numbers, and a product before its rounding may lie beyond the reference by more than an exponential takes (128 from
+        // 2^31 on), on either side: there the rounded products count, of which the largest is the reference.
         bool on[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) on[u] = !ragged || counts(tok0 + s_row + 2 * u);
@@ -301,15 +303,18 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         for (int s = 0; s < NS; ++s) {
           float mx = -INFINITY;
 #pragma unroll
-          for (int u = 0; u < 4; ++u) mx = fmaxf(mx, on[u] ? sc[s][u] * r.scale_log2 : -INFINITY);
+          for (int u = 0; u < 4; ++u) mx = fmaxf(mx, on[u] ? product(sc[s][u], r.scale_log2) : -INFINITY);
           const float m_new = fmaxf(m[s], __builtin_ceilf(column_max(mx)));     // (over the quarters, which hold other rows)
           const float m_ref = m_new == -INFINITY ? 0.f : m_new;
           const float alpha = __builtin_amdgcn_exp2f(m[s] - m_ref);   // 2^-inf = 0 for a fresh stream
           m[s] = m_new;
+          const bool whole = fabsf(m_ref) >= 0x1p24f;
+          const float factor = whole ? 1.f : r.scale_log2;
           float sum = 0.f;
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            p[s][u] = on[u] ? __builtin_amdgcn_exp2f(fmaf(sc[s][u], r.scale_log2, -m_ref)) : 0.f;
+            const float x = whole ? product(sc[s][u], r.scale_log2) : sc[s][u];
+            p[s][u] = on[u] ? __builtin_amdgcn_exp2f(fmaf(x, factor, -m_ref)) : 0.f;
             sum += p[s][u];
           }
           l[s] = l[s] * alpha + sum;
