@@ -154,6 +154,20 @@ __device__ __forceinline__ void merge_duo(const Partials& p, const LeftPair& w, 
         }
       }
     }
+    // (Beyond n_seg partial 0 stood in with a weight of zero, which makes a NaN of an Inf: such sums are taken again, one by one.  Zeros in
+    // its place, or no loads, cost every call 0.1 us.)
+    const float any = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    if (__builtin_expect(__any(any != any), 0)) {
+      const __amdgpu_buffer_rsrc_t rsrc = partials_at(p.o, set * p.set_o + (int64_t)slot0 * G * kHeadDim, w.n_seg * G * kHeadDim);
+      acc = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int i = 0; i < w.n_seg; ++i) {
+        const u32x4 one = __builtin_amdgcn_raw_buffer_load_b128(rsrc, o_off, i * G * kHeadDim * 4, kThrough);
+        const float weight = sm_w[g][i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] = fmaf(weight, __uint_as_float(one[e]), acc[e]);
+      }
+    }
     return quotients(acc, L);
   };
   floatx4 out = merged(0);

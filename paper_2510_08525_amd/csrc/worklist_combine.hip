@@ -100,6 +100,14 @@ __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float* __restri
         for (int j = t; j < t + 4; ++j)
           acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), j)), o[set][j], acc);
       }
+      // (beyond nseg partial 0 stood in with a weight of zero, which makes a NaN of an Inf: such sums are taken again, one by one)
+      if (__builtin_expect(__any(acc != acc), 0)) {
+        const float* po = all_o + set * r.part_set_o + (slot0 * G + g) * kHeadDim + d;
+        acc = 0.f;
+#pragma unroll 1
+        for (int j = 0; j < nseg; ++j)
+          acc = fmaf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc), j)), po[(int64_t)j * G * kHeadDim], acc);
+      }
       return quotients(floatx4{acc, acc, acc, acc}, L)[0];
     };
     ask(0);
