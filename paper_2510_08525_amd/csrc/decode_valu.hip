@@ -308,13 +308,16 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
           const float m_ref = m_new == -INFINITY ? 0.f : m_new;
           const float alpha = __builtin_amdgcn_exp2f(m[s] - m_ref);   // 2^-inf = 0 for a fresh stream
           m[s] = m_new;
+          float sum = 0.f, factor = r.scale_log2;
           const bool whole = fabsf(m_ref) >= 0x1p24f;
-          const float factor = whole ? 1.f : r.scale_log2;
-          float sum = 0.f;
+          if (__builtin_expect(__any(whole), 0)) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sc[s][u] = whole ? product(sc[s][u], r.scale_log2) : sc[s][u];
+            factor = whole ? 1.f : r.scale_log2;
+          }
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float x = whole ? product(sc[s][u], r.scale_log2) : sc[s][u];
-            p[s][u] = on[u] ? __builtin_amdgcn_exp2f(fmaf(x, factor, -m_ref)) : 0.f;
+            p[s][u] = on[u] ? __builtin_amdgcn_exp2f(fmaf(sc[s][u], factor, -m_ref)) : 0.f;
             sum += p[s][u];
           }
           l[s] = l[s] * alpha + sum;
