@@ -255,7 +255,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       };
       auto work = [&](Rows& rw, int tile, auto scored) {
         const int tok0 = tile * kTile + row0;
-        const bool ragged = tok0 + kBatch > n_eff || (GATED && pass == 1);
+        const bool ragged = tok0 + kBatch > n_eff || (GATED && pass == 1 && tok0 + kBatch > keep_lo && tok0 < keep_from);
         float sc[NS][4];                       // [set][u]: rows s_row + 2 u of the batch
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
@@ -326,11 +326,14 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
             for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
           }
         }
-        // (a row that does not count may be the one another wavefront is writing: nothing of it may reach a sum)
-        if (FUSED && ragged) {
+        // (a row that does not count may hold anything, and of a step be the one another wavefront is writing: nothing of it may reach a sum)
+        if (ragged) {
 #pragma unroll
-          for (int t = 0; t < kLoads; ++t)
-            if (!counts(tok0 + t * 2 + half)) rw.v[t] = Four{};
+          for (int t = 0; t < kLoads; ++t) {
+            uint32_t keep = counts(tok0 + t * 2 + half) ? 0xffffffffu : 0u;
+            asm("" : "+v"(keep));                       // (a mask in a vector register: eight comparisons in scalar ones are kept in lanes)
+            rw.v[t] &= keep;
+          }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
