@@ -387,6 +387,13 @@ int32_t rlkv_plan_list_kind(int32_t kernel, int32_t dtype, int32_t group, int32_
                             int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
                             const int32_t* lengths /* host */, const uint8_t* active /* host */);
 
+/* Where the split-K partials of a rlkv_decode_attention_noalloc call are in the static buffer of 16384 x 130 floats; exposed for tests.
+ *   gated : some full head of the layer has a gate below 1
+ *   at    : host [4], out, in floats: the rows' maxima, their normalisers (the accumulators are at 0), and the way from the first set of
+ *           rows to that of the local sums, of accumulators and of maxima or normalisers (0: there is one set)
+ * Returns the floats in use, or -1: an invalid argument, or RLKV_ERR_TOO_LARGE of the call. */
+int64_t rlkv_plan_static_scratch(int32_t n_workgroups, int32_t n_pairs, int32_t group, int32_t gated, int64_t* at /* host */);
+
 /* Shares that every full-head workgroup of a prefill chunk (128 / group chunk positions) is divided into in the
  * single-group form of the kernel (the one rlkv_plan_prefill_form calls narrow; small chunks of blending layers take it too): as many (at most 8) as
  * fit one round over the compute units and the scratch slots and leave every share min_share_tiles tiles; 1 = undivided.

@@ -900,24 +900,36 @@ rlkv_status_t rlkv_decode_attention(rlkv_cache_t* cache, int32_t layer, const vo
   return decode_with_view(cache, cache->dv, layer, q, out, softmax_scale, as_stream(stream));
 }
 
+// Rows of partials a launch can write: one per (workgroup or pair, query head), as many again for the local sums of a layer that
+// blends.  The second set is there whenever it fits (a recorded launch of row-major stores writes one if gates are set later); else both
+// sets are the first one.
+int64_t rlkv_plan_static_scratch(int32_t n_workgroups, int32_t n_pairs, int32_t group, int32_t gated, int64_t* at) {
+  if (!at || n_workgroups < 1 || n_pairs < 1 || group < 1 || group > kMaxGroup) return -1;
+  const int64_t rows_per_set = ((int64_t)n_workgroups + n_pairs) * group;
+  if (rows_per_set * (gated ? 2 : 1) > kStaticRows) return -1;
+  const int sets = 2 * rows_per_set <= kStaticRows ? 2 : 1;
+  at[0] = sets * rows_per_set * kHeadDim;                 // O: [sets][rows_per_set][head_dim], then m and l: [sets][rows_per_set] each
+  at[1] = at[0] + sets * rows_per_set;
+  at[2] = sets == 2 ? rows_per_set * kHeadDim : 0;        // from one set to the next
+  at[3] = sets == 2 ? rows_per_set : 0;
+  return at[1] + sets * rows_per_set;
+}
+
 rlkv_status_t rlkv_decode_attention_noalloc(rlkv_cache_t* cache, int32_t layer, const void* q, void* out,
                                             float softmax_scale, void* stream) {
   if (rlkv_status_t st = decode_checks(cache, layer, q, out, softmax_scale)) return st;
-  // rows of partials the launch can write: one per (workgroup or pair, query head), twice that in a layer that blends
   const DeviceView& own = cache->dv;
-  const int64_t slots = (int64_t)own.n_wg + own.n_pairs;
-  const int64_t rows_per_set = slots * own.group;
-  const int64_t rows = rows_per_set * (cache->layer_gated[layer] ? 2 : 1);
-  if (rows > kStaticRows) return RLKV_ERR_TOO_LARGE;
+  int64_t at[4];
+  if (rlkv_plan_static_scratch(own.n_wg, own.n_pairs, own.group, cache->layer_gated[layer], at) < 0) return RLKV_ERR_TOO_LARGE;
   if (hipSetDevice(cache->cfg.device) != hipSuccess) return RLKV_ERR_HIP;
   float* ptr = scratch_on_device(cache->cfg.device);     // looked up at rlkv_cache_create; a table read here
   if (!ptr) return RLKV_ERR_HIP;
   DeviceView dv = own;
-  dv.part_o = ptr;                                        // [2][rows_per_set][head_dim]
-  dv.part_m = ptr + 2 * rows_per_set * kHeadDim;          // [2][rows_per_set]
-  dv.part_l = dv.part_m + 2 * rows_per_set;               // [2][rows_per_set]
-  dv.part_set_ml = rows_per_set;
-  dv.part_set_o = rows_per_set * kHeadDim;
+  dv.part_o = ptr;
+  dv.part_m = ptr + at[0];
+  dv.part_l = ptr + at[1];
+  dv.part_set_o = at[2];
+  dv.part_set_ml = at[3];
   return decode_with_view(cache, dv, layer, q, out, softmax_scale, as_stream(stream));
 }
 

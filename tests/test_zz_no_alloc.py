@@ -72,3 +72,21 @@ def test_calls_beyond_the_static_buffer_are_refused(gpu_device):
     torch.cuda.synchronize()
     assert (out == 0).all() and torch.isfinite(ref.float()).all()
     cache.close()
+
+
+@pytest.mark.parametrize("pairs", [300, 768])
+def test_calls_that_fill_the_static_buffer(gpu_device, pairs):
+    """(256 + 300) * 16 = 8896 rows leave no room for the second set of rows that a layer that blends would have; 1024 * 16 is the limit."""
+    cache = rl.Cache(1, 16, 1, 128, pairs, 4, 28, BF16, [1], [800] * pairs)
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    k = torch.randn(pairs, 1, 700, 128, device="cuda:0").to(torch.bfloat16)
+    cache.append(0, k, torch.randn_like(k))
+    q = torch.randn(pairs, 16, 128, device="cuda:0").to(torch.bfloat16)
+    out, ref = torch.zeros_like(q), torch.zeros_like(q)
+    cache.decode_attention(0, q, ref, 0.1)
+    for _ in range(2):
+        out.fill_(float("nan"))
+        cache.decode_attention_noalloc(0, q, out, 0.1)
+        torch.cuda.synchronize()
+        assert torch.isfinite(ref.float()).all() and torch.equal(out, ref)
+    cache.close()
