@@ -460,6 +460,7 @@ hipError_t launch_decode_mfma(const DeviceView& dv, int layer, bool gated, const
   // (the plain launch when no timestamps are asked for: that form can be recorded into a graph)
 #define RLKV_LAUNCH(F, GT, PG)                                                                                    \
   do {                                                                                                            \
+    static_assert(late_arguments_are_last<decltype(&decode_mfma_kernel<F, GT, PG>), DecodeRest>());               \
     if (ev_start || ev_stop)                                                                                      \
       hipExtLaunchKernelGGL((decode_mfma_kernel<F, GT, PG>), grid, dim3(kThreads), 0, stream, ev_start, ev_stop, 0, \
                             list, dv.kv_base, (const uint16_t*)q, (const uint16_t*)k_new, (const uint16_t*)v_new, \

@@ -498,6 +498,7 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
   // (without events: the plain launch, which a stream capture can record)
 #define RLKV_LAUNCH_ROWS(NS)                                                                                         \
   do {                                                                                                               \
+    static_assert(late_arguments_are_last<decltype(&decode_valu_kernel<T, NS, FUSED, GATED>), DecodeRest<T>>());     \
     if (e0 || e1)                                                                                                    \
       hipExtLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED, GATED>), grid, dim3(waves_for(NS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
                             qp, kp, vp, shape, grow, dv.window, dv.recent, r);                                       \

@@ -10,6 +10,9 @@
 // It replaces a launch that every call waited for; where that pays: merges_in_launch in rlkv_api.hip, with the figures.
 #pragma once
 
+#include <tuple>
+#include <type_traits>
+
 #include "mfma_tile.h"
 
 namespace rlkv {
@@ -62,12 +65,27 @@ __device__ __forceinline__ Partials partials_at(RLKV_CONST Partials& p) { return
 // The arguments of an attention kernel beyond the 14 words that are in registers when it starts, asked for where this is called: left
 // alone the compiler asks for all of them, and computes what depends on them or on the thread's number alone, in front of the first loads
 // (of fp32 rows 470 instructions, 90 of them to keep scalars in lanes of vector registers).
+constexpr int kLateArgumentsAt = 14 * 4;
 template <typename Rest>
 __device__ __forceinline__ RLKV_CONST Rest* late_arguments() {
-  constexpr int kAt = 14 * 4;
-  auto* p = (RLKV_CONST Rest*)((RLKV_CONST char*)__builtin_amdgcn_kernarg_segment_ptr() + kAt);
+  auto* p = (RLKV_CONST Rest*)((RLKV_CONST char*)__builtin_amdgcn_kernarg_segment_ptr() + kLateArgumentsAt);
   asm volatile("" : "+s"(p));
   return p;
+}
+
+// Where a kernel's last argument begins, and its type: of every kernel that reads it by late_arguments checked where it is launched.
+template <typename Kernel> struct LastArgument;
+template <typename... Args> struct LastArgument<void (*)(Args...)> {
+  typedef std::tuple_element_t<sizeof...(Args) - 1, std::tuple<Args...>> type;
+  static constexpr int begin() {
+    int at = 0, next = 0;
+    ((at = (next + (int)alignof(Args) - 1) / (int)alignof(Args) * (int)alignof(Args), next = at + (int)sizeof(Args)), ...);
+    return at;
+  }
+};
+template <typename Kernel, typename Rest>
+constexpr bool late_arguments_are_last() {
+  return std::is_same_v<typename LastArgument<Kernel>::type, Rest> && LastArgument<Kernel>::begin() == kLateArgumentsAt;
 }
 
 // Four columns of head g and partial `slot`; m and l by the thread that has the first four.
