@@ -205,6 +205,7 @@ __device__ __forceinline__ void finish_pairs(const Partials& p, const LeftPair* 
   constexpr int kDuos = kMaxGroup / 2;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (wave * 2 >= G) return;
+  asm volatile("" ::: "memory");           // (no store of a partial behind the wait)
   __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0): the partials of this wavefront have arrived where every XCD sees them
   asm volatile("" ::: "memory");
   for (int duo = wave; duo * 2 < G; duo += kThreads / 64) {
