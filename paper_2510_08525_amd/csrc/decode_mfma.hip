@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kThreads, 1) void decode_mfma_kernel(const char* __
   constexpr int kRow = kHeadDim + 4;                   // (the 16 heads of a store fall into different banks)
   __shared__ floatx4 sm_o[kWaves][kMaxGroup][kRow / 4];
   __shared__ float2 sm_ml[kMaxGroup][kWaves];
-  __shared__ float sm_w[kMaxGroup][kMergeFew];
+  __shared__ alignas(16) float sm_w[kMaxGroup][kMergeFew];     // (merge_duo reads four weights at a time)
   __shared__ LeftPair sm_left[2];                      // (in LDS only to spare registers)
 
   // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
 
   __shared__ floatx4 sm_o[kWaves][NS * 4][kHeadDim / 4];
   __shared__ float2 sm_ml[NS * 4][kWaves];
-  __shared__ float sm_w[NS * 4][kMergeFew];
+  __shared__ alignas(16) float sm_w[NS * 4][kMergeFew];        // (merge_duo reads four weights at a time)
   __shared__ LeftPair sm_left[2];                      // (in LDS only to spare registers)
 
   const int wg = blockIdx.x;
