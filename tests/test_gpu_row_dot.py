@@ -1,5 +1,6 @@
-"""Scores of the row-major fp32 kernel: a lane's two 16-byte chunks of a row, 64 elements apart, are summed on their own
-before they are added.  One chain over both would lose what is below half an ulp of the first chunk's sum, element by element."""
+"""Scores of the row-major fp32 kernel: a block of the matrix instruction sums 16 neighbouring columns of a row in four sums of four, which
+are added last, and the eight blocks of a row are added after that.  One chain over the 16 would lose what is below half an ulp of a large
+product ahead of it, element by element; so would one over columns of several blocks."""
 import numpy as np
 import pytest
 import torch
@@ -11,8 +12,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("fused", [False, True], ids=["decode", "fused step"])
-@pytest.mark.parametrize("big", [0, 23, 63])
-def test_small_products_behind_a_large_one(gpu_device, big, fused):
+@pytest.mark.parametrize("big,small", [(0, 64), (23, 84), (63, 124),               # in another block
+                                       (0, 4), (16, 28), (17, 24), (50, 60), (112, 124)])      # in another four columns of the same one
+def test_small_products_behind_a_large_one(gpu_device, big, small, fused):
     """q . k = 2048 + 4 x 2^-13 for one key and 2048 for the other.  Each small product is half an ulp of 2048, which a chain
     behind 2048 rounds away (to even); their own sum is two ulps, so that both scores are exact in fp32.  The scale, ln 2,
     makes the factor on the scores exactly 1, so nothing else is rounded before the exponentials (of 0 and 2^-11, 1 ulp each).
@@ -24,9 +26,8 @@ def test_small_products_behind_a_large_one(gpu_device, big, fused):
     q = np.zeros((1, 1, D), np.float32)
     q[0, 0, big] = 1.0
     k[0, 0, :, big] = 2048.0
-    chunk = big // 4 * 4 + 64
-    q[0, 0, chunk:chunk + 4] = 1.0
-    k[0, 0, 0, chunk:chunk + 4] = 2.0 ** -13
+    q[0, 0, small:small + 4] = 1.0
+    k[0, 0, 0, small:small + 4] = 2.0 ** -13
     v[0, 0, 0], v[0, 0, 1] = 1.0, -1.0
     c = rl.Cache(1, 1, 1, D, 1, 4, 28, rl.RLKV_F32, [1], [8], kernel=rl.RLKV_KERNEL_VALU)
     put = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(gpu_device)
