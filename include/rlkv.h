@@ -387,6 +387,12 @@ int32_t rlkv_plan_list_kind(int32_t kernel, int32_t dtype, int32_t group, int32_
                             int32_t n_kv_heads, int32_t n_full_heads, int32_t window, int32_t batch,
                             const int32_t* lengths /* host */, const uint8_t* active /* host */);
 
+/* Whether a call under a list of shares merges the partials inside the attention launch (1) or by a launch behind it (0; recorded
+ * calls, and calls with a prepared step outstanding, always do), -1 on an invalid argument; exposed for tests.
+ *   gated : some full head of the layer has a gate below 1
+ *   used, most_partials : workgroups the list uses; most of them that share a pair (rlkv_plan_shares) */
+int32_t rlkv_plan_merge_inside(int32_t kernel, int32_t group, int32_t gated, int32_t n_workgroups, int32_t used, int32_t most_partials);
+
 /* Where the split-K partials of a rlkv_decode_attention_noalloc call are in the static buffer of 16384 x 130 floats; exposed for tests.
  *   gated : some full head of the layer has a gate below 1
  *   at    : host [4], out, in floats: the rows' maxima, their normalisers (the accumulators are at 0), and the way from the first set of

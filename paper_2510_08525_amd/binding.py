@@ -80,6 +80,7 @@ def load_library():
         "rlkv_plan_whole_pairs": (i32, [vp, i32, i32, vp, vp, vp]),
         "rlkv_plan_list_whole": (i32, [i32] * 10 + [vp, vp]),
         "rlkv_plan_list_kind": (i32, [i32] * 10 + [vp, vp]),
+        "rlkv_plan_merge_inside": (i32, [i32] * 6),
         "rlkv_plan_static_scratch": (ctypes.c_int64, [i32, i32, i32, i32, vp]),
         "rlkv_plan_narrow_split": (i32, [i32, i32, i32, i32, vp, vp, i32]),
         "rlkv_plan_blend_form": (i32, [i32, i32, i32, i32, vp, i32]),
@@ -103,7 +104,7 @@ EXPORTED_SYMBOLS = (
     "rlkv_cache_required_bytes", "rlkv_cache_create", "rlkv_cache_destroy", "rlkv_cache_reset",
     "rlkv_append", "rlkv_append_ragged", "rlkv_decode_attention", "rlkv_decode_attention_noalloc", "rlkv_set_active", "rlkv_set_gates", "rlkv_append_decode", "rlkv_append_decode_prepare", "rlkv_append_decode_launch", "rlkv_worklists_built", "rlkv_prefill_attention", "rlkv_profile_enable",
     "rlkv_profile_collect", "rlkv_get_lengths",
-    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_list_kind", "rlkv_plan_static_scratch", "rlkv_plan_narrow_split", "rlkv_plan_blend_form", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_plan_prefill_item", "rlkv_cache_kernel", "rlkv_pool_pages_free",
+    "rlkv_get_slot_positions", "rlkv_resident_bytes", "rlkv_probe_stream_read", "rlkv_plan_shares", "rlkv_plan_whole_pairs", "rlkv_plan_list_whole", "rlkv_plan_list_kind", "rlkv_plan_merge_inside", "rlkv_plan_static_scratch", "rlkv_plan_narrow_split", "rlkv_plan_blend_form", "rlkv_plan_prefill_form", "rlkv_plan_prefill_rows", "rlkv_plan_prefill_block", "rlkv_plan_prefill_item", "rlkv_cache_kernel", "rlkv_pool_pages_free",
     "rlkv_pool_shuffle", "rlkv_status_string",
 )
 

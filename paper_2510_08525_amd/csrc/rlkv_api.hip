@@ -835,11 +835,16 @@ static bool stream_is_capturing(hipStream_t s) {
 // 3000 .. 5000 25.6 / 26.3; short: one of 2000, 16 on 1 10.1 / 7.4.  Row-major, four wavefronts beyond group 8: prompts of 500 and 2500, 16
 // on 1, and 8 steps 129 / 162.)  Only where the host knows the list's growth: without the merge kernel nobody could advance it while
 // workgroups read it.
+int32_t rlkv_plan_merge_inside(int32_t kernel, int32_t group, int32_t gated, int32_t n_workgroups, int32_t used, int32_t most_partials) {
+  if ((kernel != RLKV_KERNEL_VALU && kernel != RLKV_KERNEL_MFMA) || group < 1 || group > kMaxGroup || n_workgroups < 1 || used < 1 ||
+      used > n_workgroups || most_partials < 1)
+    return -1;
+  if (most_partials > kMergeFew || (group > 8 && kernel != RLKV_KERNEL_MFMA)) return 0;
+  return (group <= 8 && !gated) || (2 * used <= n_workgroups && most_partials <= 16);
+}
 static bool merges_in_launch(const rlkv_cache_t* cache, int32_t layer) {
-  if (cache->list_whole[layer] || cache->list_partials[layer] > kMergeFew) return false;
-  const DeviceView& dv = cache->dv;
-  if (dv.group > 8 && dv.kernel != RLKV_KERNEL_MFMA) return false;
-  return (dv.group <= 8 && !cache->layer_gated[layer]) || (2 * cache->list_used[layer] <= dv.n_wg && cache->list_partials[layer] <= 16);
+  return !cache->list_whole[layer] && rlkv_plan_merge_inside(cache->dv.kernel, cache->dv.group, cache->layer_gated[layer], cache->dv.n_wg,
+                                                             cache->list_used[layer], cache->list_partials[layer]) == 1;
 }
 
 // Decode attention of one layer with the kernels looking for their tables and partials in `dv` (the cache's own

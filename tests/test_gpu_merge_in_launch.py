@@ -1,26 +1,50 @@
 """Pairs cut into shares are merged by the last workgroup that leaves one, inside the attention launch: call after call the same bits as
-the merge launch behind a recorded call gives, for two to 33 partials, groups that fill a wavefront's two heads and that do not,
-shares that end in one pair and begin in the next, outputs at any element, and steps whose growth the host counts."""
+the merge launch behind a recorded call gives, for 3 to 32 partials, groups that fill a wavefront's two heads and that do not,
+shares that end in one pair and begin in the next, outputs at any element, and steps whose growth the host counts.  The lists beyond the
+lines between the two merges (33 partials; 17, or more than half of the grid, where heads blend or groups are beyond 8; row-major groups
+beyond 8) take the merge launch in either kind of call and go through the same."""
 import numpy as np
 import pytest
 import torch
 
 import paper_2510_08525_amd as rl
 from harness import Case
+from list_plan import plan
 
 pytestmark = pytest.mark.gpu
 
-KINDS = [(rl.RLKV_BF16, rl.RLKV_KERNEL_MFMA), (rl.RLKV_F32, rl.RLKV_KERNEL_VALU), (rl.RLKV_BF16, rl.RLKV_KERNEL_VALU)]
+KINDS = {"mfma": (rl.RLKV_BF16, rl.RLKV_KERNEL_MFMA), "valu-f32": (rl.RLKV_F32, rl.RLKV_KERNEL_VALU), "valu-bf16": (rl.RLKV_BF16, rl.RLKV_KERNEL_VALU)}
+S, R = 8, 56
 
 
-@pytest.mark.parametrize("dtype,kernel", KINDS, ids=["mfma", "valu-f32", "valu-bf16"])
-@pytest.mark.parametrize("gate", [None, 0.375], ids=["plain", "blending"])
-@pytest.mark.parametrize("group", [1, 4, 7, 16])
-@pytest.mark.parametrize("lengths", [[1400], [2010], [4100], [3000, 2500, 1400], [1200] * 40], ids=lambda x: f"{len(x)}x{x[0]}")
-def test_same_bits_as_the_merge_launch(gpu_device, lengths, group, gate, dtype, kernel):
+def mask(lengths):
+    return [1, 0] if len(lengths) < 40 else [1, 1]
+
+
+def inside(lengths, group, gate, kind):
+    return plan(*KINDS[kind], group, mask(lengths), S, R, lengths, max(lengths) + 8, gated=gate is not None)[3]
+
+
+ALL = [(lengths, group, gate, kind)
+       for lengths in [[900], [1400], [2010], [4100], [7900], [8100], [3000, 2500, 1400], [1200] * 40]
+       for group in [1, 4, 7, 16] for gate in [None, 0.375] for kind in KINDS]
+name = lambda c: f"{len(c[0])}x{c[0][0]}-{c[1]}-{'plain' if c[2] is None else 'blending'}-{c[3]}"
+
+
+@pytest.mark.parametrize("case", [c for c in ALL if inside(*c)], ids=name)
+def test_same_bits_as_the_merge_launch(gpu_device, case):
+    run(*case)
+
+
+@pytest.mark.parametrize("case", [c for c in ALL if not inside(*c)], ids=name)
+def test_lists_beyond_the_lines(gpu_device, case):
+    run(*case)
+
+
+def run(lengths, group, gate, kind):
+    dtype, kernel = KINDS[kind]
     B = len(lengths)
-    c = Case(Hq=2 * group, Hkv=2, B=B, S=8, R=56, dtype=dtype, kernel=kernel, mask=[1, 0] if B < 40 else [1, 1], cap=max(lengths) + 8,
-             seed=group)
+    c = Case(Hq=2 * group, Hkv=2, B=B, S=S, R=R, dtype=dtype, kernel=kernel, mask=mask(lengths), cap=max(lengths) + 8, seed=group)
     if gate is not None:
         c.cache.set_gates(np.asarray([gate, 1.0], dtype=np.float32))
     while (c.n < np.asarray(lengths)).any():
