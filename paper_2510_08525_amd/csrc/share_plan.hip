@@ -158,24 +158,25 @@ bool wants_whole_pairs(int kernel, int dtype, int group, bool gated, bool step, 
 }
 
 // The kind of list a layer gets (true: whole pairs).  wants_whole_pairs was fitted with a merge launch behind the shares; where the
-// tiled kernel merges them itself (merges_in_launch in rlkv_api.hip), they are better by kInsideSaves, and a list of at least
-// three rounds that goes out at one per workgroup and fills at most half of the grid is always the faster one (whole / shares,
-// us: a step of one sequence, 32 on 8 heads, half compressed, 150 tokens 6.9 / 7.2, 230 6.9 / 7.0, 300 7.7 / 7.3, 480 8.6 / 7.0; 8 of
-// 480, 28 on 4 9.6 / 7.5; 4 of 300, 16 on 1 8.1 / 7.3; 4 of 500 that blend, 28 on 4 11.5 / 9.3.  Longer lists: 16 of 800, 32 on 8
-// 13.7 / 12.4, of 500 10.4 / 11.2; 16 of 600, 8 on 8 12.0 / 11.3).
+// tiled kernel merges them itself (merges_in_launch in rlkv_api.hip), they are better by kInsideSaves, and a list that goes out at one
+// round per workgroup and fills at most half of the grid is one of shares beyond 352 rows, where heads blend beyond 256, which the eight
+// wavefronts take in one go.  Whole / shares, us, decode and step: one sequence, 32 on 8 heads, half compressed, 230 tokens 4.1 / 4.9 and
+// 5.2 / 5.8, 300 4.4 / 4.9 and 5.4 / 5.5, 350 4.4 / 4.9 and 5.2 / 5.8, 1000 6.8 / 5.3 and 7.6 / 6.1; 8 of 28 on 4, 230 4.3 / 5.4 and 5.5 / 6.2, 350
+// 5.7 / 5.6 and 6.3 / 6.2, 400 6.0 / 5.5 and 7.2 / 6.1; with heads that blend, 230 6.6 / 7.5 and 7.7 / 8.4, 260 7.3 / 7.4 and 8.1 / 8.0, 350 7.9 / 7.6 and
+// 8.8 / 8.6, 400 9.3 / 7.5 and 10.1 / 8.2.
 bool list_is_whole(int kernel, int dtype, int group, bool gated, bool step, int n_wg, int n_kv_heads, int n_full, int window,
                    int batch, const int32_t* lengths, const uint8_t* active) {
   const bool tiled = kernel == RLKV_KERNEL_MFMA;
   if (tiled) {
     auto rounds = [&](int64_t n) { return (n + kWorklistSlack + kTile * kRound - 1) / (kTile * kRound); };
-    int64_t most = 0, all = 0;
+    int64_t longest = 0, all = 0;                            // rows of the longest pair; rounds of all
     for (int b = 0; b < batch; ++b) {
       if (active && !active[b]) continue;
-      const int64_t full = rounds(lengths[b]), ring = rounds(std::min(lengths[b], window));
-      most = std::max(most, n_full > 0 ? full : ring);
-      all += n_full * full + (n_kv_heads - n_full) * ring;
+      const int64_t ring = std::min(lengths[b], window);
+      longest = std::max<int64_t>(longest, n_full > 0 ? lengths[b] : ring);
+      all += n_full * rounds(lengths[b]) + (n_kv_heads - n_full) * rounds(ring);
     }
-    if (most >= 3 && most <= 16 && 2 * all <= n_wg) return false;
+    if (longest > (gated ? 256 : 352) && rounds(longest) <= 16 && 2 * all <= n_wg) return false;
   }
   return wants_whole_pairs(kernel, dtype, group, gated, step, n_wg, n_kv_heads, n_full, window, batch, lengths, active,
                            tiled && group <= 8 && !gated);

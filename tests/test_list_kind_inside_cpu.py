@@ -15,8 +15,8 @@ def kind(kernel, dtype, q_heads, kv_heads, n_full, batch, n, gated=0, step=0, fn
 
 # (q heads, KV heads, full heads, sequences, gated, tokens of whole pairs, tokens of shares)
 @pytest.mark.parametrize("Hq,Hkv,full,B,gated,yes,no", [
-    (32, 8, 4, 1, 0, 224, 225), (28, 4, 2, 1, 0, 150, 300), (28, 4, 2, 8, 0, 150, 480), (8, 8, 4, 4, 0, 150, 300), (16, 1, 1, 4, 0, 150, 300),
-    (28, 4, 4, 4, 1, 130, 500), (32, 8, 8, 1, 1, 130, 500), (32, 8, 4, 16, 0, 350, 800), (8, 8, 4, 16, 0, 300, 800),
+    (32, 8, 4, 1, 0, 352, 353), (28, 4, 2, 1, 0, 300, 400), (28, 4, 2, 8, 0, 300, 480), (8, 8, 4, 4, 0, 300, 400), (16, 1, 1, 4, 0, 300, 400),
+    (28, 4, 4, 4, 1, 256, 257), (32, 8, 8, 1, 1, 256, 257), (32, 8, 4, 16, 0, 350, 800), (8, 8, 4, 16, 0, 300, 800),
 ], ids=lambda x: str(x))
 @pytest.mark.parametrize("step", [0, 1], ids=["decode", "step"])
 def test_lines(Hq, Hkv, full, B, gated, yes, no, step):
