@@ -112,16 +112,18 @@ void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_
 // of this one, merges_in_launch)
 // and costs the time that the longest pair takes one CU beyond an even share of all rows.
 // Tiled stores: the difference in us, whole pairs minus shares, as a sum over what both depend on; the factors were fitted to 1277
-// pairs of timings (1 to 64 sequences of 100 to 8000 tokens, even and ragged, groups 1 to 16, 1 to 256 pairs), of which this
-// rule picks the slower side by 0.2 to 0.4 % on average and by more than 10 % five times; limits on the rows alone, which had
-// been measured at group 4, were up to 1.7 x slower at others.  Whole / shares, us: decode, one sequence of 32 query and 8 KV
-// heads, half compressed, 800 tokens 7.5 / 8.1, 1000 8.8 / 8.3; 16 of them, 800 11.7 / 13.0, 1200 16.2 / 13.6; 32, 1400 20.8 / 22.8;
-// one of 16 heads on 1, 700 8.8 / 9.2, 1000 11.0 / 9.5; a step of 4 of 28 and 4 heads that blend, 300 12.6 / 14.0, 700 16.2 / 13.6;
-// 3 of 8 and 8 of 182, 316 and 500 tokens 6.6 / 8.2.  (Beyond 800 rows of excess nothing was fitted.)
-// Row-major stores have no wide form, so rounds of four tiles count: one always pays (fp32, group 16, one sequence of 100 tokens
-// 20.6 / 24.0, of 130 27.0 / 24.0); bf16 without gates two up to group 4 (one sequence, group 4: 200 9.0 / 10.1, 260 10.8 /
-// 10.2), three up to group 2 (300 7.2 / 8.1, 400 8.2 / 8.1); fp32, group 4: 130 10.2 / 11.0, 260 13.2 / 11.2; beyond that only
-// pairs that fill the CUs about evenly (fp32, 64 of 28 and 4 heads, 400 tokens: 27.8 / 29.6; 32 of 64 and 4, 130: 31.7 / 26.7).
+// pairs of timings of a kernel with four wavefronts and the merge launch (1 to 64 sequences of 100 to 8000 tokens, even and ragged, groups
+// 1 to 16, 1 to 256 pairs); limits on the rows alone, which had been measured at group 4, were up to 1.7 x slower at others.  With the present
+// kernel and what list_is_whole adds, over 396 timings (nine shapes of 1 to 64 sequences, groups 1 to 16, 40 to 1300 tokens, decode and step,
+// plain and blending) the kind picked is the slower one by 0.5 % on average and by more than 10 % five times.  (Beyond 800 rows of excess
+// nothing was fitted.)
+// Row-major stores have no wide form, so rounds of four tiles count: one always pays; bf16 without gates two up to group 4, three up to
+// group 2; beyond that only pairs that fill the CUs about evenly.  These limits are of the kernel before the matrix instructions; with the
+// present one they pick the slower kind by 1.5 % on average of 792 timings as above, by more than 10 % 43 times: of fp32 beyond group 4 with 65 to
+// 128 tokens, and of groups up to 2 with 200 to 400.  Whole / shares, us: fp32, one sequence, 16 heads on 1, 40 tokens 8.3 / 10.3, 100 11.6 /
+// 10.4, 130 14.9 / 10.3; 32 on 8, half compressed, 100 5.0 / 5.6, 130 5.9 / 5.6, 260 7.8 / 5.8; bf16, the same, 130 5.4 / 6.3, 200 6.6 / 6.3, 260
+// 7.2 / 6.3; 16 on 8, 160 5.3 / 6.0, 200 6.7 / 6.1, 330 8.7 / 6.3; 16 on 1, 100 10.9 / 12.9, 130 14.3 / 13.1; fp32, 64 of 28 and 4 heads that
+// blend, 400 32.2 / 34.0; 32 of 64 and 4, 130 16.1 / 15.1.
 struct WholeCost {
   double fixed;          // merge launch saved, start of eight wavefronts
   double longest, even;  // per 1000 rows of the longest pair; of an even share
