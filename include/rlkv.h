@@ -48,7 +48,7 @@ typedef enum { RLKV_F32 = 0, RLKV_BF16 = 1 } rlkv_dtype_t;
 
 /* Which decode kernel (and with it which in-HBM store layout) a cache uses.
  *   RLKV_KERNEL_VALU : row-major stores [slot][head_dim]; products of fp32 values on the
- *                      matrix cores, 4 x 4 blocks.  fp32 and bf16.  The fp32 path, and for
+ *                      matrix cores, 4 x 4 blocks (groups of 1 and 2: the vector ALU).  fp32 and bf16.  The fp32 path, and for
  *                      bf16 the comparison baseline: its operands are brought into order in
  *                      registers and its instructions are those for fp32, so at a group size
  *                      of 7 it is slower than the MFMA kernel; no paging, no prefill.

@@ -15,6 +15,12 @@
 //   output   blocks 0..7 = one row, 8..15 the next: A = V as loaded, B = the weights of 4 heads, one
 //            instruction per column of a lane: lane l holds 16 sums of head l%4, of the even rows or of the odd ones
 // The partial scores of the blocks are dealt out as they are summed: each quarter of the wavefront keeps 4 of the 16 rows.
+// Groups of one and two heads would leave most of a 4 x 4 block empty: they take multiply-adds of the vector ALU on rows as loaded, every
+// lane its four columns of every head, the scores summed over the lanes of a row and dealt out in the same way.  us a launch with the
+// matrix cores / with these: bf16, 48 of up to 700 tokens, 8 heads on 8, decode 19.7 / 16.7, a step 22.2 / 19.1, with blending heads 37.1 / 30.4
+// and 46.0 / 37.4; 16 on 8 20.1 / 18.5 and 22.7 / 21.0, blending 37.0 / 34.0 and 46.2 / 42.5; fp32, one of 1500, 8 on 8 6.7 / 6.2, blending
+// 10.5 / 9.5; 16 of 700, 16 on 8 13.0 / 12.5.  At three heads the matrix cores had gained on the former vector kernel (bf16, 24 on 8, 16 of up
+// to 4000, 23.0 / 19.7).  Error against 64 bits the same (40 inputs each of four shapes: 1.48 to 2.02e-7 / 1.48 to 1.97e-7).
 // With the vector ALU alone a batch of 16 rows and 4 fp32 heads was 520 instructions and 3300 clocks, which two wavefronts of a SIMD
 // do not share; now 2000, 512 of them of the matrix cores.  References of the running maxima are whole numbers, so that moving a sum
 // from one to another rounds nothing: error against 64 bits over 13 fp32 shapes 1.4e-7 .. 3.1e-7, before 1.5e-7 .. 4.7e-7, and no
@@ -85,7 +91,7 @@ __device__ __forceinline__ floatx4 mfma_4x4(float a, float b, const floatx4& c) 
 }
 
 constexpr uint32_t kShapeGroup = 31;           // of `shape`
-constexpr int waves_for(int sets) { return sets > 2 ? 4 : 8; }
+constexpr int waves_for(int heads) { return heads > 8 ? 4 : 8; }
 template <typename T>
 struct DecodeRest {
   T* out;
@@ -98,27 +104,30 @@ struct DecodeRest {
   uint32_t recent_inverse;       // inverse_of(recent)
 };
 
-// GATED: some full head may have a gate below 1.  NS: sets of four heads.  FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the batch of
+// GATED: some full head may have a gate below 1.  HEADS: room for heads, 1 and 2 on the vector ALU, else sets of four.
+// FUSED: the step's append as well, in the manner of decode_mfma_kernel: the wavefront that owns the batch of
 // rows with the new slot writes the row, every byte by the lane that loads it.
 // Of every tile two wavefronts take a batch of 16 rows each, one register image, K refilled behind the scores and V behind the
 // products; eight wavefronts, two per SIMD, up to group 8, four beyond (Q and the sums of four sets take 128 registers).  The first arguments are in registers when the kernel starts (decode_mfma.hip).
-template <typename T, int NS, bool FUSED, bool GATED>
-__global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(const char* __restrict__ list, char* __restrict__ kv_base,
+template <typename T, int HEADS, bool FUSED, bool GATED>
+__global__ __launch_bounds__(waves_for(HEADS) * 64, 1) void decode_valu_kernel(const char* __restrict__ list, char* __restrict__ kv_base,
                                                              const T* __restrict__ q, const T* __restrict__ k_new,
                                                              const T* __restrict__ v_new, uint32_t shape, int grow_known,
                                                              int window, int recent, DecodeRest<T> r) {
   using E = Elem<T>;
   typedef typename E::Four Four;
-  constexpr int kWaves = waves_for(NS), kThreads = kWaves * 64;
+  constexpr int kWaves = waves_for(HEADS), kThreads = kWaves * 64;
+  constexpr bool kVector = HEADS <= 2;          // (a set is one head then, the same in every lane)
+  constexpr int NS = kVector ? HEADS : HEADS / 4;
   constexpr int kBatch = 16;                    // rows of a batch
   constexpr int kLoads = kBatch / 2;            // loads of K and of V in a batch, two rows each
   constexpr int kBatches = kTile / kBatch;      // batches of a tile, one wavefront each
   constexpr int kStride = kWaves / kBatches;    // tiles a workgroup works at a time
   constexpr int kRowBytes = kHeadDim * sizeof(T);
 
-  __shared__ floatx4 sm_o[kWaves][NS * 4][kHeadDim / 4];
-  __shared__ float2 sm_ml[NS * 4][kWaves];
-  __shared__ alignas(16) float sm_w[NS * 4][kMergeFew];        // (merge_duo reads four weights at a time)
+  __shared__ floatx4 sm_o[kWaves][HEADS][kHeadDim / 4];
+  __shared__ float2 sm_ml[HEADS][kWaves];
+  __shared__ alignas(16) float sm_w[HEADS][kMergeFew];        // (merge_duo reads four weights at a time)
   __shared__ LeftPair sm_left[2];                      // (in LDS only to spare registers)
 
   const int wg = blockIdx.x;
@@ -211,10 +220,15 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         vn = *reinterpret_cast<const Four*>(reinterpret_cast<const char*>(v_new) + (int64_t)pi * kRowBytes + off);
       }
     }
-    // Q: the block's 16 columns of head hl of every set (past the group: its last head again; nobody reads what comes of it)
-    float qf[NS][16];
+    // Q: the block's 16 columns of head hl of every set (past the group: its last head again; nobody reads what comes of it); on the
+    // vector ALU the lane's four columns of every head
+    float qf[NS][kVector ? 4 : 16];
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
+      if constexpr (kVector) {
+        E::unpack(*reinterpret_cast<const Four*>(reinterpret_cast<const char*>(q) + ((int64_t)pi * HEADS + s) * kRowBytes + off), qf[s]);
+        continue;
+      }
       const int g = s * 4 + hl < G ? s * 4 + hl : G - 1;
       const Four* src = reinterpret_cast<const Four*>(reinterpret_cast<const char*>(q) + ((int64_t)pi * G + g) * kRowBytes) + ((lane >> 2) & 7) * 4;
 #pragma unroll
@@ -227,18 +241,19 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
     const int keep_lo = sink, keep_from = n - recent;              // local pass: row < S or row >= n - R
     const int sink_tiles = (keep_lo + kTile - 1) / kTile;
     const int recent_tile0 = keep_from > 0 ? keep_from / kTile : 0;
-    constexpr int kPasses = (NS * 4 * kHeadDim / 4 + kThreads - 1) / kThreads;
+    constexpr int kPasses = (HEADS * kHeadDim / 4 + kThreads - 1) / kThreads;
     floatx4 held[kPasses];                                         // full-pass results of a whole-pair segment
 #pragma unroll 1
     for (int pass = 0; pass < (two_pass ? 2 : 1); ++pass) {
       float m[NS], l[NS];
-      floatx4 acc[NS][4];                              // [set][column of four]: D row i = columns 4 * (4 * (block % 8) + i) + e
+      // [set][column of four]: D row i = columns 4 * (4 * (block % 8) + i) + e; on the vector ALU [head][0], the lane's four columns
+      floatx4 acc[NS][kVector ? 1 : 4];
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         m[s] = -INFINITY;
         l[s] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[s][e] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int e = 0; e < (kVector ? 1 : 4); ++e) acc[s][e] = floatx4{0.f, 0.f, 0.f, 0.f};
       }
 
       struct Rows { Four k[kLoads], v[kLoads]; };
@@ -257,6 +272,31 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         const int tok0 = tile * kTile + row0;
         const bool ragged = tok0 + kBatch > n_eff || (GATED && pass == 1 && tok0 + kBatch > keep_lo && tok0 < keep_from);
         float sc[NS][4];                       // [set][u]: rows s_row + 2 u of the batch
+        if constexpr (kVector) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            float kf[2][4];
+            E::unpack(rw.k[u], kf[0]);
+            E::unpack(rw.k[4 + u], kf[1]);
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+              float x[2];
+#pragma unroll
+              for (int i = 0; i < 2; ++i) {
+                x[i] = kf[i][0] * qf[s][0];
+#pragma unroll
+                for (int e = 1; e < 4; ++e) x[i] = fmaf(kf[i][e], qf[s][e], x[i]);
+              }
+              const TwoValues y = deal16(x[0], x[1]);
+              float z = y.a + y.b;
+              z += row_ror<0x128>(z);
+              z += row_ror<0x124>(z);
+              z += row_ror<0x122>(z);
+              z += row_ror<0x121>(z);
+              sc[s][u] = z;
+            }
+          }
+        } else
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
           Four x[4];
@@ -323,7 +363,7 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
           l[s] = l[s] * alpha + sum;
           if (__any(alpha != 1.f)) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[s][e] *= alpha;
+            for (int e = 0; e < (kVector ? 1 : 4); ++e) acc[s][e] *= alpha;
           }
         }
         // (a row that does not count may hold anything, and of a step be the one another wavefront is writing: nothing of it may reach a sum)
@@ -343,6 +383,11 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
 #pragma unroll
           for (int s = 0; s < NS; ++s) {
             const TwoValues w = swap16(p[s][u]);       // rows 2u and 2u + 1 in the halves, then 8 + 2u and 9 + 2u
+            if constexpr (kVector) {
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[s][0][e] = fmaf(vf[1][e], w.b, fmaf(vf[0][e], w.a, acc[s][0][e]));
+              continue;
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[s][e] = mfma_4x4(vf[0][e], w.a, acc[s][e]);
 #pragma unroll
@@ -409,6 +454,10 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
       for (int s = 0; s < NS; ++s) {
         const TwoValues l16 = swap16(l[s]);
         const TwoValues l32 = swap32(l16.a + l16.b);
+        if constexpr (kVector) {
+          if (lane == 0) sm_ml[s][wave] = make_float2(m[s], l32.a + l32.b);
+          continue;
+        }
         if (lane < 4) sm_ml[s * 4 + hl][wave] = make_float2(m[s], l32.a + l32.b);
         floatx4 o[2];
 #pragma unroll
@@ -422,6 +471,15 @@ __global__ __launch_bounds__(waves_for(NS) * 64, 1) void decode_valu_kernel(cons
         const int at = ((lane >> 2) & 7) * 4 + (lane >> 5) * 2;
         sm_o[wave][s * 4 + hl][at] = o[0];
         sm_o[wave][s * 4 + hl][at + 1] = o[1];
+      }
+      if constexpr (kVector) {
+        floatx4 o;                             // head 0 in the lower half, the last one in the upper
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const TwoValues x = deal32(acc[0][0][e], acc[NS - 1][0][e]);
+          o[e] = x.a + x.b;
+        }
+        sm_o[wave][(lane >> 5) * (HEADS - 1)][lane & 31] = o;
       }
       __syncthreads();
       // merge the wavefronts, four outputs of a head per thread; emit the final output or a partial for the combine pass
@@ -496,19 +554,21 @@ hipError_t launch_t(const DeviceView& dv, int layer, const void* q, void* out, f
   r.len0 = len_of(dv, 0, layer); r.len1 = len_of(dv, 1, layer); r.slot_pos = dv.slot_pos;
   r.recent_inverse = inverse_of(dv.recent);
   // (without events: the plain launch, which a stream capture can record)
-#define RLKV_LAUNCH_ROWS(NS)                                                                                         \
+#define RLKV_LAUNCH_ROWS(HEADS)                                                                                         \
   do {                                                                                                               \
-    static_assert(late_arguments_are_last<decltype(&decode_valu_kernel<T, NS, FUSED, GATED>), DecodeRest<T>>());     \
+    static_assert(late_arguments_are_last<decltype(&decode_valu_kernel<T, HEADS, FUSED, GATED>), DecodeRest<T>>());     \
     if (e0 || e1)                                                                                                    \
-      hipExtLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED, GATED>), grid, dim3(waves_for(NS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
+      hipExtLaunchKernelGGL((decode_valu_kernel<T, HEADS, FUSED, GATED>), grid, dim3(waves_for(HEADS) * 64), 0, stream, e0, e1, 0, list, dv.kv_base, \
                             qp, kp, vp, shape, grow, dv.window, dv.recent, r);                                       \
     else                                                                                                             \
-      hipLaunchKernelGGL((decode_valu_kernel<T, NS, FUSED, GATED>), grid, dim3(waves_for(NS) * 64), 0, stream, list, dv.kv_base, qp, kp, vp,   \
+      hipLaunchKernelGGL((decode_valu_kernel<T, HEADS, FUSED, GATED>), grid, dim3(waves_for(HEADS) * 64), 0, stream, list, dv.kv_base, qp, kp, vp,   \
                          shape, grow, dv.window, dv.recent, r);                                                      \
   } while (0)
-  if (G <= 4) RLKV_LAUNCH_ROWS(1);
-  else if (G <= 8) RLKV_LAUNCH_ROWS(2);
-  else RLKV_LAUNCH_ROWS(4);
+  if (G == 1) RLKV_LAUNCH_ROWS(1);
+  else if (G == 2) RLKV_LAUNCH_ROWS(2);
+  else if (G <= 4) RLKV_LAUNCH_ROWS(4);
+  else if (G <= 8) RLKV_LAUNCH_ROWS(8);
+  else RLKV_LAUNCH_ROWS(16);
 #undef RLKV_LAUNCH_ROWS
   return hipGetLastError();
 }
