@@ -120,10 +120,10 @@ void plan_whole_pairs(const int32_t* rounds, int n_pairs, int n_wg, int32_t* wg_
 // Row-major stores have no wide form, so rounds of four tiles count: one always pays; bf16 without gates two up to group 4, three up to
 // group 2; beyond that only pairs that fill the CUs about evenly.  These limits are of the kernel before the matrix instructions; with the
 // present one they pick the slower kind by 1.5 % on average of 792 timings as above, by more than 10 % 43 times: of fp32 beyond group 4 with 65 to
-// 128 tokens, and of groups up to 2 with 200 to 400 (measured while those ran on the matrix cores too).  Whole / shares, us: fp32, one sequence, 16 heads on 1, 40 tokens 8.3 / 10.3, 100 11.6 /
-// 10.4, 130 14.9 / 10.3; 32 on 8, half compressed, 100 5.0 / 5.6, 130 5.9 / 5.6, 260 7.8 / 5.8; bf16, the same, 130 5.4 / 6.3, 200 6.6 / 6.3, 260
-// 7.2 / 6.3; 16 on 1, 100 10.9 / 12.9, 130 14.3 / 13.1; fp32, 64 of 28 and 4 heads that
-// blend, 400 32.2 / 34.0; 32 of 64 and 4, 130 16.1 / 15.1.
+// 128 tokens, and of groups up to 2 with 200 to 400 (measured while those ran on the matrix cores too). Whole / shares, us: fp32, one
+// sequence, 16 heads on 1, 40 tokens 8.3 / 10.3, 100 11.6 / 10.4, 130 14.9 / 10.3; 32 on 8, half compressed, 100 5.0 / 5.6, 130 5.9 / 5.6,
+// 260 7.8 / 5.8; bf16, the same, 130 5.4 / 6.3, 200 6.6 / 6.3, 260 7.2 / 6.3; 16 on 1, 100 10.9 / 12.9, 130 14.3 / 13.1; fp32, 64 of 28 and
+// 4 heads that blend, 400 32.2 / 34.0; 32 of 64 and 4, 130 16.1 / 15.1.
 struct WholeCost {
   double fixed;          // merge launch saved, start of eight wavefronts
   double longest, even;  // per 1000 rows of the longest pair; of an even share
